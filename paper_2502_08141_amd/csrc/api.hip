@@ -396,7 +396,7 @@ static lowra_status check_linear(const lowra_layout* L, int op, const uint8_t* p
     if (!aligned16(packed) || !aligned16(absmax) || !aligned16(mappings) || !aligned16(act) || !aligned16(out) ||
         (r > 0 && (!aligned16(A) || !aligned16(B))))
         return LOWRA_MISALIGNED;
-    const size_t need = lowra::linear_workspace_bytes(*L, op, M, r);
+    const size_t need = lowra::linear_workspace_min(*L, op, M, r);
     if (need > 0) {
         if (!workspace) return LOWRA_INVALID_ARG;
         if (!aligned16(workspace)) return LOWRA_MISALIGNED;
@@ -411,7 +411,7 @@ lowra_status lowra_linear_fwd(const lowra_layout* L, const uint8_t* packed, cons
                               size_t workspace_bytes, void* stream) {
     lowra_status st = check_linear(L, LOWRA_OP_LINEAR_FWD, packed, absmax, mappings, x, M, A, B, r, y, workspace, workspace_bytes);
     if (st != LOWRA_OK || M == 0 || L->N == 0) return st;
-    lowra::LinearArgs a{packed, absmax, mappings, x, M, A, B, r, s, y, workspace};
+    lowra::LinearArgs a{packed, absmax, mappings, x, M, A, B, r, s, y, workspace, workspace ? workspace_bytes : 0};
     return lowra::launch_linear_fwd(*L, a, g_linear_path.load(), g_fwd_tiling.load(), static_cast<hipStream_t>(stream)) == hipSuccess
                ? LOWRA_OK : LOWRA_HIP_ERROR;
 }
@@ -420,7 +420,7 @@ lowra_status lowra_linear_fwd_static(const lowra_layout* L, const uint8_t* packe
                                      const float* mappings, const uint16_t* x, int M, const uint16_t* A,
                                      const uint16_t* B, int r, float s, uint16_t* y, void* stream) {
     if (!L) return LOWRA_INVALID_ARG;
-    const size_t need = M > 0 ? lowra::linear_workspace_bytes(*L, LOWRA_OP_LINEAR_FWD, M, r) : 0;
+    const size_t need = M > 0 ? lowra::linear_workspace_min(*L, LOWRA_OP_LINEAR_FWD, M, r) : 0;
     if (need > (size_t)LOWRA_STATIC_SCRATCH_BYTES) return LOWRA_WORKSPACE_TOO_SMALL;   // beyond the static scratch: use lowra_linear_fwd
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return LOWRA_HIP_ERROR;
@@ -439,7 +439,7 @@ lowra_status lowra_linear_bwd_input(const lowra_layout* L, const uint8_t* packed
     if (L->N == 0) {   // empty contraction: dX = 0, written by a fill kernel (no memset node, so the call can be captured)
         return lowra::launch_zero_bf16(dX, (size_t)M * L->K, static_cast<hipStream_t>(stream)) == hipSuccess ? LOWRA_OK : LOWRA_HIP_ERROR;
     }
-    lowra::LinearArgs a{packed, absmax, mappings, dY, M, A, B, r, s, dX, workspace};
+    lowra::LinearArgs a{packed, absmax, mappings, dY, M, A, B, r, s, dX, workspace, workspace ? workspace_bytes : 0};
     return lowra::launch_linear_bwd_input(*L, a, g_linear_path.load(), static_cast<hipStream_t>(stream)) == hipSuccess
                ? LOWRA_OK : LOWRA_HIP_ERROR;
 }

@@ -819,4 +819,10 @@ BwdSplitPlan gemm_bwd_split_plan(int N, int K, int M) {
     return pl;
 }
 
+double gemm_bwd_steps(int N, int K, int M) {
+    const BwdSplitPlan pl = gemm_bwd_split_plan(N, K, M);
+    const int cus = device_compute_units(), steps = (N + BK - 1) / BK, whole = pl.splits > 1 ? pl.first : pl.first + pl.tail;
+    return (double)((whole + cus - 1) / cus) * steps + (pl.splits > 1 ? pl.rows_per_split / BK : 0);
+}
+
 }  // namespace lowra

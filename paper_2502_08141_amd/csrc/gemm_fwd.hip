@@ -22,7 +22,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "gemm_common.h"
+#include "gemm_mid.h"
 
 namespace lowra {
 
@@ -730,7 +730,7 @@ static double plan_makespan(long ta, double ca, long tb, double cb, int P) {
 }
 
 struct FwdChoice { int tma, tmb, cols_a; };
-static FwdChoice plan_fwd(int N, int M, int forced, int units = 0) {
+static FwdChoice plan_fwd(int N, int M, int forced, int units = 0, double* cost = nullptr) {
     const int cols = (N + BN - 1) / BN;
     if (forced >= 0) return FwdChoice{(forced >> 8) & 15, (forced >> 4) & 15, std::min(forced >> 12, cols)};
     const int P = units > 0 ? units : device_compute_units();
@@ -745,7 +745,18 @@ static FwdChoice plan_fwd(int N, int M, int forced, int units = 0) {
             if (t < best_t * (1.0 - 1e-9)) { best_t = t; best = FwdChoice{pr[0], pr[1], ca}; }
         }
     }
+    if (cost) *cost = best_t;
     return best;
+}
+
+// An odd number of groups, or fewer than four, takes the general step: three to four times the pipelined one's time.
+double gemm_fwd_steps(int N, int K, int M, double enough) {
+    const int G = K / KS;
+    const double steps = (double)G * (G % 2 || G < 4 ? 3.0 : 1.0);
+    if (steps * tile_cost(4) > enough) return steps * tile_cost(4);    // one round of the lowest tiles is too much already
+    double cost = 0.0;
+    plan_fwd(N, M, -1, 0, &cost);
+    return steps * cost;
 }
 
 template <int TMA, int TMB>

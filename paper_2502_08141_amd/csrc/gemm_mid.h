@@ -1,0 +1,36 @@
+// The mid-token fused GEMMs (gemm_mid.hip): parameters and plan.
+#pragma once
+#include "gemm_common.h"
+
+namespace lowra {
+
+constexpr int kMidCols = 128;            // output columns per workgroup
+constexpr int kMidLutBooks = 64;         // codebooks the input gradient keeps in LDS as a whole (more: a step's 64 rows are staged)
+
+struct MidParams {
+    const RowInfo* rows;
+    const uint8_t* packed;
+    const void* absmax;          // fp32, or bf16 with scale_bf16
+    const float* mappings;
+    const uint16_t* act;         // x [M,K] or dY [M,N]
+    const uint16_t* ext_act;     // s x A^T or s dY B, bf16 [M,RP]
+    const uint16_t* lora;        // B [N,r] (forward) or A [r,K] (input gradient)
+    uint16_t* out;               // y [M,N] or dX [M,K]
+    float* part;                 // splits > 1: fp32 partial tiles
+    int M, N, K, G, C, r, RP, scale_bf16;
+    int tiles_c, tiles_m;        // output tiles: 128 columns x 32 TM tokens
+    int splits, per_split;       // workgroups per output tile; contraction steps of each (forward: 256 features; input gradient: 64 channels)
+};
+
+struct MidPlan { int TM, tiles_c, tiles_m, splits, per_split; };         // TM == 0: the call belongs to another kernel
+// contraction steps of a whole 256 x 256 tile that the 256-column kernels' plans come to (forward: any value above
+// `enough` may stand for a larger one)
+double gemm_fwd_steps(int N, int K, int M, double enough);
+double gemm_bwd_steps(int N, int K, int M);
+BwdSplitPlan gemm_bwd_split_plan(int N, int K, int M);
+MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_bytes);
+inline size_t mid_part_bytes(const MidPlan& pl) { return (size_t)pl.splits * pl.tiles_c * pl.tiles_m * pl.TM * (32 * kMidCols * sizeof(float)); }
+
+hipError_t launch_gemm_mid(const MidParams& p, int op, int TM, bool wide, hipStream_t st);
+
+}  // namespace lowra

@@ -1,0 +1,772 @@
+// Fused dequant-GEMMs for the token counts between the small-token kernels and the large output grids: the forward
+// y = [x | s x A^T] [What | B]^T and the input gradient dX = [dY | s dY B] [What ; A] (Sec. 2.1 LoRA form; App. A.2
+// decode).
+//
+// The 256-column kernels of gemm_fwd.hip and gemm_bwd.hip hold a compute unit with one workgroup of 256 x (128..256)
+// outputs that walks the whole contraction.  With few output tiles that leaves most of the chip idle: 128 tokens of a
+// 4096 x 4096 matrix are 16 workgroups and 64 steps in a row.  Here a workgroup owns 128 output columns x 32 TM tokens
+// (TM = 1..4), two or three of them share a compute unit and cover each other's latencies, and the contraction is split
+// between workgroups until they fill the chip; the splits leave fp32 partial tiles in accumulator order that
+// mid_sum_kernel adds in split order (deterministic, no atomics).  Any K from 128 on (an odd number of groups
+// included), any mix of widths, any number of codebooks.
+#include <algorithm>
+#include <type_traits>
+
+#include "gemm_mid.h"
+
+namespace lowra {
+
+namespace {
+
+constexpr int MID_COLS = kMidCols;       // output columns per workgroup: 32 per wavefront
+constexpr int MID_THREADS = 256;
+
+typedef unsigned int u32x2a4_t __attribute__((ext_vector_type(2), aligned(4)));
+typedef unsigned int u32x4a4_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int u32x4v_t __attribute__((ext_vector_type(4)));
+typedef short mid_v4i16_t __attribute__((ext_vector_type(4)));
+typedef short mid_v8i16_t __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) mid_v4i16_t* mid_lds_v4i16_ptr;
+
+// packed rows start at multiples of 8 bytes only (K = 64 x an odd number): no 16-byte alignment to rely on
+__device__ __forceinline__ uint4 load16_u(const uint8_t* q) {
+    const u32x4a4_t v = *reinterpret_cast<const u32x4a4_t*>(q);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint2 load8_u(const uint8_t* q) {
+    const u32x2a4_t v = *reinterpret_cast<const u32x2a4_t*>(q);
+    return make_uint2(v.x, v.y);
+}
+__device__ __forceinline__ float load_scale(const MidParams& p, size_t i) {
+    return p.scale_bf16 ? bf16_bits_to_float(static_cast<const uint16_t*>(p.absmax)[i]) : static_cast<const float*>(p.absmax)[i];
+}
+__device__ __forceinline__ bf16x8_t frag_of(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    const u32x4v_t v = {a, b, c, d};
+    return __builtin_bit_cast(bf16x8_t, v);
+}
+
+// The unified decode of a 1- or 2-bit row (gemm_fwd.hip): byte tables of the row's levels times the group's absmax,
+// rounded to bf16, and per-lane constants that make both widths one instruction stream.
+struct NarrowConsts { uint32_t mul, mask, orc, sell, selh, width; };
+__device__ __forceinline__ NarrowConsts narrow_consts(bool two) {
+    NarrowConsts c;
+    c.mul = two ? 0x404101u : 0x808101u;
+    c.mask = two ? 0x03030303u : 0x01010101u;
+    c.orc = two ? 0x04000400u : 0x02000200u;
+    c.sell = two ? 0x06040200u : 0x03010200u;
+    c.selh = two ? 0x07050301u : 0x03010200u;
+    c.width = two ? 4u : 2u;                    // bits per pair of codes
+    return c;
+}
+// 8 codes (low bits of cw) -> 8 bf16
+__device__ __forceinline__ bf16x8_t narrow8(uint32_t cw, uint32_t SL, uint32_t SH, const NarrowConsts& c) {
+    uint32_t d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t q = __builtin_amdgcn_ubfe(cw, j * c.width, c.width);
+        d[j] = __builtin_amdgcn_perm(SH, SL, (__umul24(q, c.mul) & c.mask) | c.orc);
+    }
+    return frag_of(d[0], d[1], d[2], d[3]);
+}
+
+// What both kernels do at the end.  Accumulator register v of token tile t: column 32 wave + 8 (v/4) + 4 (lane/32) + v%4,
+// token 32 t + lane%32.
+template <int TM>
+__device__ __forceinline__ void mid_epilogue(const MidParams& p, const floatx16_t (&acc)[TM], uint8_t* smem, int wave, int lane,
+                                             int split, int tile, int c0, int m0, int cols) {
+    const int fi = lane & 31, h = lane >> 5;
+    if (p.splits > 1) {
+        const int ntiles = p.tiles_c * p.tiles_m;
+        float4* dst = reinterpret_cast<float4*>(p.part) + (((size_t)split * ntiles + tile) * 4 + wave) * (TM * 256) + lane;
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq)
+                dst[(t * 4 + vq) * 64] = make_float4(acc[t][4 * vq], acc[t][4 * vq + 1], acc[t][4 * vq + 2], acc[t][4 * vq + 3]);
+        return;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+            const uint2 v = make_uint2(pack_bf16x2(acc[t][4 * vq], acc[t][4 * vq + 1]), pack_bf16x2(acc[t][4 * vq + 2], acc[t][4 * vq + 3]));
+            *reinterpret_cast<uint2*>(smem + (32 * t + fi) * 256 + (((wave * 4 + vq) ^ (fi & 15)) << 4) + 8 * h) = v;
+        }
+    __syncthreads();
+    const int c = threadIdx.x & 15;
+    if (c0 + 8 * c < cols) {                                          // cols is a multiple of 8
+#pragma unroll
+        for (int it = 0; it < 2 * TM; ++it) {
+            const int r = it * 16 + (threadIdx.x >> 4);
+            if (m0 + r < p.M)
+                *reinterpret_cast<uint4*>(p.out + (size_t)(m0 + r) * cols + c0 + 8 * c) =
+                    *reinterpret_cast<const uint4*>(smem + r * 256 + ((c ^ (r & 15)) << 4));
+        }
+    }
+}
+
+// ---- forward.  Wavefront w owns channels c0 + 32 w .. + 31 (weights as the A operand, decoded straight into operand
+// registers) x all tokens of the tile; the activations come through a ring of three LDS stages by global -> LDS
+// transfers two steps ahead.  A superstep is 256 input features: lane (row, h) decodes the 128 features from 128 h on,
+// which are 16, 32 or 64 contiguous bytes of its row, so that its codes are asked for once per superstep, one
+// superstep ahead.  Step j (0..3) contracts features 32 j .. + 31 of both halves; LDS chunk c (16 bytes) of a token
+// row holds half c / 4, features 8 (c % 4) .. + 7 of the step, at physical chunk c ^ ((row >> 1) & 7).
+// WIDE: the matrix has 4-bit rows.  Every lane then keeps the 16 levels of its row times the current group's absmax,
+// rounded to bf16 (App. A.2 on 16 values instead of 64), in a table of its own in LDS: entry q of lane l at
+// 256 q + 4 l, so that a lookup touches bank l whatever the code -- no conflicts, one shift-add per address.
+template <int TM, bool WIDE>
+__global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    constexpr int STAGE = TM * 4096;                                  // 32 TM token rows x 128 bytes
+    constexpr int TAB0 = 3 * STAGE;                                   // WIDE: 4 KB per wavefront
+    const uint32_t smem_lds = (uint32_t)(uintptr_t)(lptr_t)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fi = lane & 31, h = lane >> 5;
+    const int ntiles = p.tiles_c * p.tiles_m;
+    const int w = xcd_tile(blockIdx.x, gridDim.x);
+    const int split = __builtin_amdgcn_readfirstlane(w / ntiles);
+    const int tile = w - split * ntiles;
+    const int mt = __builtin_amdgcn_readfirstlane(tile / p.tiles_c);
+    const int n0 = (tile - mt * p.tiles_c) * MID_COLS, m0 = mt * (32 * TM);
+    const int G = p.G, K = p.K;
+    const int nsuper = (G + 3) >> 2;
+    const int s_lo = split * p.per_split, s_hi = min(s_lo + p.per_split, nsuper);
+    // steps of the last superstep: a single group left is the first half's first two steps
+    const int t_lo = s_lo * 4, t_hi = s_hi == nsuper ? (s_hi - 1) * 4 + ((G & 3) == 1 ? 2 : 4) : s_hi * 4;
+
+    // my row
+    const int n = n0 + wave * 32 + fi;
+    const bool row_ok = n < p.N;
+    const int nc = row_ok ? n : p.N - 1;
+    const RowInfo rec = p.rows[nc];
+
+    // activation transfers: wavefront w moves rows 8 (w TM + i) .. + 7, i < TM
+    const int m_last = p.M - 1 - m0;
+    const uint16_t* act0 = p.act + (size_t)m0 * K;
+    uint32_t voff[TM], roff[TM];
+    int koff[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int r = (wave * TM + i) * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ ((r >> 1) & 7);
+        koff[i] = (c >> 2) * 128 + (c & 3) * 8;
+        roff[i] = (uint32_t)min(r, m_last) * (uint32_t)K * 2u;        // rows past M are clamped (never stored)
+        voff[i] = roff[i] + (uint32_t)koff[i] * 2u;
+    }
+    auto issue = [&](int t, int stage) __attribute__((always_inline)) {
+        const int k = (t >> 2) * 256 + (t & 3) * 32;
+        const uint32_t dst = smem_lds + stage * STAGE + wave * (TM * 1024);
+        if ((t >> 2) * 256 + 256 <= K) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) dma16_s(act0 + k, voff[i], dst + i * 1024);
+        } else {                                                      // features past K: valid bytes of the same row, zero weights
+#pragma unroll
+            for (int i = 0; i < TM; ++i) dma16_s(act0, roff[i] + (uint32_t)min(k + koff[i], K - 8) * 2u, dst + i * 1024);
+        }
+    };
+    issue(t_lo, 0);
+    issue(min(t_lo + 1, t_hi - 1), 1);
+    issue(min(t_lo + 2, t_hi - 1), 2);
+
+    const int bits = rec.bits();
+    const float* tab = p.mappings + (size_t)rec.cb() * kTableStride;
+    constexpr int NLEV = WIDE ? 16 : 4;
+    float lev[NLEV];
+#pragma unroll
+    for (int q = 0; q < NLEV; q += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(tab + q);
+        lev[q] = v.x; lev[q + 1] = v.y; lev[q + 2] = v.z; lev[q + 3] = v.w;
+    }
+    const bool one = bits == 1, four = bits == 4;
+    const NarrowConsts nk = narrow_consts(bits == 2);
+
+    // my codes and scales of one superstep
+    constexpr int NP = WIDE ? 4 : 2;
+    const uint8_t* row = p.packed + rec.offset;
+    const size_t srow = (size_t)nc * G;
+    auto load_super = [&](int ss, uint4 (&c)[NP], float (&a)[2]) __attribute__((always_inline)) {
+        const int gh = ss * 4 + 2 * h;                                // my two groups
+        a[0] = load_scale(p, srow + min(gh, G - 1));
+        a[1] = load_scale(p, srow + min(gh + 1, G - 1));
+        if (gh >= G || !row_ok) a[0] = 0.0f;
+        if (gh + 1 >= G || !row_ok) a[1] = 0.0f;
+        const uint8_t* q0 = row + (size_t)gh * 8 * bits;
+        if (ss * 4 + 4 <= G) {                                        // uniform
+#pragma unroll
+            for (int q = 0; q < NP; ++q) c[q] = q < bits ? load16_u(q0 + 16 * q) : make_uint4(0u, 0u, 0u, 0u);
+        } else {                                                      // the row's end: 8 bytes at a time
+            const int have = min(max(G - gh, 0), 2) * 8 * bits;
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const uint2 lo = 16 * q + 8 <= have ? load8_u(q0 + 16 * q) : make_uint2(0u, 0u);
+                const uint2 hi = 16 * q + 16 <= have ? load8_u(q0 + 16 * q + 8) : make_uint2(0u, 0u);
+                c[q] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+        }
+    };
+
+    floatx16_t acc[TM];
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+    int kof[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) kof[kk] = fi * 128 + (((4 * h + kk) ^ ((fi >> 1) & 7)) << 4);
+    uint8_t* mytab = smem + TAB0 + wave * 4096 + lane * 4;
+
+    // Operands of one slice (16 of a step's 64 features).  WIDE keeps the looked-up values and packs them right before
+    // the MFMAs, a slice after the lookups were issued.
+    struct Slice { bf16x8_t f[TM]; uint32_t e[8]; bf16x8_t wf; };
+    uint32_t c[4 * NP], SL = 0, SH = 0;
+    float a0 = 0.0f, a1 = 0.0f;
+    auto new_group = [&](float a) __attribute__((always_inline)) {    // the tables of my row's next group
+        if (WIDE) {
+#pragma unroll
+            for (int q = 0; q < NLEV; ++q) {
+                const float v = lev[q] * a;
+                *reinterpret_cast<uint32_t*>(mytab + 256 * q) = pack_bf16x2(v, v);
+            }
+        } else {
+            const uint32_t P01 = pack_bf16x2(lev[0] * a, lev[1] * a), P23 = pack_bf16x2(lev[2] * a, lev[3] * a);
+            SL = __builtin_amdgcn_perm(P23, P01, nk.sell);
+            SH = __builtin_amdgcn_perm(P23, P01, nk.selh);
+        }
+    };
+    auto decode = [&](int j, int kk, Slice& o) __attribute__((always_inline)) {
+        const uint32_t c2 = c[2 * j + (kk >> 1)] >> (16 * (kk & 1)), c1 = c[j] >> (8 * kk);
+        const uint32_t c21 = one ? c1 : c2;
+        if (WIDE) {
+            const uint32_t cw = four ? c[(4 * j + kk) % (4 * NP)] : c21;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                o.e[i] = *reinterpret_cast<const uint32_t*>(mytab + (__builtin_amdgcn_ubfe(cw, (uint32_t)(i * bits), (uint32_t)bits) << 8));
+        } else {
+            o.wf = narrow8(c21, SL, SH, nk);
+        }
+    };
+    auto read_act = [&](int stage, int kk, Slice& o) __attribute__((always_inline)) {
+        const uint8_t* sb = smem + stage * STAGE + kof[kk];
+#pragma unroll
+        for (int tt = 0; tt < TM; ++tt) o.f[tt] = *reinterpret_cast<const bf16x8_t*>(sb + tt * 4096);
+    };
+    auto multiply = [&](const Slice& o) __attribute__((always_inline)) {
+        const bf16x8_t wf = WIDE ? frag_of(__builtin_amdgcn_perm(o.e[1], o.e[0], 0x05040100u), __builtin_amdgcn_perm(o.e[3], o.e[2], 0x05040100u),
+                                           __builtin_amdgcn_perm(o.e[5], o.e[4], 0x05040100u), __builtin_amdgcn_perm(o.e[7], o.e[6], 0x05040100u))
+                                 : o.wf;
+#pragma unroll
+        for (int tt = 0; tt < TM; ++tt) acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, o.f[tt], acc[tt], 0, 0, 0);
+    };
+
+    // The instruction order of a slice at TM = 4: after each MFMA a share of the work that prepares the next slice
+    // (MFMAs issued back to back hold the wavefront at its next one for 32 cycles each; 94 -> 90 us on 4096 x 4096,
+    // 2048 tokens; at lower tiles no gain).
+    auto spread = [&]() __attribute__((always_inline)) {
+        if (WIDE) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+#pragma unroll
+        for (int t = 0; t < TM; ++t) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, WIDE ? 3 : 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    uint4 cn[NP];
+    float an[2];
+    auto next_super = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) { c[4 * q] = cn[q].x; c[4 * q + 1] = cn[q].y; c[4 * q + 2] = cn[q].z; c[4 * q + 3] = cn[q].w; }
+        a0 = an[0]; a1 = an[1];
+    };
+    load_super(s_lo, cn, an);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // all three activation tiles
+    __syncthreads();
+    next_super();
+    new_group(a0);
+    Slice sl[2];
+    decode(0, 0, sl[0]);
+    read_act(0, 0, sl[0]);
+
+    // Step t.  Its barrier sits before the last slice, when every wavefront holds that slice's operands: stage t % 3 is
+    // then free for tile t + 3, and the operands of (step t + 1, slice 0) are read under the last slice's MFMAs.
+    int st = 0;                                                       // stage of step t
+    for (int ss = s_lo; ss < s_hi; ++ss) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int t = ss * 4 + j;
+            if (t >= t_hi) break;                                     // uniform
+            const int stn = st == 2 ? 0 : st + 1;
+#pragma unroll
+            for (int kk = 0; kk < 3; ++kk) {
+                read_act(st, kk + 1, sl[(kk + 1) & 1]);
+                decode(j, kk + 1, sl[(kk + 1) & 1]);
+                if (TM < 4) __builtin_amdgcn_sched_barrier(0);
+                multiply(sl[kk & 1]);
+                if (TM == 4) spread();
+            }
+            // Tile t + 1 has landed when only the transfers of tile t + 2 are outstanding.  The loads of the next
+            // superstep's codes are issued behind the transfers of step j = 0, at least two of them.
+            if (t + 3 <= t_hi) {
+                if (j == 1 && ss + 1 < s_hi) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM + 2) : "memory");
+                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM) : "memory");
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            __syncthreads();
+            if (j == 3) next_super();                                 // (the loaded codes are waited for here, not behind the transfers below)
+            __builtin_amdgcn_sched_barrier(0);
+            if (t + 3 < t_hi) issue(t + 3, st);
+            __builtin_amdgcn_sched_barrier(0);
+            if (j == 0 && ss + 1 < s_hi) load_super(ss + 1, cn, an);
+            if (j == 1) new_group(a1);
+            if (j == 3) new_group(a0);
+            read_act(stn, 0, sl[0]);
+            decode((j + 1) & 3, 0, sl[0]);
+            if (TM < 4) __builtin_amdgcn_sched_barrier(0);
+            multiply(sl[1]);
+            if (TM == 4) spread();
+            st = stn;
+        }
+    }
+
+    // the rank-r term: the last split contracts over t = s x A^T, 64 ranks at a time; rank 64 e + 16 kk + 8 h + i
+    if (p.r > 0 && s_hi == nsuper) {
+        for (int e = 0; e * 64 < p.r; ++e) {
+            __syncthreads();                                          // the stage's last reader is done
+            const uint32_t dst = smem_lds + wave * (TM * 1024);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int r = (wave * TM + i) * 8 + (lane >> 3);
+                dma16_s(p.ext_act + (size_t)m0 * p.RP + e * 64,
+                        (uint32_t)min(r, m_last) * (uint32_t)p.RP * 2u + (uint32_t)(((lane & 7) ^ ((r >> 1) & 7)) << 4), dst + i * 1024);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const int r0 = e * 64 + 16 * kk;
+                if (r0 >= p.r) break;                                 // uniform
+                const uint16_t* src = p.lora + (size_t)nc * p.r + r0 + 8 * h;
+                bf16x8_t wf;
+                if ((p.r & 7) == 0) {                                 // uniform: 16-byte pieces, in or out as a whole
+                    const uint4 v = r0 + 8 * h < p.r ? *reinterpret_cast<const uint4*>(src) : make_uint4(0u, 0u, 0u, 0u);
+                    wf = frag_of(v.x, v.y, v.z, v.w);
+                } else {
+                    uint32_t v[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = r0 + 8 * h + i < p.r ? src[i] : 0u;
+                    wf = frag_of(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+                }
+#pragma unroll
+                for (int tt = 0; tt < TM; ++tt) {
+                    const bf16x8_t f = *reinterpret_cast<const bf16x8_t*>(smem + (32 * tt + fi) * 128 + (((2 * kk + h) ^ ((fi >> 1) & 7)) << 4));
+                    acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, f, acc[tt], 0, 0, 0);
+                }
+            }
+        }
+    }
+    mid_epilogue<TM>(p, acc, smem, wave, lane, split, tile, n0, m0, p.N);
+}
+
+// ---- input gradient.  The contraction runs over channels while codes are packed along k (gemm_bwd.hip): a step's
+// 64 channels x 128 input features are decoded into an LDS tile [channel][k] and read back transposed.  Two roles per
+// thread: as mover (row 16 w + lane / 4, piece lane % 4) it brings 16 bytes of a row's codes, four of its levels and
+// its scales into registers two steps ahead and into LDS one step ahead, so that a row's 16, 32 or 64 code bytes are
+// one run of neighbouring lanes; as decoder (row lane, features 32 w .. + 31) it decodes 32 weights of ONE row and ONE
+// group.  Wavefront w multiplies output columns c0 + 32 w .. + 31 (weights as the A operand) with all tokens.
+constexpr int BM_WROW = 256;                                          // bytes per row of the weight tile: 128 k x bf16
+__device__ __forceinline__ int bmid_swz(int r, int c) { return r * BM_WROW + ((c ^ (((r & 3) << 2) | ((r >> 2) & 3))) << 4); }
+
+template <int TM, bool WIDE>
+struct BwdLds {
+    static constexpr int A = TM * 4096, W = 64 * BM_WROW;
+    static constexpr int C = WIDE ? 4096 : 2048;                      // staged codes: 64 rows x 64 (32) bytes
+    static constexpr int W0 = 2 * A, C0 = W0 + 2 * W, META0 = C0 + 2 * C, TAB0 = META0 + 2 * 1024;
+    // TAB0: WIDE with shared tables: all of them, once; else two buffers of a step's 64 rows (64 or 16 bytes each)
+};
+
+template <int TM, bool WIDE>
+__global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    using L = BwdLds<TM, WIDE>;
+    constexpr int ROWTAB = WIDE ? 64 : 16;                            // bytes of a row's staged levels
+    const uint32_t smem_lds = (uint32_t)(uintptr_t)(lptr_t)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fi = lane & 31, h = lane >> 5;
+    const int ntiles = p.tiles_c * p.tiles_m;
+    const int wg = xcd_tile(blockIdx.x, gridDim.x);
+    const int split = __builtin_amdgcn_readfirstlane(wg / ntiles);
+    const int tile = wg - split * ntiles;
+    const int mt = __builtin_amdgcn_readfirstlane(tile / p.tiles_c);
+    const int k0 = (tile - mt * p.tiles_c) * MID_COLS, m0 = mt * (32 * TM);
+    const int G = p.G, K = p.K, N = p.N;
+    const int nsteps = (N + 63) >> 6;
+    const int s_lo = split * p.per_split, s_hi = min(s_lo + p.per_split, nsteps);
+    const bool shared_tab = WIDE && p.C <= kMidLutBooks;
+    if (shared_tab)
+        for (int e = tid; e < p.C * kTableStride; e += MID_THREADS) reinterpret_cast<float*>(smem + L::TAB0)[e] = p.mappings[e];
+
+    // ---- activations: dY[m0.., 64 s ..], 128 bytes per token row, chunk c at c ^ ((row >> 1) & 7)
+    const int m_last = p.M - 1 - m0;
+    const uint16_t* act0 = p.act + (size_t)m0 * N;
+    uint32_t voff[TM], roff[TM];
+    int coff[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int r = (wave * TM + i) * 8 + (lane >> 3);
+        coff[i] = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+        roff[i] = (uint32_t)min(r, m_last) * (uint32_t)N * 2u;
+        voff[i] = roff[i] + (uint32_t)coff[i] * 2u;
+    }
+    auto issue = [&](int s, int buf) __attribute__((always_inline)) {
+        const uint32_t dst = smem_lds + buf * L::A + wave * (TM * 1024);
+        if (s * 64 + 64 <= N) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) dma16_s(act0 + s * 64, voff[i], dst + i * 1024);
+        } else {                                                      // channels past N: valid bytes, zero weights
+#pragma unroll
+            for (int i = 0; i < TM; ++i) dma16_s(act0, roff[i] + (uint32_t)min(s * 64 + coff[i], N - 8) * 2u, dst + i * 1024);
+        }
+    };
+
+    // ---- mover role
+    const int mrow = 16 * wave + (lane >> 2), piece = lane & 3;
+    const int g0 = k0 >> 6;
+    const bool two_groups = g0 + 1 < G;
+    struct Raw { uint4 codes; float4 lev; float a0, a1; RowInfo rec; };
+    auto load_rec = [&](int s) -> RowInfo { return p.rows[min(s * 64 + mrow, N - 1)]; };
+    auto load_raw = [&](int s, const RowInfo& rec, Raw& d) __attribute__((always_inline)) {
+        const int nr = s * 64 + mrow, ncl = min(nr, N - 1), bits = rec.bits();
+        const int row_bytes = K / 8 * bits;
+        // a piece past the row's codes of this tile fetches the last one again; 16 bytes before the row's end at the latest
+        const int off = min(k0 / 8 * bits + 16 * min(piece, bits - 1), row_bytes - 16);
+        d.codes = load16_u(p.packed + rec.offset + off);
+        if (!shared_tab) d.lev = *reinterpret_cast<const float4*>(p.mappings + (size_t)rec.cb() * kTableStride + (WIDE ? 4 * piece : 0));
+        d.a0 = load_scale(p, (size_t)ncl * G + g0);
+        d.a1 = load_scale(p, (size_t)ncl * G + (two_groups ? g0 + 1 : g0));
+        if (nr >= N) { d.a0 = 0.0f; d.a1 = 0.0f; }
+        if (!two_groups) d.a1 = 0.0f;
+        d.rec = rec;
+    };
+    auto stage_in = [&](int buf, const Raw& d) __attribute__((always_inline)) {
+        if (WIDE || piece < 2)
+            *reinterpret_cast<uint4*>(smem + L::C0 + buf * L::C + mrow * (WIDE ? 64 : 32) + ((piece ^ (WIDE ? (mrow >> 2) & 3 : (mrow >> 3) & 1)) << 4)) = d.codes;
+        if (piece == 0)
+            *reinterpret_cast<uint4*>(smem + L::META0 + buf * 1024 + mrow * 16) =
+                make_uint4(__builtin_bit_cast(uint32_t, d.a0), __builtin_bit_cast(uint32_t, d.a1), d.rec.bits_cb, 0u);
+        if (WIDE && !shared_tab) {                                    // level q of row r at 256 q + 4 r: a lookup touches bank r whatever the code
+            float* tab = reinterpret_cast<float*>(smem + L::TAB0 + buf * (64 * ROWTAB) + piece * 1024 + mrow * 4);
+            tab[0] = d.lev.x; tab[64] = d.lev.y; tab[128] = d.lev.z; tab[192] = d.lev.w;
+        } else if (!WIDE && piece == 0) {
+            *reinterpret_cast<float4*>(smem + L::TAB0 + buf * (64 * ROWTAB) + mrow * ROWTAB) = d.lev;
+        }
+    };
+
+    // ---- decoder role: 32 weights of row `lane`, features 32 wave .. + 31 of the tile (group wave / 2)
+    const bool tail_shift = !two_groups && K >= 128;                  // a 1-bit row's 16 bytes then start one group early
+    const int tab_shift = shared_tab ? 2 : 8;                         // uniform
+    struct Dec { uint32_t lo, hi, c4[4]; float a, v[2][8]; int bits; const uint8_t* tb; uint32_t SL, SH; };
+    Dec d;
+    auto decode_begin = [&](int buf) __attribute__((always_inline)) {
+        const uint4 meta = *reinterpret_cast<const uint4*>(smem + L::META0 + buf * 1024 + lane * 16);
+        d.a = __builtin_bit_cast(float, (wave >> 1) ? meta.y : meta.x);
+        d.bits = (int)(meta.z & 0xffu);
+        const bool one = d.bits == 1;
+        // my 32 codes: 4 bits: piece `wave`; 2 bits: half (wave & 1) of piece wave / 2; 1 bit: dword `wave` of piece 0
+        const int pc = d.bits == 4 ? wave : one ? 0 : wave >> 1;
+        const uint4 q = *reinterpret_cast<const uint4*>(smem + L::C0 + buf * L::C + lane * (WIDE ? 64 : 32) +
+                                                        ((pc ^ (WIDE ? (lane >> 2) & 3 : (lane >> 3) & 1)) << 4));
+        const int d1 = (wave + (tail_shift ? 2 : 0)) & 3;             // uniform
+        const uint32_t q1 = d1 == 0 ? q.x : d1 == 1 ? q.y : d1 == 2 ? q.z : q.w;
+        d.lo = one ? q1 : (wave & 1) ? q.z : q.x;
+        d.hi = (wave & 1) ? q.w : q.y;
+        if (WIDE) {
+            d.c4[0] = q.x; d.c4[1] = q.y; d.c4[2] = q.z; d.c4[3] = q.w;
+            d.tb = smem + L::TAB0 + (shared_tab ? (int)(meta.z >> 8) * (kTableStride * 4) : buf * (64 * ROWTAB) + lane * 4);
+        } else {
+            const NarrowConsts nk = narrow_consts(!one);
+            const float4 lv = *reinterpret_cast<const float4*>(smem + L::TAB0 + buf * (64 * ROWTAB) + lane * ROWTAB);
+            const uint32_t P01 = pack_bf16x2(lv.x * d.a, lv.y * d.a), P23 = pack_bf16x2(lv.z * d.a, lv.w * d.a);
+            d.SL = __builtin_amdgcn_perm(P23, P01, nk.sell); d.SH = __builtin_amdgcn_perm(P23, P01, nk.selh);
+        }
+    };
+    auto decode_look = [&](int kk) __attribute__((always_inline)) {   // WIDE: the lookups of chunk kk
+        if (!WIDE) return;
+        const uint32_t c2 = ((kk >> 1) ? d.hi : d.lo) >> (16 * (kk & 1)), c1 = d.lo >> (8 * kk);
+        const uint32_t c21 = d.bits == 1 ? c1 : c2;
+        const uint32_t cw = d.bits == 4 ? d.c4[kk] : c21;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            d.v[kk & 1][i] = *reinterpret_cast<const float*>(d.tb + (__builtin_amdgcn_ubfe(cw, (uint32_t)(i * d.bits), (uint32_t)d.bits) << tab_shift));
+    };
+    auto decode_put = [&](int kk, uint8_t* wt) __attribute__((always_inline)) {
+        if (WIDE) {
+            const float (&v)[8] = d.v[kk & 1];
+            *reinterpret_cast<uint4*>(wt + bmid_swz(lane, wave * 4 + kk)) =
+                make_uint4(pack_bf16x2(v[0] * d.a, v[1] * d.a), pack_bf16x2(v[2] * d.a, v[3] * d.a), pack_bf16x2(v[4] * d.a, v[5] * d.a),
+                           pack_bf16x2(v[6] * d.a, v[7] * d.a));
+        } else {
+            const uint32_t c2 = ((kk >> 1) ? d.hi : d.lo) >> (16 * (kk & 1)), c1 = d.lo >> (8 * kk);
+            *reinterpret_cast<bf16x8_t*>(wt + bmid_swz(lane, wave * 4 + kk)) =
+                narrow8(d.bits == 1 ? c1 : c2, d.SL, d.SH, narrow_consts(d.bits != 1));
+        }
+    };
+
+    // ---- multiplier role
+    floatx16_t acc[TM];
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+    int aoff[4], troff[2];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) aoff[kk] = fi * 128 + (((2 * kk + h) ^ ((fi >> 1) & 7)) << 4);
+    {   // transposing reads: lane L of a 16-lane group points at channel L / 4 of its four, 8 bytes at k 4 (L % 4)
+        const int L16 = lane & 15, grp = (lane >> 4) & 1;
+#pragma unroll
+        for (int eb = 0; eb < 2; ++eb)
+            troff[eb] = bmid_swz(h * 8 + eb * 4 + (L16 >> 2), wave * 4 + grp * 2 + ((L16 & 3) >> 1)) + (L16 & 1) * 8;
+    }
+    struct Slice { bf16x8_t f[TM], wf; };
+    auto read_slice = [&](const uint8_t* at, uint32_t wt_lds, int kk, Slice& o) __attribute__((always_inline)) {
+        const mid_v4i16_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((mid_lds_v4i16_ptr)(uintptr_t)(wt_lds + troff[0] + kk * 16 * BM_WROW));
+        const mid_v4i16_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((mid_lds_v4i16_ptr)(uintptr_t)(wt_lds + troff[1] + kk * 16 * BM_WROW));
+        const mid_v8i16_t v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        o.wf = __builtin_bit_cast(bf16x8_t, v);
+#pragma unroll
+        for (int t = 0; t < TM; ++t) o.f[t] = *reinterpret_cast<const bf16x8_t*>(at + aoff[kk] + t * 4096);
+    };
+    auto multiply = [&](const Slice& o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < TM; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.wf, o.f[t], acc[t], 0, 0, 0);
+    };
+
+    // Pipeline.  Step s, buffers s & 1: slices 0..2 multiply while the weight tile of step s + 1 is decoded from the staged
+    // codes; then the step's barrier (tile s + 1 is complete, the buffers of step s are free); under slice 3 the first
+    // operands of step s + 1 are read, the activations of step s + 2 are sent for, the raw data of step s + 3 goes from
+    // registers to LDS and that of step s + 4 is asked for.  Steps past the end fetch the last one again: what is decoded
+    // of them is never multiplied.
+    const int s_end = s_hi - 1;
+    Raw raw;
+    RowInfo rec = load_rec(s_lo);
+    issue(s_lo, s_lo & 1);
+    issue(min(s_lo + 1, s_end), (s_lo + 1) & 1);
+    load_raw(s_lo, rec, raw);
+    rec = load_rec(min(s_lo + 1, s_end));
+    stage_in(s_lo & 1, raw);
+    load_raw(min(s_lo + 1, s_end), rec, raw);
+    rec = load_rec(min(s_lo + 2, s_end));
+    stage_in((s_lo + 1) & 1, raw);
+    load_raw(min(s_lo + 2, s_end), rec, raw);
+    rec = load_rec(min(s_lo + 3, s_end));
+    __syncthreads();
+    decode_begin(s_lo & 1);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) { decode_look(kk); decode_put(kk, smem + L::W0 + (s_lo & 1) * L::W); }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    stage_in(s_lo & 1, raw);                                          // step s_lo + 2
+    load_raw(min(s_lo + 3, s_end), rec, raw);
+    rec = load_rec(min(s_lo + 4, s_end));
+    Slice sl[2];
+    read_slice(smem + (s_lo & 1) * L::A, smem_lds + L::W0 + (s_lo & 1) * L::W, 0, sl[0]);
+
+    auto step = [&](int s, auto B_) __attribute__((always_inline)) {
+        constexpr int b = decltype(B_)::value;
+        const uint8_t* at = smem + b * L::A;
+        const uint32_t wt_lds = smem_lds + L::W0 + b * L::W;
+        uint8_t* wn = smem + L::W0 + (b ^ 1) * L::W;
+        decode_begin(b ^ 1);
+        read_slice(at, wt_lds, 1, sl[1]);
+        decode_look(0);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(sl[0]);
+        decode_look(1);
+        read_slice(at, wt_lds, 2, sl[0]);
+        decode_put(0, wn);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(sl[1]);
+        decode_look(2);
+        read_slice(at, wt_lds, 3, sl[1]);
+        decode_put(1, wn);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(sl[0]);
+        decode_look(3);
+        decode_put(2, wn);
+        decode_put(3, wn);
+        // the activation transfers of step s + 1 are older than the loads for the steps ahead: at least four of those
+        // (codes, two scales, record) may stay in flight
+        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        __syncthreads();
+        stage_in(b ^ 1, raw);                                         // step s + 3
+        asm volatile("" : "+v"(rec.offset), "+v"(rec.bits_cb));       // wait for the record here, not behind the transfers below
+        read_slice(smem + (b ^ 1) * L::A, smem_lds + L::W0 + (b ^ 1) * L::W, 0, sl[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(sl[1]);
+        issue(min(s + 2, s_end), b);
+        __builtin_amdgcn_sched_barrier(0);
+        load_raw(min(s + 4, s_end), rec, raw);
+        rec = load_rec(min(s + 5, s_end));
+    };
+    int s = s_lo;
+    if (s & 1) step(s++, std::integral_constant<int, 1>{});
+    for (; s + 2 <= s_hi; s += 2) {
+        step(s, std::integral_constant<int, 0>{});
+        step(s + 1, std::integral_constant<int, 1>{});
+    }
+    if (s < s_hi) step(s, std::integral_constant<int, 0>{});
+
+    // the rank-r term: the last split contracts over u = s dY B against the rows of A, 64 ranks at a time
+    if (p.r > 0 && s_hi == nsteps) {
+        for (int e = 0; e * 64 < p.r; ++e) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // no transfer of the steps above lands here any more
+            __syncthreads();                                          // ... and the buffers' last readers are done
+            const uint32_t dst = smem_lds + wave * (TM * 1024);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                dma16_s(p.ext_act + (size_t)m0 * p.RP + e * 64,
+                        (uint32_t)min((wave * TM + i) * 8 + (lane >> 3), m_last) * (uint32_t)p.RP * 2u + (uint32_t)coff[i] * 2u, dst + i * 1024);
+            const int j = e * 64 + lane;
+            const bool ok = j < p.r && k0 + 32 * wave < K;
+            const uint4* src = reinterpret_cast<const uint4*>(p.lora + (size_t)(ok ? j : 0) * K + (ok ? k0 + 32 * wave : 0));
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+                *reinterpret_cast<uint4*>(smem + L::W0 + bmid_swz(lane, wave * 4 + kk)) = ok ? src[kk] : make_uint4(0u, 0u, 0u, 0u);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) { read_slice(smem, smem_lds + L::W0, kk, sl[0]); multiply(sl[0]); }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // transfers past the end: none may land in the output stage
+    mid_epilogue<TM>(p, acc, smem, wave, lane, split, tile, k0, m0, K);
+}
+
+// out = bf16(sum of the splits' partial tiles, in split order).  A thread owns four columns of one token.
+__global__ __launch_bounds__(256) void mid_sum_kernel(const float4* __restrict__ part, int splits, int ntiles, int tiles_c, int TM,
+                                                      int M, int cols, uint16_t* __restrict__ out) {
+    const size_t per = (size_t)ntiles * TM * 1024;                    // float4 per split
+    const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= per) return;
+    float4 a = part[e];
+    int s = 1;
+    for (; s + 3 < splits; s += 4) {
+        const float4 b0 = part[s * per + e], b1 = part[(s + 1) * per + e], b2 = part[(s + 2) * per + e], b3 = part[(s + 3) * per + e];
+        a.x = (((a.x + b0.x) + b1.x) + b2.x) + b3.x; a.y = (((a.y + b0.y) + b1.y) + b2.y) + b3.y;
+        a.z = (((a.z + b0.z) + b1.z) + b2.z) + b3.z; a.w = (((a.w + b0.w) + b1.w) + b2.w) + b3.w;
+    }
+    for (; s < splits; ++s) {
+        const float4 b = part[s * per + e];
+        a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    }
+    const int lane = (int)(e & 63), vq = (int)(e >> 6) & 3;
+    const int q = (int)(e >> 8), t = q % TM, wt = q / TM, wave = wt & 3, tile = wt >> 2;
+    const int col = (tile % tiles_c) * MID_COLS + 32 * wave + 8 * vq + 4 * (lane >> 5);
+    const int m = (tile / tiles_c) * (32 * TM) + 32 * t + (lane & 31);
+    if (m < M && col < cols) *reinterpret_cast<uint2*>(out + (size_t)m * cols + col) = make_uint2(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w));
+}
+
+template <int TM, bool WIDE>
+hipError_t launch_mid_variant(const MidParams& p, int op, hipStream_t st) {
+    const unsigned grid = (unsigned)(p.tiles_c * p.tiles_m * p.splits);
+    if (op == 0) {
+        constexpr int sh = 3 * TM * 4096 + (WIDE ? 4 * 4096 : 0);
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mid_fwd_kernel<TM, WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize, sh);
+        if (attr != hipSuccess) return attr;
+        mid_fwd_kernel<TM, WIDE><<<dim3(grid), dim3(MID_THREADS), sh, st>>>(p);
+    } else {
+        using L = BwdLds<TM, WIDE>;
+        constexpr int most = L::TAB0 + 2 * 64 * (WIDE ? 64 : 16);
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mid_bwd_kernel<TM, WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+        if (attr != hipSuccess) return attr;
+        const int sh = WIDE && p.C <= kMidLutBooks ? L::TAB0 + p.C * kTableStride * 4 : most;
+        static_assert(kMidLutBooks * kTableStride * 4 <= 2 * 64 * 64, "either table scheme fits the region");
+        mid_bwd_kernel<TM, WIDE><<<dim3(grid), dim3(MID_THREADS), sh, st>>>(p);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// ---- which calls take these kernels, with which tile height and how many splits: the shortest estimated time.  The
+// estimate of a plan is a launch cost, the steps of a workgroup times the time of a step, and with splits the partial
+// tiles' way out and back.  A step takes `solo` us while its compute unit has few workgroups and `share` us per resident
+// workgroup once their instructions fill it; the figures are least-squares fits to 2493 timings (7 shapes from
+// 4096 x 1024 to 5120 x 13824, 24 to 2048 tokens, all heights, 1 to 32 splits; rms error 7 - 14 %, and the plan picked is
+// on average within 1 % of the best one measured).  The 256-column kernels' time, fitted in the same way, is compared
+// with it: they win once their tiles fill the chip, from about 1300 tokens of a 4096 x 4096 layer (forward) or 700 (input
+// gradient) on: 2048 tokens at 50/50 % of 1-/2-bit rows, forward 70 us against 75, input gradient 80 against 94.
+struct MidCost {
+    double solo[4], share[4];        // us per step (64 of the contraction) at TM = 1..4
+    double launch, split, per_byte;  // us per call; us more when split; us per byte of partial tiles
+    double big_launch, big_step;     // the 256-column kernel: us per call, us per step of a 256 x 256 tile
+};
+static const MidCost kMidCost[2][3] = {
+    // forward: 1- and 2-bit rows only; with 4-bit rows, up to kMidLutBooks codebooks; with 4-bit rows, more codebooks
+    {{{0.47, 0.47, 0.53, 0.77}, {0.24, 0.39, 0.45, 0.60}, 3.9, 6.7, 1.6e-7, 5.4, 1.32},
+     {{0.47, 0.64, 0.65, 0.80}, {0.35, 0.41, 0.54, 0.60}, 6.0, 5.2, 2.6e-7, 7.9, 1.89},
+     {{0.48, 0.63, 0.66, 0.81}, {0.36, 0.42, 0.55, 0.62}, 7.3, 3.8, 2.5e-7, 8.6, 1.87}},
+    // input gradient
+    {{{0.62, 0.73, 0.81, 0.95}, {0.47, 0.55, 0.58, 0.66}, 6.0, 4.7, 2.8e-7, 14.8, 1.28},
+     {{0.80, 1.01, 0.95, 1.01}, {0.51, 0.65, 0.68, 0.76}, 7.1, 4.3, 2.7e-7, 9.6, 2.03},
+     {{0.78, 0.84, 1.00, 1.00}, {0.64, 0.68, 0.70, 0.80}, 8.7, 2.8, 2.8e-7, 14.8, 2.50}}};
+static const int kMidResident[2][4] = {{4, 3, 2, 2}, {3, 3, 2, 2}};   // workgroups per compute unit (registers, LDS)
+constexpr size_t kMidPartMax = (size_t)64 << 20;
+
+MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_bytes) {
+    MidPlan best{0, 0, 0, 0, 0};
+    const int cols = op == 0 ? N : K, unit = op == 0 ? 4 : 1;         // steps that a split takes as a whole
+    const int units = op == 0 ? (K / 64 + 3) / 4 : (N + 63) / 64;
+    const int tiles_c = (cols + kMidCols - 1) / kMidCols, cus = device_compute_units();
+    if ((long long)tiles_c * ((M + 127) / 128) > 16LL * cus) return best;   // far beyond what is compared below
+    const int cls = !wide ? 0 : C <= kMidLutBooks ? 1 : 2;
+    const MidCost& mc = kMidCost[op][cls];
+    const size_t cap = std::min(part_bytes, kMidPartMax);
+    double best_t = 1e300;
+    // with a table per row the input gradient's LDS holds one workgroup of four tile rows per compute unit, not two
+    const int tm_max = op == 1 && cls == 2 ? 3 : 4;
+    for (int TM = 1; TM <= tm_max && (TM == 1 || 32 * (TM - 1) < M); ++TM) {
+        MidPlan pl{TM, tiles_c, (M + 32 * TM - 1) / (32 * TM), 0, 0};
+        const int res = kMidResident[op][TM - 1];
+        for (int S = 1; S <= 32 && S <= units; S += S < 6 ? 1 : S < 12 ? 2 : 4) {
+            pl.per_split = (units + S - 1) / S;
+            pl.splits = (units + pl.per_split - 1) / pl.per_split;
+            if (pl.splits > 1 && mid_part_bytes(pl) > cap) break;
+            const long long wgs = (long long)pl.tiles_c * pl.tiles_m * pl.splits, n = (wgs + cus - 1) / cus;
+            auto step = [&](long long k) { return k ? std::max(mc.solo[TM - 1], (double)k * mc.share[TM - 1]) : 0.0; };
+            double t = mc.launch + (double)pl.per_split * unit * ((double)(n / res) * step(res) + step(n % res));
+            if (pl.splits > 1) t += mc.split + (double)mid_part_bytes(pl) * mc.per_byte;
+            if (t < best_t * (1.0 - 1e-9)) { best_t = t; best = pl; }
+        }
+    }
+    const double big = op == 0 ? gemm_fwd_steps(N, K, M, (best_t - mc.big_launch) / mc.big_step) : gemm_bwd_steps(N, K, M);
+    double big_t = mc.big_launch + big * mc.big_step;
+    if (op == 1) {
+        const BwdSplitPlan sp = gemm_bwd_split_plan(N, K, M);
+        if (sp.splits > 1) big_t += 5.0 + (double)sp.splits * sp.tail * BM * BN * sizeof(float) * mc.per_byte;
+    }
+    // (the two estimates' errors are about this large: without the margin 2048 tokens of a 4096 x 4096 layer came here
+    // and a training step on it took 1 % longer)
+    if (big_t <= 1.08 * best_t) best = MidPlan{0, 0, 0, 0, 0};
+    return best;
+}
+
+hipError_t launch_gemm_mid(const MidParams& p, int op, int TM, bool wide, hipStream_t st) {
+    hipError_t e = hipErrorInvalidValue;
+    if (TM == 1) e = wide ? launch_mid_variant<1, true>(p, op, st) : launch_mid_variant<1, false>(p, op, st);
+    if (TM == 2) e = wide ? launch_mid_variant<2, true>(p, op, st) : launch_mid_variant<2, false>(p, op, st);
+    if (TM == 3) e = wide ? launch_mid_variant<3, true>(p, op, st) : launch_mid_variant<3, false>(p, op, st);
+    if (TM == 4) e = wide ? launch_mid_variant<4, true>(p, op, st) : launch_mid_variant<4, false>(p, op, st);
+    if (e != hipSuccess || p.splits <= 1) return e;
+    const int ntiles = p.tiles_c * p.tiles_m;
+    const int cols = op == 0 ? p.N : p.K;
+    mid_sum_kernel<<<dim3((unsigned)((size_t)ntiles * TM * 4)), dim3(256), 0, st>>>(reinterpret_cast<const float4*>(p.part), p.splits, ntiles,
+                                                                                   p.tiles_c, TM, p.M, cols, p.out);
+    return hipGetLastError();
+}
+
+}  // namespace lowra

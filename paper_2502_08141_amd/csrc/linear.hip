@@ -10,7 +10,7 @@
 #include <atomic>
 #include <new>
 
-#include "gemm_common.h"
+#include "gemm_mid.h"
 
 namespace lowra {
 
@@ -80,8 +80,36 @@ size_t expanded_scale_bytes(const lowra_layout& L) {
 static size_t gemv_workspace_bytes(const lowra_layout& L, int r);
 static size_t linear_workspace_bytes_fp32(const lowra_layout& L, int op, int M, int r);
 static size_t bwd_split_bytes(const lowra_layout& L, int M);
-size_t linear_workspace_bytes(const lowra_layout& L, int op, int M, int r) {
+
+// The mid-token GEMM's plan for a call under LOWRA_PATH_AUTO (TM == 0: another kernel takes it).  `gemm`: no small-token
+// kernel takes the call.  `part_bytes`: workspace left for partial tiles.
+static MidPlan mid_plan_of(const lowra_layout& L, int op, int M, int r, int gemm, size_t part_bytes) {
+    MidPlan none{0, 0, 0, 0, 0};
+    if (!gemm || L.G < 2 || M < 1) return none;
+    if (M <= 16 && (op == 0 ? gemv_fwd_supported(L, M) : gemv_stream_bwd_supported(L, M, r))) return none;
+    return plan_mid(op, L.N, L.K, M, L.n_by_bits[4] > 0, L.C, part_bytes);
+}
+static MidParams mid_params(const lowra_layout& L, const LinearArgs& a, int op, int RP, const uint16_t* side, const MidPlan& pl, size_t least) {
+    MidParams p;
+    p.rows = L.d_rows; p.packed = a.packed; p.absmax = a.absmax; p.mappings = a.mappings; p.act = a.act; p.ext_act = side;
+    p.lora = op == 0 ? a.B : a.A; p.out = a.out;
+    p.part = pl.splits > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(a.workspace) + align256(least)) : nullptr;
+    p.M = a.M; p.N = L.N; p.K = L.K; p.G = L.G; p.C = L.C; p.r = a.r; p.RP = RP; p.scale_bf16 = L.scale_bf16;
+    p.tiles_c = pl.tiles_c; p.tiles_m = pl.tiles_m; p.splits = pl.splits; p.per_split = pl.per_split;
+    return p;
+}
+static MidPlan mid_plan_call(const lowra_layout& L, const LinearArgs& a, int op, bool gemm) {
+    const size_t least = align256(linear_workspace_min(L, op, a.M, a.r));
+    return mid_plan_of(L, op, a.M, a.r, gemm, a.workspace && a.workspace_bytes > least ? a.workspace_bytes - least : 0);
+}
+size_t linear_workspace_min(const lowra_layout& L, int op, int M, int r) {
     return align256(linear_workspace_bytes_fp32(L, op, M, r)) + expanded_scale_bytes(L);
+}
+// what a call can use: the scratch it cannot do without, then the partial tiles of a mid-token GEMM's splits
+size_t linear_workspace_bytes(const lowra_layout& L, int op, int M, int r) {
+    const size_t least = linear_workspace_min(L, op, M, r);
+    const MidPlan pl = mid_plan_of(L, op, M, r, 1, ~(size_t)0);
+    return pl.splits > 1 ? align256(least) + mid_part_bytes(pl) : least;
 }
 // With bf16 scales: widen them behind the call's own scratch and run the call on the copy.
 static hipError_t with_fp32_scales(const lowra_layout& L, int op, const LinearArgs& a, LinearArgs& b, bool native, hipStream_t st) {
@@ -132,7 +160,9 @@ static size_t gemv_workspace_bytes(const lowra_layout& L, int r) {
 hipError_t launch_linear_fwd(const lowra_layout& L, const LinearArgs& a_in, int path, int tiling, hipStream_t st) {
     if (a_in.M == 0 || L.N == 0) return hipSuccess;
     LinearArgs a;
-    hipError_t e_scales = with_fp32_scales(L, 0, a_in, a, path == 1 && gemv_stream_supported(L, a_in.M, a_in.r), st);
+    // LOWRA_PATH_GEMM and a forced tiling keep the 256-column kernels
+    const MidPlan mid = mid_plan_call(L, a_in, 0, path != 2 && tiling < 0);
+    hipError_t e_scales = with_fp32_scales(L, 0, a_in, a, mid.TM > 0 || (path == 1 && gemv_stream_supported(L, a_in.M, a_in.r)), st);
     if (e_scales != hipSuccess) return e_scales;
     const int RP = a.r > 0 ? round_up(a.r, BK) : 0;
     // A single matrix is too little work for the streaming kernel's set-up (descriptor kernel, tables, pipeline fill):
@@ -150,6 +180,17 @@ hipError_t launch_linear_fwd(const lowra_layout& L, const LinearArgs& a_in, int 
         g.M = a.M; g.N = L.N; g.K = L.K; g.G = L.G; g.r = a.r; g.RT = a.r > 0 ? round_up(a.r, 16) : 0;
         KernelTimer timer(st);
         return launch_gemv_fwd(g, st);
+    }
+    if (mid.TM > 0) {
+        uint16_t* ws_t = static_cast<uint16_t*>(a.workspace);
+        if (RP) {
+            hipError_t e = launch_skinny_ws(a.act, L.K, a.M, a.A, L.K, a.r, L.K, a.s, ws_t, RP,
+                                            reinterpret_cast<float*>(static_cast<uint8_t*>(a.workspace) + align256((size_t)a.M * RP * 2) +
+                                                                     (a.r == RP ? 0 : align256((size_t)L.N * RP * 2))), st);
+            if (e != hipSuccess) return e;
+        }
+        KernelTimer timer(st);
+        return launch_gemm_mid(mid_params(L, a, 0, RP, ws_t, mid, linear_workspace_min(L, 0, a.M, a.r)), 0, mid.TM, L.n_by_bits[4] > 0, st);
     }
     GemmParams p;
     fill_params(p, L, a, RP);
@@ -174,7 +215,8 @@ hipError_t launch_linear_fwd(const lowra_layout& L, const LinearArgs& a_in, int 
 hipError_t launch_linear_bwd_input(const lowra_layout& L, const LinearArgs& a_in, int path, hipStream_t st) {
     if (a_in.M == 0) return hipSuccess;
     LinearArgs a;
-    hipError_t e_scales = with_fp32_scales(L, 1, a_in, a, path != 2 && gemv_stream_bwd_supported(L, a_in.M, a_in.r), st);
+    const MidPlan mid = mid_plan_call(L, a_in, 1, path != 2);
+    hipError_t e_scales = with_fp32_scales(L, 1, a_in, a, mid.TM > 0 || (path != 2 && gemv_stream_bwd_supported(L, a_in.M, a_in.r)), st);
     if (e_scales != hipSuccess) return e_scales;
     // Few tokens: the streaming kernel reads the codes once at the memory's pace (the GEMM below would pad the tokens
     // to a 256-row tile).  LOWRA_PATH_GEMM keeps the GEMM.
@@ -209,6 +251,8 @@ hipError_t launch_linear_bwd_input(const lowra_layout& L, const LinearArgs& a_in
         p.ext_act = ws_u;
     }
     KernelTimer timer(st);
+    if (mid.TM > 0)
+        return launch_gemm_mid(mid_params(L, a, 1, RP, p.ext_act, mid, linear_workspace_min(L, 1, a.M, a.r)), 1, mid.TM, L.n_by_bits[4] > 0, st);
     return launch_gemm_bwd(p, st);
 }
 

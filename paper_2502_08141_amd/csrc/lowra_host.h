@@ -155,6 +155,7 @@ struct LinearArgs {
     float s;
     uint16_t* out;         // y [M,N] (fwd) or dX [M,K] (bwd)
     void* workspace;
+    size_t workspace_bytes;
 };
 // bf16 group scales -> fp32 (exact), for the kernels that read fp32 scales
 hipError_t launch_expand_scales(const uint16_t* src, size_t count, float* dst, hipStream_t st);
@@ -168,7 +169,8 @@ struct KernelTimer {
     explicit KernelTimer(hipStream_t s);
     ~KernelTimer();
 };
-size_t linear_workspace_bytes(const lowra_layout& L, int op, int M, int r);
+size_t linear_workspace_min(const lowra_layout& L, int op, int M, int r);     // less than this is refused
+size_t linear_workspace_bytes(const lowra_layout& L, int op, int M, int r);   // what lowra_workspace_bytes reports: room to split as well
 void plan_fwd_tiling(int N, int M, int units, int* rows_a, int* rows_b, int* cols_a);
 // tiling: -1, or the forward GEMM's tile plan forced by lowra_set_fwd_tiling
 hipError_t launch_linear_fwd(const lowra_layout& L, const LinearArgs& a, int path, int tiling, hipStream_t st);

@@ -1,0 +1,96 @@
+"""The fused GEMMs for the token counts between the small-token kernels and the large output grids (17 to a few hundred
+tokens, and 1 to 16 where no small-token kernel takes the shape), under LOWRA_PATH_AUTO.
+
+Every case is held to the oracle by the 2e-2 rule of the linear outputs, and to the 256-column kernels
+(LOWRA_PATH_GEMM), which multiply the same bf16 weights and activations: the two differ in the order of fp32 sums only,
+so by at most one unit in the last place of the bf16 output, 2^-7 of the entry (or of the output's rms, where
+cancellation leaves an entry smaller than its terms)."""
+import pytest
+import torch
+
+from oracle import lowra_oracle as orc
+from paper_2502_08141_amd import lowra, synth
+from tests.gpu_util import REL_TOL, bf16_host_f64, rel_err
+from tests.gpu_util import DeviceLayer
+
+pytestmark = pytest.mark.gpu
+
+ORDER_TOL = 2.0 ** -7
+
+MIXED, NARROW = (0.4, 0.3, 0.3), (0.5, 0.5, 0.0)
+# N, K, M, r, shares of 1/2/4-bit rows, one table per channel, bf16 scales.  Token counts around the tile heights of 32,
+# 64, 96 and 128 rows; group counts of every remainder by four (a superstep is four groups; odd counts leave the input
+# gradient half a column tile); channels that leave partial tiles and steps; ranks below, across and above 64.
+CASES = [
+    (264, 128, 17, 8, MIXED, False, False),
+    (136, 192, 33, 5, MIXED, True, True),
+    (520, 320, 40, 64, NARROW, False, False),
+    (8, 704, 100, 100, (0.0, 0.0, 1.0), False, False),
+    (1136, 832, 66, 8, MIXED, False, True),
+    (1000, 1088, 130, 12, (0.85, 0.15, 0.0), True, False),
+    (72, 2112, 300, 0, (1.0, 0.0, 0.0), False, False),
+    (200, 256, 257, 64, (0.0, 1.0, 0.0), False, True),
+    (2056, 1024, 96, 128, MIXED, True, False),
+    (4096, 2048, 31, 16, NARROW, False, False),
+    (1032, 4160, 128, 64, MIXED, False, False),
+    (328, 128, 9, 40, MIXED, False, False),
+    (136, 576, 3, 64, NARROW, True, False),
+    (512, 512, 500, 32, MIXED, False, False),
+]
+
+
+@pytest.mark.parametrize("shape", CASES, ids=lambda s: f"{s[0]}x{s[1]}m{s[2]}r{s[3]}")
+def test_mid_token_linear(shape):
+    N, K, M, r, fr, per_channel, bf16_scales = shape
+    print(f"[mid {shape}]", flush=True)
+    L = synth.make_custom(N, K, M, max(r, 1), fractions=fr, seed=700 + N % 97, per_channel_tables=per_channel)
+    D = DeviceLayer(L)
+    if bf16_scales:
+        D.layout.set_scale_dtype(torch.bfloat16)
+    packed, absmax = lowra.lowra_quantize(D.layout, D.W, D.thr)
+    A, B = (D.A, D.B) if r else (None, None)
+    rp, ra = orc.quantize(L.W, L.bits, L.cb, L.thresholds, **({"scale_dtype": "bf16"} if bf16_scales else {}))
+    hA, hB = (L.A, L.B) if r else (None, None)
+    calls = {
+        "forward": (lambda ws: lowra.lowra_linear_fwd(D.layout, packed, absmax, D.mp, D.x, A, B, L.s, workspace=ws), lowra.OP_LINEAR_FWD,
+                    orc.linear_fwd(rp, ra, L.bits, L.cb, L.mappings, L.x, hA, hB, L.s)),
+        "input gradient": (lambda ws: lowra.lowra_linear_bwd_input(D.layout, packed, absmax, D.mp, D.dY, A, B, L.s, workspace=ws), lowra.OP_LINEAR_BWD_INPUT,
+                           orc.linear_bwd_input(rp, ra, L.bits, L.cb, L.mappings, L.dY, hA, hB, L.s, L.K)),
+    }
+    for name, (call, op, ref) in calls.items():
+        need = D.layout.workspace_bytes(op, M, r)
+        ws = torch.empty(max(need, 256), dtype=torch.uint8, device="cuda")
+        got = call(ws)
+        again = call(ws)
+        lowra.lowra_set_linear_path(lowra.PATH_GEMM)
+        try:
+            gemm = call(ws)
+        finally:
+            lowra.lowra_set_linear_path(lowra.PATH_AUTO)
+        torch.cuda.synchronize()
+        assert torch.equal(got.view(torch.int16), again.view(torch.int16)), name          # splits are added in a fixed order
+        g, e = bf16_host_f64(got), rel_err(bf16_host_f64(got), ref)
+        print(f"    {name}: rel {e:.2e}, against the 256-column kernel {rel_err(g, bf16_host_f64(gemm)):.2e}", flush=True)
+        assert e <= REL_TOL, name
+        if M > 16:                                            # (with fewer the forward is a small-token kernel: another decode)
+            assert rel_err(g, bf16_host_f64(gemm)) <= ORDER_TOL, name
+
+
+def test_mid_token_less_workspace():
+    """A workspace that holds less than lowra_workspace_bytes asks for, but what the call cannot do without, is taken: the
+    contraction is then split between fewer workgroups, or not at all."""
+    L = synth.make_custom(1032, 2048, 40, 64, fractions=MIXED, seed=771)
+    D = DeviceLayer(L)
+    D.quantize()
+    want = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, L.s)
+    need = D.layout.workspace_bytes(lowra.OP_LINEAR_FWD, L.M, L.r)
+    side = (L.M * 64 * 2 + 255) // 256 * 256                  # the rank-r intermediate alone
+    assert need > side                                        # 40 tokens of this shape are split
+    for size in (need - 256, (need + side) // 2, side):
+        got = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, L.s,
+                                     workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        assert rel_err(bf16_host_f64(got), bf16_host_f64(want)) <= ORDER_TOL
+    with pytest.raises(lowra.LowraError, match="workspace too small"):
+        lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, L.s,
+                               workspace=torch.empty(side - 256, dtype=torch.uint8, device="cuda"))
