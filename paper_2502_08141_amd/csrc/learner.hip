@@ -277,31 +277,47 @@ hipError_t launch_learn_tables(const lowra_layout& L, const float* W, const floa
 // ---------------------------------------------------------------------------------------------
 // Threshold averaging (Sec. 5): entry j of every b-bit channel becomes the mean of entry j over
 // the matrix's b-bit channels.  One workgroup per (width, entry): fixed-order fp64 sum, then the
-// write-back.  In place on thr [N][16].
-__global__ __launch_bounds__(256) void average_thresholds_kernel(const RowInfo* __restrict__ rows, int N, float* __restrict__ thr) {
-    __shared__ double part[4];
-    __shared__ long long cnt_part[4];
-    const int widx = blockIdx.x / 15, j = blockIdx.x % 15;      // widths 1, 2, 4
+// write-back.  In place on thr [N][16].  A column's entries lie in one cache line each, so a workgroup's time is
+// that of its round trips: 1024 threads with twelve channels each in flight per trip.  11008 channels, half of
+// them 1- and half 2-bit: 14.5 us; 256 threads with one dependent pair of loads at a time took 34.
+__global__ __launch_bounds__(1024) void average_thresholds_kernel(const RowInfo* __restrict__ rows, int N, float* __restrict__ thr) {
+    __shared__ double part[16];
+    __shared__ int cnt_part[16];
+    const int widx = blockIdx.x < 1 ? 0 : blockIdx.x < 4 ? 1 : 2;         // 1 + 3 + 15 columns for widths 1, 2, 4
+    const int j = (int)blockIdx.x - (widx == 0 ? 0 : widx == 1 ? 1 : 4);
     const int b = 1 << widx;
-    if (j >= (1 << b) - 1) return;                               // uniform
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double s = 0.0, c = 0.0;
-    for (int n = tid; n < N; n += 256)
-        if (rows[n].bits() == b) { s += (double)thr[(size_t)n * kTableStride + j]; c += 1.0; }
-    s = wave_sum(s); c = wave_sum(c);
-    if (lane == 0) { part[wave] = s; cnt_part[wave] = (long long)c; }
+    constexpr int U = 12;
+    double s = 0.0;
+    int c = 0;
+    for (int n0 = tid; n0 < N; n0 += 1024 * U) {
+        bool mine[U];
+        float v[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) mine[i] = n0 + 1024 * i < N && (int)(rows[min(n0 + 1024 * i, N - 1)].bits_cb & 0xffu) == b;
+#pragma unroll
+        for (int i = 0; i < U; ++i) v[i] = mine[i] ? thr[(size_t)(n0 + 1024 * i) * kTableStride + j] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < U; ++i) { s += (double)v[i]; c += mine[i] ? 1 : 0; }
+    }
+    s = wave_sum(s);
+    for (int o = 32; o; o >>= 1) c += __shfl_xor(c, o);
+    if (lane == 0) { part[wave] = s; cnt_part[wave] = c; }
     __syncthreads();
-    const double tot = part[0] + part[1] + part[2] + part[3];
-    const long long cnt = cnt_part[0] + cnt_part[1] + cnt_part[2] + cnt_part[3];
+    double tot = 0.0;
+    int cnt = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) { tot += part[w]; cnt += cnt_part[w]; }
     if (cnt == 0) return;
     const float m = (float)(tot / (double)cnt);
-    for (int n = tid; n < N; n += 256)
-        if (rows[n].bits() == b) thr[(size_t)n * kTableStride + j] = m;
+    for (int n = tid; n < N; n += 1024)
+        if ((int)(rows[n].bits_cb & 0xffu) == b) thr[(size_t)n * kTableStride + j] = m;
 }
 
 hipError_t launch_average_thresholds(const lowra_layout& L, float* thr, hipStream_t st) {
     if (L.N == 0) return hipSuccess;
-    average_thresholds_kernel<<<dim3(45), dim3(256), 0, st>>>(L.d_rows, L.N, thr);
+    const int cols = L.n_by_bits[4] > 0 ? 19 : L.n_by_bits[2] > 0 ? 4 : 1;        // widths the matrix has, narrowest first
+    average_thresholds_kernel<<<dim3(cols), dim3(1024), 0, st>>>(L.d_rows, L.N, thr);
     return hipGetLastError();
 }
 
