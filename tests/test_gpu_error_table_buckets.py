@@ -1,0 +1,51 @@
+"""Both ways the error table finds a 4-bit code (one threshold per bucket of [-1, 1]; bisection where a bucket holds two,
+or a threshold lies above every ordinary normalised weight), and threshold averaging over several passes of its loop."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import lowra_oracle as orc
+from paper_2502_08141_amd import lowra, synth
+
+pytestmark = pytest.mark.gpu
+
+TABLES = {
+    "spread": np.linspace(-0.93, 0.93, 15),
+    "on the edges of buckets": (np.arange(15) - 7) / 8.0,
+    "two in one bucket": np.concatenate([[-0.9, -0.899], np.linspace(-0.7, 0.9, 13)]),
+    "equal neighbours": np.concatenate([[-0.5, -0.5, -0.5], np.linspace(-0.4, 0.9, 12)]),
+    "below -1": np.concatenate([[-3.0], np.linspace(-0.8, 0.8, 14)]),
+    "above 1": np.concatenate([np.linspace(-0.8, 0.8, 12), [1.0, 2.0, np.inf]]),
+}
+
+
+@pytest.mark.parametrize("name", list(TABLES))
+@pytest.mark.parametrize("N,K", [(1, 64), (5, 4160)])
+def test_error_table(name, N, K):
+    print(f"[error table {name} {N}x{K}]", flush=True)
+    thr, mp, _ = synth.shared_codebooks()
+    thr = thr.copy()
+    thr[2, :15] = TABLES[name].astype(np.float32)
+    W = np.random.default_rng(N * K).normal(0, 0.02, (N, K)).astype(np.float32)
+    edges = np.concatenate([thr[2, :15][np.abs(thr[2, :15]) <= 1], [-1.0, 1.0, 0.0, 0.03125, -0.03125]]).astype(np.float32)
+    W[0, :edges.size] = edges                                 # a block whose absmax is 1: weights on thresholds and bucket edges
+    W[0, edges.size:64] = 0.5
+    if N > 2:
+        W[2, :64] = 1e-41                                     # subnormal block: 1 / absmax is infinite
+        W[2, 64:128] = 0.0
+    got = lowra.lowra_channel_mse(torch.from_numpy(W).cuda(), torch.from_numpy(thr).cuda(), torch.from_numpy(mp).cuda())
+    want = orc.channel_mse(W, thr, mp)
+    assert np.allclose(got.cpu().numpy(), want, rtol=1e-5, atol=0)   # fp32 partial sums per thread against fp64
+
+
+@pytest.mark.parametrize("fractions", [(0.4, 0.3, 0.3), (0.5, 0.5, 0.0), (1.0, 0.0, 0.0), (0.0, 0.0, 1.0)])
+def test_average_thresholds_many_channels(fractions):
+    N = 13001                                                 # past the 12288 channels of one pass
+    bits = synth.assign_bits(N, fractions, np.random.default_rng(5))
+    thr = np.sort(np.random.default_rng(6).uniform(-1, 1, (N, 16)).astype(np.float32), axis=1)
+    thr[np.arange(16)[None, :] >= (1 << bits.astype(np.int64))[:, None] - 1] = np.inf
+    lay = lowra.Layout(64, bits, np.arange(N, dtype=np.int32), bits)
+    got = lowra.lowra_average_thresholds(lay, torch.from_numpy(thr).cuda()).cpu().numpy()
+    want = orc.average_thresholds(bits, thr)
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), fin) and np.abs(got[fin] - want[fin]).max() <= 2.0 ** -24   # both sums are fp64
