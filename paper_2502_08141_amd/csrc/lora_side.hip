@@ -41,10 +41,10 @@ __device__ __forceinline__ void wait_newer(int newer) {
 // (wavefront w takes columns [KW w / NC, KW (w+1) / NC), v_mfma_f32_16x16x32_bf16); one barrier
 // per stage hands the buffers over.  LDS rows hold KW bf16; 16-byte chunk c of row r sits at
 // c ^ (r & 15), which makes the operand reads (16 rows, same chunk) conflict-free.
-// QT: Q is given transposed, [Kc][64] row-major with rank 64 (LoRA B as the caller holds it): a stage's
-// 128 contraction rows of 128 bytes are one contiguous 16 KB block, moved as it lies (16-byte chunk c
-// of row n at chunk c ^ (n & 7)) and read with transposing LDS reads -- two ds_read_b64_tr_b16 give a
-// lane the 8 consecutive contraction elements of its column.
+// QT: Q is given transposed, [Kc][r] row-major with a rank that is a multiple of eight (LoRA B as the caller holds
+// it): a stage's 128 contraction rows, contiguous in memory, go to LDS rows of 128 bytes (16-byte chunk c of row n
+// at chunk c ^ (n & 7); chunks past the rank repeat the last one and count as zero when read) and are read with
+// transposing LDS reads -- two ds_read_b64_tr_b16 give a lane the 8 consecutive contraction elements of its column.
 typedef short sk_v4i16_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) sk_v4i16_t* sk_lds_v4i16_ptr;
 
@@ -101,7 +101,8 @@ __global__ __launch_bounds__(128 * NC) void skinny_nt_kernel(const uint16_t* __r
                 const bool from_p = t * NC * RPI < PR;               // known at compile time: PR is a multiple of NC RPI
                 // columns past Kc: any valid bytes, zeroed at the read
                 if (QT && !from_p)
-                    dma16_s(Q, (uint32_t)min(kbeg + st * KW + (int)voff[t], Kc - 1) * 128u + lc16[t], smem_lds + (st % RING) * STAGE + q * 1024);
+                    dma16_s(Q, (uint32_t)min(kbeg + st * KW + (int)voff[t], Kc - 1) * (uint32_t)(2 * r) + min(lc16[t], (uint32_t)(2 * r - 16)),
+                            smem_lds + (st % RING) * STAGE + q * 1024);
                 else if (from_p)
                     dma16_s(P, voff[t] + min(kb2 + lc16[t], kmax_byte), smem_lds + (st % RING) * STAGE + q * 1024);
                 else
@@ -232,6 +233,23 @@ static SkinnyPlan skinny_plan(int M, int Kc, int RP) {
     slices = (Kc + kslice - 1) / kslice;
     return slices > 1 ? SkinnyPlan{slices, kslice} : SkinnyPlan{1, 0};
 }
+// Few tokens: 16-row workgroups leave most of the chip idle and each walks the whole contraction, 0.33 us per stage of
+// 128 columns.  With room for the slices' partial sums (`extra` below) the contraction is split until the grid has
+// about one workgroup per compute unit; the kernel that adds the slices costs about 2.5 us, so contractions below 1536
+// (twelve stages, 4 us) stay whole.  Kernel times: 333 tokens, 4096 columns 10.6 -> 4.7 + 3 us; 512 tokens, 11008
+// columns 28 -> 7 + 3 us; 9 tokens, 4096 columns 11.8 -> 4.1 + 2.8 us.
+static SkinnyPlan skinny_few_plan(int M, int Kc, int RP) {
+    const int blocks = (M + 15) / 16;
+    if (RP != 64 || M < 1 || Kc < 1536 || 2 * blocks > device_compute_units()) return SkinnyPlan{1, 0};
+    int slices = std::min(std::min(device_compute_units() / blocks, Kc / 512), 16);
+    const int kslice = ((Kc + slices - 1) / slices + 127) / 128 * 128;
+    slices = (Kc + kslice - 1) / kslice;
+    return slices > 1 ? SkinnyPlan{slices, kslice} : SkinnyPlan{1, 0};
+}
+size_t skinny_extra_bytes(int M, int Kc, int RP) {
+    const SkinnyPlan pl = skinny_few_plan(M, Kc, RP);
+    return pl.slices > 1 ? (size_t)pl.slices * M * RP * sizeof(float) : 0;
+}
 size_t skinny_scratch_bytes(int M, int Kc, int RP) {
     const SkinnyPlan pl = skinny_plan(M, Kc, RP);
     return pl.slices > 1 ? (size_t)pl.slices * M * RP * sizeof(float) : 0;
@@ -239,11 +257,27 @@ size_t skinny_scratch_bytes(int M, int Kc, int RP) {
 
 template <bool QT>
 static hipError_t launch_skinny_any(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
-                                    float s, uint16_t* out, int RP, float* scratch, hipStream_t st) {
+                                    float s, uint16_t* out, int RP, float* scratch, float* extra, size_t extra_bytes, hipStream_t st) {
     // the kernel addresses P rows with 32-bit byte offsets: very tall inputs go in slabs of rows
     const long long max_rows = ((1LL << 31) / ((long long)ldp * 2)) & ~63LL;
-    if (max_rows < 64 || (long long)r * ldq * 2 >= (1LL << 31) || (QT && (RP != 64 || (long long)Kc * 128 >= (1LL << 32)))) return hipErrorInvalidValue;
+    if (max_rows < 64 || (long long)r * ldq * 2 >= (1LL << 31) || (QT && (RP != 64 || (r & 7) || (long long)Kc * r * 2 >= (1LL << 32)))) return hipErrorInvalidValue;
     const SkinnyPlan pl = scratch && M <= max_rows ? skinny_plan(M, Kc, RP) : SkinnyPlan{1, 0};
+    if (extra && M <= max_rows) {
+        const SkinnyPlan few = skinny_few_plan(M, Kc, RP);
+        if (few.slices > 1 && (size_t)few.slices * M * RP * sizeof(float) <= extra_bytes) {
+            constexpr int sh = 7 * (16 + 64) * 128 * 2;
+            static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_nt_kernel<4, 128, 4, 7, 1, QT>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, sh);
+            if (attr != hipSuccess) return attr;
+            skinny_nt_kernel<4, 128, 4, 7, 1, QT><<<dim3((M + 15) / 16, few.slices), dim3(512), sh, st>>>(P, ldp, M, Q, ldq, r, Kc, s, out, extra, few.kslice);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            const size_t n4 = (size_t)M * RP / 4;
+            skinny_sum_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(reinterpret_cast<const float4*>(extra), few.slices, n4, s,
+                                                                                       reinterpret_cast<uint2*>(out));
+            return hipGetLastError();
+        }
+    }
     // One slice: every workgroup brings in all of Q next to its rows of P, and a compute unit fetches at a fixed rate
     // (about 55 GB/s), so a workgroup costs (its rows + Q's rows) and the call costs that times the rounds its
     // workgroups need on the chip.  64-row workgroups win once the 16-row ones need several rounds
@@ -294,18 +328,19 @@ static hipError_t launch_skinny_any(const uint16_t* P, int ldp, int M, const uin
     }
     return hipGetLastError();
 }
+// `scratch`: skinny_scratch_bytes of it, or null; `extra`: more of it that may be there (skinny_extra_bytes is what is used)
 hipError_t launch_skinny_ws(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
-                            float s, uint16_t* out, int RP, float* scratch, hipStream_t st) {
-    return launch_skinny_any<false>(P, ldp, M, Q, ldq, r, Kc, s, out, RP, scratch, st);
+                            float s, uint16_t* out, int RP, float* scratch, float* extra, size_t extra_bytes, hipStream_t st) {
+    return launch_skinny_any<false>(P, ldp, M, Q, ldq, r, Kc, s, out, RP, scratch, extra, extra_bytes, st);
 }
-// out[m][j] = bf16( s * sum_c P[m][c] Qt[c][j] ) with Qt [Kc][64] row-major (rank exactly 64): no transposed copy needed
-hipError_t launch_skinny_qt(const uint16_t* P, int ldp, int M, const uint16_t* Qt, int Kc, float s, uint16_t* out,
-                            float* scratch, hipStream_t st) {
-    return launch_skinny_any<true>(P, ldp, M, Qt, 64, 64, Kc, s, out, 64, scratch, st);
+// out[m][j] = bf16( s * sum_c P[m][c] Qt[c][j] ) with Qt [Kc][r] row-major, r a multiple of 8 up to 64: no transposed copy needed
+hipError_t launch_skinny_qt(const uint16_t* P, int ldp, int M, const uint16_t* Qt, int r, int Kc, float s, uint16_t* out,
+                            float* scratch, float* extra, size_t extra_bytes, hipStream_t st) {
+    return launch_skinny_any<true>(P, ldp, M, Qt, r, r, Kc, s, out, 64, scratch, extra, extra_bytes, st);
 }
 hipError_t launch_skinny(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
                          float s, uint16_t* out, int RP, hipStream_t st) {
-    return launch_skinny_ws(P, ldp, M, Q, ldq, r, Kc, s, out, RP, nullptr, st);
+    return launch_skinny_ws(P, ldp, M, Q, ldq, r, Kc, s, out, RP, nullptr, nullptr, 0, st);
 }
 hipError_t launch_pad_cols(const uint16_t* src, int R, int c, uint16_t* dst, int CP, hipStream_t st) {
     const size_t tot = (size_t)R * CP;
