@@ -116,16 +116,17 @@ def _check(st: int, where: str):
         raise LowraError(st, where)
 
 
-def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """Raw handle of the current device's current stream (torch.cuda.current_stream() builds a Python object: 1.5 us)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
-def _ptr(t):
-    return C.c_void_p(0 if t is None else t.data_ptr())
+def _ptr(t) -> int:
+    return 0 if t is None else t.data_ptr()
 
 
 def _dev(t: torch.Tensor, dtype, name: str):
-    if not (t.is_cuda and t.is_contiguous() and t.dtype == dtype):
+    if not (t.dtype is dtype and t.is_cuda and t.is_contiguous()):
         raise TypeError(f"{name}: need a contiguous {dtype} device tensor")
     return t
 
@@ -153,7 +154,7 @@ class Layout:
                                        self.C, self.cb_bits.ctypes.data, C.byref(h))
         _check(st, "lowra_layout_create")
         self.handle = h
-
+        self.packed_bytes = int(lib().lowra_packed_bytes(h))
         self.scale_dtype = torch.float32
 
     def set_scale_dtype(self, dtype):
@@ -163,17 +164,13 @@ class Layout:
         self.scale_dtype = dtype
         return self
 
-    @property
-    def packed_bytes(self) -> int:
-        return int(lib().lowra_packed_bytes(self.handle))
-
     def workspace_bytes(self, op: int, M: int, r: int) -> int:
         return int(lib().lowra_workspace_bytes(self.handle, int(op), int(M), int(r)))
 
     def close(self):
         if getattr(self, "handle", None):
             lib().lowra_layout_destroy(self.handle)
-            self.handle = None
+            self.handle, self.packed_bytes = None, 0
 
     def __del__(self):
         try:
@@ -269,12 +266,13 @@ def _linear(fn, name, op, layout, packed, absmax, mappings, act, act_cols, out_c
     _dev(out, torch.bfloat16, "out")
     if tuple(out.shape) != (M, out_cols):
         raise ValueError("output shape mismatch")
-    need = layout.workspace_bytes(op, M, r)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=act.device)
+    if workspace is None:                                     # (a caller's own is checked by the library)
+        need = layout.workspace_bytes(op, M, r)
+        if need:
+            workspace = torch.empty(need, dtype=torch.uint8, device=act.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(fn(layout.handle, _ptr(packed), _ptr(absmax), _ptr(mappings), _ptr(act), M, _ptr(A), _ptr(B), r,
-              C.c_float(s), _ptr(out), _ptr(workspace), C.c_size_t(ws_bytes), _stream()), name)
+    _check(fn(layout.handle, packed.data_ptr(), absmax.data_ptr(), mappings.data_ptr(), act.data_ptr(), M, _ptr(A), _ptr(B), r,
+              s, out.data_ptr(), _ptr(workspace), ws_bytes, _stream()), name)
     return out
 
 
@@ -342,9 +340,8 @@ def lowra_adapter_grads(layout: Layout, x, dY, A, B, s, workspace=None):
     if tuple(x.shape) != (M, layout.K) or tuple(dY.shape) != (M, layout.N) or tuple(A.shape) != (r, layout.K) or \
             tuple(B.shape) != (layout.N, r):
         raise ValueError("shape mismatch")
-    need = layout.workspace_bytes(OP_ADAPTER_GRADS, M, r)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=x.device)
+        workspace = torch.empty(max(layout.workspace_bytes(OP_ADAPTER_GRADS, M, r), 16), dtype=torch.uint8, device=x.device)
     dA = torch.empty((r, layout.K), dtype=torch.float32, device=x.device)
     dB = torch.empty((layout.N, r), dtype=torch.float32, device=x.device)
     _check(lib().lowra_adapter_grads(layout.handle, _ptr(x), _ptr(dY), M, _ptr(A), _ptr(B), r, float(s), _ptr(dA), _ptr(dB),
@@ -369,9 +366,8 @@ def lowra_adapter_grads_from_side(layout: Layout, x, dY, r, st, su, workspace=No
     M, r = int(x.shape[0]), int(r)
     if tuple(x.shape) != (M, layout.K) or tuple(dY.shape) != (M, layout.N) or tuple(st.shape) != (M, 64) or tuple(su.shape) != (M, 64):
         raise ValueError("shape mismatch")
-    need = layout.workspace_bytes(OP_ADAPTER_GRADS, M, r)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=x.device)
+        workspace = torch.empty(max(layout.workspace_bytes(OP_ADAPTER_GRADS, M, r), 16), dtype=torch.uint8, device=x.device)
     dA = torch.empty((r, layout.K), dtype=torch.float32, device=x.device)
     dB = torch.empty((layout.N, r), dtype=torch.float32, device=x.device)
     _check(lib().lowra_adapter_grads_from_side(layout.handle, _ptr(x), _ptr(dY), M, r, _ptr(st), _ptr(su), _ptr(dA), _ptr(dB),
