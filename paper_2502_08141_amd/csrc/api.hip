@@ -470,27 +470,35 @@ size_t lowra_fwd_batch_workspace_bytes(int n, const lowra_fwd_item* items, int r
 
 static lowra_status fwd_batch_create_impl(int n, const lowra_fwd_item* items, const float* mappings, int M, int r, float s,
                                           void* workspace, lowra_fwd_batch*& b) {
-    std::vector<lowra::GemvParams> ps;
+    std::vector<lowra::GemvParams> all, ps;
     std::vector<lowra::GsBatchItem> fast;
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     const int path = g_linear_path.load();
+    bool streams = path != LOWRA_PATH_GEMV_GENERAL, fp32_scales = true;
+    for (int i = 0; i < n; ++i) {
+        const lowra_layout& L = *items[i].layout;
+        lowra::GemvParams g;
+        g.sorted_rows = L.d_sorted_rows; g.packed = items[i].packed; g.packed_bytes = L.packed_bytes; g.absmax = items[i].absmax;
+        g.mappings = mappings; g.x = items[i].x; g.A = items[i].A; g.B = items[i].B; g.tp = reinterpret_cast<float*>(ws);
+        g.y = items[i].y; g.s = s;
+        g.M = M; g.N = L.N; g.K = L.K; g.G = L.G; g.r = r; g.RT = r > 0 ? (r + 15) / 16 * 16 : 0; g.xbufs = 0;
+        all.push_back(g);
+        fp32_scales = fp32_scales && !L.scale_bf16;
+        ws += batch_item_ws(L, r);
+    }
+    // LOWRA_PATH_AUTO: a batch too small for the streaming kernel goes to the general one (which reads fp32 scales)
+    if (path == LOWRA_PATH_AUTO && fp32_scales && lowra::gemv_batch_us(all) < lowra::gemv_stream_batch_us(all)) streams = false;
     for (int i = 0; i < n; ++i) {
         const lowra_layout& L = *items[i].layout;
         // the streaming kernel builds one set of tables per launch: its matrices must agree on the codebooks' widths
-        const bool stream = path != LOWRA_PATH_GEMV_GENERAL && lowra::gemv_stream_supported(L, M, r) &&
+        const bool stream = streams && lowra::gemv_stream_supported(L, M, r) &&
                             (fast.empty() || (fast[0].L->cb_bits == L.cb_bits && fast[0].L->scale_bf16 == L.scale_bf16));
         if (!stream && L.scale_bf16) return LOWRA_UNSUPPORTED;      // the general kernel reads fp32 scales
-        if (stream) {
-            fast.push_back(lowra::GsBatchItem{&L, items[i].packed, items[i].absmax, items[i].x, items[i].A, items[i].B, items[i].y, ws});
-        } else {
-            lowra::GemvParams g;
-            g.sorted_rows = L.d_sorted_rows; g.packed = items[i].packed; g.packed_bytes = L.packed_bytes; g.absmax = items[i].absmax;
-            g.mappings = mappings; g.x = items[i].x; g.A = items[i].A; g.B = items[i].B; g.tp = reinterpret_cast<float*>(ws);
-            g.y = items[i].y; g.s = s;
-            g.M = M; g.N = L.N; g.K = L.K; g.G = L.G; g.r = r; g.RT = r > 0 ? (r + 15) / 16 * 16 : 0; g.xbufs = 0;
-            ps.push_back(g);
-        }
-        ws += batch_item_ws(L, r);
+        if (stream)
+            fast.push_back(lowra::GsBatchItem{&L, items[i].packed, items[i].absmax, items[i].x, items[i].A, items[i].B, items[i].y,
+                                              reinterpret_cast<uint8_t*>(all[i].tp)});
+        else
+            ps.push_back(all[i]);
     }
     b = new (std::nothrow) lowra_fwd_batch;
     if (!b) return LOWRA_OUT_OF_MEMORY;

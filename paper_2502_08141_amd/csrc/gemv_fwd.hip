@@ -309,6 +309,9 @@ static size_t gemv_lds(GemvParams& p) {
     const int nblk = (p.G + 3) / 4, per = (nblk + W - 1) / W;
     const size_t base = (size_t)fixed + (size_t)16 * p.RT * 2, xbuf = (size_t)W * rows2 * 1024;
     p.xbufs = base + per * xbuf <= (size_t)kMaxLds ? per : 2;     // a buffer per round when they fit
+    // ... but not at the price of the second workgroup on a compute unit (5120 features, 6 tokens, three matrices of 5120
+    // channels: 34 -> 25 us)
+    if (W == 8 && per > 2 && 2 * (base + per * xbuf) > (size_t)kMaxLds && 2 * (base + 2 * xbuf) <= (size_t)kMaxLds) p.xbufs = 2;
     const size_t sh = base + (size_t)p.xbufs * xbuf;
     return sh > (size_t)kMaxLds ? 0 : sh;
 }
@@ -357,7 +360,9 @@ static GemvChoice gemv_choose(const GemvParams& p, bool many_strips = false) {
                        (size_t)std::min((nblk + 15) / 16, 2) * 16 * rows2 * 1024 <= (size_t)160 * 1024;
     const int nstrips = (p.N + 15) / 16;
     const size_t lds8 = (size_t)16 * GV_TABROW + 64 + (size_t)16 * p.RT * 2 + (size_t)std::min((nblk + 7) / 8, 2) * 8 * rows2 * 1024;
-    const bool pair8 = (many_strips || nstrips > compute_units_cached()) && 2 * lds8 <= (size_t)150 * 1024 && nblk <= 16;
+    // (up to 24 blocks: 5120 features, three rounds; one token, three matrices of 5120 channels 34 -> 24 us, two of 13824
+    // 59 -> 38 us against one 16-wavefront workgroup per unit)
+    const bool pair8 = (many_strips || nstrips > compute_units_cached()) && 2 * lds8 <= (size_t)150 * 1024 && nblk <= 24;
     if (fit16 && !pair8) {
         if (nblk <= 16) return {16, 1};     // K <= 4096
         if (nblk <= 32) return {16, 2};
@@ -399,6 +404,39 @@ hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
         if (e != hipSuccess) return e;
     }
     return gemv_dispatch(gemv_choose(p), LaunchSingle{p, st});
+}
+
+// Which kernel a batch takes: estimated times, fitted to runs of one to seven matrices of 1024 to 13824 features with 1
+// to 16 tokens.  This kernel pays per strip (4- and 8-wavefront workgroups, several per compute unit) or per round of
+// strips over the compute units (16 wavefronts); the streaming kernel pays 17 us and more before its first byte (its t
+// kernel, set-up, pipeline fill and drain) and then streams at 3 GB/ms.  A decoder layer of 4096 x 11008 taken apart by
+// data dependence, 4 tokens: q,k,v 18.4 us here against 26.0, o 9.7 / 20.1, gate,up 29.3 / 30.1, down 16.1 / 38.2; all
+// seven matrices in one batch 59 / 56.
+// LDS of an 8-wavefront workgroup with two activation buffers per wavefront, or fewer where it has fewer rounds
+static size_t lds8_of(const GemvParams& p, int per) {
+    return (size_t)16 * GV_TABROW + 64 + (size_t)16 * p.RT * 2 + (size_t)std::min(per, 2) * 8 * ((std::min(p.M, 16) + 1) / 2) * 1024;
+}
+double gemv_batch_us(const std::vector<GemvParams>& items) {
+    double t = items.empty() || items[0].RT == 0 ? 3.0 : 5.0;
+    double rounds16[5] = {0, 0, 0, 0, 0};
+    for (GemvParams p : items) {
+        const GemvChoice c = gemv_choose(p, LOWRA_BATCH_SMALL_WG != 0);
+        const int nblk = (p.G + 3) / 4, per = (nblk + c.W - 1) / c.W, strips = (p.N + 15) / 16;
+        if (c.W == 16) rounds16[std::min(per, 4)] += (double)strips / compute_units_cached();
+        else if (c.W == 8) t += (2 * lds8_of(p, per) > (size_t)160 * 1024 ? 0.0111 : per > 2 ? 0.0066 : 0.0083) * strips * per;   // one workgroup per unit, or more
+        else t += (p.M > 12 ? 0.0125 : p.M > 8 ? 0.0085 : 0.005) * strips * per;
+    }
+    for (int per = 1; per <= 4; ++per) t += (double)(long long)(rounds16[per] + 0.999) * (3.2 + 2.6 * per);
+    return t;
+}
+double gemv_stream_batch_us(const std::vector<GemvParams>& items) {
+    double bytes = 0.0;
+    int kmax = 0, M = 1, rt = 0;
+    for (const GemvParams& p : items) {
+        bytes += (double)p.packed_bytes + (double)p.N * p.G * sizeof(float);
+        kmax = std::max(kmax, p.K); M = p.M; rt = p.RT;
+    }
+    return (rt ? 7.7 + 4.5 * ((kmax - 1) / 4096) : 0.0) + 9.5 + 0.35 * M + bytes / 3.0e6 + (kmax > 4096 ? 5.0 : 0.0);
 }
 
 // ---- several matrices in one launch per instantiation.  The descriptors (every pointer of every matrix)

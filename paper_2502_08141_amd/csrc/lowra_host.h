@@ -139,6 +139,8 @@ hipError_t gemv_stream_bwd_batch_build(const std::vector<GbBatchItem>& items, co
                                        float* part, GbBatch& b);
 hipError_t gemv_stream_bwd_batch_run(const GbBatch& b, hipStream_t st);
 void gemv_stream_bwd_batch_free(GbBatch& b);
+double gemv_batch_us(const std::vector<GemvParams>& items);          // estimated time of a run by the general kernel ...
+double gemv_stream_batch_us(const std::vector<GemvParams>& items);   // ... and by the streaming kernel
 hipError_t gemv_batch_build(std::vector<GemvParams>& items, lowra_fwd_batch& b);
 hipError_t gemv_batch_run(const lowra_fwd_batch& b, hipStream_t st);
 void gemv_batch_free(lowra_fwd_batch& b);
