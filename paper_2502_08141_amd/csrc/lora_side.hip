@@ -241,7 +241,10 @@ static SkinnyPlan skinny_plan(int M, int Kc, int RP) {
 static SkinnyPlan skinny_few_plan(int M, int Kc, int RP) {
     const int blocks = (M + 15) / 16;
     if (RP != 64 || M < 1 || Kc < 1536 || 2 * blocks > device_compute_units()) return SkinnyPlan{1, 0};
-    int slices = std::min(std::min(device_compute_units() / blocks, Kc / 512), 16);
+    // (at most Kc rows of partial sums: the adapter gradients' workspace always has that room, so that they split as the
+    // linear calls do and their intermediates agree bit for bit)
+    int slices = std::min(std::min(std::min(device_compute_units() / blocks, Kc / 512), 16), Kc / M);
+    if (slices < 2) return SkinnyPlan{1, 0};
     const int kslice = ((Kc + slices - 1) / slices + 127) / 128 * 128;
     slices = (Kc + kslice - 1) / kslice;
     return slices > 1 ? SkinnyPlan{slices, kslice} : SkinnyPlan{1, 0};

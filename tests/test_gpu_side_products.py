@@ -36,3 +36,19 @@ def test_side_products(N, K, M, r):
             assert not side[:, r:].any() and torch.isfinite(out.float()).all()
     dA, dB = lowra.lowra_adapter_grads(D.layout, D.x, D.dY, D.A, D.B, L.s)
     assert rel(dB, D.dY.double().T @ want[lowra.OP_LINEAR_FWD]) <= 2e-2 and rel(dA, want[lowra.OP_LINEAR_BWD_INPUT].T @ D.x.double()) <= 2e-2
+
+
+@pytest.mark.parametrize("N,K,M,r", [(1536, 1536, 1300, 64), (1536, 2048, 700, 32), (1800, 1600, 500, 24), (4096, 1536, 20, 64)])
+def test_adapter_gradients_form_the_same_products(N, K, M, r):
+    """Where the contraction is split, the standalone call has the room to split it as the linear calls do: same bits."""
+    print(f"[side grads {N}x{K} M{M} r{r}]", flush=True)
+    D = DeviceLayer(synth.make_custom(N, K, M, r, fractions=(0.5, 0.5, 0.0), seed=830 + r))
+    D.quantize()
+    L, side = D.L, []
+    for op, call, act in ((lowra.OP_LINEAR_FWD, lowra.lowra_linear_fwd, D.x), (lowra.OP_LINEAR_BWD_INPUT, lowra.lowra_linear_bwd_input, D.dY)):
+        ws = torch.empty(D.layout.workspace_bytes(op, M, r), dtype=torch.uint8, device="cuda")
+        call(D.layout, D.packed, D.absmax, D.mp, act, D.A, D.B, L.s, workspace=ws)
+        side.append(lowra.lowra_linear_side_product(D.layout, op, M, r, ws))
+    dA, dB = lowra.lowra_adapter_grads_from_side(D.layout, D.x, D.dY, r, *side)
+    rA, rB = lowra.lowra_adapter_grads(D.layout, D.x, D.dY, D.A, D.B, L.s)
+    assert torch.equal(dA, rA) and torch.equal(dB, rB)
