@@ -176,7 +176,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ Z, 
     }
 }
 
-// ---- G = the sum of the partial matrices, entry by entry in chunk order, in the same block-by-block layout.  A kernel
+// ---- G [64][64] (the blocks on and below the diagonal) = the sum of the partial matrices, entry by entry in chunk order.  A kernel
 // of its own because one compute unit fetches about 30 GB/s: the 0.5 MB of partial matrices took the factorisation's
 // single workgroup 18 us, half of its time; spread over the chip the sum is a microsecond.
 __global__ __launch_bounds__(64) void gram_sum_kernel(const double* __restrict__ Gp, int chunks, double* __restrict__ G) {
@@ -192,21 +192,25 @@ __global__ __launch_bounds__(64) void gram_sum_kernel(const double* __restrict__
         for (int q = 0; q < 16; ++q)
             if (c0 + q < chunks) sum += part[q];
     }
-    G[e] = sum;
+    G[(4 * bi + ((e >> 2) & 3)) * 64 + 4 * bj + (e & 3)] = sum;
 }
 
-// ---- G = L L^T (fp64, one workgroup).  Output Lf fp32 [64][64]: L below the
-// diagonal, 1 / L[i][i] on it, zero elsewhere.  A pivot that vanishes (a row of Z inside the span of
-// the earlier ones, a row >= r, or Z = 0) gets a zero column and a zero reciprocal: that row of A
-// comes out zero and the rest stays orthonormal.
-// Thread (bi, bj) keeps the 4 x 4 block of rows 4 bi.., columns 4 bj.. in registers for the whole
-// right-looking factorisation (blocks above the diagonal hold nothing of use), which goes by panels of four
-// columns: the sixteen owners of a panel -- neighbouring lanes of one wavefront, the diagonal block among them,
-// so that its ten entries reach them by lane reads -- factor the diagonal block (every lane the same
-// arithmetic) and solve their own four rows against it, then publish the four columns through LDS (double
-// buffered: ONE barrier per panel); every thread whose block lies right of the panel, on or below the diagonal,
-// subtracts the rank-4 product.  Published rows up to the panel's last are zero, so that this update needs no
-// test per entry, and what it writes above the diagonal of a diagonal block is never read.
+// ---- G = L L^T (fp64) and A = L^-1 Z by forward substitution: orthonormal rows, written as bf16 [64][K] (rows >= r zero)
+// and transposed, At [K][64].  One workgroup of eight wavefronts per 64 columns of Z; every workgroup factors G for
+// itself, since a serial 64 x 64 factorisation takes one compute unit as long as it takes sixty-four, and a launch of
+// its own cost its gap and a round trip of the factor through memory.
+// A pivot that vanishes (a row of Z inside the span of the earlier ones, a row >= r, or Z = 0) gets a zero column and
+// a zero reciprocal: that row of A comes out zero and the rest stays orthonormal.
+// The factorisation is a chain of 64 pivots, each waiting for the one before: what bounds it is the latency of one
+// pivot.  So wavefront p keeps panel p, columns 8 p .. 8 p + 7, with one row per lane: its eight pivots need no LDS and
+// no barrier (the pivot and the panel's own rows reach the lanes by lane reads) and solve all rows below the panel on
+// the way; the panel is then published through LDS (double buffered, ONE barrier per panel) and every wavefront to its
+// right takes the rank-8 product off its own.  FACTORFIGS
+// The substitution that follows has a lane per column of Z, wavefront w the rows 8 w .. 8 w + 7: in stage jb wavefront
+// jb solves its 8 x 8 triangle and publishes its eight rows through LDS; the wavefronts below take that block's
+// contribution off their rows (eight independent chains of multiply-adds) -- one column per lane alone would be a single
+// chain of 2016 dependent operations per wavefront.  L comes from LDS with the same address in every lane; a wavefront
+// fetches the block of the next stage before it waits at the barrier.
 // 1 / d for d > 0 from the hardware's approximation and two Newton steps (about 1e-15 relative), 1 / sqrt(d) with
 // one step (about 1e-13; the factor is rounded to fp32 afterwards): the library's correctly rounded division and
 // square root are some forty instructions each, and four square roots sit on the critical path of every panel.
@@ -228,130 +232,62 @@ __device__ __forceinline__ double lq_readlane(double v, int lane) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-__global__ __launch_bounds__(256) void chol_kernel(const double* __restrict__ G, float* __restrict__ Lf) {
-    __shared__ __align__(16) double col[2][4][64];                   // [buffer][column of the panel][row]
-    __shared__ double diag[64];
-    // the sixteen owners of a block column are sixteen neighbouring lanes of one wavefront
-    const int tid = threadIdx.x, bj = tid >> 4, bi = tid & 15;
-    double g[4][4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) g[u][v] = 0.0;
-    if (bj <= bi) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const double4 row = *reinterpret_cast<const double4*>(G + tid * 16 + 4 * u);
-            g[u][0] = row.x; g[u][1] = row.y; g[u][2] = row.z; g[u][3] = row.w;
-        }
-    }
-    if (bi == bj) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) diag[4 * bi + u] = g[u][u];
-    }
-    __syncthreads();
-    double maxdiag = 0.0;
-    for (int i = 0; i < 64; ++i) maxdiag = fmax(maxdiag, diag[i]);
-    const double tiny = 1e-12 * maxdiag;
-    for (int jb = 0; jb < 16; ++jb) {
-        const int buf = jb & 1;
-        // the diagonal block sits with thread (bi = jb, bj = jb), lane 16 (jb % 4) + jb of the owners' wavefront
-        const int src = 16 * (jb & 3) + jb;
-        double d[4][4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int v = 0; v <= u; ++v) d[u][v] = lq_readlane(g[u][v], src);
-        if (bj == jb) {
-            // L of the diagonal block, column by column; is[v] = 1 / L[v][v], or zero for a pivot that vanishes
-            double is[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                double pv = d[v][v];
-#pragma unroll
-                for (int w = 0; w < v; ++w) pv = fma(-d[v][w], d[v][w], pv);
-                is[v] = pv > tiny ? lq_rsqrt(pv) : 0.0;
-                d[v][v] = pv * is[v];
-#pragma unroll
-                for (int u = v + 1; u < 4; ++u) {
-                    double x = d[u][v];
-#pragma unroll
-                    for (int w = 0; w < v; ++w) x = fma(-d[u][w], d[v][w], x);
-                    d[u][v] = x * is[v];
-                }
-            }
-            // my four rows against it: y L^T = x, entry by entry; for the diagonal block itself this repeats the
-            // factorisation (its entries on and below the diagonal are the ones kept)
-            double y[4][4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    double x = g[u][v];
-#pragma unroll
-                    for (int w = 0; w < v; ++w) x = fma(-y[u][w], d[v][w], x);
-                    y[u][v] = x * is[v];
-                }
-            // (entries above the diagonal, which this also overwrites, are never read)
-            const bool below = bi > jb;                              // rows up to the panel's last are published as zero
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) g[u][v] = y[u][v];
-                double2* dst = reinterpret_cast<double2*>(&col[buf][v][4 * bi]);
-                if (below) { dst[0] = make_double2(y[0][v], y[1][v]); dst[1] = make_double2(y[2][v], y[3][v]); }
-                else { dst[0] = make_double2(0.0, 0.0); dst[1] = make_double2(0.0, 0.0); }
-            }
-        }
-        __syncthreads();
-        if (bj <= jb || bi < bj) continue;                           // finished columns and blocks above the diagonal: nothing to update
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const double2 la = *reinterpret_cast<const double2*>(&col[buf][w][4 * bi]), lb = *reinterpret_cast<const double2*>(&col[buf][w][4 * bi + 2]);
-            const double2 ka = *reinterpret_cast<const double2*>(&col[buf][w][4 * bj]), kb = *reinterpret_cast<const double2*>(&col[buf][w][4 * bj + 2]);
-            const double li[4] = {la.x, la.y, lb.x, lb.y}, lk[4] = {ka.x, ka.y, kb.x, kb.y};
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) g[u][v] = fma(-li[u], lk[v], g[u][v]);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        float o[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i = 4 * bi + u, k = 4 * bj + v;
-            o[v] = 0.0f;
-            if (k < i) o[v] = (float)g[u][v];
-            if (k == i) o[v] = g[u][v] > 0.0 ? (float)lq_rcp(g[u][v]) : 0.0f;
-        }
-        *reinterpret_cast<float4*>(Lf + (4 * bi + u) * 64 + 4 * bj) = make_float4(o[0], o[1], o[2], o[3]);
-    }
-}
-
-// ---- A = L^-1 Z by forward substitution: orthonormal rows, written as bf16 [64][K] (rows >= r zero) and
-// transposed, At [K][64].  One workgroup of eight wavefronts per 64 columns of Z, a lane per column, wavefront w
-// the rows 8 w .. 8 w + 7.  In stage jb wavefront jb solves its 8 x 8 triangle and publishes its eight rows
-// through LDS; the wavefronts below take that block's contribution off their rows (eight independent chains of
-// multiply-adds) -- one column per lane alone would be a single chain of 2016 dependent operations per wavefront.
-// L comes from LDS with the same address in every lane; a wavefront fetches the block of the next stage before it
-// waits at the barrier.
 constexpr int LQ_APPLY_THREADS = 512;
-__global__ __launch_bounds__(LQ_APPLY_THREADS) void apply_kernel(const float* __restrict__ Z, const float* __restrict__ Lf, int K, int r,
-                                                                 uint16_t* __restrict__ A, uint16_t* __restrict__ At) {
-    __shared__ __align__(16) float Ls[64 * 64];
+__global__ __launch_bounds__(LQ_APPLY_THREADS) void factor_apply_kernel(const float* __restrict__ Z, const double* __restrict__ G, int K, int r,
+                                                                        uint16_t* __restrict__ A, uint16_t* __restrict__ At) {
+    __shared__ double2 pan[2][4][64];                                // [buffer][pair of columns of the panel][row]
+    __shared__ __align__(16) float Ls[64 * 64];                      // L below the diagonal, 1 / L[i][i] on it
     __shared__ float as[64][64];                                     // as[row][lane]: finished rows of A
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int k = blockIdx.x * 64 + lane;
     const bool live = k < K;
+    double g[8];                                                     // row `lane` of my panel; rows above the panel are never used
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double2 v = lane >= 8 * w ? reinterpret_cast<const double2*>(G + lane * 64 + 8 * w)[q] : make_double2(0.0, 0.0);
+        g[2 * q] = v.x; g[2 * q + 1] = v.y;
+    }
+    double maxdiag = G[lane * 65];
     float s[8];
 #pragma unroll
     for (int ii = 0; ii < 8; ++ii) s[ii] = (live && 8 * w + ii < r) ? Z[(size_t)(8 * w + ii) * K + k] : 0.0f;
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-        reinterpret_cast<float4*>(Ls)[q * LQ_APPLY_THREADS + threadIdx.x] = reinterpret_cast<const float4*>(Lf)[q * LQ_APPLY_THREADS + threadIdx.x];
-    __syncthreads();
+    for (int o = 1; o < 64; o <<= 1) maxdiag = fmax(maxdiag, __shfl_xor(maxdiag, o, 64));
+    const double tiny = 1e-12 * fmax(maxdiag, 0.0);
+    for (int p = 0; p < 8; ++p) {
+        double2 (*pp)[64] = pan[p & 1];
+        if (w == p) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const double pv = lq_readlane(g[j], 8 * p + j);
+                g[j] *= pv > tiny ? lq_rsqrt(pv) : 0.0;
+#pragma unroll
+                for (int c = j + 1; c < 8; ++c) g[c] = fma(-g[j], lq_readlane(g[j], 8 * p + c), g[c]);
+            }
+            float o[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (j & 1) pp[j >> 1][lane] = make_double2(g[j - 1], g[j]);
+                o[j] = (float)g[j];
+                if (lane == 8 * p + j) o[j] = g[j] > 0.0 ? (float)lq_rcp(g[j]) : 0.0f;
+            }
+            float4* dst = reinterpret_cast<float4*>(Ls + lane * 64 + 8 * p);
+            dst[0] = make_float4(o[0], o[1], o[2], o[3]);
+            dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+        }
+        __syncthreads();
+        if (w > p) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double2 mine = pp[q][lane];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const double2 l = pp[q][8 * w + c];
+                    g[c] = fma(-mine.y, l.y, fma(-mine.x, l.x, g[c]));
+                }
+            }
+        }
+    }
     float ld[8][8], lb[8][8];                                        // my rows of L: the triangle's block, the current stage's block
     auto fetch = [&](float (&dst)[8][8], int cb) {
 #pragma unroll
@@ -403,7 +339,7 @@ __global__ __launch_bounds__(256) void copy_cols_kernel(const uint16_t* __restri
 static inline size_t lq_align(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct LoftqWs {
-    size_t F, E, Y, Z, partial, Gp, G, Lf, A, At, total;
+    size_t F, E, Y, Z, partial, Gp, G, A, At, total;
 };
 static LoftqWs loftq_ws(int N, int K) {
     LoftqWs w;
@@ -415,7 +351,6 @@ static LoftqWs loftq_ws(int N, int K) {
     w.partial = o; o += lq_align(tn_partial_bytes(K, N, LQ_RP));
     w.Gp = o; o += lq_align((size_t)((K + LQ_GCH - 1) / LQ_GCH) * 4096 * sizeof(double));
     w.G = o; o += lq_align(4096 * sizeof(double));
-    w.Lf = o; o += lq_align(4096 * sizeof(float));
     w.A = o; o += lq_align((size_t)LQ_RP * K * 2);
     w.At = o; o += lq_align((size_t)K * LQ_RP * 2);
     w.total = o;
@@ -440,7 +375,6 @@ hipError_t launch_loftq(const lowra_layout& L, const float* W, const float* thre
     float* partial = reinterpret_cast<float*>(ws + o.partial);
     double* Gp = reinterpret_cast<double*>(ws + o.Gp);
     double* G = reinterpret_cast<double*>(ws + o.G);
-    float* Lf = reinterpret_cast<float*>(ws + o.Lf);
     uint16_t* A = reinterpret_cast<uint16_t*>(ws + o.A);
     uint16_t* At = reinterpret_cast<uint16_t*>(ws + o.At);
     const int chunks = (K + LQ_GCH - 1) / LQ_GCH;
@@ -460,8 +394,7 @@ hipError_t launch_loftq(const lowra_layout& L, const float* W, const float* thre
             if ((e = launch_tn_skinny(E, K, N, Y, LQ_RP, r, 1, partial, Z, st)) != hipSuccess) return e;            // Z = Y^T E
             gram_kernel<<<dim3(4 * chunks), dim3(256), 0, st>>>(Z, K, r, Gp);
             gram_sum_kernel<<<dim3(64), dim3(64), 0, st>>>(Gp, chunks, G);
-            chol_kernel<<<dim3(1), dim3(256), 0, st>>>(G, Lf);
-            apply_kernel<<<dim3((K + 63) / 64), dim3(LQ_APPLY_THREADS), 0, st>>>(Z, Lf, K, r, A, At);
+            factor_apply_kernel<<<dim3((K + 63) / 64), dim3(LQ_APPLY_THREADS), 0, st>>>(Z, G, K, r, A, At);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             Aq = A;
         }
