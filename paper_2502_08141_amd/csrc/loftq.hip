@@ -203,22 +203,25 @@ __global__ __launch_bounds__(64) void gram_sum_kernel(const double* __restrict__
 // a zero reciprocal: that row of A comes out zero and the rest stays orthonormal.
 // The factorisation is a chain of 64 pivots, each waiting for the one before: what bounds it is the latency of one
 // pivot.  So wavefront p keeps panel p, columns 8 p .. 8 p + 7, with one row per lane: its eight pivots need no LDS and
-// no barrier (the pivot and the panel's own rows reach the lanes by lane reads) and solve all rows below the panel on
-// the way; the panel is then published through LDS (double buffered, ONE barrier per panel) and every wavefront to its
-// right takes the rank-8 product off its own.  FACTORFIGS
-// The substitution that follows has a lane per column of Z, wavefront w the rows 8 w .. 8 w + 7: in stage jb wavefront
-// jb solves its 8 x 8 triangle and publishes its eight rows through LDS; the wavefronts below take that block's
-// contribution off their rows (eight independent chains of multiply-adds) -- one column per lane alone would be a single
-// chain of 2016 dependent operations per wavefront.  L comes from LDS with the same address in every lane; a wavefront
-// fetches the block of the next stage before it waits at the barrier.
-// 1 / d for d > 0 from the hardware's approximation and two Newton steps (about 1e-15 relative), 1 / sqrt(d) with
-// one step (about 1e-13; the factor is rounded to fp32 afterwards): the library's correctly rounded division and
-// square root are some forty instructions each, and four square roots sit on the critical path of every panel.
-__device__ __forceinline__ double lq_rcp(double d) {
-    double r = __builtin_amdgcn_rcp(d);
-    r = r * fma(-d, r, 2.0);
-    return r * fma(-d, r, 2.0);
-}
+// no barrier and solve all rows below the panel on the way; the panel is then published through LDS (double
+// buffered) and every wavefront to its right takes the rank-8 product off its own, the next one first: a 16-byte LDS read
+// of one address costs as much as one of 64 (eight cycles of the unit's LDS), and with all seven at it each waited for 250
+// of them.  The next pivot's value is formed beside the column, from two entries read before the reciprocal root is known,
+// so that only arithmetic is on the chain.
+// The substitution goes by blocks of 16 rows on the matrix cores (fp32): the blocks on L's diagonal are inverted in fp64
+// -- each by a wavefront that has nothing left to factor, while the factorisation goes on -- and
+//     a_b = L_bb^-1 s_b,   a_b += L_bb^-1 (s_b - L_bb a_b),   s_c -= L_cb a_b   for the blocks c below.
+// (The second product makes it as exact as row-by-row substitution: without it the rounding of the inverse costs up to
+// twice that error where the rows are nearly dependent.)
+// A wavefront takes 16 columns through all four blocks: with k = 4 (lane / 16) + v as the contraction index of the v-th
+// MFMA, a result lies in the registers as the next product reads it, so there is no barrier and no LDS on that chain.
+// Measured at 64 x 4096: 15.9 us, of them 1.2 the loads, 9.8 the factorisation (3600 cycles a panel: its eight pivots
+// 1500, the product off the next panel 950, the rest LDS and barriers), 1.8 the last block's inverse and 1.9 the
+// substitution (in fp64 on the matrix cores this alone took 4 us more).  The two launches before, a panel of four columns over sixteen lanes of one workgroup and a substitution
+// on the vector units with L broadcast from LDS, took 16.3 + 8 us.
+// 1 / sqrt(d) for d > 0 from the hardware's approximation and one Newton step (about 1e-13; the factor is rounded to fp32
+// afterwards): the library's correctly rounded division and square root are some forty instructions each, and one
+// reciprocal root sits on the critical path of every pivot.
 __device__ __forceinline__ double lq_rsqrt(double d) {
     const double r = __builtin_amdgcn_rsq(d);
     return r * fma(-0.5 * d * r, r, 1.5);
@@ -232,100 +235,140 @@ __device__ __forceinline__ double lq_readlane(double v, int lane) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// lane `c` of my row of sixteen lanes (c < 16, a constant)
+template <int C>
+__device__ __forceinline__ double lq_row_bcast(double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, 0x150 + C, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), 0x150 + C, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// one step of the inversion below: the rows under row C lose their share of it (l[C] is zero in the others)
+template <int C>
+__device__ __forceinline__ void lq_invert_from(double (&x)[4], const double (&l)[16], const double* rd) {
+    const double rc = rd[C];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = fma(-l[C], lq_row_bcast<C>(x[v]) * rc, x[v]);
+    if constexpr (C < 14) lq_invert_from<C + 1>(x, l, rd);
+}
+
 constexpr int LQ_APPLY_THREADS = 512;
+constexpr int LQ_LS = 68;                                            // row stride of Ls: 16-byte reads of 16 rows meet all banks
 __global__ __launch_bounds__(LQ_APPLY_THREADS) void factor_apply_kernel(const float* __restrict__ Z, const double* __restrict__ G, int K, int r,
                                                                         uint16_t* __restrict__ A, uint16_t* __restrict__ At) {
     __shared__ double2 pan[2][4][64];                                // [buffer][pair of columns of the panel][row]
-    __shared__ __align__(16) float Ls[64 * 64];                      // L below the diagonal, 1 / L[i][i] on it
-    __shared__ float as[64][64];                                     // as[row][lane]: finished rows of A
+    __shared__ double2 diag[4][16][8];                               // the 16 x 16 blocks on L's diagonal (below their diagonals)
+    __shared__ __align__(16) float Lb[4][16][20];                    // the same blocks whole, for the substitution
+    __shared__ __align__(16) double rdiag[64];                       // 1 / L[i][i]
+    __shared__ __align__(16) float Ls[64 * LQ_LS];                   // L below its diagonal blocks, these blocks' inverses
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int k = blockIdx.x * 64 + lane;
-    const bool live = k < K;
-    double g[8];                                                     // row `lane` of my panel; rows above the panel are never used
+    const int i = lane & 15, h = lane >> 4;
+    const int k = blockIdx.x * 64 + 16 * w + i;                      // K is a multiple of 64: wavefronts 0 .. 3 have a column per i
+    double g[8], is[8];                                              // row `lane` of my panel (rows above it are never used); 1 / its pivots
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const double2 v = lane >= 8 * w ? reinterpret_cast<const double2*>(G + lane * 64 + 8 * w)[q] : make_double2(0.0, 0.0);
         g[2 * q] = v.x; g[2 * q + 1] = v.y;
     }
     double maxdiag = G[lane * 65];
-    float s[8];
+    floatx4_t s[4];                                                  // s[b][v]: row 16 b + 4 h + v of column k
 #pragma unroll
-    for (int ii = 0; ii < 8; ++ii) s[ii] = (live && 8 * w + ii < r) ? Z[(size_t)(8 * w + ii) * K + k] : 0.0f;
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s[b][v] = (w < 4 && 16 * b + 4 * h + v < r) ? Z[(size_t)(16 * b + 4 * h + v) * K + k] : 0.0f;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) maxdiag = fmax(maxdiag, __shfl_xor(maxdiag, o, 64));
     const double tiny = 1e-12 * fmax(maxdiag, 0.0);
-    for (int p = 0; p < 8; ++p) {
-        double2 (*pp)[64] = pan[p & 1];
-        if (w == p) {
+    auto factor = [&](int p) {                                       // my panel, p == w: factored and published
+        double pv = lq_readlane(g[0], 8 * p);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const double pv = lq_readlane(g[j], 8 * p + j);
-                g[j] *= pv > tiny ? lq_rsqrt(pv) : 0.0;
-#pragma unroll
-                for (int c = j + 1; c < 8; ++c) g[c] = fma(-g[j], lq_readlane(g[j], 8 * p + c), g[c]);
+        for (int j = 0; j < 8; ++j) {
+            is[j] = pv > tiny ? lq_rsqrt(pv) : 0.0;
+            double l = 0.0;
+            if (j < 7) {                                             // the same operations as in the column below
+                l = lq_readlane(g[j], 8 * p + j + 1) * is[j];
+                pv = fma(-l, l, lq_readlane(g[j + 1], 8 * p + j + 1));
             }
-            float o[8];
+            g[j] *= is[j];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if (j & 1) pp[j >> 1][lane] = make_double2(g[j - 1], g[j]);
-                o[j] = (float)g[j];
-                if (lane == 8 * p + j) o[j] = g[j] > 0.0 ? (float)lq_rcp(g[j]) : 0.0f;
-            }
-            float4* dst = reinterpret_cast<float4*>(Ls + lane * 64 + 8 * p);
-            dst[0] = make_float4(o[0], o[1], o[2], o[3]);
-            dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+            for (int c = j + 1; c < 8; ++c) g[c] = fma(-g[j], c == j + 1 ? l : lq_readlane(g[j], 8 * p + c), g[c]);
         }
-        __syncthreads();
-        if (w > p) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double2 mine = pp[q][lane];
+        for (int q = 0; q < 4; ++q) pan[p & 1][q][lane] = make_double2(g[2 * q], g[2 * q + 1]);
+    };
+    auto update = [&](int p) {                                       // my panel less panel p's rank-8 product
 #pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const double2 l = pp[q][8 * w + c];
-                    g[c] = fma(-mine.y, l.y, fma(-mine.x, l.x, g[c]));
-                }
+        for (int q = 0; q < 4; ++q) {
+            const double2 mine = pan[p & 1][q][lane];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const double2 l = pan[p & 1][q][8 * w + c];
+                g[c] = fma(-mine.y, l.y, fma(-mine.x, l.x, g[c]));
             }
-        }
-    }
-    float ld[8][8], lb[8][8];                                        // my rows of L: the triangle's block, the current stage's block
-    auto fetch = [&](float (&dst)[8][8], int cb) {
-#pragma unroll
-        for (int ii = 0; ii < 8; ++ii) {
-            const float4 l0 = *reinterpret_cast<const float4*>(&Ls[(8 * w + ii) * 64 + 8 * cb]);
-            const float4 l1 = *reinterpret_cast<const float4*>(&Ls[(8 * w + ii) * 64 + 8 * cb + 4]);
-            dst[ii][0] = l0.x; dst[ii][1] = l0.y; dst[ii][2] = l0.z; dst[ii][3] = l0.w;
-            dst[ii][4] = l1.x; dst[ii][5] = l1.y; dst[ii][6] = l1.z; dst[ii][7] = l1.w;
         }
     };
-    fetch(ld, w);
-    if (w > 0) fetch(lb, 0);
-    for (int jb = 0; jb < 8; ++jb) {
-        if (w == jb) {
-            uint32_t pk[4];
+    if (w == 0) factor(0);
+    for (int p = 0; p < 8; ++p) {
+        __syncthreads();                                             // panel p is published
+        if (w == p + 1) update(p);                                   // the next panel first, with the LDS to itself
+        if (w == p) {
+            if (h == p >> 1) {
 #pragma unroll
-            for (int ii = 0; ii < 8; ++ii) {
-#pragma unroll
-                for (int jj = 0; jj < ii; ++jj) s[ii] = fmaf(-ld[ii][jj], s[jj], s[ii]);
-                s[ii] *= ld[ii][ii];                                 // the diagonal holds 1 / L[i][i]
-                as[8 * w + ii][lane] = s[ii];
-                const uint32_t b = pack_bf16x2(s[ii], 0.0f) & 0xffffu;
-                if (live) A[(size_t)(8 * w + ii) * K + k] = (uint16_t)b;
-                if (ii & 1) pk[ii >> 1] |= b << 16; else pk[ii >> 1] = b;
+                for (int q = 0; q < 4; ++q) {
+                    diag[h][i][4 * (p & 1) + q] = make_double2(g[2 * q], g[2 * q + 1]);
+                    const int c = 8 * (p & 1) + 2 * q;
+                    *reinterpret_cast<float2*>(&Lb[h][i][c]) = make_float2(c <= i ? (float)g[2 * q] : 0.0f, c + 1 <= i ? (float)g[2 * q + 1] : 0.0f);
+                }
             }
-            if (live) reinterpret_cast<uint4*>(At + (size_t)k * LQ_RP)[w] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+            if (lane == 0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) reinterpret_cast<double2*>(rdiag + 8 * p)[q] = make_double2(is[2 * q], is[2 * q + 1]);
+            }
+            if (h > p >> 1) {
+                float4* dst = reinterpret_cast<float4*>(Ls + lane * LQ_LS + 8 * p);
+                dst[0] = make_float4((float)g[0], (float)g[1], (float)g[2], (float)g[3]);
+                dst[1] = make_float4((float)g[4], (float)g[5], (float)g[6], (float)g[7]);
+            }
         }
         __syncthreads();
-        if (w > jb) {
-            float aj[8];
+        if (w == p + 1) factor(p + 1);
+        else if (w > p) update(p);
+        else if ((p & 1) && w == p - 1) {                            // block p / 2 of the diagonal is complete: its inverse
+            const int b = p >> 1;
+            double l[16], x[4];                                      // row i of L's block; entries 4 h + v of row i of the inverse
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) aj[jj] = as[8 * jb + jj][lane];
+            for (int q = 0; q < 8; ++q) {
+                const double2 v = diag[b][i][q];
+                l[2 * q] = i > 2 * q ? v.x : 0.0; l[2 * q + 1] = i > 2 * q + 1 ? v.y : 0.0;
+            }
+            const double mine = rdiag[16 * b + i];
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj)
-#pragma unroll
-                for (int ii = 0; ii < 8; ++ii) s[ii] = fmaf(-lb[ii][jj], aj[jj], s[ii]);
-            if (jb + 1 < w) fetch(lb, jb + 1);
+            for (int v = 0; v < 4; ++v) x[v] = i == 4 * h + v ? 1.0 : 0.0;
+            lq_invert_from<0>(x, l, rdiag + 16 * b);
+            *reinterpret_cast<float4*>(Ls + (16 * b + i) * LQ_LS + 16 * b + 4 * h) =
+                make_float4((float)(x[0] * mine), (float)(x[1] * mine), (float)(x[2] * mine), (float)(x[3] * mine));
         }
+    }
+    __syncthreads();
+    if (w >= 4) return;                                              // whole wavefronts; no barrier follows
+    auto block = [&](const float* at, float sign, const floatx4_t& x, floatx4_t acc) {   // acc + sign times the block at `at`, x
+        const float4 l = *reinterpret_cast<const float4*>(at);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sign * l.x, x[0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sign * l.y, x[1], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sign * l.z, x[2], acc, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(sign * l.w, x[3], acc, 0, 0, 0);
+    };
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const float* at = Ls + (16 * b + i) * LQ_LS + 16 * b + 4 * h;
+        floatx4_t a = block(at, 1.0f, s[b], floatx4_t{0.0f, 0.0f, 0.0f, 0.0f});
+        a = block(at, 1.0f, block(&Lb[b][i][4 * h], -1.0f, a, s[b]), a);
+#pragma unroll
+        for (int c = b + 1; c < 4; ++c) s[c] = block(at + 16 * (c - b) * LQ_LS, -1.0f, a, s[c]);
+        const uint32_t lo = pack_bf16x2(a[0], a[1]), hi = pack_bf16x2(a[2], a[3]);
+        uint16_t* dst = A + (size_t)(16 * b + 4 * h) * K + k;
+        dst[0] = (uint16_t)lo; dst[K] = (uint16_t)(lo >> 16); dst[2 * (size_t)K] = (uint16_t)hi; dst[3 * (size_t)K] = (uint16_t)(hi >> 16);
+        *reinterpret_cast<uint2*>(At + (size_t)k * LQ_RP + 16 * b + 4 * h) = make_uint2(lo, hi);
     }
 }
 

@@ -249,3 +249,18 @@ def test_loftq_full_size_objective():
         assert float((G - torch.eye(64, device="cuda")).abs().max()) <= ORTHONORMAL_TOL
     print(f"    plain {plain:.3f}  step 1 {objs[0]:.3f}  step 5 {objs[1]:.3f}", flush=True)
     assert objs[1] < objs[0] < plain
+
+
+@pytest.mark.parametrize("r", [1, 15, 17, 47, 63, 64])
+def test_loftq_nearly_dependent_start(r):
+    """Ranks at the edges of the factorisation's panels of 8 and blocks of 16, from a start whose rows are one row plus eight
+    percent each: one round has to take rows apart that share all but 6e-3 of their energy (condition of the factor some
+    1e2, so that fp32 products with it lose about 1e-5 of the unit rows, well inside the bf16 rounding of A)."""
+    seed, N, K, fr = 8, 512, 576, (0.4, 0.3, 0.3)
+    W, bits, cb, cbb, thr, mp = make(seed, N, K, fr, lowrank=False)
+    rng = np.random.default_rng([synth.SEED, 407, r])
+    om = synth.to_bf16_bits(rng.normal(0, 1, (1, K)) + 0.08 * rng.normal(0, 1, (r, K)))
+    p, a, A, B = gpu_run(W, bits, cb, cbb, thr, mp, r, om, 1, iters=1)
+    assert np.isfinite(A).all() and np.abs(A @ A.T - np.eye(r)).max() <= ORTHONORMAL_TOL
+    E = W.astype(np.float64) - orc.dequantize(p, a, bits, cb, mp, K, "fp32")
+    assert rel_err(B, E @ A.T) <= REL_TOL
