@@ -50,7 +50,7 @@ enum {
     LOWRA_INVALID_ARG = 1,         /* null pointer, non-positive size, inconsistent tables */
     LOWRA_UNSUPPORTED = 2,         /* group != 64, bits outside {1,2,4}, K % 64 != 0, ... */
     LOWRA_MISALIGNED = 3,          /* a base pointer is not 16-byte aligned */
-    LOWRA_WORKSPACE_TOO_SMALL = 4, /* workspace_bytes < lowra_workspace_bytes(...) */
+    LOWRA_WORKSPACE_TOO_SMALL = 4, /* workspace_bytes < lowra_workspace_bytes(...); the linear calls: see there */
     LOWRA_HIP_ERROR = 5,           /* a HIP runtime call or kernel launch failed */
     LOWRA_OUT_OF_MEMORY = 6        /* a host allocation inside the library failed */
 };
@@ -108,7 +108,9 @@ size_t lowra_packed_bytes(const lowra_layout* layout);
 /* Device scratch a linear call needs (op = LOWRA_OP_*), for M tokens and LoRA rank r.
  * It holds the rank-r intermediate and padded copies of the adapter operands; for the forward with
  * M <= 16 also the small-token kernel's descriptors and per-chunk partial outputs, so it can be
- * non-zero at r == 0. */
+ * non-zero at r == 0; and, for the token counts whose contraction is split between workgroups, the splits'
+ * fp32 partial tiles.  A linear call with less is refused only below what it cannot do without (all but the
+ * room for these splits): it then splits less, which takes longer and adds in another order. */
 size_t lowra_workspace_bytes(const lowra_layout* layout, int op, int M, int r);
 
 /* Quantize (App. A.1).  For every 64-element group: absmax a = max|w| is stored; every weight is
@@ -160,12 +162,12 @@ lowra_status lowra_linear_fwd(const lowra_layout* layout, const uint8_t* packed,
 /* lowra_linear_fwd for callers that cannot allocate device memory and have no workspace to pass: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and
  * results as lowra_linear_fwd (both paths, bit for bit) without `workspace`: the rank-r intermediate and
- * the padded adapter copy live in a static device array of LOWRA_STATIC_SCRATCH_BYTES that every GPU the
- * library runs on holds until the process ends.  The call allocates and frees nothing (no hipMalloc /
+ * the padded adapter copy live in a static device array (LOWRA_STATIC_SCRATCH_BYTES and the room that splits
+ * take at most) that every GPU the library runs on holds until the process ends.  The call allocates and frees nothing (no hipMalloc /
  * hipFree, no allocating library routine); the array's device address is looked up once per device, in
  * lowra_layout_create or at the first call on that device.
- *   WORKSPACE_TOO_SMALL: lowra_workspace_bytes(layout, LOWRA_OP_LINEAR_FWD, M, r) exceeds
- *   LOWRA_STATIC_SCRATCH_BYTES (e.g. more than 32768 tokens at rank 64) -- use lowra_linear_fwd.
+ *   WORKSPACE_TOO_SMALL: what the call cannot do without (lowra_workspace_bytes less the room for splits)
+ *   exceeds LOWRA_STATIC_SCRATCH_BYTES (e.g. more than 32768 tokens at rank 64) -- use lowra_linear_fwd.
  *   INVALID_ARG also when the current device is not the layout's.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two
  * threads) race on it; calls on one stream are ordered and safe.  The array keeps the last call's

@@ -38,7 +38,10 @@ lowra_status plan_rows(int N, int K, int group, const uint8_t* bits, int64_t* of
 // process ends.  In host code the array's NAME is only a handle for hipGetSymbolAddress: the device
 // address is looked up once per device (with that device current) and kept; kernels and copies only
 // ever get that looked-up pointer.
-static __device__ __align__(256) unsigned char scratch[LOWRA_STATIC_SCRATCH_BYTES];
+// Beyond what a call cannot do without (at most LOWRA_STATIC_SCRATCH_BYTES) it has the room that a contraction's splits
+// may ask for, so that the call takes the plan of lowra_linear_fwd with a whole workspace and gives the same bits.
+constexpr size_t kStaticBytes = (size_t)LOWRA_STATIC_SCRATCH_BYTES + lowra::kMidPartMax;
+static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -427,7 +430,7 @@ lowra_status lowra_linear_fwd_static(const lowra_layout* L, const uint8_t* packe
     if (dev != L->device) return LOWRA_INVALID_ARG;               // the layout's index arrays live on another device
     void* ws = static_scratch_of_current_device();
     if (!ws) return LOWRA_HIP_ERROR;
-    return lowra_linear_fwd(L, packed, absmax, mappings, x, M, A, B, r, s, y, ws, (size_t)LOWRA_STATIC_SCRATCH_BYTES, stream);
+    return lowra_linear_fwd(L, packed, absmax, mappings, x, M, A, B, r, s, y, ws, kStaticBytes, stream);
 }
 
 lowra_status lowra_linear_bwd_input(const lowra_layout* L, const uint8_t* packed, const float* absmax,

@@ -715,7 +715,6 @@ static const MidCost kMidCost[2][3] = {
      {{0.80, 1.01, 0.95, 1.01}, {0.51, 0.65, 0.68, 0.76}, 7.1, 4.3, 2.7e-7, 9.6, 2.03},
      {{0.78, 0.84, 1.00, 1.00}, {0.64, 0.68, 0.70, 0.80}, 8.7, 2.8, 2.8e-7, 14.8, 2.50}}};
 static const int kMidResident[2][4] = {{4, 3, 2, 2}, {3, 3, 2, 2}};   // workgroups per compute unit (registers, LDS)
-constexpr size_t kMidPartMax = (size_t)64 << 20;
 
 MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_bytes) {
     MidPlan best{0, 0, 0, 0, 0};

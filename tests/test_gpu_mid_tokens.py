@@ -94,3 +94,14 @@ def test_mid_token_less_workspace():
     with pytest.raises(lowra.LowraError, match="workspace too small"):
         lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, L.s,
                                workspace=torch.empty(side - 256, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("N,K,M,r", [(4096, 4096, 128, 64), (11008, 4096, 66, 16), (4096, 11008, 300, 0), (1032, 4160, 40, 24)])
+def test_static_scratch_splits_the_same_way(N, K, M, r):
+    """The forward without a workspace has the same room for partial tiles: same plan, same bits."""
+    print(f"[mid static {N}x{K} M{M} r{r}]", flush=True)
+    D = DeviceLayer(synth.make_custom(N, K, M, r, fractions=(0.4, 0.3, 0.3), seed=870 + r))
+    D.quantize()
+    want = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, D.L.s)
+    y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    assert torch.equal(lowra.lowra_linear_fwd_static(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, D.L.s, y), want)
