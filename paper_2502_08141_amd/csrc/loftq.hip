@@ -110,8 +110,8 @@ __global__ __launch_bounds__(256) void residual_of_decode_kernel(const RowInfo* 
 }
 
 // ---- partial Gram matrices of Z [r][K]: the sum over a chunk's columns of Z[i][k] Z[j][k] (fp64), kept block by block:
-// Gp[chunk][16 bj + bi][4 u + v] is entry (4 bi + u, 4 bj + v), so that the thread of the factorisation that owns a
-// 4 x 4 block reads one 128-byte line per chunk.  Only the blocks on and below the diagonal are written or read.
+// Gp[chunk][16 bj + bi][4 u + v] is entry (4 bi + u, 4 bj + v), so that a thread writes its block as one 128-byte line.
+// Only the blocks on and below the diagonal are written or read.
 // One workgroup per (chunk, band of 16 rows): the contraction is bound by a compute unit's fp64 rate, so the 64 x 64
 // outputs of a chunk are dealt over four workgroups.  Wavefront w takes the chunk's columns [32 w, 32 w + 32), lane
 // (bi, bj) the 4 x 4 block of rows 16 band + 4 bi.., columns 4 bj.. ; the four wavefronts' sums meet in LDS and are
@@ -177,8 +177,8 @@ __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ Z, 
 }
 
 // ---- G [64][64] (the blocks on and below the diagonal) = the sum of the partial matrices, entry by entry in chunk order.  A kernel
-// of its own because one compute unit fetches about 30 GB/s: the 0.5 MB of partial matrices took the factorisation's
-// single workgroup 18 us, half of its time; spread over the chip the sum is a microsecond.
+// of its own because one compute unit fetches about 30 GB/s: the 0.5 MB of partial matrices took a single workgroup of
+// the factorisation 18 us; spread over the chip the sum is a microsecond.
 __global__ __launch_bounds__(64) void gram_sum_kernel(const double* __restrict__ Gp, int chunks, double* __restrict__ G) {
     const int e = blockIdx.x * 64 + threadIdx.x;                     // entry 4 u + v of block 16 bj + bi
     const int bj = e >> 8, bi = (e >> 4) & 15;
@@ -217,8 +217,8 @@ __global__ __launch_bounds__(64) void gram_sum_kernel(const double* __restrict__
 // MFMA, a result lies in the registers as the next product reads it, so there is no barrier and no LDS on that chain.
 // Measured at 64 x 4096: 15.9 us, of them 1.2 the loads, 9.8 the factorisation (3600 cycles a panel: its eight pivots
 // 1500, the product off the next panel 950, the rest LDS and barriers), 1.8 the last block's inverse and 1.9 the
-// substitution (in fp64 on the matrix cores this alone took 4 us more).  The two launches before, a panel of four columns over sixteen lanes of one workgroup and a substitution
-// on the vector units with L broadcast from LDS, took 16.3 + 8 us.
+// substitution (in fp64 on the matrix cores this alone took 4 us more).  The two launches before, a panel of four columns
+// over sixteen lanes of one workgroup and a substitution on the vector units with L broadcast from LDS, took 16.3 + 8 us.
 // 1 / sqrt(d) for d > 0 from the hardware's approximation and one Newton step (about 1e-13; the factor is rounded to fp32
 // afterwards): the library's correctly rounded division and square root are some forty instructions each, and one
 // reciprocal root sits on the critical path of every pivot.
