@@ -19,11 +19,10 @@ hipError_t launch_gemm_bwd(const GemmParams& p, hipStream_t st);
 BwdSplitPlan gemm_bwd_split_plan(int N, int K, int M);
 hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st);
 hipError_t launch_skinny_ws(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
-                            float s, uint16_t* out, int RP, float* scratch, float* extra, size_t extra_bytes, hipStream_t st);
+                            float s, uint16_t* out, int RP, float* scratch, float* few, int out_cols, hipStream_t st);
 size_t skinny_scratch_bytes(int M, int Kc, int RP);
-size_t skinny_extra_bytes(int M, int Kc, int RP);
 hipError_t launch_skinny_qt(const uint16_t* P, int ldp, int M, const uint16_t* Qt, int r, int Kc, float s, uint16_t* out,
-                            float* scratch, float* extra, size_t extra_bytes, hipStream_t st);
+                            float* scratch, float* few, int out_cols, hipStream_t st);
 hipError_t launch_pad_cols(const uint16_t* src, int R, int c, uint16_t* dst, int CP, hipStream_t st);
 hipError_t launch_transpose(const uint16_t* src, int R, int c, uint16_t* dst, hipStream_t st);
 
@@ -106,21 +105,11 @@ static MidPlan mid_plan_call(const lowra_layout& L, const LinearArgs& a, int op,
 size_t linear_workspace_min(const lowra_layout& L, int op, int M, int r) {
     return align256(linear_workspace_bytes_fp32(L, op, M, r)) + expanded_scale_bytes(L);
 }
-// what a call can use: the scratch it cannot do without, then room for a rank-r product's partial sums and, after
-// that product is done, for the partial tiles of a mid-token GEMM's splits
+// what a call can use: the scratch it cannot do without, then room for the partial tiles of a mid-token GEMM's splits
 size_t linear_workspace_bytes(const lowra_layout& L, int op, int M, int r) {
     const size_t least = linear_workspace_min(L, op, M, r);
     const MidPlan pl = mid_plan_of(L, op, M, r, 1, ~(size_t)0);
-    const bool small = M <= 16 && (op == 0 ? gemv_fwd_supported(L, M) : gemv_stream_bwd_supported(L, M, r));
-    const size_t more = std::max(pl.splits > 1 ? mid_part_bytes(pl) : 0, r > 0 && !small ? skinny_extra_bytes(M, op == 0 ? L.K : L.N, round_up(r, BK)) : 0);
-    return more ? align256(least) + more : least;
-}
-// that room of a call's workspace
-struct MoreRoom { float* p; size_t bytes; };
-static MoreRoom more_room(const lowra_layout& L, int op, const LinearArgs& a) {
-    const size_t least = align256(linear_workspace_min(L, op, a.M, a.r));
-    if (!a.workspace || a.workspace_bytes <= least) return MoreRoom{nullptr, 0};
-    return MoreRoom{reinterpret_cast<float*>(static_cast<uint8_t*>(a.workspace) + least), a.workspace_bytes - least};
+    return pl.splits > 1 ? align256(least) + mid_part_bytes(pl) : least;
 }
 // With bf16 scales: widen them behind the call's own scratch and run the call on the copy.
 static hipError_t with_fp32_scales(const lowra_layout& L, int op, const LinearArgs& a, LinearArgs& b, bool native, hipStream_t st) {
@@ -194,10 +183,9 @@ hipError_t launch_linear_fwd(const lowra_layout& L, const LinearArgs& a_in, int 
     }
     uint16_t* ws_t = static_cast<uint16_t*>(a.workspace);
     if (RP) {
-        const MoreRoom more = more_room(L, 0, a_in);
         float* scratch = reinterpret_cast<float*>(static_cast<uint8_t*>(a.workspace) + align256((size_t)a.M * RP * 2) +
                                                   (a.r == RP ? 0 : align256((size_t)L.N * RP * 2)));
-        hipError_t e = launch_skinny_ws(a.act, L.K, a.M, a.A, L.K, a.r, L.K, a.s, ws_t, RP, scratch, more.p, more.bytes, st);
+        hipError_t e = launch_skinny_ws(a.act, L.K, a.M, a.A, L.K, a.r, L.K, a.s, ws_t, RP, scratch, reinterpret_cast<float*>(a.out), L.N, st);
         if (e != hipSuccess) return e;
     }
     if (mid.TM > 0) {
@@ -250,12 +238,11 @@ hipError_t launch_linear_bwd_input(const lowra_layout& L, const LinearArgs& a_in
         uint16_t* ws_bt = reinterpret_cast<uint16_t*>(ws + align256((size_t)a.M * RP * 2));
         float* scratch = reinterpret_cast<float*>(ws + align256((size_t)a.M * RP * 2) + align256((size_t)a.r * L.N * 2));
         hipError_t e;
-        const MoreRoom more = more_room(L, 1, a_in);
         if (a.r % 8 == 0 && RP == 64) {                                      // B [N, r] is read in place
-            if ((e = launch_skinny_qt(a.act, L.N, a.M, a.B, a.r, L.N, a.s, ws_u, scratch, more.p, more.bytes, st)) != hipSuccess) return e;
+            if ((e = launch_skinny_qt(a.act, L.N, a.M, a.B, a.r, L.N, a.s, ws_u, scratch, reinterpret_cast<float*>(a.out), L.K, st)) != hipSuccess) return e;
         } else {
             if ((e = launch_transpose(a.B, L.N, a.r, ws_bt, st)) != hipSuccess) return e;          // B^T [r, N]
-            if ((e = launch_skinny_ws(a.act, L.N, a.M, ws_bt, L.N, a.r, L.N, a.s, ws_u, RP, scratch, more.p, more.bytes, st)) != hipSuccess) return e;
+            if ((e = launch_skinny_ws(a.act, L.N, a.M, ws_bt, L.N, a.r, L.N, a.s, ws_u, RP, scratch, reinterpret_cast<float*>(a.out), L.K, st)) != hipSuccess) return e;
         }
         p.ext_act = ws_u;
     }

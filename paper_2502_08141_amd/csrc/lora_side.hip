@@ -234,24 +234,22 @@ static SkinnyPlan skinny_plan(int M, int Kc, int RP) {
     return slices > 1 ? SkinnyPlan{slices, kslice} : SkinnyPlan{1, 0};
 }
 // Few tokens: 16-row workgroups leave most of the chip idle and each walks the whole contraction, 0.33 us per stage of
-// 128 columns.  With room for the slices' partial sums (`extra` below) the contraction is split until the grid has
-// about one workgroup per compute unit; the kernel that adds the slices costs about 2.5 us, so contractions below 1536
-// (twelve stages, 4 us) stay whole.  Kernel times: 333 tokens, 4096 columns 10.6 -> 4.7 + 3 us; 512 tokens, 11008
-// columns 28 -> 7 + 3 us; 9 tokens, 4096 columns 11.8 -> 4.1 + 2.8 us.
-static SkinnyPlan skinny_few_plan(int M, int Kc, int RP) {
+// 128 columns.  The contraction is split until the grid has about one workgroup per compute unit; the kernel that adds
+// the slices costs about 2.5 us, so contractions below 1536 (twelve stages, 4 us) stay whole.  Kernel times: 333 tokens,
+// 4096 columns 10.6 -> 4.7 + 3 us; 512 tokens, 11008 columns 28 -> 7 + 3 us; 9 tokens, 4096 columns 11.8 -> 4.1 + 2.8 us.
+// The split is a function of the shape alone, never of the workspace a caller happens to pass: the linear calls and the
+// adapter gradients must form the same bits.  So the slices' partial sums go where every call has room: a linear call
+// puts them into its own output [M, out_cols] bf16, which its last kernel writes afterwards (hence out_cols / 128
+// slices at most: 256 bytes per token and slice); the adapter gradients, into the region of their partial tiles, which
+// holds a row of 256 bytes per channel and per feature (hence Kc rows at most).
+static SkinnyPlan skinny_few_plan(int M, int Kc, int RP, int out_cols) {
     const int blocks = (M + 15) / 16;
     if (RP != 64 || M < 1 || Kc < 1536 || 2 * blocks > device_compute_units()) return SkinnyPlan{1, 0};
-    // (at most Kc rows of partial sums: the adapter gradients' workspace always has that room, so that they split as the
-    // linear calls do and their intermediates agree bit for bit)
-    int slices = std::min(std::min(std::min(device_compute_units() / blocks, Kc / 512), 16), Kc / M);
+    int slices = std::min(std::min(std::min(device_compute_units() / blocks, Kc / 512), 16), std::min(Kc / M, out_cols / 128));
     if (slices < 2) return SkinnyPlan{1, 0};
     const int kslice = ((Kc + slices - 1) / slices + 127) / 128 * 128;
     slices = (Kc + kslice - 1) / kslice;
     return slices > 1 ? SkinnyPlan{slices, kslice} : SkinnyPlan{1, 0};
-}
-size_t skinny_extra_bytes(int M, int Kc, int RP) {
-    const SkinnyPlan pl = skinny_few_plan(M, Kc, RP);
-    return pl.slices > 1 ? (size_t)pl.slices * M * RP * sizeof(float) : 0;
 }
 size_t skinny_scratch_bytes(int M, int Kc, int RP) {
     const SkinnyPlan pl = skinny_plan(M, Kc, RP);
@@ -260,23 +258,23 @@ size_t skinny_scratch_bytes(int M, int Kc, int RP) {
 
 template <bool QT>
 static hipError_t launch_skinny_any(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
-                                    float s, uint16_t* out, int RP, float* scratch, float* extra, size_t extra_bytes, hipStream_t st) {
+                                    float s, uint16_t* out, int RP, float* scratch, float* few, int out_cols, hipStream_t st) {
     // the kernel addresses P rows with 32-bit byte offsets: very tall inputs go in slabs of rows
     const long long max_rows = ((1LL << 31) / ((long long)ldp * 2)) & ~63LL;
     if (max_rows < 64 || (long long)r * ldq * 2 >= (1LL << 31) || (QT && (RP != 64 || (r & 7) || (long long)Kc * r * 2 >= (1LL << 32)))) return hipErrorInvalidValue;
     const SkinnyPlan pl = scratch && M <= max_rows ? skinny_plan(M, Kc, RP) : SkinnyPlan{1, 0};
-    if (extra && M <= max_rows) {
-        const SkinnyPlan few = skinny_few_plan(M, Kc, RP);
-        if (few.slices > 1 && (size_t)few.slices * M * RP * sizeof(float) <= extra_bytes) {
+    if (few && M <= max_rows) {
+        const SkinnyPlan fp = skinny_few_plan(M, Kc, RP, out_cols);
+        if (fp.slices > 1) {
             constexpr int sh = 7 * (16 + 64) * 128 * 2;
             static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_nt_kernel<4, 128, 4, 7, 1, QT>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, sh);
             if (attr != hipSuccess) return attr;
-            skinny_nt_kernel<4, 128, 4, 7, 1, QT><<<dim3((M + 15) / 16, few.slices), dim3(512), sh, st>>>(P, ldp, M, Q, ldq, r, Kc, s, out, extra, few.kslice);
+            skinny_nt_kernel<4, 128, 4, 7, 1, QT><<<dim3((M + 15) / 16, fp.slices), dim3(512), sh, st>>>(P, ldp, M, Q, ldq, r, Kc, s, out, few, fp.kslice);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
             const size_t n4 = (size_t)M * RP / 4;
-            skinny_sum_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(reinterpret_cast<const float4*>(extra), few.slices, n4, s,
+            skinny_sum_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(reinterpret_cast<const float4*>(few), fp.slices, n4, s,
                                                                                        reinterpret_cast<uint2*>(out));
             return hipGetLastError();
         }
@@ -331,15 +329,15 @@ static hipError_t launch_skinny_any(const uint16_t* P, int ldp, int M, const uin
     }
     return hipGetLastError();
 }
-// `scratch`: skinny_scratch_bytes of it, or null; `extra`: more of it that may be there (skinny_extra_bytes is what is used)
+// `scratch`: skinny_scratch_bytes of it, or null; `few`: where few tokens' partial sums go (above), or null: no such split
 hipError_t launch_skinny_ws(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
-                            float s, uint16_t* out, int RP, float* scratch, float* extra, size_t extra_bytes, hipStream_t st) {
-    return launch_skinny_any<false>(P, ldp, M, Q, ldq, r, Kc, s, out, RP, scratch, extra, extra_bytes, st);
+                            float s, uint16_t* out, int RP, float* scratch, float* few, int out_cols, hipStream_t st) {
+    return launch_skinny_any<false>(P, ldp, M, Q, ldq, r, Kc, s, out, RP, scratch, few, out_cols, st);
 }
 // out[m][j] = bf16( s * sum_c P[m][c] Qt[c][j] ) with Qt [Kc][r] row-major, r a multiple of 8 up to 64: no transposed copy needed
 hipError_t launch_skinny_qt(const uint16_t* P, int ldp, int M, const uint16_t* Qt, int r, int Kc, float s, uint16_t* out,
-                            float* scratch, float* extra, size_t extra_bytes, hipStream_t st) {
-    return launch_skinny_any<true>(P, ldp, M, Qt, r, r, Kc, s, out, 64, scratch, extra, extra_bytes, st);
+                            float* scratch, float* few, int out_cols, hipStream_t st) {
+    return launch_skinny_any<true>(P, ldp, M, Qt, r, r, Kc, s, out, 64, scratch, few, out_cols, st);
 }
 hipError_t launch_skinny(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
                          float s, uint16_t* out, int RP, hipStream_t st) {
