@@ -84,7 +84,8 @@ __device__ __forceinline__ void mse_row(const float4* __restrict__ w4, int units
                     float l2 = (T.t2a < u[i]) ? T.m2b : T.m2a;         // the highest threshold below u decides
                     l2 = (T.t2b < u[i]) ? T.m2c : l2;
                     l2 = (T.t2c < u[i]) ? T.m2d : l2;
-                    const float d1 = fmaf(-l1, a, v[i]), d2 = fmaf(-l2, a, v[i]), d4 = fmaf(-l4[i], a, v[i]);
+                    // the decoded weight is the product ROUNDED to fp32: a weight that equals it has no error
+                    const float d1 = v[i] - l1 * a, d2 = v[i] - l2 * a, d4 = v[i] - l4[i] * a;
                     e1 = fmaf(d1, d1, e1); e2 = fmaf(d2, d2, e2); e4 = fmaf(d4, d4, e4);   // (the build does not contract on its own)
                 }
             }

@@ -38,6 +38,25 @@ def test_error_table(name, N, K):
     assert np.allclose(got.cpu().numpy(), want, rtol=1e-5, atol=0)   # fp32 partial sums per thread against fp64
 
 
+def test_decoded_weights_have_no_error():
+    """Weights that are already decoded values (level times absmax, rounded to fp32) quantize to themselves: the error at
+    their own width is exactly zero, so that an assignment of widths gains nothing by a wider one."""
+    thr, mp, _ = synth.shared_codebooks()
+    thr, mp = thr.copy(), mp.copy()
+    rng = np.random.default_rng(3)
+    for p, b in enumerate((1, 2, 4)):
+        lv = np.linspace(-1, 1, 1 << b) * np.where(np.abs(np.linspace(-1, 1, 1 << b)) == 1, 1, 1 + 0.02 * rng.normal(size=1 << b))
+        mp[p, :1 << b] = lv
+        thr[p, :(1 << b) - 1] = (lv[1:] + lv[:-1]) / 2
+        code = rng.integers(0, 1 << b, (37, 320))
+        code[:, ::64] = 0                                     # level -1 in every block: its absmax is the scale itself
+        a = rng.uniform(0.01, 0.1, (37, 5)).astype(np.float32).repeat(64, axis=1)
+        W = mp[p][code] * a
+        assert W.dtype == np.float32
+        got = lowra.lowra_channel_mse(torch.from_numpy(W).cuda(), torch.from_numpy(thr).cuda(), torch.from_numpy(mp).cuda()).cpu()
+        assert not got[:, p].any(), f"{b} bits: {got[:, p].max()}"
+
+
 @pytest.mark.parametrize("fractions", [(0.4, 0.3, 0.3), (0.5, 0.5, 0.0), (1.0, 0.0, 0.0), (0.0, 0.0, 1.0)])
 def test_average_thresholds_many_channels(fractions):
     N = 13001                                                 # past the 12288 channels of one pass
