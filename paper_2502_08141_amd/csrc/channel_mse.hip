@@ -120,8 +120,9 @@ __global__ __launch_bounds__(256) void channel_mse_kernel(const float* __restric
         bucket[1][tid] = lev4[below];
         bucket[2][tid] = lev4[min(below + 1, 15)];
     }
-    // an infinite u (a block of subnormal weights) may pass any threshold: those tables keep the bisection as well
-    crowded = crowded || (tid < 15 && thr4[tid] >= 1.5f);
+    // an infinite u (a block of subnormal weights) may pass any threshold: those tables keep the bisection as well, and so
+    // do thresholds that are not ascending (the bucket counts below would name another one than the bucket's own)
+    crowded = crowded || (tid < 15 && thr4[tid] >= 1.5f) || (tid < 14 && !(thr4[tid] <= thr4[tid + 1]));
     const bool bisect = __syncthreads_or(crowded) != 0;
     for (int n = blockIdx.x * 2; n < min((int)blockIdx.x * 2 + 2, N); ++n) {
         const float4* w4 = reinterpret_cast<const float4*>(W + (size_t)n * K);

@@ -38,6 +38,26 @@ def test_error_table(name, N, K):
     assert np.allclose(got.cpu().numpy(), want, rtol=1e-5, atol=0)   # fp32 partial sums per thread against fp64
 
 
+@pytest.mark.parametrize("seed", range(3))
+def test_thresholds_out_of_order(seed):
+    """A violated precondition: any code below 16 would do, and it is the one that the bisection ends at."""
+    rng = np.random.default_rng(seed)
+    thr, mp, _ = synth.shared_codebooks()
+    thr = thr.copy()
+    T = np.linspace(-0.93, 0.93, 15).astype(np.float32)       # one to a bucket
+    T = rng.permutation(T) if seed else np.concatenate([T[:2], T[9:10], T[3:9], T[2:3], T[10:]])
+    thr[2, :15] = T
+    W = rng.normal(0, 0.02, (7, 640)).astype(np.float32)
+    got = lowra.lowra_channel_mse(torch.from_numpy(W).cuda(), torch.from_numpy(thr).cuda(), torch.from_numpy(mp).cuda()).cpu().numpy()
+    a = np.abs(W.reshape(7, 10, 64)).max(axis=2).repeat(64, axis=1)
+    u = W * (np.float32(1) / a)
+    c = np.zeros(W.shape, np.int64)
+    for at in (lambda c: 8 * c + 7, lambda c: 8 * c + 3, lambda c: 4 * c + 1, lambda c: 2 * c):   # the code's bits from the top
+        c = 2 * c + (T[at(c)] < u)
+    want = np.square((W - mp[2][c] * a).astype(np.float64)).mean(axis=1)
+    assert np.allclose(got[:, 2], want, rtol=1e-5, atol=0)
+
+
 def test_decoded_weights_have_no_error():
     """Weights that are already decoded values (level times absmax, rounded to fp32) quantize to themselves: the error at
     their own width is exactly zero, so that an assignment of widths gains nothing by a wider one."""
