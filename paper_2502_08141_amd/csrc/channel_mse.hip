@@ -28,7 +28,8 @@
 namespace lowra {
 
 constexpr int kMseBuckets = 64;
-__device__ __forceinline__ int mse_bucket(float u) { return min(max((int)fmaf(u, 32.0f, 32.0f), 0), kMseBuckets - 1); }
+// (clamped before the conversion: thresholds and the u of a block of subnormal weights may be infinite, or not numbers)
+__device__ __forceinline__ int mse_bucket(float u) { return (int)fminf(fmaxf(fmaf(u, 32.0f, 32.0f), 0.0f), kMseBuckets - 1.0f); }
 
 struct MseTabs { float t1, t2a, t2b, t2c, t4_3, t4_7, t4_11, m1a, m1b, m2a, m2b, m2c, m2d; };
 // squared errors of one channel at 1, 2 and 4 bits, this thread's share
