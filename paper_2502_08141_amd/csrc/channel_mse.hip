@@ -6,17 +6,20 @@
 // with absmax, normalisation and binning exactly as in the quantize kernel (App. A.1) and the fp32
 // decode of App. A.2: quantize -> decode -> squared error fused in one pass over W, nothing packed.
 //
-// Mapping: one workgroup per two channels, a lane owns 8 consecutive weights (a block is 8 adjacent
+// Mapping: one workgroup per channel or two, a lane owns 8 consecutive weights (a block is 8 adjacent
 // lanes), all three widths from the same registers; the narrow widths' levels are selected in
-// registers.  What bounds it is plain-ALU work per weight, beside 4 bytes from HBM once: the 4-bit code
-// -- the number of thresholds strictly below u, App. A.1 -- was found by bisection (14 instructions and
-// three LDS reads).  Now [-1, 1] is cut into 64 buckets; a bucket's entry holds the one threshold inside it and
-// the levels on its two sides, so that a scaled conversion, three LDS reads without conflicts, one compare and
-// one select give the level.  The bucket of a value is a monotone function of it, the same for thresholds
-// and weights, so thresholds of lower buckets are below u and those of higher ones are not: the code is
-// the bisection's.  Tables with two thresholds in one bucket keep the bisection.
-// 11008 x 4096: 41 us = 4.4 TB/s (bisection for every weight: 46.5 us); 25 plain-ALU instructions per weight are left, which
-// is 38 us at 2.1 GHz.
+// registers.  What bounds it is plain-ALU work per weight, beside 4 bytes from HBM once.  The 4-bit code
+// -- the number of thresholds strictly below u, App. A.1 -- is found by bisection (14 instructions and
+// three LDS reads) or, in long rows, by buckets: [-1, 1] is cut into 64; a bucket's entry holds the one threshold
+// inside it and the levels on its two sides, so that a scaled conversion, three LDS reads without conflicts, one
+// compare and one select give the level.  The bucket of a value is a monotone function of it, the same for
+// thresholds and weights, so thresholds of lower buckets are below u and those of higher ones are not: the code is
+// the bisection's.  Tables with two thresholds in one bucket, or out of order, keep the bisection.
+// The form by sizes, kernel times of calls in a graph (bisection, one channel per workgroup | buckets, one | two):
+//   below 4096 features the entries cost more than they save: 11008 x 2048 23.3 | 28.7 | 25.4 us, 2048 x 1024 5.4 |
+//   7.2 | 6.4; 4096 x 11008 38.4 | 34.3 | 35.5, 11008 x 4096 37.6 | 39.1 | 36.9 us (4.9 TB/s);
+//   two channels share the entries from 2048 channels on: 16384 x 4096 54.0 | 55.7 | 52.1, 2048 x 4096 9.9 | 10.5 |
+//   10.1; fewer leave half of the workgroups' places empty: 1536 x 11008 18.8 | 16.8 | 18.2, 128 x 4096 4.0 | 4.6 | 6.1.
 #include <algorithm>
 #include <queue>
 #include <tuple>
@@ -94,8 +97,9 @@ __device__ __forceinline__ void mse_row(const float4* __restrict__ w4, int units
     }
 }
 
+template <bool BUCKETS>
 __global__ __launch_bounds__(256) void channel_mse_kernel(const float* __restrict__ W, const float* __restrict__ thr3,
-                                                          const float* __restrict__ map3, float* __restrict__ mse, int N, int K) {
+                                                          const float* __restrict__ map3, float* __restrict__ mse, int N, int K, int per) {
     __shared__ float bucket[3][kMseBuckets];                      // threshold; level below it; level above it: bank = bucket, no conflicts
     __shared__ float lev4[16];
     __shared__ float thr4[16];                                    // sorted, entry 15 unused
@@ -107,8 +111,8 @@ __global__ __launch_bounds__(256) void channel_mse_kernel(const float* __restric
                          thr3[2 * kTableStride + 3], thr3[2 * kTableStride + 7], thr3[2 * kTableStride + 11],
                          map3[0], map3[1], map3[kTableStride], map3[kTableStride + 1], map3[kTableStride + 2], map3[kTableStride + 3]};
     __syncthreads();
-    bool crowded = false;
-    if (tid < kMseBuckets) {
+    bool crowded = !BUCKETS;
+    if (BUCKETS && tid < kMseBuckets) {
         int below = 0, inside = 0;
 #pragma unroll
         for (int j = 0; j < 15; ++j) {
@@ -124,11 +128,11 @@ __global__ __launch_bounds__(256) void channel_mse_kernel(const float* __restric
     // an infinite u (a block of subnormal weights) may pass any threshold: those tables keep the bisection as well, and so
     // do thresholds that are not ascending (the bucket counts below would name another one than the bucket's own)
     crowded = crowded || (tid < 15 && thr4[tid] >= 1.5f) || (tid < 14 && !(thr4[tid] <= thr4[tid + 1]));
-    const bool bisect = __syncthreads_or(crowded) != 0;
-    for (int n = blockIdx.x * 2; n < min((int)blockIdx.x * 2 + 2, N); ++n) {
+    const bool bisect = !BUCKETS || __syncthreads_or(crowded) != 0;
+    for (int n = blockIdx.x * per; n < min((int)blockIdx.x * per + per, N); ++n) {
         const float4* w4 = reinterpret_cast<const float4*>(W + (size_t)n * K);
         float e1 = 0.0f, e2 = 0.0f, e4 = 0.0f;
-        if (bisect) mse_row<true>(w4, units, tid, bucket, thr4, lev4, tab, e1, e2, e4);
+        if (!BUCKETS || bisect) mse_row<true>(w4, units, tid, bucket, thr4, lev4, tab, e1, e2, e4);
         else mse_row<false>(w4, units, tid, bucket, thr4, lev4, tab, e1, e2, e4);
         const double s1 = wave_sum((double)e1), s2 = wave_sum((double)e2), s4 = wave_sum((double)e4);
         __syncthreads();                                          // the previous channel's sums have been read
@@ -141,7 +145,9 @@ __global__ __launch_bounds__(256) void channel_mse_kernel(const float* __restric
 hipError_t launch_channel_mse(int N, int K, const float* W, const float* thr3, const float* map3, float* mse, hipStream_t st) {
     if (N == 0) return hipSuccess;
     KernelTimer timer(st);
-    channel_mse_kernel<<<dim3((N + 1) / 2), dim3(256), 0, st>>>(W, thr3, map3, mse, N, K);
+    const int per = K >= 4096 && N >= 2048 ? 2 : 1;               // channels per workgroup
+    if (K >= 4096) channel_mse_kernel<true><<<dim3((N + per - 1) / per), dim3(256), 0, st>>>(W, thr3, map3, mse, N, K, per);
+    else channel_mse_kernel<false><<<dim3(N), dim3(256), 0, st>>>(W, thr3, map3, mse, N, K, 1);
     return hipGetLastError();
 }
 

@@ -20,7 +20,7 @@ TABLES = {
 
 
 @pytest.mark.parametrize("name", list(TABLES))
-@pytest.mark.parametrize("N,K", [(1, 64), (5, 4160)])
+@pytest.mark.parametrize("N,K", [(1, 64), (5, 4160), (3, 4032), (1, 4096), (2049, 4096)])   # bisection below 4096 features; pairs from 2048 channels
 def test_error_table(name, N, K):
     print(f"[error table {name} {N}x{K}]", flush=True)
     thr, mp, _ = synth.shared_codebooks()
