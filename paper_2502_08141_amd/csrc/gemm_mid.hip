@@ -28,6 +28,8 @@ typedef short mid_v4i16_t __attribute__((ext_vector_type(4)));
 typedef short mid_v8i16_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) mid_v4i16_t* mid_lds_v4i16_ptr;
 
+__device__ const uint4 mid_zeros[1] = {};        // what a transfer reads for features past the end of a row
+
 // packed rows start at multiples of 8 bytes only (K = 64 x an odd number): no 16-byte alignment to rely on
 __device__ __forceinline__ uint4 load16_u(const uint8_t* q) {
     const u32x4a4_t v = *reinterpret_cast<const u32x4a4_t*>(q);
@@ -161,9 +163,12 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
         if ((t >> 2) * 256 + 256 <= K) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) dma16_s(act0 + k, voff[i], dst + i * 1024);
-        } else {                                                      // features past K: valid bytes of the same row, zero weights
+        } else {                                                      // features past K are zeros: an infinity times a zero weight is none
 #pragma unroll
-            for (int i = 0; i < TM; ++i) dma16_s(act0, roff[i] + (uint32_t)min(k + koff[i], K - 8) * 2u, dst + i * 1024);
+            for (int i = 0; i < TM; ++i) {                            // (at least one transfer per i: the waits below count them)
+                if (koff[i] < K - k) dma16_s(act0 + k, voff[i], dst + i * 1024);
+                else dma16_s(mid_zeros, 0u, dst + i * 1024);
+            }
         }
     };
     issue(t_lo, 0);
