@@ -387,6 +387,10 @@ lowra_status lowra_assign_precisions(int N, const int64_t* channel_params_host, 
                ? LOWRA_OK : LOWRA_INVALID_ARG;
 }
 
+// The bytes of a linear call's workspace that it may use.  A call that needs none takes any pointer, also one that is not
+// aligned: such a workspace is left alone, as if it were not there.
+static size_t usable_bytes(const void* workspace, size_t bytes) { return workspace && aligned16(workspace) ? bytes : 0; }
+
 static lowra_status check_linear(const lowra_layout* L, int op, const uint8_t* packed, const float* absmax,
                                  const float* mappings, const uint16_t* act, int M, const uint16_t* A,
                                  const uint16_t* B, int r, const uint16_t* out, const void* workspace,
@@ -414,7 +418,7 @@ lowra_status lowra_linear_fwd(const lowra_layout* L, const uint8_t* packed, cons
                               size_t workspace_bytes, void* stream) {
     lowra_status st = check_linear(L, LOWRA_OP_LINEAR_FWD, packed, absmax, mappings, x, M, A, B, r, y, workspace, workspace_bytes);
     if (st != LOWRA_OK || M == 0 || L->N == 0) return st;
-    lowra::LinearArgs a{packed, absmax, mappings, x, M, A, B, r, s, y, workspace, workspace ? workspace_bytes : 0};
+    lowra::LinearArgs a{packed, absmax, mappings, x, M, A, B, r, s, y, workspace, usable_bytes(workspace, workspace_bytes)};
     return lowra::launch_linear_fwd(*L, a, g_linear_path.load(), g_fwd_tiling.load(), static_cast<hipStream_t>(stream)) == hipSuccess
                ? LOWRA_OK : LOWRA_HIP_ERROR;
 }
@@ -442,7 +446,7 @@ lowra_status lowra_linear_bwd_input(const lowra_layout* L, const uint8_t* packed
     if (L->N == 0) {   // empty contraction: dX = 0, written by a fill kernel (no memset node, so the call can be captured)
         return lowra::launch_zero_bf16(dX, (size_t)M * L->K, static_cast<hipStream_t>(stream)) == hipSuccess ? LOWRA_OK : LOWRA_HIP_ERROR;
     }
-    lowra::LinearArgs a{packed, absmax, mappings, dY, M, A, B, r, s, dX, workspace, workspace ? workspace_bytes : 0};
+    lowra::LinearArgs a{packed, absmax, mappings, dY, M, A, B, r, s, dX, workspace, usable_bytes(workspace, workspace_bytes)};
     return lowra::launch_linear_bwd_input(*L, a, g_linear_path.load(), static_cast<hipStream_t>(stream)) == hipSuccess
                ? LOWRA_OK : LOWRA_HIP_ERROR;
 }

@@ -119,6 +119,20 @@ def test_mid_token_less_workspace():
                                workspace=torch.empty(side - 256, dtype=torch.uint8, device="cuda"))
 
 
+def test_mid_token_unaligned_workspace():
+    """Without a LoRA term the forward needs no workspace, so a pointer that is not aligned is no error: nothing is put there."""
+    L = synth.make_custom(1032, 2048, 40, 1, fractions=MIXED, seed=772)
+    D = DeviceLayer(L)
+    D.quantize()
+    call = lambda ws: lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, None, None, L.s, workspace=ws)
+    need = D.layout.workspace_bytes(lowra.OP_LINEAR_FWD, L.M, 0)
+    assert need > 0                                           # an aligned one would hold partial tiles
+    buf = torch.full((need + 16,), 0x5a, dtype=torch.uint8, device="cuda")
+    got = call(buf[4:])
+    assert torch.equal(got, call(torch.empty(0, dtype=torch.uint8, device="cuda")))
+    assert (buf == 0x5a).all()
+
+
 @pytest.mark.parametrize("N,K,M,r", [(4096, 4096, 128, 64), (11008, 4096, 66, 16), (4096, 11008, 300, 0), (1032, 4160, 40, 24)])
 def test_static_scratch_splits_the_same_way(N, K, M, r):
     """The forward without a workspace has the same room for partial tiles: same plan, same bits."""
