@@ -138,10 +138,8 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
     // steps of the last superstep: a single group left is the first half's first two steps
     const int t_lo = s_lo * 4, t_hi = s_hi == nsuper ? (s_hi - 1) * 4 + ((G & 3) == 1 ? 2 : 4) : s_hi * 4;
 
-    // my row
-    const int n = n0 + wave * 32 + fi;
-    const bool row_ok = n < p.N;
-    const int nc = row_ok ? n : p.N - 1;
+    // my row (past N: the last one again, into output columns that are never stored)
+    const int nc = min(n0 + wave * 32 + fi, p.N - 1);
     const RowInfo rec = p.rows[nc];
 
     // activation transfers: wavefront w moves rows 8 (w TM + i) .. + 7, i < TM
@@ -195,8 +193,6 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
         const int gh = ss * 4 + 2 * h;                                // my two groups
         a[0] = load_scale(p, srow + min(gh, G - 1));
         a[1] = load_scale(p, srow + min(gh + 1, G - 1));
-        if (gh >= G || !row_ok) a[0] = 0.0f;
-        if (gh + 1 >= G || !row_ok) a[1] = 0.0f;
         const uint8_t* q0 = row + (size_t)gh * 8 * bits;
         if (ss * 4 + 4 <= G) {                                        // uniform
 #pragma unroll
@@ -281,15 +277,17 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
 
     uint4 cn[NP];
     float an[2];
-    auto next_super = [&]() __attribute__((always_inline)) {
+    auto next_super = [&](int ss) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < NP; ++q) { c[4 * q] = cn[q].x; c[4 * q + 1] = cn[q].y; c[4 * q + 2] = cn[q].z; c[4 * q + 3] = cn[q].w; }
-        a0 = an[0]; a1 = an[1];
+        // (zero past the row's end: here, not where they are loaded, so that every load_super issues both loads)
+        a0 = ss * 4 + 2 * h < G ? an[0] : 0.0f;
+        a1 = ss * 4 + 2 * h + 1 < G ? an[1] : 0.0f;
     };
     load_super(s_lo, cn, an);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // all three activation tiles
     __syncthreads();
-    next_super();
+    next_super(s_lo);
     new_group(a0);
     Slice sl[2];
     decode(0, 0, sl[0]);
@@ -313,7 +311,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
                 if (TM == 4) spread();
             }
             // Tile t + 1 has landed when only the transfers of tile t + 2 are outstanding.  The loads of the next
-            // superstep's codes are issued behind the transfers of step j = 0, at least two of them.
+            // superstep are issued behind the transfers of step j = 0, at least two of them: its two scales, always.
             if (t + 3 <= t_hi) {
                 if (j == 1 && ss + 1 < s_hi) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM + 2) : "memory");
                 else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM) : "memory");
@@ -321,7 +319,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
             __syncthreads();
-            if (j == 3) next_super();                                 // (the loaded codes are waited for here, not behind the transfers below)
+            if (j == 3) next_super(ss + 1);                                 // (the loaded codes are waited for here, not behind the transfers below)
             __builtin_amdgcn_sched_barrier(0);
             if (t + 3 < t_hi) issue(t + 3, st);
             __builtin_amdgcn_sched_barrier(0);
@@ -442,27 +440,32 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     const int mrow = 16 * wave + (lane >> 2), piece = lane & 3;
     const int g0 = k0 >> 6;
     const bool two_groups = g0 + 1 < G;
+    // The step's wait counts four loads (codes, two scales, record) behind the activation transfers.  So the second scale is
+    // a load of its own in the last column tile as well, where it repeats the first: its distance is opaque to the
+    // compiler, which could neither drop nor join the two, and values of no use are replaced by zero in stage_in.
+    int second = __builtin_amdgcn_readfirstlane(two_groups ? 1 : 0);
+    asm volatile("" : "+s"(second));
     struct Raw { uint4 codes; float4 lev; float a0, a1; RowInfo rec; };
     auto load_rec = [&](int s) -> RowInfo { return p.rows[min(s * 64 + mrow, N - 1)]; };
     auto load_raw = [&](int s, const RowInfo& rec, Raw& d) __attribute__((always_inline)) {
-        const int nr = s * 64 + mrow, ncl = min(nr, N - 1), bits = rec.bits();
+        const int ncl = min(s * 64 + mrow, N - 1), bits = rec.bits();
         const int row_bytes = K / 8 * bits;
         // a piece past the row's codes of this tile fetches the last one again; 16 bytes before the row's end at the latest
         const int off = min(k0 / 8 * bits + 16 * min(piece, bits - 1), row_bytes - 16);
         d.codes = load16_u(p.packed + rec.offset + off);
         if (!shared_tab) d.lev = *reinterpret_cast<const float4*>(p.mappings + (size_t)rec.cb() * kTableStride + (WIDE ? 4 * piece : 0));
         d.a0 = load_scale(p, (size_t)ncl * G + g0);
-        d.a1 = load_scale(p, (size_t)ncl * G + (two_groups ? g0 + 1 : g0));
-        if (nr >= N) { d.a0 = 0.0f; d.a1 = 0.0f; }
-        if (!two_groups) d.a1 = 0.0f;
+        d.a1 = load_scale(p, (size_t)ncl * G + g0 + second);
         d.rec = rec;
     };
-    auto stage_in = [&](int buf, const Raw& d) __attribute__((always_inline)) {
+    auto stage_in = [&](int buf, int s, const Raw& d) __attribute__((always_inline)) {   // d: what load_raw(s) loaded
         if (WIDE || piece < 2)
             *reinterpret_cast<uint4*>(smem + L::C0 + buf * L::C + mrow * (WIDE ? 64 : 32) + ((piece ^ (WIDE ? (mrow >> 2) & 3 : (mrow >> 3) & 1)) << 4)) = d.codes;
-        if (piece == 0)
+        if (piece == 0) {
+            const bool row = s * 64 + mrow < N;
             *reinterpret_cast<uint4*>(smem + L::META0 + buf * 1024 + mrow * 16) =
-                make_uint4(__builtin_bit_cast(uint32_t, d.a0), __builtin_bit_cast(uint32_t, d.a1), d.rec.bits_cb, 0u);
+                make_uint4(row ? __builtin_bit_cast(uint32_t, d.a0) : 0u, row && two_groups ? __builtin_bit_cast(uint32_t, d.a1) : 0u, d.rec.bits_cb, 0u);
+        }
         if (WIDE && !shared_tab) {                                    // level q of row r at 256 q + 4 r: a lookup touches bank r whatever the code
             float* tab = reinterpret_cast<float*>(smem + L::TAB0 + buf * (64 * ROWTAB) + piece * 1024 + mrow * 4);
             tab[0] = d.lev.x; tab[64] = d.lev.y; tab[128] = d.lev.z; tab[192] = d.lev.w;
@@ -562,10 +565,10 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     issue(min(s_lo + 1, s_end), (s_lo + 1) & 1);
     load_raw(s_lo, rec, raw);
     rec = load_rec(min(s_lo + 1, s_end));
-    stage_in(s_lo & 1, raw);
+    stage_in(s_lo & 1, s_lo, raw);
     load_raw(min(s_lo + 1, s_end), rec, raw);
     rec = load_rec(min(s_lo + 2, s_end));
-    stage_in((s_lo + 1) & 1, raw);
+    stage_in((s_lo + 1) & 1, min(s_lo + 1, s_end), raw);
     load_raw(min(s_lo + 2, s_end), rec, raw);
     rec = load_rec(min(s_lo + 3, s_end));
     __syncthreads();
@@ -574,7 +577,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     for (int kk = 0; kk < 4; ++kk) { decode_look(kk); decode_put(kk, smem + L::W0 + (s_lo & 1) * L::W); }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    stage_in(s_lo & 1, raw);                                          // step s_lo + 2
+    stage_in(s_lo & 1, min(s_lo + 2, s_end), raw);
     load_raw(min(s_lo + 3, s_end), rec, raw);
     rec = load_rec(min(s_lo + 4, s_end));
     Slice sl[2];
@@ -607,7 +610,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
         // (codes, two scales, record) may stay in flight
         asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         __syncthreads();
-        stage_in(b ^ 1, raw);                                         // step s + 3
+        stage_in(b ^ 1, min(s + 3, s_end), raw);
         asm volatile("" : "+v"(rec.offset), "+v"(rec.bits_cb));       // wait for the record here, not behind the transfers below
         read_slice(smem + (b ^ 1) * L::A, smem_lds + L::W0 + (b ^ 1) * L::W, 0, sl[0]);
         __builtin_amdgcn_sched_barrier(0);
