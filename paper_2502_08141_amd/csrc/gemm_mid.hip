@@ -39,9 +39,12 @@ __device__ __forceinline__ uint2 load8_u(const uint8_t* q) {
     const u32x2a4_t v = *reinterpret_cast<const u32x2a4_t*>(q);
     return make_uint2(v.x, v.y);
 }
-__device__ __forceinline__ float load_scale(const MidParams& p, size_t i) {
-    return p.scale_bf16 ? bf16_bits_to_float(static_cast<const uint16_t*>(p.absmax)[i]) : static_cast<const float*>(p.absmax)[i];
+// A group's scale as it is stored, fp32 or bf16 bits; scale_of() widens it.  Apart, because a conversion beside the load
+// would wait for it there, and for every transfer under way with it (11008 x 4096, 333 tokens, input gradient: 80 -> 73 us).
+__device__ __forceinline__ uint32_t load_scale(const MidParams& p, size_t i) {
+    return p.scale_bf16 ? static_cast<const uint16_t*>(p.absmax)[i] : static_cast<const uint32_t*>(p.absmax)[i];
 }
+__device__ __forceinline__ uint32_t scale_of(const MidParams& p, uint32_t bits) { return bits << (p.scale_bf16 ? 16 : 0); }
 __device__ __forceinline__ bf16x8_t frag_of(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
     const u32x4v_t v = {a, b, c, d};
     return __builtin_bit_cast(bf16x8_t, v);
@@ -189,10 +192,12 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
     constexpr int NP = WIDE ? 4 : 2;
     const uint8_t* row = p.packed + rec.offset;
     const size_t srow = (size_t)nc * G;
-    auto load_super = [&](int ss, uint4 (&c)[NP], float (&a)[2]) __attribute__((always_inline)) {
+    auto load_super = [&](int ss, uint4 (&c)[NP], uint32_t (&a)[2]) __attribute__((always_inline)) {
         const int gh = ss * 4 + 2 * h;                                // my two groups
         a[0] = load_scale(p, srow + min(gh, G - 1));
         a[1] = load_scale(p, srow + min(gh + 1, G - 1));
+        if (gh >= G) a[0] = 0u;                                       // past the row's end
+        if (gh + 1 >= G) a[1] = 0u;
         const uint8_t* q0 = row + (size_t)gh * 8 * bits;
         if (ss * 4 + 4 <= G) {                                        // uniform
 #pragma unroll
@@ -276,18 +281,16 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
     };
 
     uint4 cn[NP];
-    float an[2];
-    auto next_super = [&](int ss) __attribute__((always_inline)) {
+    uint32_t an[2];
+    auto next_super = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < NP; ++q) { c[4 * q] = cn[q].x; c[4 * q + 1] = cn[q].y; c[4 * q + 2] = cn[q].z; c[4 * q + 3] = cn[q].w; }
-        // (zero past the row's end: here, not where they are loaded, so that every load_super issues both loads)
-        a0 = ss * 4 + 2 * h < G ? an[0] : 0.0f;
-        a1 = ss * 4 + 2 * h + 1 < G ? an[1] : 0.0f;
+        a0 = __builtin_bit_cast(float, scale_of(p, an[0])); a1 = __builtin_bit_cast(float, scale_of(p, an[1]));
     };
     load_super(s_lo, cn, an);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // all three activation tiles
     __syncthreads();
-    next_super(s_lo);
+    next_super();
     new_group(a0);
     Slice sl[2];
     decode(0, 0, sl[0]);
@@ -310,16 +313,12 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
                 multiply(sl[kk & 1]);
                 if (TM == 4) spread();
             }
-            // Tile t + 1 has landed when only the transfers of tile t + 2 are outstanding.  The loads of the next
-            // superstep are issued behind the transfers of step j = 0, at least two of them: its two scales, always.
-            if (t + 3 <= t_hi) {
-                if (j == 1 && ss + 1 < s_hi) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM + 2) : "memory");
-                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM) : "memory");
-            } else {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            }
+            // Tile t + 1 has landed when no more is outstanding than was issued for tile t + 2, TM transfers at least.  (Loads
+            // issued behind those are not counted on: the compiler may order, join or wait for them as it likes.)
+            if (t + 3 <= t_hi) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            if (j == 3) next_super(ss + 1);                                 // (the loaded codes are waited for here, not behind the transfers below)
+            if (j == 3) next_super();                                 // (the loaded codes are waited for here, not behind the transfers below)
             __builtin_amdgcn_sched_barrier(0);
             if (t + 3 < t_hi) issue(t + 3, st);
             __builtin_amdgcn_sched_barrier(0);
@@ -445,7 +444,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     // compiler, which could neither drop nor join the two, and values of no use are replaced by zero in stage_in.
     int second = __builtin_amdgcn_readfirstlane(two_groups ? 1 : 0);
     asm volatile("" : "+s"(second));
-    struct Raw { uint4 codes; float4 lev; float a0, a1; RowInfo rec; };
+    struct Raw { uint4 codes; float4 lev; uint32_t a0, a1; RowInfo rec; };
     auto load_rec = [&](int s) -> RowInfo { return p.rows[min(s * 64 + mrow, N - 1)]; };
     auto load_raw = [&](int s, const RowInfo& rec, Raw& d) __attribute__((always_inline)) {
         const int ncl = min(s * 64 + mrow, N - 1), bits = rec.bits();
@@ -464,7 +463,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
         if (piece == 0) {
             const bool row = s * 64 + mrow < N;
             *reinterpret_cast<uint4*>(smem + L::META0 + buf * 1024 + mrow * 16) =
-                make_uint4(row ? __builtin_bit_cast(uint32_t, d.a0) : 0u, row && two_groups ? __builtin_bit_cast(uint32_t, d.a1) : 0u, d.rec.bits_cb, 0u);
+                make_uint4(row ? scale_of(p, d.a0) : 0u, row && two_groups ? scale_of(p, d.a1) : 0u, d.rec.bits_cb, 0u);
         }
         if (WIDE && !shared_tab) {                                    // level q of row r at 256 q + 4 r: a lookup touches bank r whatever the code
             float* tab = reinterpret_cast<float*>(smem + L::TAB0 + buf * (64 * ROWTAB) + piece * 1024 + mrow * 4);
