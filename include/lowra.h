@@ -151,7 +151,7 @@ lowra_status lowra_dequantize(const lowra_layout* layout, const uint8_t* packed,
  * decoded on the fly (never written to HBM), bf16 operands, fp32 accumulation, bf16 result.
  *   x [M,K] bf16 dev | A [r,K] bf16 dev | B [N,r] bf16 dev | y [M,N] bf16 dev (out)
  *   r == 0 drops the LoRA term (A, B may be null).  N % 8 == 0 is required (UNSUPPORTED).
- *   y must not overlap an input or the workspace: besides the result it holds partial sums of x A^T on the way.
+ *   y must not overlap an input or the workspace: besides the result it may hold partial sums of x A^T on the way.
  *   workspace: dev, >= lowra_workspace_bytes(layout, LOWRA_OP_LINEAR_FWD, M, r), 16-byte aligned;
  *   contents are scratch.  M <= 16 takes the bandwidth-bound small-token path. */
 lowra_status lowra_linear_fwd(const lowra_layout* layout, const uint8_t* packed,

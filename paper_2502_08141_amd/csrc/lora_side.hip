@@ -238,10 +238,11 @@ static SkinnyPlan skinny_plan(int M, int Kc, int RP) {
 // the slices costs about 2.5 us, so contractions below 1536 (twelve stages, 4 us) stay whole.  Kernel times: 333 tokens,
 // 4096 columns 10.6 -> 4.7 + 3 us; 512 tokens, 11008 columns 28 -> 7 + 3 us; 9 tokens, 4096 columns 11.8 -> 4.1 + 2.8 us.
 // The split is a function of the shape alone, never of the workspace a caller happens to pass: the linear calls and the
-// adapter gradients must form the same bits.  So the slices' partial sums go where every call has room: a linear call
-// puts them into its own output [M, out_cols] bf16, which its last kernel writes afterwards (hence out_cols / 128
-// slices at most: 256 bytes per token and slice); the adapter gradients, into the region of their partial tiles, which
-// holds a row of 256 bytes per channel and per feature (hence Kc rows at most).
+// adapter gradients must form the same bits.  So the slices' partial sums must find room in every call: a linear call
+// without spare workspace puts them into its own output [M, out_cols] bf16, which its last kernel writes afterwards
+// (hence out_cols / 128 slices at most: 256 bytes per token and slice); the adapter gradients, into the region of their
+// partial tiles, which holds a row of 256 bytes per channel and per feature (hence Kc rows at most).  (Spare workspace
+// comes first: the sum of 128 tokens' slices takes 2.5 us from there and 3.8 from the output.)
 static SkinnyPlan skinny_few_plan(int M, int Kc, int RP, int out_cols) {
     const int blocks = (M + 15) / 16;
     if (RP != 64 || M < 1 || Kc < 1536 || 2 * blocks > device_compute_units()) return SkinnyPlan{1, 0};
@@ -250,6 +251,10 @@ static SkinnyPlan skinny_few_plan(int M, int Kc, int RP, int out_cols) {
     const int kslice = ((Kc + slices - 1) / slices + 127) / 128 * 128;
     slices = (Kc + kslice - 1) / kslice;
     return slices > 1 ? SkinnyPlan{slices, kslice} : SkinnyPlan{1, 0};
+}
+size_t skinny_few_bytes(int M, int Kc, int RP, int out_cols) {
+    const SkinnyPlan pl = skinny_few_plan(M, Kc, RP, out_cols);
+    return pl.slices > 1 ? (size_t)pl.slices * M * RP * sizeof(float) : 0;
 }
 size_t skinny_scratch_bytes(int M, int Kc, int RP) {
     const SkinnyPlan pl = skinny_plan(M, Kc, RP);
