@@ -109,8 +109,9 @@ size_t lowra_packed_bytes(const lowra_layout* layout);
  * It holds the rank-r intermediate and padded copies of the adapter operands; for the forward with
  * M <= 16 also the small-token kernel's descriptors and per-chunk partial outputs, so it can be
  * non-zero at r == 0; and, for the token counts whose contraction is split between workgroups, the splits'
- * fp32 partial tiles.  A linear call with less is refused only below what it cannot do without (all but the
- * room for these splits): it then splits less, which takes longer and adds in another order. */
+ * fp32 partial tiles (at most 64 MiB).  A linear call with less is refused only below what it cannot do without
+ * (all but the room for these splits): it forms the partial tiles in up to eight pieces, with the same results;
+ * with still less it splits less, which takes longer and adds in another order. */
 size_t lowra_workspace_bytes(const lowra_layout* layout, int op, int M, int r);
 
 /* Quantize (App. A.1).  For every 64-element group: absmax a = max|w| is stored; every weight is
@@ -163,10 +164,10 @@ lowra_status lowra_linear_fwd(const lowra_layout* layout, const uint8_t* packed,
 /* lowra_linear_fwd for callers that cannot allocate device memory and have no workspace to pass: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and
  * results as lowra_linear_fwd (both paths, bit for bit) without `workspace`: the rank-r intermediate and
- * the padded adapter copy live in a static device array (LOWRA_STATIC_SCRATCH_BYTES and the room that splits
- * take at most) that every GPU the library runs on holds until the process ends.  The call allocates and frees nothing (no hipMalloc /
- * hipFree, no allocating library routine); the array's device address is looked up once per device, in
- * lowra_layout_create or at the first call on that device.
+ * the padded adapter copy live in a static device array of LOWRA_STATIC_ARRAY_BYTES that every GPU the library runs on
+ * holds until the process ends; partial tiles of a split contraction that exceed its room are formed and summed in pieces.
+ * The call allocates and frees nothing (no hipMalloc / hipFree, no allocating library routine); the array's device address
+ * is looked up once per device, in lowra_layout_create or at the first call on that device.
  *   WORKSPACE_TOO_SMALL: what the call cannot do without (lowra_workspace_bytes less the room for splits)
  *   exceeds LOWRA_STATIC_SCRATCH_BYTES (e.g. more than 32768 tokens at rank 64) -- use lowra_linear_fwd.
  *   INVALID_ARG also when the current device is not the layout's.
@@ -174,6 +175,7 @@ lowra_status lowra_linear_fwd(const lowra_layout* layout, const uint8_t* packed,
  * threads) race on it; calls on one stream are ordered and safe.  The array keeps the last call's
  * contents; the call needs nothing in it to start at zero. */
 #define LOWRA_STATIC_SCRATCH_BYTES (4u << 20)
+#define LOWRA_STATIC_ARRAY_BYTES (36u << 20)
 lowra_status lowra_linear_fwd_static(const lowra_layout* layout, const uint8_t* packed,
                                      const float* absmax, const float* mappings, const uint16_t* x,
                                      int M, const uint16_t* A, const uint16_t* B, int r, float s,

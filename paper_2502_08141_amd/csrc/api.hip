@@ -6,7 +6,7 @@
 #include <numeric>
 
 #include "../../include/lowra.h"
-#include "gemm_common.h"
+#include "gemm_mid.h"
 
 namespace {
 
@@ -38,9 +38,14 @@ lowra_status plan_rows(int N, int K, int group, const uint8_t* bits, int64_t* of
 // process ends.  In host code the array's NAME is only a handle for hipGetSymbolAddress: the device
 // address is looked up once per device (with that device current) and kept; kernels and copies only
 // ever get that looked-up pointer.
-// Beyond what a call cannot do without (at most LOWRA_STATIC_SCRATCH_BYTES) it has the room that a contraction's splits
-// may ask for, so that the call takes the plan of lowra_linear_fwd with a whole workspace and gives the same bits.
-constexpr size_t kStaticBytes = (size_t)LOWRA_STATIC_SCRATCH_BYTES + lowra::kMidPartMax;
+// Beyond what a call cannot do without (at most LOWRA_STATIC_SCRATCH_BYTES) it has room for the partial tiles of a
+// contraction's splits, in at most kMidPieces pieces, so that the call takes the plan of lowra_linear_fwd with a whole
+// workspace and gives the same bits.  32 MiB hold the tiles of nearly all plans at once (in two pieces: 11008 x 4096 at 256
+// tokens 51 -> 69 us, 5120 x 13824 at 1024 tokens 228 -> 235); 24 MiB cost 4096 x 11008 at 1024 tokens 126 -> 179 us, and 64,
+// room for all, every process 26 ms at its start (36 MiB in all: 13; the 4 without any such room: none to speak of).
+constexpr size_t kStaticBytes = (size_t)LOWRA_STATIC_ARRAY_BYTES;
+static_assert((kStaticBytes - LOWRA_STATIC_SCRATCH_BYTES - 256) / lowra::kMidTileMax * lowra::kMidTileMax * lowra::kMidPieces >= lowra::kMidPartMax,
+              "every split plan fits in pieces");
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 namespace {
 constexpr int kMaxDevices = 64;

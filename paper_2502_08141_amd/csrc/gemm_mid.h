@@ -5,6 +5,8 @@
 namespace lowra {
 
 constexpr int kMidCols = 128;            // output columns per workgroup
+constexpr int kMidMaxSplits = 32;
+static_assert(kMidMaxSplits * 128 * kMidCols * sizeof(float) <= kMidTileMax, "32 TM = 128 rows at most");
 constexpr int kMidLutBooks = 64;         // codebooks the input gradient keeps in LDS as a whole (more: a step's 64 rows are staged)
 
 struct MidParams {
@@ -16,9 +18,11 @@ struct MidParams {
     const uint16_t* ext_act;     // s x A^T or s dY B, bf16 [M,RP]
     const uint16_t* lora;        // B [N,r] (forward) or A [r,K] (input gradient)
     uint16_t* out;               // y [M,N] or dX [M,K]
-    float* part;                 // splits > 1: fp32 partial tiles
+    float* part;                 // splits > 1: fp32 partial tiles of the launch's tiles
+    size_t part_bytes;           // room there
     int M, N, K, G, C, r, RP, scale_bf16;
     int tiles_c, tiles_m;        // output tiles: 128 columns x 32 TM tokens
+    int tile0, ntiles;           // this launch: tiles [tile0, tile0 + ntiles) of them
     int splits, per_split;       // workgroups per output tile; contraction steps of each (forward: 256 features; input gradient: 64 channels)
 };
 
@@ -29,7 +33,16 @@ double gemm_fwd_steps(int N, int K, int M, double enough);
 double gemm_bwd_steps(int N, int K, int M);
 BwdSplitPlan gemm_bwd_split_plan(int N, int K, int M);
 MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_bytes);
-inline size_t mid_part_bytes(const MidPlan& pl) { return (size_t)pl.splits * pl.tiles_c * pl.tiles_m * pl.TM * (32 * kMidCols * sizeof(float)); }
+inline size_t mid_tile_bytes(int splits, int TM) { return (size_t)splits * TM * (32 * kMidCols * sizeof(float)); }
+inline size_t mid_part_bytes(const MidPlan& pl) { return mid_tile_bytes(pl.splits, pl.TM) * pl.tiles_c * pl.tiles_m; }
+// With room for some of a plan's partial tiles only, as many output tiles as fit are computed and summed at a time: the
+// same sums in the same order.  At most kMidPieces such pieces (0: more would be needed); beyond that fewer splits are the
+// better plan.
+constexpr int kMidPieces = 8;
+inline int mid_pieces(const MidPlan& pl, size_t room) {
+    const size_t fit = room / mid_tile_bytes(pl.splits, pl.TM), tiles = (size_t)pl.tiles_c * pl.tiles_m;
+    return fit == 0 || (tiles + fit - 1) / fit > (size_t)kMidPieces ? 0 : (int)((tiles + fit - 1) / fit);
+}
 
 hipError_t launch_gemm_mid(const MidParams& p, int op, int TM, bool wide, hipStream_t st);
 

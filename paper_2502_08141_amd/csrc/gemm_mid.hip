@@ -81,7 +81,7 @@ __device__ __forceinline__ void mid_epilogue(const MidParams& p, const floatx16_
                                              int split, int tile, int c0, int m0, int cols) {
     const int fi = lane & 31, h = lane >> 5;
     if (p.splits > 1) {
-        const int ntiles = p.tiles_c * p.tiles_m;
+        const int ntiles = p.ntiles;
         float4* dst = reinterpret_cast<float4*>(p.part) + (((size_t)split * ntiles + tile) * 4 + wave) * (TM * 256) + lane;
 #pragma unroll
         for (int t = 0; t < TM; ++t)
@@ -129,10 +129,10 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fi = lane & 31, h = lane >> 5;
-    const int ntiles = p.tiles_c * p.tiles_m;
+    const int ntiles = p.ntiles;
     const int w = xcd_tile(blockIdx.x, gridDim.x);
     const int split = __builtin_amdgcn_readfirstlane(w / ntiles);
-    const int tile = w - split * ntiles;
+    const int tile = p.tile0 + w - split * ntiles;
     const int mt = __builtin_amdgcn_readfirstlane(tile / p.tiles_c);
     const int n0 = (tile - mt * p.tiles_c) * MID_COLS, m0 = mt * (32 * TM);
     const int G = p.G, K = p.K;
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
             }
         }
     }
-    mid_epilogue<TM>(p, acc, smem, wave, lane, split, tile, n0, m0, p.N);
+    mid_epilogue<TM>(p, acc, smem, wave, lane, split, tile - p.tile0, n0, m0, p.N);
 }
 
 // ---- input gradient.  The contraction runs over channels while codes are packed along k (gemm_bwd.hip): a step's
@@ -399,10 +399,10 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fi = lane & 31, h = lane >> 5;
-    const int ntiles = p.tiles_c * p.tiles_m;
+    const int ntiles = p.ntiles;
     const int wg = xcd_tile(blockIdx.x, gridDim.x);
     const int split = __builtin_amdgcn_readfirstlane(wg / ntiles);
-    const int tile = wg - split * ntiles;
+    const int tile = p.tile0 + wg - split * ntiles;
     const int mt = __builtin_amdgcn_readfirstlane(tile / p.tiles_c);
     const int k0 = (tile - mt * p.tiles_c) * MID_COLS, m0 = mt * (32 * TM);
     const int G = p.G, K = p.K, N = p.N;
@@ -650,11 +650,11 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // transfers past the end: none may land in the output stage
-    mid_epilogue<TM>(p, acc, smem, wave, lane, split, tile, k0, m0, K);
+    mid_epilogue<TM>(p, acc, smem, wave, lane, split, tile - p.tile0, k0, m0, K);
 }
 
 // out = bf16(sum of the splits' partial tiles, in split order).  A thread owns four columns of one token.
-__global__ __launch_bounds__(256) void mid_sum_kernel(const float4* __restrict__ part, int splits, int ntiles, int tiles_c, int TM,
+__global__ __launch_bounds__(256) void mid_sum_kernel(const float4* __restrict__ part, int splits, int ntiles, int tile0, int tiles_c, int TM,
                                                       int M, int cols, uint16_t* __restrict__ out) {
     const size_t per = (size_t)ntiles * TM * 1024;                    // float4 per split
     const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(256) void mid_sum_kernel(const float4* __restrict__
         a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
     }
     const int lane = (int)(e & 63), vq = (int)(e >> 6) & 3;
-    const int q = (int)(e >> 8), t = q % TM, wt = q / TM, wave = wt & 3, tile = wt >> 2;
+    const int q = (int)(e >> 8), t = q % TM, wt = q / TM, wave = wt & 3, tile = tile0 + (wt >> 2);
     const int col = (tile % tiles_c) * MID_COLS + 32 * wave + 8 * vq + 4 * (lane >> 5);
     const int m = (tile / tiles_c) * (32 * TM) + 32 * t + (lane & 31);
     if (m < M && col < cols) *reinterpret_cast<uint2*>(out + (size_t)m * cols + col) = make_uint2(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w));
@@ -679,7 +679,7 @@ __global__ __launch_bounds__(256) void mid_sum_kernel(const float4* __restrict__
 
 template <int TM, bool WIDE>
 hipError_t launch_mid_variant(const MidParams& p, int op, hipStream_t st) {
-    const unsigned grid = (unsigned)(p.tiles_c * p.tiles_m * p.splits);
+    const unsigned grid = (unsigned)(p.ntiles * p.splits);
     if (op == 0) {
         constexpr int sh = 3 * TM * 4096 + (WIDE ? 4 * 4096 : 0);
         static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mid_fwd_kernel<TM, WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize, sh);
@@ -738,7 +738,7 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
     for (int TM = 1; TM <= tm_max && (TM == 1 || 32 * (TM - 1) < M); ++TM) {
         MidPlan pl{TM, tiles_c, (M + 32 * TM - 1) / (32 * TM), 0, 0};
         const int res = kMidResident[op][TM - 1];
-        for (int S = 1; S <= 32 && S <= units; S += S < 6 ? 1 : S < 12 ? 2 : 4) {
+        for (int S = 1; S <= kMidMaxSplits && S <= units; S += S < 6 ? 1 : S < 12 ? 2 : 4) {
             pl.per_split = (units + S - 1) / S;
             pl.splits = (units + pl.per_split - 1) / pl.per_split;
             if (pl.splits > 1 && mid_part_bytes(pl) > cap) break;
@@ -761,18 +761,26 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
     return best;
 }
 
-hipError_t launch_gemm_mid(const MidParams& p, int op, int TM, bool wide, hipStream_t st) {
-    hipError_t e = hipErrorInvalidValue;
-    if (TM == 1) e = wide ? launch_mid_variant<1, true>(p, op, st) : launch_mid_variant<1, false>(p, op, st);
-    if (TM == 2) e = wide ? launch_mid_variant<2, true>(p, op, st) : launch_mid_variant<2, false>(p, op, st);
-    if (TM == 3) e = wide ? launch_mid_variant<3, true>(p, op, st) : launch_mid_variant<3, false>(p, op, st);
-    if (TM == 4) e = wide ? launch_mid_variant<4, true>(p, op, st) : launch_mid_variant<4, false>(p, op, st);
-    if (e != hipSuccess || p.splits <= 1) return e;
-    const int ntiles = p.tiles_c * p.tiles_m;
-    const int cols = op == 0 ? p.N : p.K;
-    mid_sum_kernel<<<dim3((unsigned)((size_t)ntiles * TM * 4)), dim3(256), 0, st>>>(reinterpret_cast<const float4*>(p.part), p.splits, ntiles,
-                                                                                   p.tiles_c, TM, p.M, cols, p.out);
-    return hipGetLastError();
+hipError_t launch_gemm_mid(const MidParams& p_in, int op, int TM, bool wide, hipStream_t st) {
+    MidParams p = p_in;
+    const int tiles = p.tiles_c * p.tiles_m, cols = op == 0 ? p.N : p.K;
+    const int fit = p.splits > 1 ? (int)std::min<size_t>(p.part_bytes / mid_tile_bytes(p.splits, TM), (size_t)tiles) : tiles;
+    if (fit < 1) return hipErrorInvalidValue;
+    const int pieces = (tiles + fit - 1) / fit, per = (tiles + pieces - 1) / pieces;     // equal ones: a short last one costs as much
+    for (p.tile0 = 0; p.tile0 < tiles; p.tile0 += per) {
+        p.ntiles = std::min(per, tiles - p.tile0);
+        hipError_t e = hipErrorInvalidValue;
+        if (TM == 1) e = wide ? launch_mid_variant<1, true>(p, op, st) : launch_mid_variant<1, false>(p, op, st);
+        if (TM == 2) e = wide ? launch_mid_variant<2, true>(p, op, st) : launch_mid_variant<2, false>(p, op, st);
+        if (TM == 3) e = wide ? launch_mid_variant<3, true>(p, op, st) : launch_mid_variant<3, false>(p, op, st);
+        if (TM == 4) e = wide ? launch_mid_variant<4, true>(p, op, st) : launch_mid_variant<4, false>(p, op, st);
+        if (e != hipSuccess) return e;
+        if (p.splits <= 1) continue;
+        mid_sum_kernel<<<dim3((unsigned)((size_t)p.ntiles * TM * 4)), dim3(256), 0, st>>>(reinterpret_cast<const float4*>(p.part), p.splits, p.ntiles, p.tile0,
+                                                                                         p.tiles_c, TM, p.M, cols, p.out);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace lowra

@@ -96,12 +96,15 @@ static MidParams mid_params(const lowra_layout& L, const LinearArgs& a, int op, 
     p.lora = op == 0 ? a.B : a.A; p.out = a.out;
     p.part = pl.splits > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(a.workspace) + align256(least)) : nullptr;
     p.M = a.M; p.N = L.N; p.K = L.K; p.G = L.G; p.C = L.C; p.r = a.r; p.RP = RP; p.scale_bf16 = L.scale_bf16;
-    p.tiles_c = pl.tiles_c; p.tiles_m = pl.tiles_m; p.splits = pl.splits; p.per_split = pl.per_split;
+    p.part_bytes = p.part ? a.workspace_bytes - align256(least) : 0;
+    p.tiles_c = pl.tiles_c; p.tiles_m = pl.tiles_m; p.tile0 = 0; p.ntiles = 0; p.splits = pl.splits; p.per_split = pl.per_split;
     return p;
 }
 static MidPlan mid_plan_call(const lowra_layout& L, const LinearArgs& a, int op, bool gemm) {
     const size_t least = align256(linear_workspace_min(L, op, a.M, a.r));
-    return mid_plan_of(L, op, a.M, a.r, gemm, a.workspace && a.workspace_bytes > least ? a.workspace_bytes - least : 0);
+    const size_t room = a.workspace_bytes > least ? a.workspace_bytes - least : 0;
+    const MidPlan whole = mid_plan_of(L, op, a.M, a.r, gemm, ~(size_t)0);       // in pieces where the room is short
+    return whole.splits <= 1 || mid_pieces(whole, room) > 0 ? whole : mid_plan_of(L, op, a.M, a.r, gemm, room);
 }
 size_t linear_workspace_min(const lowra_layout& L, int op, int M, int r) {
     return align256(linear_workspace_bytes_fp32(L, op, M, r)) + expanded_scale_bytes(L);

@@ -17,7 +17,7 @@ LIB_PATH = os.path.join(_HERE, "liblowra_hip.so")
 _lib = None
 
 OK, INVALID_ARG, UNSUPPORTED, MISALIGNED, WORKSPACE_TOO_SMALL, HIP_ERROR, OUT_OF_MEMORY = range(7)
-STATIC_SCRATCH_BYTES = 4 << 20
+STATIC_SCRATCH_BYTES, STATIC_ARRAY_BYTES = 4 << 20, 36 << 20
 OP_LINEAR_FWD, OP_LINEAR_BWD_INPUT, OP_ADAPTER_GRADS, OP_LOFTQ_INIT = 0, 1, 2, 3
 OUT_BF16, OUT_FP32 = 0, 1
 PATH_AUTO, PATH_GEMV, PATH_GEMM, PATH_GEMV_GENERAL = 0, 1, 2, 3

@@ -27,6 +27,13 @@ def test_library_exports_every_declared_symbol():
         assert getattr(L, name) is not None
 
 
+def test_static_scratch_sizes_are_the_headers():
+    text = open(os.path.join(ROOT, "include", "lowra.h")).read()
+    for name in ("STATIC_SCRATCH_BYTES", "STATIC_ARRAY_BYTES"):
+        n, shift = re.search(rf"#define LOWRA_{name} \((\d+)u << (\d+)\)", text).groups()
+        assert int(n) << int(shift) == getattr(lowra, name)
+
+
 def test_status_strings():
     assert lowra.status_string(0) == "ok"
     assert len({lowra.status_string(i) for i in range(6)}) == 6
