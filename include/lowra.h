@@ -308,6 +308,21 @@ lowra_status lowra_set_fwd_tiling(int rows_a, int rows_b, int cols_a);
  * null pointer. */
 lowra_status lowra_plan_fwd_tiling(int N, int M, int compute_units, int* rows_a, int* rows_b, int* cols_a);
 
+/* Test and measurement hook: the plan of the mid-token GEMMs, which take linear calls under LOWRA_PATH_AUTO whose output
+ * has too few tiles for the 256-column kernels.  While rows (32, 64, 96 or 128 tokens a tile) and splits (1..32 workgroups
+ * that share a tile's contraction; as many as it has steps, and one where the partial tiles would exceed 64 MiB) are set,
+ * every call that no small-token kernel takes and whose K is at least 128 runs them with that plan;
+ * lowra_set_mid_tiling(0, 0) returns to the planner.  The order of the fp32 sums depends on the splits.  Process-wide (one
+ * atomic); not for production use.  INVALID_ARG on any other value. */
+lowra_status lowra_set_mid_tiling(int rows, int splits);
+
+/* Host only: the plan of a linear call (op LOWRA_OP_LINEAR_FWD or LOWRA_OP_LINEAR_BWD_INPUT) of an N x K matrix with M tokens
+ * that no small-token kernel takes, under LOWRA_PATH_AUTO and with a whole workspace, for the current device's compute units
+ * (256 without one): *rows tokens a tile and *splits, or *rows = 0 for the 256-column kernels.  has_4bit: the matrix has
+ * 4-bit channels; codebooks: its number of table rows.  INVALID_ARG: another op, a non-positive size, K % 64 != 0, a null
+ * pointer. */
+lowra_status lowra_plan_mid_tiling(int op, int N, int K, int M, int has_4bit, int codebooks, int* rows, int* splits);
+
 /* Several small-token forwards as one run (the operation of lowra_linear_fwd, Sec. 2.1 / Sec. 3, for
  * M <= 16 tokens on n independent matrices: e.g. the projections of one decoder layer that read the
  * same activations, or a pass over a whole weight set).  A single matrix at 1-2 bits is only a few MB,

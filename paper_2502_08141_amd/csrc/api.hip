@@ -665,4 +665,20 @@ lowra_status lowra_set_fwd_tiling(int rows_a, int rows_b, int cols_a) {
     return LOWRA_OK;
 }
 
+lowra_status lowra_set_mid_tiling(int rows, int splits) {
+    const bool planner = rows == 0 && splits == 0;
+    if (!planner && (rows < 32 || rows > 128 || rows % 32 != 0 || splits < 1 || splits > lowra::kMidMaxSplits)) return LOWRA_INVALID_ARG;
+    lowra::force_mid_plan(rows, splits);
+    return LOWRA_OK;
+}
+
+lowra_status lowra_plan_mid_tiling(int op, int N, int K, int M, int has_4bit, int codebooks, int* rows, int* splits) {
+    if (op != LOWRA_OP_LINEAR_FWD && op != LOWRA_OP_LINEAR_BWD_INPUT) return LOWRA_INVALID_ARG;
+    if (N <= 0 || K <= 0 || K % lowra::kGroup != 0 || M <= 0 || codebooks <= 0 || !rows || !splits) return LOWRA_INVALID_ARG;
+    const lowra::MidPlan pl = K < 2 * lowra::kGroup ? lowra::MidPlan{0, 0, 0, 0, 0} : lowra::plan_mid(op, N, K, M, has_4bit != 0, codebooks, ~(size_t)0);
+    *rows = 32 * pl.TM;
+    *splits = pl.TM ? pl.splits : 0;
+    return LOWRA_OK;
+}
+
 }  // extern "C"

@@ -33,6 +33,7 @@ double gemm_fwd_steps(int N, int K, int M, double enough);
 double gemm_bwd_steps(int N, int K, int M);
 BwdSplitPlan gemm_bwd_split_plan(int N, int K, int M);
 MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_bytes);
+void force_mid_plan(int rows, int splits);         // lowra_set_mid_tiling; 0, 0: the planner
 inline size_t mid_tile_bytes(int splits, int TM) { return (size_t)splits * TM * (32 * kMidCols * sizeof(float)); }
 inline size_t mid_part_bytes(const MidPlan& pl) { return mid_tile_bytes(pl.splits, pl.TM) * pl.tiles_c * pl.tiles_m; }
 // With room for some of a plan's partial tiles only, as many output tiles as fit are computed and summed at a time: the

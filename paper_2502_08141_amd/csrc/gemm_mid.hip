@@ -10,6 +10,7 @@
 // mid_sum_kernel adds in split order (deterministic, no atomics).  Any K from 128 on (an odd number of groups
 // included), any mix of widths, any number of codebooks.
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "gemm_mid.h"
@@ -723,15 +724,24 @@ static const MidCost kMidCost[2][3] = {
      {{0.78, 0.84, 1.00, 1.00}, {0.64, 0.68, 0.70, 0.80}, 8.7, 2.8, 2.8e-7, 14.8, 2.50}}};
 static const int kMidResident[2][4] = {{4, 3, 2, 2}, {3, 3, 2, 2}};   // workgroups per compute unit (registers, LDS)
 
+static std::atomic<int> g_mid_forced{0};                              // rows << 8 | splits
+void force_mid_plan(int rows, int splits) { g_mid_forced.store(rows << 8 | splits); }
+
 MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_bytes) {
     MidPlan best{0, 0, 0, 0, 0};
     const int cols = op == 0 ? N : K, unit = op == 0 ? 4 : 1;         // steps that a split takes as a whole
     const int units = op == 0 ? (K / 64 + 3) / 4 : (N + 63) / 64;
     const int tiles_c = (cols + kMidCols - 1) / kMidCols, cus = device_compute_units();
+    const size_t cap = std::min(part_bytes, kMidPartMax);
+    if (const int forced = g_mid_forced.load()) {
+        const int TM = (forced >> 8) / 32, per = (units + (forced & 255) - 1) / (forced & 255);
+        best = MidPlan{TM, tiles_c, (M + 32 * TM - 1) / (32 * TM), (units + per - 1) / per, per};
+        if (best.splits > 1 && mid_part_bytes(best) > cap) { best.splits = 1; best.per_split = units; }
+        return best;
+    }
     if ((long long)tiles_c * ((M + 127) / 128) > 16LL * cus) return best;   // far beyond what is compared below
     const int cls = !wide ? 0 : C <= kMidLutBooks ? 1 : 2;
     const MidCost& mc = kMidCost[op][cls];
-    const size_t cap = std::min(part_bytes, kMidPartMax);
     double best_t = 1e300;
     // with a table per row the input gradient's LDS holds one workgroup of four tile rows per compute unit, not two
     const int tm_max = op == 1 && cls == 2 ? 3 : 4;

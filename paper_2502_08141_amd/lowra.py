@@ -26,7 +26,8 @@ SCALE_FP32, SCALE_BF16 = 0, 1
 SYMBOLS = [
     "lowra_status_string", "lowra_plan_rows", "lowra_layout_create", "lowra_layout_destroy", "lowra_layout_set_scale_dtype",
     "lowra_packed_bytes", "lowra_workspace_bytes", "lowra_quantize", "lowra_quantize_batch", "lowra_dequantize",
-    "lowra_linear_fwd", "lowra_linear_fwd_static", "lowra_linear_bwd_input", "lowra_set_linear_path", "lowra_set_fwd_tiling", "lowra_plan_fwd_tiling", "lowra_set_kernel_timer",
+    "lowra_linear_fwd", "lowra_linear_fwd_static", "lowra_linear_bwd_input", "lowra_set_linear_path", "lowra_set_fwd_tiling", "lowra_plan_fwd_tiling", "lowra_set_mid_tiling",
+    "lowra_plan_mid_tiling", "lowra_set_kernel_timer",
     "lowra_learn_tables", "lowra_average_thresholds", "lowra_channel_mse", "lowra_assign_precisions",
     "lowra_adapter_grads", "lowra_linear_side_product", "lowra_adapter_grads_from_side", "lowra_loftq_init",
     "lowra_fwd_batch_workspace_bytes", "lowra_fwd_batch_create", "lowra_fwd_batch_run", "lowra_fwd_batch_destroy",
@@ -102,6 +103,8 @@ def lib() -> C.CDLL:
         L.lowra_set_linear_path.argtypes = [C.c_int]
         L.lowra_set_fwd_tiling.argtypes = [C.c_int, C.c_int, C.c_int]
         L.lowra_plan_fwd_tiling.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
+        L.lowra_set_mid_tiling.argtypes = [C.c_int, C.c_int]
+        L.lowra_plan_mid_tiling.argtypes = [C.c_int] * 6 + [C.POINTER(C.c_int)] * 2
         L.lowra_set_kernel_timer.argtypes = [vp, vp]
         _lib = L
     return _lib
@@ -537,6 +540,18 @@ def lowra_plan_fwd_tiling(N: int, M: int, compute_units: int = 256):
 
 def lowra_set_fwd_tiling(rows_a: int = 0, rows_b: int = 0, cols_a: int = 0):
     _check(lib().lowra_set_fwd_tiling(int(rows_a), int(rows_b), int(cols_a)), "lowra_set_fwd_tiling")
+
+
+def lowra_set_mid_tiling(rows: int = 0, splits: int = 0):
+    _check(lib().lowra_set_mid_tiling(int(rows), int(splits)), "lowra_set_mid_tiling")
+
+
+def lowra_plan_mid_tiling(op: int, N: int, K: int, M: int, has_4bit: bool, codebooks: int):
+    """(rows, splits) of a linear call's mid-token GEMM, (0, 0) where another kernel takes it (host only)."""
+    rows, splits = C.c_int(), C.c_int()
+    _check(lib().lowra_plan_mid_tiling(int(op), int(N), int(K), int(M), int(has_4bit), int(codebooks), C.byref(rows), C.byref(splits)),
+           "lowra_plan_mid_tiling")
+    return rows.value, splits.value
 
 
 def lowra_set_kernel_timer(start_event=None, stop_event=None):

@@ -137,3 +137,30 @@ def test_forward_tiling_planner():
     assert lowra.lowra_plan_fwd_tiling(5120, 4096, 256) == (192, 192, 20)
     L = lowra.lib()
     assert L.lowra_plan_fwd_tiling(0, 4, 256, None, None, None) == lowra.INVALID_ARG
+
+
+def test_mid_token_planner():
+    """Host only: the mid-token GEMMs' planner and the hook that forces a plan."""
+    FWD, BWD = lowra.OP_LINEAR_FWD, lowra.OP_LINEAR_BWD_INPUT
+    L = lowra.lib()
+    for bad in [(2, 256, 256, 40, 0, 3), (FWD, 0, 256, 40, 0, 3), (FWD, 256, 100, 40, 0, 3), (BWD, 256, 256, 0, 0, 3), (BWD, 256, 256, 40, 0, 0)]:
+        with pytest.raises(lowra.LowraError):
+            lowra.lowra_plan_mid_tiling(*bad)
+    for bad in [(0, 1), (32, 0), (48, 1), (160, 1), (64, 33), (-32, 1), (64, -1)]:
+        assert L.lowra_set_mid_tiling(*bad) == lowra.INVALID_ARG, bad
+    assert lowra.lowra_plan_mid_tiling(FWD, 4096, 64, 40, True, 3) == (0, 0)               # one group: no mid-token kernel
+    for op in (FWD, BWD):
+        for wide, books in ((False, 3), (True, 3), (True, 4096)):
+            rows, splits = lowra.lowra_plan_mid_tiling(op, 4096, 4096, 128, wide, books)
+            assert rows in (32, 64, 96, 128) and splits > 1                                # 32 tiles at most: the contraction is split
+            assert lowra.lowra_plan_mid_tiling(op, 11008, 4096, 4096, wide, books) == (0, 0)   # the 256-column kernels' tiles fill the chip
+    lowra.lowra_set_mid_tiling(96, 3)
+    try:
+        assert lowra.lowra_plan_mid_tiling(FWD, 328, 1088, 40, True, 3) == (96, 3)         # 5 supersteps: 2 + 2 + 1
+        assert lowra.lowra_plan_mid_tiling(FWD, 328, 832, 40, True, 3) == (96, 2)          # 4: 2 + 2
+        assert lowra.lowra_plan_mid_tiling(BWD, 328, 832, 40, True, 3) == (96, 3)          # 6 steps
+        assert lowra.lowra_plan_mid_tiling(BWD, 64, 832, 40, True, 3) == (96, 1)
+        assert lowra.lowra_plan_mid_tiling(FWD, 1 << 15, 1088, 4096, False, 3) == (96, 1)  # the partial tiles would exceed 64 MiB
+    finally:
+        lowra.lowra_set_mid_tiling()
+    assert lowra.lowra_plan_mid_tiling(FWD, 11008, 4096, 4096, True, 3) == (0, 0)

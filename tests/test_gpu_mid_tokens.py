@@ -4,7 +4,10 @@ tokens, and 1 to 16 where no small-token kernel takes the shape), under LOWRA_PA
 Every case is held to the oracle by the 2e-2 rule of the linear outputs, and to the 256-column kernels
 (LOWRA_PATH_GEMM), which multiply the same bf16 weights and activations: the two differ in the order of fp32 sums only,
 so by at most one unit in the last place of the bf16 output, 2^-7 of the entry (or of the output's rms, where
-cancellation leaves an entry smaller than its terms)."""
+cancellation leaves an entry smaller than its terms).
+
+test_mid_token_linear runs the plans that the planner picks (at these sizes nearly always tiles of 32 tokens);
+test_every_variant forces each tile height, split and width class in turn."""
 import pytest
 import torch
 
@@ -18,9 +21,9 @@ pytestmark = pytest.mark.gpu
 ORDER_TOL = 2.0 ** -7
 
 MIXED, NARROW = (0.4, 0.3, 0.3), (0.5, 0.5, 0.0)
-# N, K, M, r, shares of 1/2/4-bit rows, one table per channel, bf16 scales.  Token counts around the tile heights of 32,
-# 64, 96 and 128 rows; group counts of every remainder by four (a superstep is four groups; odd counts leave the input
-# gradient half a column tile); channels that leave partial tiles and steps; ranks below, across and above 64.
+# N, K, M, r, shares of 1/2/4-bit rows, one table per channel, bf16 scales.  Group counts of every remainder by four (a
+# superstep is four groups; odd counts leave the input gradient half a column tile); channels that leave partial tiles and
+# steps; token counts that leave partial tiles; ranks below, across and above 64.
 CASES = [
     (264, 128, 17, 8, MIXED, False, False),
     (136, 192, 33, 5, MIXED, True, True),
@@ -74,6 +77,41 @@ def test_mid_token_linear(shape):
         assert e <= REL_TOL, name
         if M > 16:                                            # (with fewer the forward is a small-token kernel: another decode)
             assert rel_err(g, bf16_host_f64(gemm)) <= ORDER_TOL, name
+
+
+@pytest.mark.parametrize("rows,K", [(32, 1088), (64, 1152), (96, 1216), (128, 1280)])      # 17 to 20 groups: every remainder by four
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("tables", ["narrow", "shared", "channel"])                        # with 4-bit rows: up to 64 codebooks, or more
+def test_every_variant(rows, K, splits, tables):
+    """Every instantiation of both kernels, its contraction whole and split, on a ragged shape: two tiles of tokens, the second
+    one not full, partial column tiles and steps."""
+    N, M, r = 328, rows + 17, 40 if splits == 1 else 13
+    bf16_scales = splits == 3 and rows in (64, 128)
+    L = synth.make_custom(N, K, M, r, fractions=NARROW if tables == "narrow" else MIXED, seed=640 + rows, per_channel_tables=tables == "channel")
+    D = DeviceLayer(L)
+    if bf16_scales:
+        D.layout.set_scale_dtype(torch.bfloat16)
+    packed, absmax = lowra.lowra_quantize(D.layout, D.W, D.thr)
+    rp, ra = orc.quantize(L.W, L.bits, L.cb, L.thresholds, **({"scale_dtype": "bf16"} if bf16_scales else {}))
+    refs = {lowra.OP_LINEAR_FWD: orc.linear_fwd(rp, ra, L.bits, L.cb, L.mappings, L.x, L.A, L.B, L.s),
+            lowra.OP_LINEAR_BWD_INPUT: orc.linear_bwd_input(rp, ra, L.bits, L.cb, L.mappings, L.dY, L.A, L.B, L.s, L.K)}
+    for op, ref in refs.items():
+        print(f"[mid variant rows {rows} splits {splits} {tables} op {op}]", flush=True)
+        fn, act = (lowra.lowra_linear_fwd, D.x) if op == lowra.OP_LINEAR_FWD else (lowra.lowra_linear_bwd_input, D.dY)
+        call = lambda: fn(D.layout, packed, absmax, D.mp, act, D.A, D.B, L.s)
+        lowra.lowra_set_mid_tiling(rows, splits)
+        try:
+            assert lowra.lowra_plan_mid_tiling(op, N, K, M, tables != "narrow", L.mappings.shape[0]) == (rows, splits)
+            got = call()
+            lowra.lowra_set_mid_tiling()
+            lowra.lowra_set_linear_path(lowra.PATH_GEMM)
+            gemm = call()
+        finally:
+            lowra.lowra_set_mid_tiling()
+            lowra.lowra_set_linear_path(lowra.PATH_AUTO)
+        torch.cuda.synchronize()
+        g = bf16_host_f64(got)
+        assert rel_err(g, ref) <= REL_TOL and rel_err(g, bf16_host_f64(gemm)) <= ORDER_TOL
 
 
 @pytest.mark.parametrize("K", [320, 384, 448, 512])           # the last superstep of 256 features holds 1, 2, 3 or all 4 groups
