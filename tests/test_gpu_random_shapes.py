@@ -2,7 +2,9 @@
 gradient and, where the rank allows, the adapter gradients, against the oracle at the linear calls' bar.  The shapes
 are drawn to reach the code paths that fixed cases reach only by design: GEMM shapes with ragged tiles and any rank,
 small-token shapes (K a multiple of 256 from 1024) with ranks that are no multiple of 8, and long contractions over
-few output tiles (the input gradient's split contraction).  One seed per case, so a failure names its shape."""
+few output tiles.  LOWRA_PATH_AUTO takes nearly all of the GEMM shapes to the mid-token kernels, so each is run under
+LOWRA_PATH_GEMM as well: the 256-column kernels' ragged tiles and the input gradient's split contraction.  One seed per
+case, so a failure names its shape."""
 import numpy as np
 import pytest
 import torch
@@ -42,12 +44,19 @@ def test_random_shape(ci):
     torch.cuda.synchronize()
     rp, ra = oracle_state(L)
     assert np.array_equal(D.packed.cpu().numpy(), rp) and np.array_equal(D.absmax.cpu().numpy(), ra)
-    y = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, L.s)
-    dX = lowra.lowra_linear_bwd_input(D.layout, D.packed, D.absmax, D.mp, D.dY, D.A, D.B, L.s)
-    torch.cuda.synchronize()
     A, B = (L.A, L.B) if r else (None, None)
-    assert rel_err(bf16_host_f64(y), orc.linear_fwd(rp, ra, L.bits, L.cb, L.mappings, L.x, A, B, L.s)) <= REL_TOL
-    assert rel_err(bf16_host_f64(dX), orc.linear_bwd_input(rp, ra, L.bits, L.cb, L.mappings, L.dY, A, B, L.s, L.K)) <= REL_TOL
+    ry = orc.linear_fwd(rp, ra, L.bits, L.cb, L.mappings, L.x, A, B, L.s)
+    rdX = orc.linear_bwd_input(rp, ra, L.bits, L.cb, L.mappings, L.dY, A, B, L.s, L.K)
+    for path in (lowra.PATH_AUTO, lowra.PATH_GEMM):
+        lowra.lowra_set_linear_path(path)
+        try:
+            y = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, L.s)
+            dX = lowra.lowra_linear_bwd_input(D.layout, D.packed, D.absmax, D.mp, D.dY, D.A, D.B, L.s)
+        finally:
+            lowra.lowra_set_linear_path(lowra.PATH_AUTO)
+        torch.cuda.synchronize()
+        assert rel_err(bf16_host_f64(y), ry) <= REL_TOL, path
+        assert rel_err(bf16_host_f64(dX), rdX) <= REL_TOL, path
     if 0 < r <= 64:
         dA, dB = lowra.lowra_adapter_grads(D.layout, D.x, D.dY, D.A, D.B, L.s)
         torch.cuda.synchronize()
