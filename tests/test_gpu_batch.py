@@ -2,7 +2,8 @@
 end of the file).  Forward: every matrix of a batch must
 come out as from its own lowra_linear_fwd call on the small-token path -- the same kernel body runs,
 possibly with the contraction split over another number of wavefronts, so up to the fp32 summation
-order: one bf16 step at most -- and within the 2e-2 rule of the fp64 oracle."""
+order: one bf16 step at most -- and within the 2e-2 rule of the fp64 oracle.  Batches of this size take the general
+kernel under LOWRA_PATH_AUTO; LOWRA_PATH_GEMV makes the streaming kernel take them."""
 import numpy as np
 import pytest
 import torch
@@ -29,13 +30,25 @@ def build(M, r):
     return layers
 
 
+def make_batch(items, mp, s, path):
+    lowra.lowra_set_linear_path(path)
+    try:
+        return lowra.FwdBatch(items, mp, s)
+    finally:
+        lowra.lowra_set_linear_path(lowra.PATH_AUTO)
+
+
+PATHS = [lowra.PATH_AUTO, lowra.PATH_GEMV]
+
+
+@pytest.mark.parametrize("path", PATHS)
 @pytest.mark.parametrize("M,r", [(1, 16), (4, 16), (16, 16), (3, 0), (16, 24)])
-def test_batch_equals_single_calls_and_oracle(M, r):
-    print(f"[batch M={M} r={r}]", flush=True)
+def test_batch_equals_single_calls_and_oracle(M, r, path):
+    print(f"[batch M={M} r={r} path={path}]", flush=True)
     layers = build(M, r)
     mp = layers[0].mp
     items = [(D.layout, D.packed, D.absmax, D.x, D.A if r else None, D.B if r else None) for D in layers]
-    batch = lowra.FwdBatch(items, mp, layers[0].L.s)
+    batch = make_batch(items, mp, layers[0].L.s, path)
     ys = batch.run()
     torch.cuda.synchronize()
     for D, y in zip(layers, ys):
@@ -73,11 +86,12 @@ def test_batch_errors():
         lowra.FwdBatch([], mp, 2.0)
 
 
-def test_batch_in_a_graph():
+@pytest.mark.parametrize("path", PATHS)
+def test_batch_in_a_graph(path):
     """The run is launches only: it can be captured and replayed."""
     layers = build(4, 16)
     mp = layers[0].mp
-    batch = lowra.FwdBatch([(D.layout, D.packed, D.absmax, D.x, D.A, D.B) for D in layers], mp, 2.0)
+    batch = make_batch([(D.layout, D.packed, D.absmax, D.x, D.A, D.B) for D in layers], mp, 2.0, path)
     ys = batch.run()
     torch.cuda.synchronize()
     want = [y.clone() for y in ys]
