@@ -722,7 +722,11 @@ static const MidCost kMidCost[2][3] = {
     {{{0.62, 0.73, 0.81, 0.95}, {0.47, 0.55, 0.58, 0.66}, 6.0, 4.7, 2.8e-7, 14.8, 1.28},
      {{0.80, 1.01, 0.95, 1.01}, {0.51, 0.65, 0.68, 0.76}, 7.1, 4.3, 2.7e-7, 9.6, 2.03},
      {{0.78, 0.84, 1.00, 1.00}, {0.64, 0.68, 0.70, 0.80}, 8.7, 2.8, 2.8e-7, 14.8, 2.50}}};
-static const int kMidResident[2][4] = {{4, 3, 2, 2}, {3, 3, 2, 2}};   // workgroups per compute unit (registers, LDS)
+// Workgroups per compute unit that the fit was made with, at TM = 1..4: part of the fitted model, not what a build holds.  By
+// registers and LDS the kernels hold, forward: 4, 3, 3, 3 without 4-bit rows and 4, 3, 2, 2 with them; input gradient: 3, 2, 2,
+// 2, and with 4-bit rows of more than kMidLutBooks codebooks 2, 2, 2, 1.  The fitted step times took up the difference.  (The
+// timings were of calls repeated on one set of buffers, without a rank-r term.)
+static const int kMidResident[2][4] = {{4, 3, 2, 2}, {3, 3, 2, 2}};
 
 static std::atomic<int> g_mid_forced{0};                              // rows << 8 | splits
 void force_mid_plan(int rows, int splits) { g_mid_forced.store(rows << 8 | splits); }
