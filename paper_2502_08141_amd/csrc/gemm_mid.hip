@@ -29,7 +29,7 @@ typedef short mid_v4i16_t __attribute__((ext_vector_type(4)));
 typedef short mid_v8i16_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) mid_v4i16_t* mid_lds_v4i16_ptr;
 
-__device__ const uint4 mid_zeros[1] = {};        // what a transfer reads for features past the end of a row
+__device__ const uint4 mid_zeros[1] = {};        // what a transfer reads for features or channels past the end of a token's row
 
 // packed rows start at multiples of 8 bytes only (K = 64 x an odd number): no 16-byte alignment to rely on
 __device__ __forceinline__ uint4 load16_u(const uint8_t* q) {
@@ -149,15 +149,14 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
     // activation transfers: wavefront w moves rows 8 (w TM + i) .. + 7, i < TM
     const int m_last = p.M - 1 - m0;
     const uint16_t* act0 = p.act + (size_t)m0 * K;
-    uint32_t voff[TM], roff[TM];
+    uint32_t voff[TM];
     int koff[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int r = (wave * TM + i) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ ((r >> 1) & 7);
         koff[i] = (c >> 2) * 128 + (c & 3) * 8;
-        roff[i] = (uint32_t)min(r, m_last) * (uint32_t)K * 2u;        // rows past M are clamped (never stored)
-        voff[i] = roff[i] + (uint32_t)koff[i] * 2u;
+        voff[i] = (uint32_t)min(r, m_last) * (uint32_t)K * 2u + (uint32_t)koff[i] * 2u;     // rows past M are clamped (never stored)
     }
     auto issue = [&](int t, int stage) __attribute__((always_inline)) {
         const int k = (t >> 2) * 256 + (t & 3) * 32;
@@ -416,23 +415,25 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     // ---- activations: dY[m0.., 64 s ..], 128 bytes per token row, chunk c at c ^ ((row >> 1) & 7)
     const int m_last = p.M - 1 - m0;
     const uint16_t* act0 = p.act + (size_t)m0 * N;
-    uint32_t voff[TM], roff[TM];
+    uint32_t voff[TM];
     int coff[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int r = (wave * TM + i) * 8 + (lane >> 3);
         coff[i] = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
-        roff[i] = (uint32_t)min(r, m_last) * (uint32_t)N * 2u;
-        voff[i] = roff[i] + (uint32_t)coff[i] * 2u;
+        voff[i] = (uint32_t)min(r, m_last) * (uint32_t)N * 2u + (uint32_t)coff[i] * 2u;
     }
     auto issue = [&](int s, int buf) __attribute__((always_inline)) {
         const uint32_t dst = smem_lds + buf * L::A + wave * (TM * 1024);
         if (s * 64 + 64 <= N) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) dma16_s(act0 + s * 64, voff[i], dst + i * 1024);
-        } else {                                                      // channels past N: valid bytes, zero weights
+        } else {                                                      // channels past N are zeros, against the last row's weights again
 #pragma unroll
-            for (int i = 0; i < TM; ++i) dma16_s(act0, roff[i] + (uint32_t)min(s * 64 + coff[i], N - 8) * 2u, dst + i * 1024);
+            for (int i = 0; i < TM; ++i) {
+                if (coff[i] < N - s * 64) dma16_s(act0 + s * 64, voff[i], dst + i * 1024);
+                else dma16_s(mid_zeros, 0u, dst + i * 1024);
+            }
         }
     };
 
@@ -441,8 +442,9 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     const int g0 = k0 >> 6;
     const bool two_groups = g0 + 1 < G;
     // The step's wait counts four loads (codes, two scales, record) behind the activation transfers.  So the second scale is
-    // a load of its own in the last column tile as well, where it repeats the first: its distance is opaque to the
-    // compiler, which could neither drop nor join the two, and values of no use are replaced by zero in stage_in.
+    // a load of its own in the last column tile as well, where it repeats the first (for columns that are never stored): its
+    // distance is opaque to the compiler, which can neither drop nor join the two, and none is replaced by zero: channels past
+    // N meet zero activations.
     int second = __builtin_amdgcn_readfirstlane(two_groups ? 1 : 0);
     asm volatile("" : "+s"(second));
     struct Raw { uint4 codes; float4 lev; uint32_t a0, a1; RowInfo rec; };
@@ -458,14 +460,11 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
         d.a1 = load_scale(p, (size_t)ncl * G + g0 + second);
         d.rec = rec;
     };
-    auto stage_in = [&](int buf, int s, const Raw& d) __attribute__((always_inline)) {   // d: what load_raw(s) loaded
+    auto stage_in = [&](int buf, const Raw& d) __attribute__((always_inline)) {
         if (WIDE || piece < 2)
             *reinterpret_cast<uint4*>(smem + L::C0 + buf * L::C + mrow * (WIDE ? 64 : 32) + ((piece ^ (WIDE ? (mrow >> 2) & 3 : (mrow >> 3) & 1)) << 4)) = d.codes;
-        if (piece == 0) {
-            const bool row = s * 64 + mrow < N;
-            *reinterpret_cast<uint4*>(smem + L::META0 + buf * 1024 + mrow * 16) =
-                make_uint4(row ? scale_of(p, d.a0) : 0u, row && two_groups ? scale_of(p, d.a1) : 0u, d.rec.bits_cb, 0u);
-        }
+        if (piece == 0)
+            *reinterpret_cast<uint4*>(smem + L::META0 + buf * 1024 + mrow * 16) = make_uint4(scale_of(p, d.a0), scale_of(p, d.a1), d.rec.bits_cb, 0u);
         if (WIDE && !shared_tab) {                                    // level q of row r at 256 q + 4 r: a lookup touches bank r whatever the code
             float* tab = reinterpret_cast<float*>(smem + L::TAB0 + buf * (64 * ROWTAB) + piece * 1024 + mrow * 4);
             tab[0] = d.lev.x; tab[64] = d.lev.y; tab[128] = d.lev.z; tab[192] = d.lev.w;
@@ -565,10 +564,10 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     issue(min(s_lo + 1, s_end), (s_lo + 1) & 1);
     load_raw(s_lo, rec, raw);
     rec = load_rec(min(s_lo + 1, s_end));
-    stage_in(s_lo & 1, s_lo, raw);
+    stage_in(s_lo & 1, raw);
     load_raw(min(s_lo + 1, s_end), rec, raw);
     rec = load_rec(min(s_lo + 2, s_end));
-    stage_in((s_lo + 1) & 1, min(s_lo + 1, s_end), raw);
+    stage_in((s_lo + 1) & 1, raw);
     load_raw(min(s_lo + 2, s_end), rec, raw);
     rec = load_rec(min(s_lo + 3, s_end));
     __syncthreads();
@@ -577,7 +576,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     for (int kk = 0; kk < 4; ++kk) { decode_look(kk); decode_put(kk, smem + L::W0 + (s_lo & 1) * L::W); }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    stage_in(s_lo & 1, min(s_lo + 2, s_end), raw);
+    stage_in(s_lo & 1, raw);                                          // step s_lo + 2
     load_raw(min(s_lo + 3, s_end), rec, raw);
     rec = load_rec(min(s_lo + 4, s_end));
     Slice sl[2];
@@ -610,7 +609,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
         // (codes, two scales, record) may stay in flight
         asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         __syncthreads();
-        stage_in(b ^ 1, min(s + 3, s_end), raw);
+        stage_in(b ^ 1, raw);                                         // step s + 3
         asm volatile("" : "+v"(rec.offset), "+v"(rec.bits_cb));       // wait for the record here, not behind the transfers below
         read_slice(smem + (b ^ 1) * L::A, smem_lds + L::W0 + (b ^ 1) * L::W, 0, sl[0]);
         __builtin_amdgcn_sched_barrier(0);

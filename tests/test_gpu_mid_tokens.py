@@ -117,24 +117,24 @@ def test_every_variant(rows, K, splits, tables):
 @pytest.mark.parametrize("K", [320, 384, 448, 512])           # the last superstep of 256 features holds 1, 2, 3 or all 4 groups
 @pytest.mark.parametrize("fr", [NARROW, MIXED])
 def test_infinite_activations_at_the_end_of_a_row(K, fr):
-    """An infinity in a token's last features makes its outputs infinite, of the weight's sign, and no other token's: nothing
-    that stands in for features past K may be multiplied with it."""
-    N, M = 264, 40
+    """An infinity in a token's last features (input gradient: channels) makes its outputs infinite, of the weight's sign, and no
+    other token's: nothing that stands in for features past K or channels past N may be multiplied with it."""
+    N, M = 200 + K // 8, 40                                   # 240, 248, 256, 264 channels
     D = DeviceLayer(synth.make_custom(N, K, M, 1, fractions=fr, seed=790 + K))
     D.quantize()
     What = lowra.lowra_dequantize(D.layout, D.packed, D.absmax, D.mp, out_dtype=torch.float32)
-    x = D.x.clone()
-    at = {0: K - 1, 3: K - 8, 17: K - 5, 39: K - 64}
-    for m, k in at.items():
-        x[m, k] = float("inf") if m % 2 else float("-inf")
-    y = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, x, None, None, 1.0).float()
-    plain = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, None, None, 1.0).float()
-    for m in range(M):
-        if m in at:
-            w = What[:, at[m]]
-            assert (w != 0).all() and torch.equal(y[m], x[m, at[m]].float() * torch.sign(w)), f"token {m}"
-        else:
-            assert torch.equal(y[m], plain[m]), f"token {m}"
+    for name, call, act, W in (("forward", lowra.lowra_linear_fwd, D.x, What), ("input gradient", lowra.lowra_linear_bwd_input, D.dY, What.T)):
+        n = act.shape[1]
+        a, at = act.clone(), {0: n - 1, 3: n - 8, 17: n - 5, 39: n - 64}
+        for m, k in at.items():
+            a[m, k] = float("inf") if m % 2 else float("-inf")
+        got, plain = (call(D.layout, D.packed, D.absmax, D.mp, v, None, None, 1.0).float() for v in (a, act))
+        for m in range(M):
+            if m in at:
+                w = W[:, at[m]]
+                assert (w != 0).all() and torch.equal(got[m], a[m, at[m]].float() * torch.sign(w)), f"{name}, token {m}"
+            else:
+                assert torch.equal(got[m], plain[m]), f"{name}, token {m}"
 
 
 def test_mid_token_less_workspace():
