@@ -77,7 +77,7 @@ size_t expanded_scale_bytes(const lowra_layout& L) {
 }
 
 // forward:  [ t : M x RP ][ B padded : N x RP, only when r % 64 != 0 ][ partial sums of t, tall inputs only ]
-// backward: [ u : M x RP ][ B^T : r x N, used unless r == 64 ][ partial sums of u, tall inputs only ]
+// backward: [ u : M x RP ][ B^T : r x N, used unless r is a multiple of 8 up to 64 ][ partial sums of u, tall inputs only ]
 static size_t gemv_workspace_bytes(const lowra_layout& L, int r);
 static size_t linear_workspace_bytes_fp32(const lowra_layout& L, int op, int M, int r);
 static size_t bwd_split_bytes(const lowra_layout& L, int M);
