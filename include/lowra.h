@@ -108,10 +108,11 @@ size_t lowra_packed_bytes(const lowra_layout* layout);
 /* Device scratch a linear call needs (op = LOWRA_OP_*), for M tokens and LoRA rank r.
  * It holds the rank-r intermediate and padded copies of the adapter operands; for the forward with
  * M <= 16 also the small-token kernel's descriptors and per-chunk partial outputs, so it can be
- * non-zero at r == 0; and, for the token counts whose contraction is split between workgroups, the splits'
- * fp32 partial tiles (at most 64 MiB).  A linear call with less is refused only below what it cannot do without
- * (all but the room for these splits): it forms the partial tiles in up to eight pieces, with the same results;
- * with still less it splits less, which takes longer and adds in another order. */
+ * non-zero at r == 0; and, for the token counts whose contractions are split between workgroups, the splits'
+ * fp32 partial sums and tiles (at most 64 MiB).  A linear call with less is refused only below what it cannot do
+ * without (all but the room for these splits): it forms the rank-r product in one workgroup per 16 rows and the
+ * partial tiles in up to eight pieces, with the same results; with still less it splits the latter less, which
+ * takes longer and adds in another order. */
 size_t lowra_workspace_bytes(const lowra_layout* layout, int op, int M, int r);
 
 /* Quantize (App. A.1).  For every 64-element group: absmax a = max|w| is stored; every weight is
@@ -152,7 +153,6 @@ lowra_status lowra_dequantize(const lowra_layout* layout, const uint8_t* packed,
  * decoded on the fly (never written to HBM), bf16 operands, fp32 accumulation, bf16 result.
  *   x [M,K] bf16 dev | A [r,K] bf16 dev | B [N,r] bf16 dev | y [M,N] bf16 dev (out)
  *   r == 0 drops the LoRA term (A, B may be null).  N % 8 == 0 is required (UNSUPPORTED).
- *   y must not overlap an input or the workspace: besides the result it may hold partial sums of x A^T on the way.
  *   workspace: dev, >= lowra_workspace_bytes(layout, LOWRA_OP_LINEAR_FWD, M, r), 16-byte aligned;
  *   contents are scratch.  M <= 16 takes the bandwidth-bound small-token path. */
 lowra_status lowra_linear_fwd(const lowra_layout* layout, const uint8_t* packed,

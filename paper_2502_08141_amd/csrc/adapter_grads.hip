@@ -275,10 +275,10 @@ hipError_t launch_zero_grads(int N, int K, int r, float* dA, float* dB, hipStrea
 
 // ---- the whole gradient call
 hipError_t launch_skinny_ws(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
-                            float s, uint16_t* out, int RP, float* scratch, float* few, int out_cols, hipStream_t st);
+                            float s, uint16_t* out, int RP, float* scratch, bool split, float* few, hipStream_t st);
 size_t skinny_scratch_bytes(int M, int Kc, int RP);
 hipError_t launch_skinny_qt(const uint16_t* P, int ldp, int M, const uint16_t* Qt, int r, int Kc, float s, uint16_t* out,
-                            float* scratch, float* few, int out_cols, hipStream_t st);
+                            float* scratch, bool split, float* few, hipStream_t st);
 hipError_t launch_transpose(const uint16_t* src, int R, int c, uint16_t* dst, hipStream_t st);
 
 static inline size_t ag_align(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -306,12 +306,12 @@ hipError_t launch_adapter_grads(const lowra_layout& L, const uint16_t* x, const 
     float* partial = reinterpret_cast<float*>(ws + 2 * tu + ag_align((size_t)r * L.N * 2));   // scratch of the side products, then the partial tiles
     hipError_t e;
     // (few tokens' partial sums, at most L.K or L.N rows of 256 bytes, fit the region: it holds at least L.N + L.K such rows)
-    if ((e = launch_skinny_ws(x, L.K, M, A, L.K, r, L.K, s, ts, kGradRP, partial, partial, L.N, st)) != hipSuccess) return e;        // s t = s x A^T
+    if ((e = launch_skinny_ws(x, L.K, M, A, L.K, r, L.K, s, ts, kGradRP, partial, true, partial, st)) != hipSuccess) return e;       // s t = s x A^T
     if (r % 8 == 0) {                                                                                   // s u = s dY B, B read in place
-        if ((e = launch_skinny_qt(dY, L.N, M, B, r, L.N, s, us, partial, partial, L.K, st)) != hipSuccess) return e;
+        if ((e = launch_skinny_qt(dY, L.N, M, B, r, L.N, s, us, partial, true, partial, st)) != hipSuccess) return e;
     } else {
         if ((e = launch_transpose(B, L.N, r, bt, st)) != hipSuccess) return e;                          // B^T [r, N]
-        if ((e = launch_skinny_ws(dY, L.N, M, bt, L.N, r, L.N, s, us, kGradRP, partial, partial, L.K, st)) != hipSuccess) return e;
+        if ((e = launch_skinny_ws(dY, L.N, M, bt, L.N, r, L.N, s, us, kGradRP, partial, true, partial, st)) != hipSuccess) return e;
     }
     return launch_adapter_grads_from_side(L, x, dY, M, r, ts, us, dA, dB, workspace, st);
 }

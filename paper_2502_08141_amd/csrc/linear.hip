@@ -19,11 +19,11 @@ hipError_t launch_gemm_bwd(const GemmParams& p, hipStream_t st);
 BwdSplitPlan gemm_bwd_split_plan(int N, int K, int M);
 hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st);
 hipError_t launch_skinny_ws(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
-                            float s, uint16_t* out, int RP, float* scratch, float* few, int out_cols, hipStream_t st);
+                            float s, uint16_t* out, int RP, float* scratch, bool split, float* few, hipStream_t st);
 size_t skinny_scratch_bytes(int M, int Kc, int RP);
-size_t skinny_few_bytes(int M, int Kc, int RP, int out_cols);
+size_t skinny_few_bytes(int M, int Kc, int RP);
 hipError_t launch_skinny_qt(const uint16_t* P, int ldp, int M, const uint16_t* Qt, int r, int Kc, float s, uint16_t* out,
-                            float* scratch, float* few, int out_cols, hipStream_t st);
+                            float* scratch, bool split, float* few, hipStream_t st);
 hipError_t launch_pad_cols(const uint16_t* src, int R, int c, uint16_t* dst, int CP, hipStream_t st);
 hipError_t launch_transpose(const uint16_t* src, int R, int c, uint16_t* dst, hipStream_t st);
 
@@ -110,21 +110,20 @@ size_t linear_workspace_min(const lowra_layout& L, int op, int M, int r) {
     return align256(linear_workspace_bytes_fp32(L, op, M, r)) + expanded_scale_bytes(L);
 }
 static size_t few_bytes(const lowra_layout& L, int op, int M, int r) {
-    return r > 0 && M > 0 ? skinny_few_bytes(M, op == 0 ? L.K : L.N, round_up(r, BK), op == 0 ? L.N : L.K) : 0;
+    return r > 0 && M > 0 ? skinny_few_bytes(M, op == 0 ? L.K : L.N, round_up(r, BK)) : 0;
 }
 // what a call can use: the scratch it cannot do without, then room for a rank-r product's partial sums and, after
 // that product is done, for the partial tiles of a mid-token GEMM's splits
 size_t linear_workspace_bytes(const lowra_layout& L, int op, int M, int r) {
     const size_t least = linear_workspace_min(L, op, M, r);
     const MidPlan pl = mid_plan_of(L, op, M, r, 1, ~(size_t)0);
-    const bool small = M <= 16 && (op == 0 ? gemv_fwd_supported(L, M) : gemv_stream_bwd_supported(L, M, r));
-    const size_t more = std::max(pl.splits > 1 ? mid_part_bytes(pl) : 0, small ? 0 : few_bytes(L, op, M, r));
+    const size_t more = std::max(pl.splits > 1 ? mid_part_bytes(pl) : 0, few_bytes(L, op, M, r));   // (with few tokens too: LOWRA_PATH_GEMM)
     return more ? align256(least) + more : least;
 }
-// where the rank-r product's partial sums go: spare workspace, or the call's output
+// spare workspace for the rank-r product's partial sums, or null
 static float* few_sums(const lowra_layout& L, int op, const LinearArgs& a) {
     const size_t least = align256(linear_workspace_min(L, op, a.M, a.r));
-    if (a.workspace_bytes < least + few_bytes(L, op, a.M, a.r)) return reinterpret_cast<float*>(a.out);
+    if (a.workspace_bytes < least + few_bytes(L, op, a.M, a.r)) return nullptr;
     return reinterpret_cast<float*>(static_cast<uint8_t*>(a.workspace) + least);
 }
 // With bf16 scales: widen them behind the call's own scratch and run the call on the copy.
@@ -201,7 +200,7 @@ hipError_t launch_linear_fwd(const lowra_layout& L, const LinearArgs& a_in, int 
     if (RP) {
         float* scratch = reinterpret_cast<float*>(static_cast<uint8_t*>(a.workspace) + align256((size_t)a.M * RP * 2) +
                                                   (a.r == RP ? 0 : align256((size_t)L.N * RP * 2)));
-        hipError_t e = launch_skinny_ws(a.act, L.K, a.M, a.A, L.K, a.r, L.K, a.s, ws_t, RP, scratch, few_sums(L, 0, a_in), L.N, st);
+        hipError_t e = launch_skinny_ws(a.act, L.K, a.M, a.A, L.K, a.r, L.K, a.s, ws_t, RP, scratch, true, few_sums(L, 0, a_in), st);
         if (e != hipSuccess) return e;
     }
     if (mid.TM > 0) {
@@ -255,10 +254,10 @@ hipError_t launch_linear_bwd_input(const lowra_layout& L, const LinearArgs& a_in
         float* scratch = reinterpret_cast<float*>(ws + align256((size_t)a.M * RP * 2) + align256((size_t)a.r * L.N * 2));
         hipError_t e;
         if (a.r % 8 == 0 && RP == 64) {                                      // B [N, r] is read in place
-            if ((e = launch_skinny_qt(a.act, L.N, a.M, a.B, a.r, L.N, a.s, ws_u, scratch, few_sums(L, 1, a_in), L.K, st)) != hipSuccess) return e;
+            if ((e = launch_skinny_qt(a.act, L.N, a.M, a.B, a.r, L.N, a.s, ws_u, scratch, true, few_sums(L, 1, a_in), st)) != hipSuccess) return e;
         } else {
             if ((e = launch_transpose(a.B, L.N, a.r, ws_bt, st)) != hipSuccess) return e;          // B^T [r, N]
-            if ((e = launch_skinny_ws(a.act, L.N, a.M, ws_bt, L.N, a.r, L.N, a.s, ws_u, RP, scratch, few_sums(L, 1, a_in), L.K, st)) != hipSuccess) return e;
+            if ((e = launch_skinny_ws(a.act, L.N, a.M, ws_bt, L.N, a.r, L.N, a.s, ws_u, RP, scratch, true, few_sums(L, 1, a_in), st)) != hipSuccess) return e;
         }
         p.ext_act = ws_u;
     }

@@ -48,7 +48,9 @@ __device__ __forceinline__ void wait_newer(int newer) {
 typedef short sk_v4i16_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) sk_v4i16_t* sk_lds_v4i16_ptr;
 
-template <int CT, int KW, int NC, int RING, int PT = 1, bool QT = false>
+// WALK: one workgroup takes all slices of its rows one after the other and adds their sums in the order of
+// skinny_sum_kernel: the same bits as a launch per slice, without room for partial sums.
+template <int CT, int KW, int NC, int RING, int PT = 1, bool QT = false, bool WALK = false>
 __global__ __launch_bounds__(128 * NC) void skinny_nt_kernel(const uint16_t* __restrict__ P, int ldp, int M,
                                                             const uint16_t* __restrict__ Q, int ldq, int r,
                                                             int Kc, float s, uint16_t* __restrict__ out,
@@ -68,118 +70,133 @@ __global__ __launch_bounds__(128 * NC) void skinny_nt_kernel(const uint16_t* __r
     const int sw = mover ? wave - NC : wave;
     const int i = lane & 15, kg = lane >> 4;
     const int m0 = blockIdx.x * PR;
-    const int kbeg = blockIdx.y * kslice, kend = min(kbeg + kslice, Kc);     // my slice of the contraction (kslice: a multiple of KW)
-    const int nst = (kend - kbeg + KW - 1) / KW;
+    constexpr int PER = PR * RP / (128 * NC);                        // outputs per thread
+    static_assert(PER * 128 * NC == PR * RP, "whole rounds of outputs");
+    const int slices = WALK ? (Kc + kslice - 1) / kslice : 1;
+    float total[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) total[e] = 0.0f;
+    for (int sl = 0; sl < slices; ++sl) {
+        const int kbeg = (WALK ? sl : (int)blockIdx.y) * kslice, kend = min(kbeg + kslice, Kc);     // my slice of the contraction (kslice: a multiple of KW)
+        const int nst = (kend - kbeg + KW - 1) / KW;
 
-    floatx4_t acc[PT][CT];
-#pragma unroll
-    for (int p = 0; p < PT; ++p)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) acc[p][c] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
-
-    if (mover) {
-        // instruction q = sw + NC t moves rows [q RPI, (q+1) RPI) of the stage: [0, PR) from P, the rest from Q
-        uint32_t voff[NIW], lc16[NIW];
-        const uint32_t kmax_byte = (uint32_t)(Kc - 8) * 2u;
-#pragma unroll
-        for (int t = 0; t < NIW; ++t) {
-            const int row = (sw + NC * t) * RPI + lane / CPR;
-            lc16[t] = (uint32_t)((lane % CPR) ^ (row & 15)) * 16u;   // logical chunk landing on my physical chunk
-            voff[t] = row < PR ? (uint32_t)min(m0 + row, M - 1) * (uint32_t)ldp * 2u
-                               : (uint32_t)min(row - PR, r - 1) * (uint32_t)ldq * 2u;
-            if (QT && row >= PR) {                                   // transposed Q: 8 contraction rows of 128 B per instruction
-                const int nloc = 8 * ((sw + NC * t) - PR / RPI) + (lane >> 3);
-                voff[t] = (uint32_t)nloc;                            // my row within the stage
-                lc16[t] = (uint32_t)((lane & 7) ^ (nloc & 7)) * 16u;
-            }
-        }
-        auto issue_stage = [&](int st) {
-            const uint32_t kb2 = (uint32_t)(kbeg + st * KW) * 2u;
-#pragma unroll
-            for (int t = 0; t < NIW; ++t) {
-                const int q = sw + NC * t;                           // uniform
-                const bool from_p = t * NC * RPI < PR;               // known at compile time: PR is a multiple of NC RPI
-                // columns past Kc: any valid bytes, zeroed at the read
-                if (QT && !from_p)
-                    dma16_s(Q, (uint32_t)min(kbeg + st * KW + (int)voff[t], Kc - 1) * (uint32_t)(2 * r) + min(lc16[t], (uint32_t)(2 * r - 16)),
-                            smem_lds + (st % RING) * STAGE + q * 1024);
-                else if (from_p)
-                    dma16_s(P, voff[t] + min(kb2 + lc16[t], kmax_byte), smem_lds + (st % RING) * STAGE + q * 1024);
-                else
-                    dma16_s(Q, voff[t] + min(kb2 + lc16[t], kmax_byte), smem_lds + (st % RING) * STAGE + q * 1024);
-            }
-        };
-        for (int st = 0; st < RING - 1 && st < nst; ++st) issue_stage(st);
-        wait_newer<NIW, RING - 2>(min(RING - 2, nst - 1));
-        __syncthreads();                                             // stage 0 is there
-        for (int it = 0; it < nst; ++it) {
-            if (it + RING - 1 < nst) issue_stage(it + RING - 1);
-            wait_newer<NIW, RING - 2>(max(0, min(RING - 2, nst - 2 - it)));   // stage it+1 has landed
-            __syncthreads();
-        }
-    } else {
-        const bf16x8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
-        __syncthreads();
-        for (int it = 0; it < nst; ++it) {
-            const uint8_t* sb = smem + (it % RING) * STAGE;
-#pragma unroll
-            for (int u = 0; u < USTEPS; ++u) {
-                const int cl = (KW / NC / 8) * sw + 4 * u + kg;      // logical chunk of my 8 columns
-                const bool kin = kbeg + it * KW + cl * 8 < kend;
-                const int pc = (cl ^ i) << 4;
-                bf16x8_t a[PT];
-#pragma unroll
-                for (int p = 0; p < PT; ++p) {
-                    a[p] = *reinterpret_cast<const bf16x8_t*>(sb + (16 * p + i) * ROWBYTES + pc);
-                    if (!kin || m0 + 16 * p + i >= M) a[p] = zero;
-                }
-#pragma unroll
-                for (int c = 0; c < CT; ++c) {
-                    bf16x8_t b;
-                    if (QT) {
-                        typedef short v8i16_t __attribute__((ext_vector_type(8)));
-                        sk_v4i16_t h[2];
-#pragma unroll
-                        for (int eb = 0; eb < 2; ++eb) {
-                            const int nr = (KW / NC) * sw + 32 * u + 8 * kg + 4 * eb + (i >> 2);     // contraction row within the stage
-                            const int ch = 2 * c + ((i & 3) >> 1);
-                            const uint32_t ad = smem_lds + (it % RING) * STAGE + PR * ROWBYTES + nr * 128 + ((ch ^ (nr & 7)) << 4) + (i & 1) * 8;
-                            h[eb] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sk_lds_v4i16_ptr)(uintptr_t)ad);
-                        }
-                        const v8i16_t v = {h[0][0], h[0][1], h[0][2], h[0][3], h[1][0], h[1][1], h[1][2], h[1][3]};
-                        b = __builtin_bit_cast(bf16x8_t, v);
-                    } else {
-                        b = *reinterpret_cast<const bf16x8_t*>(sb + (PR + 16 * c + i) * ROWBYTES + pc);
-                    }
-                    if (!kin || 16 * c + i >= r) b = zero;
-#pragma unroll
-                    for (int p = 0; p < PT; ++p) acc[p][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[p], b, acc[p][c], 0, 0, 0);
-                }
-            }
-            __syncthreads();                                         // stage it is free again, stage it+1 is there
-        }
-    }
-    // lane (i, kg) of a multiplying wavefront holds out[16 p + 4 kg + v][16 c + i]
-    float* red = reinterpret_cast<float*>(smem);   // [NC][PR][RP]
-    if (!mover) {
+        floatx4_t acc[PT][CT];
 #pragma unroll
         for (int p = 0; p < PT; ++p)
 #pragma unroll
-            for (int c = 0; c < CT; ++c)
+            for (int c = 0; c < CT; ++c) acc[p][c] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+        if (mover) {
+            // instruction q = sw + NC t moves rows [q RPI, (q+1) RPI) of the stage: [0, PR) from P, the rest from Q
+            uint32_t voff[NIW], lc16[NIW];
+            const uint32_t kmax_byte = (uint32_t)(Kc - 8) * 2u;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) red[(sw * PR + 16 * p + 4 * kg + v) * RP + c * 16 + i] = acc[p][c][v];
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < PR * RP; idx += 128 * NC) {
-        const int row = idx / RP, col = idx % RP;
-        float v = 0.0f;
+            for (int t = 0; t < NIW; ++t) {
+                const int row = (sw + NC * t) * RPI + lane / CPR;
+                lc16[t] = (uint32_t)((lane % CPR) ^ (row & 15)) * 16u;   // logical chunk landing on my physical chunk
+                voff[t] = row < PR ? (uint32_t)min(m0 + row, M - 1) * (uint32_t)ldp * 2u
+                                   : (uint32_t)min(row - PR, r - 1) * (uint32_t)ldq * 2u;
+                if (QT && row >= PR) {                                   // transposed Q: 8 contraction rows of 128 B per instruction
+                    const int nloc = 8 * ((sw + NC * t) - PR / RPI) + (lane >> 3);
+                    voff[t] = (uint32_t)nloc;                            // my row within the stage
+                    lc16[t] = (uint32_t)((lane & 7) ^ (nloc & 7)) * 16u;
+                }
+            }
+            auto issue_stage = [&](int st) {
+                const uint32_t kb2 = (uint32_t)(kbeg + st * KW) * 2u;
 #pragma unroll
-        for (int w = 0; w < NC; ++w) v += red[(w * PR + row) * RP + col];
-        const int mo = m0 + row;
-        if (mo < M) {
-            if (partial) partial[((size_t)blockIdx.y * M + mo) * RP + col] = v;          // one slice: unscaled, summed later
-            else out[(size_t)mo * RP + col] = (uint16_t)(pack_bf16x2(v * s, 0.0f) & 0xffffu);
+                for (int t = 0; t < NIW; ++t) {
+                    const int q = sw + NC * t;                           // uniform
+                    const bool from_p = t * NC * RPI < PR;               // known at compile time: PR is a multiple of NC RPI
+                    // columns past Kc: any valid bytes, zeroed at the read
+                    if (QT && !from_p)
+                        dma16_s(Q, (uint32_t)min(kbeg + st * KW + (int)voff[t], Kc - 1) * (uint32_t)(2 * r) + min(lc16[t], (uint32_t)(2 * r - 16)),
+                                smem_lds + (st % RING) * STAGE + q * 1024);
+                    else if (from_p)
+                        dma16_s(P, voff[t] + min(kb2 + lc16[t], kmax_byte), smem_lds + (st % RING) * STAGE + q * 1024);
+                    else
+                        dma16_s(Q, voff[t] + min(kb2 + lc16[t], kmax_byte), smem_lds + (st % RING) * STAGE + q * 1024);
+                }
+            };
+            for (int st = 0; st < RING - 1 && st < nst; ++st) issue_stage(st);
+            wait_newer<NIW, RING - 2>(min(RING - 2, nst - 1));
+            __syncthreads();                                             // stage 0 is there
+            for (int it = 0; it < nst; ++it) {
+                if (it + RING - 1 < nst) issue_stage(it + RING - 1);
+                wait_newer<NIW, RING - 2>(max(0, min(RING - 2, nst - 2 - it)));   // stage it+1 has landed
+                __syncthreads();
+            }
+        } else {
+            const bf16x8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
+            __syncthreads();
+            for (int it = 0; it < nst; ++it) {
+                const uint8_t* sb = smem + (it % RING) * STAGE;
+#pragma unroll
+                for (int u = 0; u < USTEPS; ++u) {
+                    const int cl = (KW / NC / 8) * sw + 4 * u + kg;      // logical chunk of my 8 columns
+                    const bool kin = kbeg + it * KW + cl * 8 < kend;
+                    const int pc = (cl ^ i) << 4;
+                    bf16x8_t a[PT];
+#pragma unroll
+                    for (int p = 0; p < PT; ++p) {
+                        a[p] = *reinterpret_cast<const bf16x8_t*>(sb + (16 * p + i) * ROWBYTES + pc);
+                        if (!kin || m0 + 16 * p + i >= M) a[p] = zero;
+                    }
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) {
+                        bf16x8_t b;
+                        if (QT) {
+                            typedef short v8i16_t __attribute__((ext_vector_type(8)));
+                            sk_v4i16_t h[2];
+#pragma unroll
+                            for (int eb = 0; eb < 2; ++eb) {
+                                const int nr = (KW / NC) * sw + 32 * u + 8 * kg + 4 * eb + (i >> 2);     // contraction row within the stage
+                                const int ch = 2 * c + ((i & 3) >> 1);
+                                const uint32_t ad = smem_lds + (it % RING) * STAGE + PR * ROWBYTES + nr * 128 + ((ch ^ (nr & 7)) << 4) + (i & 1) * 8;
+                                h[eb] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sk_lds_v4i16_ptr)(uintptr_t)ad);
+                            }
+                            const v8i16_t v = {h[0][0], h[0][1], h[0][2], h[0][3], h[1][0], h[1][1], h[1][2], h[1][3]};
+                            b = __builtin_bit_cast(bf16x8_t, v);
+                        } else {
+                            b = *reinterpret_cast<const bf16x8_t*>(sb + (PR + 16 * c + i) * ROWBYTES + pc);
+                        }
+                        if (!kin || 16 * c + i >= r) b = zero;
+#pragma unroll
+                        for (int p = 0; p < PT; ++p) acc[p][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[p], b, acc[p][c], 0, 0, 0);
+                    }
+                }
+                __syncthreads();                                         // stage it is free again, stage it+1 is there
+            }
         }
+        // lane (i, kg) of a multiplying wavefront holds out[16 p + 4 kg + v][16 c + i]
+        float* red = reinterpret_cast<float*>(smem);   // [NC][PR][RP]
+        if (!mover) {
+#pragma unroll
+            for (int p = 0; p < PT; ++p)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) red[(sw * PR + 16 * p + 4 * kg + v) * RP + c * 16 + i] = acc[p][c][v];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            const int idx = threadIdx.x + 128 * NC * e, row = idx / RP, col = idx % RP;
+            float v = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NC; ++w) v += red[(w * PR + row) * RP + col];
+            if (WALK) {
+                total[e] = sl > 0 ? total[e] + v : v;
+                if (sl + 1 < slices) continue;
+                v = total[e];
+            }
+            const int mo = m0 + row;
+            if (mo < M) {
+                if (partial) partial[((size_t)blockIdx.y * M + mo) * RP + col] = v;          // one slice: unscaled, summed later
+                else out[(size_t)mo * RP + col] = (uint16_t)(pack_bf16x2(v * s, 0.0f) & 0xffffu);
+            }
+        }
+        if (WALK) __syncthreads();                                   // the sums have been read: the next slice's stages may come
     }
 }
 
@@ -238,22 +255,20 @@ static SkinnyPlan skinny_plan(int M, int Kc, int RP) {
 // the slices costs about 2.5 us, so contractions below 1536 (twelve stages, 4 us) stay whole.  Kernel times: 333 tokens,
 // 4096 columns 10.6 -> 4.7 + 3 us; 512 tokens, 11008 columns 28 -> 7 + 3 us; 9 tokens, 4096 columns 11.8 -> 4.1 + 2.8 us.
 // The split is a function of the shape alone, never of the workspace a caller happens to pass: the linear calls and the
-// adapter gradients must form the same bits.  So the slices' partial sums must find room in every call: a linear call
-// without spare workspace puts them into its own output [M, out_cols] bf16, which its last kernel writes afterwards
-// (hence out_cols / 128 slices at most: 256 bytes per token and slice); the adapter gradients, into the region of their
-// partial tiles, which holds a row of 256 bytes per channel and per feature (hence Kc rows at most).  (Spare workspace
-// comes first: the sum of 128 tokens' slices takes 2.5 us from there and 3.8 from the output.)
-static SkinnyPlan skinny_few_plan(int M, int Kc, int RP, int out_cols) {
+// adapter gradients must form the same bits.  A linear call without room for the partial sums walks the slices in one
+// workgroup per 16 rows; the adapter gradients always have it, in the region of their partial tiles, which holds a row of
+// 256 bytes per channel and per feature (hence Kc rows of sums at most).
+static SkinnyPlan skinny_few_plan(int M, int Kc, int RP) {
     const int blocks = (M + 15) / 16;
     if (RP != 64 || M < 1 || Kc < 1536 || 2 * blocks > device_compute_units()) return SkinnyPlan{1, 0};
-    int slices = std::min(std::min(std::min(device_compute_units() / blocks, Kc / 512), 16), std::min(Kc / M, out_cols / 128));
+    int slices = std::min(std::min(std::min(device_compute_units() / blocks, Kc / 512), 16), Kc / M);
     if (slices < 2) return SkinnyPlan{1, 0};
     const int kslice = ((Kc + slices - 1) / slices + 127) / 128 * 128;
     slices = (Kc + kslice - 1) / kslice;
     return slices > 1 ? SkinnyPlan{slices, kslice} : SkinnyPlan{1, 0};
 }
-size_t skinny_few_bytes(int M, int Kc, int RP, int out_cols) {
-    const SkinnyPlan pl = skinny_few_plan(M, Kc, RP, out_cols);
+size_t skinny_few_bytes(int M, int Kc, int RP) {
+    const SkinnyPlan pl = skinny_few_plan(M, Kc, RP);
     return pl.slices > 1 ? (size_t)pl.slices * M * RP * sizeof(float) : 0;
 }
 size_t skinny_scratch_bytes(int M, int Kc, int RP) {
@@ -263,13 +278,21 @@ size_t skinny_scratch_bytes(int M, int Kc, int RP) {
 
 template <bool QT>
 static hipError_t launch_skinny_any(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
-                                    float s, uint16_t* out, int RP, float* scratch, float* few, int out_cols, hipStream_t st) {
+                                    float s, uint16_t* out, int RP, float* scratch, bool split, float* few, hipStream_t st) {
     // the kernel addresses P rows with 32-bit byte offsets: very tall inputs go in slabs of rows
     const long long max_rows = ((1LL << 31) / ((long long)ldp * 2)) & ~63LL;
     if (max_rows < 64 || (long long)r * ldq * 2 >= (1LL << 31) || (QT && (RP != 64 || (r & 7) || (long long)Kc * r * 2 >= (1LL << 32)))) return hipErrorInvalidValue;
     const SkinnyPlan pl = scratch && M <= max_rows ? skinny_plan(M, Kc, RP) : SkinnyPlan{1, 0};
-    if (few && M <= max_rows) {
-        const SkinnyPlan fp = skinny_few_plan(M, Kc, RP, out_cols);
+    if (split && M <= max_rows) {
+        const SkinnyPlan fp = skinny_few_plan(M, Kc, RP);
+        if (fp.slices > 1 && !few) {
+            constexpr int sh = 7 * (16 + 64) * 128 * 2;
+            static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_nt_kernel<4, 128, 4, 7, 1, QT, true>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, sh);
+            if (attr != hipSuccess) return attr;
+            skinny_nt_kernel<4, 128, 4, 7, 1, QT, true><<<dim3((M + 15) / 16), dim3(512), sh, st>>>(P, ldp, M, Q, ldq, r, Kc, s, out, nullptr, fp.kslice);
+            return hipGetLastError();
+        }
         if (fp.slices > 1) {
             constexpr int sh = 7 * (16 + 64) * 128 * 2;
             static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_nt_kernel<4, 128, 4, 7, 1, QT>),
@@ -334,19 +357,20 @@ static hipError_t launch_skinny_any(const uint16_t* P, int ldp, int M, const uin
     }
     return hipGetLastError();
 }
-// `scratch`: skinny_scratch_bytes of it, or null; `few`: where few tokens' partial sums go (above), or null: no such split
+// `scratch`: skinny_scratch_bytes of it, or null; `split`: few tokens' contraction is split (above), its partial sums in
+// `few`, skinny_few_bytes of it, or, where that is null, slice by slice in one workgroup
 hipError_t launch_skinny_ws(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
-                            float s, uint16_t* out, int RP, float* scratch, float* few, int out_cols, hipStream_t st) {
-    return launch_skinny_any<false>(P, ldp, M, Q, ldq, r, Kc, s, out, RP, scratch, few, out_cols, st);
+                            float s, uint16_t* out, int RP, float* scratch, bool split, float* few, hipStream_t st) {
+    return launch_skinny_any<false>(P, ldp, M, Q, ldq, r, Kc, s, out, RP, scratch, split, few, st);
 }
 // out[m][j] = bf16( s * sum_c P[m][c] Qt[c][j] ) with Qt [Kc][r] row-major, r a multiple of 8 up to 64: no transposed copy needed
 hipError_t launch_skinny_qt(const uint16_t* P, int ldp, int M, const uint16_t* Qt, int r, int Kc, float s, uint16_t* out,
-                            float* scratch, float* few, int out_cols, hipStream_t st) {
-    return launch_skinny_any<true>(P, ldp, M, Qt, r, r, Kc, s, out, 64, scratch, few, out_cols, st);
+                            float* scratch, bool split, float* few, hipStream_t st) {
+    return launch_skinny_any<true>(P, ldp, M, Qt, r, r, Kc, s, out, 64, scratch, split, few, st);
 }
 hipError_t launch_skinny(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
                          float s, uint16_t* out, int RP, hipStream_t st) {
-    return launch_skinny_ws(P, ldp, M, Q, ldq, r, Kc, s, out, RP, nullptr, nullptr, 0, st);
+    return launch_skinny_ws(P, ldp, M, Q, ldq, r, Kc, s, out, RP, nullptr, false, nullptr, st);
 }
 hipError_t launch_pad_cols(const uint16_t* src, int R, int c, uint16_t* dst, int CP, hipStream_t st) {
     const size_t tot = (size_t)R * CP;

@@ -54,7 +54,7 @@ def test_side_products(N, K, M, r):
 
 @pytest.mark.parametrize("N,K,M,r,path", [(1536, 1536, 1300, 64, lowra.PATH_AUTO), (1536, 2048, 700, 32, lowra.PATH_AUTO),
                                           (1800, 1600, 500, 24, lowra.PATH_AUTO), (4096, 1536, 20, 64, lowra.PATH_AUTO),
-                                          (136, 4096, 40, 16, lowra.PATH_AUTO), (264, 1600, 300, 64, lowra.PATH_AUTO),
+                                          (136, 4096, 40, 16, lowra.PATH_AUTO), (264, 1600, 300, 64, lowra.PATH_AUTO), (8, 9024, 37, 24, lowra.PATH_AUTO),
                                           (1544, 2112, 9, 64, lowra.PATH_GEMM), (4096, 1536, 16, 8, lowra.PATH_GEMM),
                                           (1536, 4096, 1, 5, lowra.PATH_GEMM)])
 def test_adapter_gradients_form_the_same_products(N, K, M, r, path):
