@@ -48,8 +48,9 @@ __device__ __forceinline__ void wait_newer(int newer) {
 typedef short sk_v4i16_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) sk_v4i16_t* sk_lds_v4i16_ptr;
 
-// WALK: one workgroup takes all slices of its rows one after the other and adds their sums in the order of
-// skinny_sum_kernel: the same bits as a launch per slice, without room for partial sums.
+// WALK: one workgroup takes all slices of its rows one after the other, in one pipeline of stages: the same bits as a
+// workgroup per slice and skinny_sum_kernel, without room for partial sums.  At the end of a slice the multiplying wavefronts
+// leave their sums in LDS behind the stages (two buffers in turn), and after the stage's barrier add them up as the others do.
 template <int CT, int KW, int NC, int RING, int PT = 1, bool QT = false, bool WALK = false>
 __global__ __launch_bounds__(128 * NC) void skinny_nt_kernel(const uint16_t* __restrict__ P, int ldp, int M,
                                                             const uint16_t* __restrict__ Q, int ldq, int r,
@@ -70,133 +71,153 @@ __global__ __launch_bounds__(128 * NC) void skinny_nt_kernel(const uint16_t* __r
     const int sw = mover ? wave - NC : wave;
     const int i = lane & 15, kg = lane >> 4;
     const int m0 = blockIdx.x * PR;
-    constexpr int PER = PR * RP / (128 * NC);                        // outputs per thread
-    static_assert(PER * 128 * NC == PR * RP, "whole rounds of outputs");
-    const int slices = WALK ? (Kc + kslice - 1) / kslice : 1;
-    float total[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) total[e] = 0.0f;
-    for (int sl = 0; sl < slices; ++sl) {
-        const int kbeg = (WALK ? sl : (int)blockIdx.y) * kslice, kend = min(kbeg + kslice, Kc);     // my slice of the contraction (kslice: a multiple of KW)
-        const int nst = (kend - kbeg + KW - 1) / KW;
+    // my slice of the contraction (kslice: a multiple of KW); WALK: all of it
+    const int kbeg = WALK ? 0 : blockIdx.y * kslice, kend = WALK ? Kc : min(kbeg + kslice, Kc);
+    const int nst = (kend - kbeg + KW - 1) / KW;
 
-        floatx4_t acc[PT][CT];
+    floatx4_t acc[PT][CT];
+#pragma unroll
+    for (int p = 0; p < PT; ++p)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[p][c] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+    if (mover) {
+        // instruction q = sw + NC t moves rows [q RPI, (q+1) RPI) of the stage: [0, PR) from P, the rest from Q
+        uint32_t voff[NIW], lc16[NIW];
+        const uint32_t kmax_byte = (uint32_t)(Kc - 8) * 2u;
+#pragma unroll
+        for (int t = 0; t < NIW; ++t) {
+            const int row = (sw + NC * t) * RPI + lane / CPR;
+            lc16[t] = (uint32_t)((lane % CPR) ^ (row & 15)) * 16u;   // logical chunk landing on my physical chunk
+            voff[t] = row < PR ? (uint32_t)min(m0 + row, M - 1) * (uint32_t)ldp * 2u
+                               : (uint32_t)min(row - PR, r - 1) * (uint32_t)ldq * 2u;
+            if (QT && row >= PR) {                                   // transposed Q: 8 contraction rows of 128 B per instruction
+                const int nloc = 8 * ((sw + NC * t) - PR / RPI) + (lane >> 3);
+                voff[t] = (uint32_t)nloc;                            // my row within the stage
+                lc16[t] = (uint32_t)((lane & 7) ^ (nloc & 7)) * 16u;
+            }
+        }
+        auto issue_stage = [&](int st) {
+            const uint32_t kb2 = (uint32_t)(kbeg + st * KW) * 2u;
+#pragma unroll
+            for (int t = 0; t < NIW; ++t) {
+                const int q = sw + NC * t;                           // uniform
+                const bool from_p = t * NC * RPI < PR;               // known at compile time: PR is a multiple of NC RPI
+                // columns past Kc: any valid bytes, zeroed at the read
+                if (QT && !from_p)
+                    dma16_s(Q, (uint32_t)min(kbeg + st * KW + (int)voff[t], Kc - 1) * (uint32_t)(2 * r) + min(lc16[t], (uint32_t)(2 * r - 16)),
+                            smem_lds + (st % RING) * STAGE + q * 1024);
+                else if (from_p)
+                    dma16_s(P, voff[t] + min(kb2 + lc16[t], kmax_byte), smem_lds + (st % RING) * STAGE + q * 1024);
+                else
+                    dma16_s(Q, voff[t] + min(kb2 + lc16[t], kmax_byte), smem_lds + (st % RING) * STAGE + q * 1024);
+            }
+        };
+        for (int st = 0; st < RING - 1 && st < nst; ++st) issue_stage(st);
+        wait_newer<NIW, RING - 2>(min(RING - 2, nst - 1));
+        __syncthreads();                                             // stage 0 is there
+        for (int it = 0; it < nst; ++it) {
+            if (it + RING - 1 < nst) issue_stage(it + RING - 1);
+            wait_newer<NIW, RING - 2>(max(0, min(RING - 2, nst - 2 - it)));   // stage it+1 has landed
+            __syncthreads();
+        }
+    } else {
+        const bf16x8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
+        constexpr int PER = PR * RP / (64 * NC);                     // WALK: outputs per multiplying thread
+        float total[PER];
+        int left = kslice / KW, slice = 0;                           // WALK: stages left of my slice
+        __syncthreads();
+        for (int it = 0; it < nst; ++it) {
+            const uint8_t* sb = smem + (it % RING) * STAGE;
+#pragma unroll
+            for (int u = 0; u < USTEPS; ++u) {
+                const int cl = (KW / NC / 8) * sw + 4 * u + kg;      // logical chunk of my 8 columns
+                const bool kin = kbeg + it * KW + cl * 8 < kend;
+                const int pc = (cl ^ i) << 4;
+                bf16x8_t a[PT];
+#pragma unroll
+                for (int p = 0; p < PT; ++p) {
+                    a[p] = *reinterpret_cast<const bf16x8_t*>(sb + (16 * p + i) * ROWBYTES + pc);
+                    if (!kin || m0 + 16 * p + i >= M) a[p] = zero;
+                }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    bf16x8_t b;
+                    if (QT) {
+                        typedef short v8i16_t __attribute__((ext_vector_type(8)));
+                        sk_v4i16_t h[2];
+#pragma unroll
+                        for (int eb = 0; eb < 2; ++eb) {
+                            const int nr = (KW / NC) * sw + 32 * u + 8 * kg + 4 * eb + (i >> 2);     // contraction row within the stage
+                            const int ch = 2 * c + ((i & 3) >> 1);
+                            const uint32_t ad = smem_lds + (it % RING) * STAGE + PR * ROWBYTES + nr * 128 + ((ch ^ (nr & 7)) << 4) + (i & 1) * 8;
+                            h[eb] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sk_lds_v4i16_ptr)(uintptr_t)ad);
+                        }
+                        const v8i16_t v = {h[0][0], h[0][1], h[0][2], h[0][3], h[1][0], h[1][1], h[1][2], h[1][3]};
+                        b = __builtin_bit_cast(bf16x8_t, v);
+                    } else {
+                        b = *reinterpret_cast<const bf16x8_t*>(sb + (PR + 16 * c + i) * ROWBYTES + pc);
+                    }
+                    if (!kin || 16 * c + i >= r) b = zero;
+#pragma unroll
+                    for (int p = 0; p < PT; ++p) acc[p][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[p], b, acc[p][c], 0, 0, 0);
+                }
+            }
+            const bool fold = WALK && (--left == 0 || it + 1 == nst);
+            float* sums = reinterpret_cast<float*>(smem + RING * STAGE) + (slice & 1) * (NC * PR * RP);     // [NC][PR][RP]
+            if (fold) {
+#pragma unroll
+                for (int p = 0; p < PT; ++p)
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) sums[(sw * PR + 16 * p + 4 * kg + v) * RP + c * 16 + i] = acc[p][c][v];
+                        acc[p][c] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                    }
+            }
+            __syncthreads();                                         // stage it is free again, stage it+1 is there
+            if (fold) {
+#pragma unroll
+                for (int e = 0; e < PER; ++e) {
+                    float v = 0.0f;
+#pragma unroll
+                    for (int w = 0; w < NC; ++w) v += sums[w * PR * RP + threadIdx.x + 64 * NC * e];
+                    total[e] = slice ? total[e] + v : v;
+                }
+                left = kslice / KW;
+                ++slice;
+            }
+        }
+        if (WALK) {
+#pragma unroll
+            for (int e = 0; e < PER; ++e) {
+                const int idx = threadIdx.x + 64 * NC * e, mo = m0 + idx / RP;
+                if (mo < M) out[(size_t)mo * RP + idx % RP] = (uint16_t)(pack_bf16x2(total[e] * s, 0.0f) & 0xffffu);
+            }
+        }
+    }
+    if (WALK) return;
+    // lane (i, kg) of a multiplying wavefront holds out[16 p + 4 kg + v][16 c + i]
+    float* red = reinterpret_cast<float*>(smem);   // [NC][PR][RP]
+    if (!mover) {
 #pragma unroll
         for (int p = 0; p < PT; ++p)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) acc[p][c] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
-
-        if (mover) {
-            // instruction q = sw + NC t moves rows [q RPI, (q+1) RPI) of the stage: [0, PR) from P, the rest from Q
-            uint32_t voff[NIW], lc16[NIW];
-            const uint32_t kmax_byte = (uint32_t)(Kc - 8) * 2u;
+            for (int c = 0; c < CT; ++c)
 #pragma unroll
-            for (int t = 0; t < NIW; ++t) {
-                const int row = (sw + NC * t) * RPI + lane / CPR;
-                lc16[t] = (uint32_t)((lane % CPR) ^ (row & 15)) * 16u;   // logical chunk landing on my physical chunk
-                voff[t] = row < PR ? (uint32_t)min(m0 + row, M - 1) * (uint32_t)ldp * 2u
-                                   : (uint32_t)min(row - PR, r - 1) * (uint32_t)ldq * 2u;
-                if (QT && row >= PR) {                                   // transposed Q: 8 contraction rows of 128 B per instruction
-                    const int nloc = 8 * ((sw + NC * t) - PR / RPI) + (lane >> 3);
-                    voff[t] = (uint32_t)nloc;                            // my row within the stage
-                    lc16[t] = (uint32_t)((lane & 7) ^ (nloc & 7)) * 16u;
-                }
-            }
-            auto issue_stage = [&](int st) {
-                const uint32_t kb2 = (uint32_t)(kbeg + st * KW) * 2u;
+                for (int v = 0; v < 4; ++v) red[(sw * PR + 16 * p + 4 * kg + v) * RP + c * 16 + i] = acc[p][c][v];
+    }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < PR * RP; idx += 128 * NC) {
+        const int row = idx / RP, col = idx % RP;
+        float v = 0.0f;
 #pragma unroll
-                for (int t = 0; t < NIW; ++t) {
-                    const int q = sw + NC * t;                           // uniform
-                    const bool from_p = t * NC * RPI < PR;               // known at compile time: PR is a multiple of NC RPI
-                    // columns past Kc: any valid bytes, zeroed at the read
-                    if (QT && !from_p)
-                        dma16_s(Q, (uint32_t)min(kbeg + st * KW + (int)voff[t], Kc - 1) * (uint32_t)(2 * r) + min(lc16[t], (uint32_t)(2 * r - 16)),
-                                smem_lds + (st % RING) * STAGE + q * 1024);
-                    else if (from_p)
-                        dma16_s(P, voff[t] + min(kb2 + lc16[t], kmax_byte), smem_lds + (st % RING) * STAGE + q * 1024);
-                    else
-                        dma16_s(Q, voff[t] + min(kb2 + lc16[t], kmax_byte), smem_lds + (st % RING) * STAGE + q * 1024);
-                }
-            };
-            for (int st = 0; st < RING - 1 && st < nst; ++st) issue_stage(st);
-            wait_newer<NIW, RING - 2>(min(RING - 2, nst - 1));
-            __syncthreads();                                             // stage 0 is there
-            for (int it = 0; it < nst; ++it) {
-                if (it + RING - 1 < nst) issue_stage(it + RING - 1);
-                wait_newer<NIW, RING - 2>(max(0, min(RING - 2, nst - 2 - it)));   // stage it+1 has landed
-                __syncthreads();
-            }
-        } else {
-            const bf16x8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
-            __syncthreads();
-            for (int it = 0; it < nst; ++it) {
-                const uint8_t* sb = smem + (it % RING) * STAGE;
-#pragma unroll
-                for (int u = 0; u < USTEPS; ++u) {
-                    const int cl = (KW / NC / 8) * sw + 4 * u + kg;      // logical chunk of my 8 columns
-                    const bool kin = kbeg + it * KW + cl * 8 < kend;
-                    const int pc = (cl ^ i) << 4;
-                    bf16x8_t a[PT];
-#pragma unroll
-                    for (int p = 0; p < PT; ++p) {
-                        a[p] = *reinterpret_cast<const bf16x8_t*>(sb + (16 * p + i) * ROWBYTES + pc);
-                        if (!kin || m0 + 16 * p + i >= M) a[p] = zero;
-                    }
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) {
-                        bf16x8_t b;
-                        if (QT) {
-                            typedef short v8i16_t __attribute__((ext_vector_type(8)));
-                            sk_v4i16_t h[2];
-#pragma unroll
-                            for (int eb = 0; eb < 2; ++eb) {
-                                const int nr = (KW / NC) * sw + 32 * u + 8 * kg + 4 * eb + (i >> 2);     // contraction row within the stage
-                                const int ch = 2 * c + ((i & 3) >> 1);
-                                const uint32_t ad = smem_lds + (it % RING) * STAGE + PR * ROWBYTES + nr * 128 + ((ch ^ (nr & 7)) << 4) + (i & 1) * 8;
-                                h[eb] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sk_lds_v4i16_ptr)(uintptr_t)ad);
-                            }
-                            const v8i16_t v = {h[0][0], h[0][1], h[0][2], h[0][3], h[1][0], h[1][1], h[1][2], h[1][3]};
-                            b = __builtin_bit_cast(bf16x8_t, v);
-                        } else {
-                            b = *reinterpret_cast<const bf16x8_t*>(sb + (PR + 16 * c + i) * ROWBYTES + pc);
-                        }
-                        if (!kin || 16 * c + i >= r) b = zero;
-#pragma unroll
-                        for (int p = 0; p < PT; ++p) acc[p][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[p], b, acc[p][c], 0, 0, 0);
-                    }
-                }
-                __syncthreads();                                         // stage it is free again, stage it+1 is there
-            }
+        for (int w = 0; w < NC; ++w) v += red[(w * PR + row) * RP + col];
+        const int mo = m0 + row;
+        if (mo < M) {
+            if (partial) partial[((size_t)blockIdx.y * M + mo) * RP + col] = v;          // one slice: unscaled, summed later
+            else out[(size_t)mo * RP + col] = (uint16_t)(pack_bf16x2(v * s, 0.0f) & 0xffffu);
         }
-        // lane (i, kg) of a multiplying wavefront holds out[16 p + 4 kg + v][16 c + i]
-        float* red = reinterpret_cast<float*>(smem);   // [NC][PR][RP]
-        if (!mover) {
-#pragma unroll
-            for (int p = 0; p < PT; ++p)
-#pragma unroll
-                for (int c = 0; c < CT; ++c)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) red[(sw * PR + 16 * p + 4 * kg + v) * RP + c * 16 + i] = acc[p][c][v];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-            const int idx = threadIdx.x + 128 * NC * e, row = idx / RP, col = idx % RP;
-            float v = 0.0f;
-#pragma unroll
-            for (int w = 0; w < NC; ++w) v += red[(w * PR + row) * RP + col];
-            if (WALK) {
-                total[e] = sl > 0 ? total[e] + v : v;
-                if (sl + 1 < slices) continue;
-                v = total[e];
-            }
-            const int mo = m0 + row;
-            if (mo < M) {
-                if (partial) partial[((size_t)blockIdx.y * M + mo) * RP + col] = v;          // one slice: unscaled, summed later
-                else out[(size_t)mo * RP + col] = (uint16_t)(pack_bf16x2(v * s, 0.0f) & 0xffffu);
-            }
-        }
-        if (WALK) __syncthreads();                                   // the sums have been read: the next slice's stages may come
     }
 }
 
@@ -286,11 +307,11 @@ static hipError_t launch_skinny_any(const uint16_t* P, int ldp, int M, const uin
     if (split && M <= max_rows) {
         const SkinnyPlan fp = skinny_few_plan(M, Kc, RP);
         if (fp.slices > 1 && !few) {
-            constexpr int sh = 7 * (16 + 64) * 128 * 2;
-            static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_nt_kernel<4, 128, 4, 7, 1, QT, true>),
+            constexpr int sh = 6 * (16 + 64) * 128 * 2 + 2 * 4 * 16 * 64 * 4;             // six stages, two buffers of sums
+            static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_nt_kernel<4, 128, 4, 6, 1, QT, true>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, sh);
             if (attr != hipSuccess) return attr;
-            skinny_nt_kernel<4, 128, 4, 7, 1, QT, true><<<dim3((M + 15) / 16), dim3(512), sh, st>>>(P, ldp, M, Q, ldq, r, Kc, s, out, nullptr, fp.kslice);
+            skinny_nt_kernel<4, 128, 4, 6, 1, QT, true><<<dim3((M + 15) / 16), dim3(512), sh, st>>>(P, ldp, M, Q, ldq, r, Kc, s, out, nullptr, fp.kslice);
             return hipGetLastError();
         }
         if (fp.slices > 1) {
