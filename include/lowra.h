@@ -110,9 +110,8 @@ size_t lowra_packed_bytes(const lowra_layout* layout);
  * M <= 16 also the small-token kernel's descriptors and per-chunk partial outputs, so it can be
  * non-zero at r == 0; and, for the token counts whose contractions are split between workgroups, the splits'
  * fp32 partial sums and tiles (at most 64 MiB).  A linear call with less is refused only below what it cannot do
- * without (all but the room for these splits): it forms the rank-r product in one workgroup per 16 rows and the
- * partial tiles in up to eight pieces, with the same results; with still less it splits the latter less, which
- * takes longer and adds in another order. */
+ * without (all but the room for these splits): it then forms the rank-r product in one workgroup per 16 rows,
+ * with the same bits, and splits the main contraction less, which takes longer and adds in another order. */
 size_t lowra_workspace_bytes(const lowra_layout* layout, int op, int M, int r);
 
 /* Quantize (App. A.1).  For every 64-element group: absmax a = max|w| is stored; every weight is

@@ -417,15 +417,21 @@ static lowra_status check_linear(const lowra_layout* L, int op, const uint8_t* p
     return LOWRA_OK;
 }
 
+static lowra_status linear_fwd(const lowra_layout* L, const uint8_t* packed, const float* absmax, const float* mappings,
+                               const uint16_t* x, int M, const uint16_t* A, const uint16_t* B, int r, float s, uint16_t* y,
+                               void* workspace, size_t workspace_bytes, bool pieces, void* stream) {
+    lowra_status st = check_linear(L, LOWRA_OP_LINEAR_FWD, packed, absmax, mappings, x, M, A, B, r, y, workspace, workspace_bytes);
+    if (st != LOWRA_OK || M == 0 || L->N == 0) return st;
+    lowra::LinearArgs a{packed, absmax, mappings, x, M, A, B, r, s, y, workspace, usable_bytes(workspace, workspace_bytes), pieces};
+    return lowra::launch_linear_fwd(*L, a, g_linear_path.load(), g_fwd_tiling.load(), static_cast<hipStream_t>(stream)) == hipSuccess
+               ? LOWRA_OK : LOWRA_HIP_ERROR;
+}
+
 lowra_status lowra_linear_fwd(const lowra_layout* L, const uint8_t* packed, const float* absmax,
                               const float* mappings, const uint16_t* x, int M, const uint16_t* A,
                               const uint16_t* B, int r, float s, uint16_t* y, void* workspace,
                               size_t workspace_bytes, void* stream) {
-    lowra_status st = check_linear(L, LOWRA_OP_LINEAR_FWD, packed, absmax, mappings, x, M, A, B, r, y, workspace, workspace_bytes);
-    if (st != LOWRA_OK || M == 0 || L->N == 0) return st;
-    lowra::LinearArgs a{packed, absmax, mappings, x, M, A, B, r, s, y, workspace, usable_bytes(workspace, workspace_bytes)};
-    return lowra::launch_linear_fwd(*L, a, g_linear_path.load(), g_fwd_tiling.load(), static_cast<hipStream_t>(stream)) == hipSuccess
-               ? LOWRA_OK : LOWRA_HIP_ERROR;
+    return linear_fwd(L, packed, absmax, mappings, x, M, A, B, r, s, y, workspace, workspace_bytes, false, stream);
 }
 
 lowra_status lowra_linear_fwd_static(const lowra_layout* L, const uint8_t* packed, const float* absmax,
@@ -439,7 +445,7 @@ lowra_status lowra_linear_fwd_static(const lowra_layout* L, const uint8_t* packe
     if (dev != L->device) return LOWRA_INVALID_ARG;               // the layout's index arrays live on another device
     void* ws = static_scratch_of_current_device();
     if (!ws) return LOWRA_HIP_ERROR;
-    return lowra_linear_fwd(L, packed, absmax, mappings, x, M, A, B, r, s, y, ws, kStaticBytes, stream);
+    return linear_fwd(L, packed, absmax, mappings, x, M, A, B, r, s, y, ws, kStaticBytes, true, stream);
 }
 
 lowra_status lowra_linear_bwd_input(const lowra_layout* L, const uint8_t* packed, const float* absmax,

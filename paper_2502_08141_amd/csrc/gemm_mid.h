@@ -36,10 +36,11 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
 void force_mid_plan(int rows, int splits);         // lowra_set_mid_tiling; 0, 0: the planner
 inline size_t mid_tile_bytes(int splits, int TM) { return (size_t)splits * TM * (32 * kMidCols * sizeof(float)); }
 inline size_t mid_part_bytes(const MidPlan& pl) { return mid_tile_bytes(pl.splits, pl.TM) * pl.tiles_c * pl.tiles_m; }
-// With room for some of a plan's partial tiles only, as many output tiles as fit are computed and summed at a time: the
-// same sums in the same order.  At most kMidPieces such pieces (0: more would be needed); beyond that fewer splits are the
-// better plan.
-constexpr int kMidPieces = 8;
+// With room for some of a plan's partial tiles only, as many output tiles as fit can be computed and summed at a time: the
+// same sums in the same order.  At most kMidPieces such pieces (0: more would be needed).  Only for calls that promise the
+// bits of the whole plan: a piece fills a part of the chip only, and fewer splits are the better plan for the time (half the
+// room: 1.2x, a third 1.5x, an eighth up to 4x).
+constexpr int kMidPieces = 3;
 inline int mid_pieces(const MidPlan& pl, size_t room) {
     const size_t fit = room / mid_tile_bytes(pl.splits, pl.TM), tiles = (size_t)pl.tiles_c * pl.tiles_m;
     return fit == 0 || (tiles + fit - 1) / fit > (size_t)kMidPieces ? 0 : (int)((tiles + fit - 1) / fit);

@@ -103,8 +103,11 @@ static MidParams mid_params(const lowra_layout& L, const LinearArgs& a, int op, 
 static MidPlan mid_plan_call(const lowra_layout& L, const LinearArgs& a, int op, bool gemm) {
     const size_t least = align256(linear_workspace_min(L, op, a.M, a.r));
     const size_t room = a.workspace_bytes > least ? a.workspace_bytes - least : 0;
-    const MidPlan whole = mid_plan_of(L, op, a.M, a.r, gemm, ~(size_t)0);       // in pieces where the room is short
-    return whole.splits <= 1 || mid_pieces(whole, room) > 0 ? whole : mid_plan_of(L, op, a.M, a.r, gemm, room);
+    if (a.pieces) {
+        const MidPlan whole = mid_plan_of(L, op, a.M, a.r, gemm, ~(size_t)0);
+        if (whole.splits <= 1 || mid_pieces(whole, room) > 0) return whole;
+    }
+    return mid_plan_of(L, op, a.M, a.r, gemm, room);
 }
 size_t linear_workspace_min(const lowra_layout& L, int op, int M, int r) {
     return align256(linear_workspace_bytes_fp32(L, op, M, r)) + expanded_scale_bytes(L);

@@ -158,6 +158,7 @@ struct LinearArgs {
     uint16_t* out;         // y [M,N] (fwd) or dX [M,K] (bwd)
     void* workspace;
     size_t workspace_bytes;
+    bool pieces = false;   // short of room for partial tiles: the whole plan in pieces, not one with fewer splits
 };
 // bf16 group scales -> fp32 (exact), for the kernels that read fp32 scales
 hipError_t launch_expand_scales(const uint16_t* src, size_t count, float* dst, hipStream_t st);

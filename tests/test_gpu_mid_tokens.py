@@ -139,8 +139,7 @@ def test_infinite_activations_at_the_end_of_a_row(K, fr):
 
 def test_mid_token_less_workspace():
     """A workspace that holds less than lowra_workspace_bytes asks for, but what the call cannot do without, is taken: the
-    partial tiles are formed in up to eight pieces (same bits), with less the contraction is split between fewer
-    workgroups, or not at all."""
+    contraction is then split between fewer workgroups, or not at all."""
     L = synth.make_custom(1032, 2048, 40, 64, fractions=MIXED, seed=771)
     D = DeviceLayer(L)
     D.quantize()
@@ -148,14 +147,11 @@ def test_mid_token_less_workspace():
     need = D.layout.workspace_bytes(lowra.OP_LINEAR_FWD, L.M, L.r)
     side = (L.M * 64 * 2 + 255) // 256 * 256                  # the rank-r intermediate alone
     assert need > side                                        # 40 tokens of this shape are split
-    # 9 x 2 tiles (40 tokens are two tiles of 32) or 9: the least room for eight pieces holds 3 of the 18, or 2 of the 9
-    pieces = [need - 256, side + (need - side) // 2, side + (need - side) * 2 // 9]
-    for size in pieces + [side + (need - side) // 10, side]:
+    for size in (need - 256, (need + side) // 2, side):
         got = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, L.s,
                                      workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
         torch.cuda.synchronize()
         assert rel_err(bf16_host_f64(got), bf16_host_f64(want)) <= ORDER_TOL
-        assert size not in pieces or torch.equal(got, want)
     with pytest.raises(lowra.LowraError, match="workspace too small"):
         lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, L.s,
                                workspace=torch.empty(side - 256, dtype=torch.uint8, device="cuda"))
