@@ -673,7 +673,7 @@ lowra_status lowra_set_fwd_tiling(int rows_a, int rows_b, int cols_a) {
 
 lowra_status lowra_set_mid_tiling(int rows, int splits) {
     const bool planner = rows == 0 && splits == 0;
-    if (!planner && (rows < 32 || rows > 128 || rows % 32 != 0 || splits < 1 || splits > lowra::kMidMaxSplits)) return LOWRA_INVALID_ARG;
+    if (!planner && (rows < 32 || (rows > 128 && rows != 192) || rows % 32 != 0 || splits < 1 || splits > lowra::kMidMaxSplits)) return LOWRA_INVALID_ARG;
     lowra::force_mid_plan(rows, splits);
     return LOWRA_OK;
 }

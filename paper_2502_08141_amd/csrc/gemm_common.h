@@ -168,6 +168,17 @@ __device__ __forceinline__ void dma4_s(const void* sbase, uint32_t voff, uint32_
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                  : : "v"(voff), "s"(sbase), "s"(lds_base_uniform) : "memory");
 }
+// The same through a buffer descriptor (raw, byte offsets): the data of a lane whose offset lies past the descriptor's
+// 2^31 - 1 bytes is zero, so that a transfer with lanes past an end needs no branch.
+typedef int bufdesc_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bufdesc_t buffer_desc(const void* base) {
+    const uint64_t a = (uint64_t)(uintptr_t)base;
+    return bufdesc_t{__builtin_amdgcn_readfirstlane((int)(uint32_t)a), __builtin_amdgcn_readfirstlane((int)((a >> 32) & 0xffffu)), 0x7fffffff, 0x00027000};
+}
+__device__ __forceinline__ void dma16_b(bufdesc_t desc, uint32_t voff, uint32_t soff, uint32_t lds_base_uniform) {
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                 : : "v"(voff), "s"(desc), "s"(soff), "s"(lds_base_uniform) : "memory");
+}
 __device__ __forceinline__ void dma_wait_all() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
 
 // 8 one-bit codes (low byte of c) -> 8 bf16 through the byte table Q = [lo0, lo1, hi0, hi1]

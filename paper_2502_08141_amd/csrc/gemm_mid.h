@@ -6,7 +6,7 @@ namespace lowra {
 
 constexpr int kMidCols = 128;            // output columns per workgroup
 constexpr int kMidMaxSplits = 32;
-static_assert(kMidMaxSplits * 128 * kMidCols * sizeof(float) <= kMidTileMax, "32 TM = 128 rows at most");
+static_assert(kMidMaxSplits * 192 * kMidCols * sizeof(float) <= kMidTileMax, "32 TM = 192 rows at most");
 constexpr int kMidLutBooks = 64;         // codebooks the input gradient keeps in LDS as a whole (more: a step's 64 rows are staged)
 
 struct MidParams {

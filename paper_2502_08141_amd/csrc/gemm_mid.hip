@@ -5,7 +5,7 @@
 // The 256-column kernels of gemm_fwd.hip and gemm_bwd.hip hold a compute unit with one workgroup of 256 x (128..256)
 // outputs that walks the whole contraction.  With few output tiles that leaves most of the chip idle: 128 tokens of a
 // 4096 x 4096 matrix are 16 workgroups and 64 steps in a row.  Here a workgroup owns 128 output columns x 32 TM tokens
-// (TM = 1..4), two or three of them share a compute unit and cover each other's latencies, and the contraction is split
+// (TM = 1..4, forward also 6), two or three of them share a compute unit and cover each other's latencies, and the contraction is split
 // between workgroups until they fill the chip; the splits leave fp32 partial tiles in accumulator order that
 // mid_sum_kernel adds in split order (deterministic, no atomics).  Any K from 128 on (an odd number of groups
 // included), any mix of widths, any number of codebooks.
@@ -118,14 +118,32 @@ __device__ __forceinline__ void mid_epilogue(const MidParams& p, const floatx16_
 // which are 16, 32 or 64 contiguous bytes of its row, so that its codes are asked for once per superstep, one
 // superstep ahead.  Step j (0..3) contracts features 32 j .. + 31 of both halves; LDS chunk c (16 bytes) of a token
 // row holds half c / 4, features 8 (c % 4) .. + 7 of the step, at physical chunk c ^ ((row >> 1) & 7).
-// WIDE: the matrix has 4-bit rows.  Every lane then keeps the 16 levels of its row times the current group's absmax,
-// rounded to bf16 (App. A.2 on 16 values instead of 64), in a table of its own in LDS: entry q of lane l at
-// 256 q + 4 l, so that a lookup touches bank l whatever the code -- no conflicts, one shift-add per address.
-template <int TM, bool WIDE>
+// WIDE: the matrix has 4-bit rows.  Every wavefront then keeps the levels of its 32 rows in LDS, level q of row i at
+// 128 q + 4 i (a lookup's bank follows from the row alone: no conflicts), and a looked-up level times the group's absmax is
+// rounded to bf16 (App. A.2 as written).
+//
+// What bounds it: plain-ALU issue.  The decode is 1.3 (WIDE 2) instructions per weight, that is 20 to 34 beside the TM MFMAs
+// of a slice, whatever TM is: two workgroups on a unit are busy for the sum of the decode's and the MFMAs' issue times.
+// Hence (a) a superstep of 16 slices without a branch: transfers past an end are zeroed by a buffer descriptor, codes and
+// scales are staged in LDS by counted transfers, an odd number of groups is its own instantiation; with a branch at every
+// transfer the compiler emptied the matrix pipe at each.  4096 x 4096, 512 tokens, 50/50 % of 1-/2-bit rows 39 -> 30 us;
+// 4096 x 1024, 777 tokens with 4-bit rows 19.8 -> 17.1.  (b) Tiles of 192 tokens, which halve the decode of tiles of 96:
+// 11008 x 4096, 333 tokens, 50/25/25 %: 77 us -> 70 (a) -> 55.  They leave LDS for one workgroup per unit.
+template <int TM, bool WIDE, bool ODD>
+struct FwdLds {
+    static constexpr int STAGE = TM * 4096;                           // 32 TM token rows x 128 bytes
+    static constexpr int NP = WIDE ? 4 : 2;                           // 16-byte pieces of a lane's codes per superstep
+    static constexpr int TAB0 = 3 * STAGE;                            // WIDE: 2 KB of levels per wavefront
+    static constexpr int CODE0 = TAB0 + (WIDE ? 4 * 2048 : 0);        // per wavefront: two scales (256 bytes each), then the pieces, 1 KB each
+    static constexpr int CODE = 512 + (NP + (ODD ? 1 : 0)) * 1024;    // (an odd number of groups: rows may start at 8 mod 16, one piece more)
+    static constexpr int BYTES = CODE0 + 4 * CODE;
+};
+
+template <int TM, bool WIDE, bool ODD>
 __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
     extern __shared__ __align__(16) uint8_t smem[];
-    constexpr int STAGE = TM * 4096;                                  // 32 TM token rows x 128 bytes
-    constexpr int TAB0 = 3 * STAGE;                                   // WIDE: 4 KB per wavefront
+    using L = FwdLds<TM, WIDE, ODD>;
+    constexpr int STAGE = L::STAGE, NP = L::NP;
     const uint32_t smem_lds = (uint32_t)(uintptr_t)(lptr_t)smem;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -139,79 +157,62 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
     const int G = p.G, K = p.K;
     const int nsuper = (G + 3) >> 2;
     const int s_lo = split * p.per_split, s_hi = min(s_lo + p.per_split, nsuper);
-    // steps of the last superstep: a single group left is the first half's first two steps
-    const int t_lo = s_lo * 4, t_hi = s_hi == nsuper ? (s_hi - 1) * 4 + ((G & 3) == 1 ? 2 : 4) : s_hi * 4;
+    const int k_hi = min(K, s_hi * 256);
 
     // my row (past N: the last one again, into output columns that are never stored)
     const int nc = min(n0 + wave * 32 + fi, p.N - 1);
     const RowInfo rec = p.rows[nc];
 
-    // activation transfers: wavefront w moves rows 8 (w TM + i) .. + 7, i < TM
+    // Activation transfers: wavefront w moves rows 8 (w TM + i) .. + 7, i < TM.  They go through a buffer descriptor: a lane
+    // whose features lie past k_hi gets an offset past its end, and zeros land in LDS without a branch around the transfer
+    // (an infinity times a stand-in weight would not be none; and a branch per transfer cuts the slices' schedule to pieces).
     const int m_last = p.M - 1 - m0;
-    const uint16_t* act0 = p.act + (size_t)m0 * K;
+    const bufdesc_t act = buffer_desc(p.act + (size_t)m0 * K);
     uint32_t voff[TM];
-    int koff[TM];
+    const int half0 = (((lane & 7) ^ ((wave * TM * 4 + (lane >> 4)) & 7)) >> 2) * 128;    // even i; odd i: the other half
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int r = (wave * TM + i) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ ((r >> 1) & 7);
-        koff[i] = (c >> 2) * 128 + (c & 3) * 8;
-        voff[i] = (uint32_t)min(r, m_last) * (uint32_t)K * 2u + (uint32_t)koff[i] * 2u;     // rows past M are clamped (never stored)
+        voff[i] = (uint32_t)min(r, m_last) * (uint32_t)K * 2u + (uint32_t)((c >> 2) * 128 + (c & 3) * 8) * 2u;     // rows past M are clamped (never stored)
     }
-    auto issue = [&](int t, int stage) __attribute__((always_inline)) {
-        const int k = (t >> 2) * 256 + (t & 3) * 32;
-        const uint32_t dst = smem_lds + stage * STAGE + wave * (TM * 1024);
-        if ((t >> 2) * 256 + 256 <= K) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) dma16_s(act0 + k, voff[i], dst + i * 1024);
-        } else {                                                      // features past K are zeros: an infinity times a zero weight is none
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {                            // (at least one transfer per i: the waits below count them)
-                if (koff[i] < K - k) dma16_s(act0 + k, voff[i], dst + i * 1024);
-                else dma16_s(mid_zeros, 0u, dst + i * 1024);
-            }
-        }
+    auto issue1 = [&](int ss, int j, int stage, int i) __attribute__((always_inline)) {   // of step j of superstep ss
+        const int left = k_hi - ss * 256 - j * 32;                    // uniform
+        const uint32_t v = ((i & 1) ? 128 - half0 : half0) < left ? voff[i] : 0x80000000u;
+        dma16_b(act, v, (uint32_t)(ss * 512 + j * 64), smem_lds + stage * STAGE + wave * (TM * 1024) + i * 1024);
     };
-    issue(t_lo, 0);
-    issue(min(t_lo + 1, t_hi - 1), 1);
-    issue(min(t_lo + 2, t_hi - 1), 2);
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int i = 0; i < (j < 2 ? TM : TM / 4); ++i) issue1(s_lo, j, j, i);
 
     const int bits = rec.bits();
     const float* tab = p.mappings + (size_t)rec.cb() * kTableStride;
-    constexpr int NLEV = WIDE ? 16 : 4;
-    float lev[NLEV];
-#pragma unroll
-    for (int q = 0; q < NLEV; q += 4) {
-        const float4 v = *reinterpret_cast<const float4*>(tab + q);
-        lev[q] = v.x; lev[q + 1] = v.y; lev[q + 2] = v.z; lev[q + 3] = v.w;
-    }
     const bool one = bits == 1, four = bits == 4;
     const NarrowConsts nk = narrow_consts(bits == 2);
 
-    // my codes and scales of one superstep
-    constexpr int NP = WIDE ? 4 : 2;
-    const uint8_t* row = p.packed + rec.offset;
-    const size_t srow = (size_t)nc * G;
-    auto load_super = [&](int ss, uint4 (&c)[NP], uint32_t (&a)[2]) __attribute__((always_inline)) {
-        const int gh = ss * 4 + 2 * h;                                // my two groups
-        a[0] = load_scale(p, srow + min(gh, G - 1));
-        a[1] = load_scale(p, srow + min(gh + 1, G - 1));
-        if (gh >= G) a[0] = 0u;                                       // past the row's end
-        if (gh + 1 >= G) a[1] = 0u;
-        const uint8_t* q0 = row + (size_t)gh * 8 * bits;
-        if (ss * 4 + 4 <= G) {                                        // uniform
+    // My codes and scales of one superstep travel as the activations do, counted with them: a register load among
+    // transfers that the compiler does not know would be waited for with all of them.  Pieces past the row's are its last
+    // one again.  The last superstep of an odd number of groups, inside which the row ends at 8 mod 16, is not staged.
+    const int s_staged = ODD ? max(min(s_hi, nsuper - 1), 1) - 1 : s_hi - 1;
+    uint8_t* const my_code = smem + L::CODE0 + wave * L::CODE;
+    const uint32_t code_lds = smem_lds + L::CODE0 + wave * L::CODE;
+    const uint32_t mis = ODD ? rec.offset & 8u : 0u;                  // the 16-byte pieces start this much before my codes
+    const uint32_t srow = (uint32_t)nc * (uint32_t)G;
+    const int scale_sh = p.scale_bf16 ? 1 : 0;                        // bf16: the dword that holds the scale
+    constexpr int NCODE = NP + 2 + (ODD ? 1 : 0);
+    auto issue_codes = [&](int ss_) __attribute__((always_inline)) {
+        const int ss = min(ss_, s_staged);
+        int gh = ss * 4 + 2 * h;                                      // my two groups
+        if (gh + 1 >= G) gh = ss * 4;                                 // past the row's end: any of the row's, its scale becomes zero
+        const uint32_t c0 = rec.offset - mis + (uint32_t)(gh * 8 * bits);
+        const int last = bits - 1 + (int)(mis >> 3);
+        dma4_s(p.absmax, ((srow + (uint32_t)gh) >> scale_sh) * 4u, code_lds);
+        dma4_s(p.absmax, ((srow + (uint32_t)gh + 1u) >> scale_sh) * 4u, code_lds + 256);
 #pragma unroll
-            for (int q = 0; q < NP; ++q) c[q] = q < bits ? load16_u(q0 + 16 * q) : make_uint4(0u, 0u, 0u, 0u);
-        } else {                                                      // the row's end: 8 bytes at a time
-            const int have = min(max(G - gh, 0), 2) * 8 * bits;
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                const uint2 lo = 16 * q + 8 <= have ? load8_u(q0 + 16 * q) : make_uint2(0u, 0u);
-                const uint2 hi = 16 * q + 16 <= have ? load8_u(q0 + 16 * q + 8) : make_uint2(0u, 0u);
-                c[q] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            }
-        }
+        for (int q = 0; q < NP + (ODD ? 1 : 0); ++q) dma16_s(p.packed, c0 + 16u * (uint32_t)min(q, last), code_lds + 512 + q * 1024);
     };
+    issue_codes(s_lo);
 
     floatx16_t acc[TM];
 #pragma unroll
@@ -221,118 +222,154 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_fwd_kernel(MidParams p) {
     int kof[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) kof[kk] = fi * 128 + (((4 * h + kk) ^ ((fi >> 1) & 7)) << 4);
-    uint8_t* mytab = smem + TAB0 + wave * 4096 + lane * 4;
+    uint8_t* mytab = smem + L::TAB0 + wave * 2048 + fi * 4;
+    float lev[4];
+#pragma unroll
+    for (int q = 0; q < (WIDE ? 16 : 4); q += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(tab + q);
+        if (WIDE) {
+            float* d = reinterpret_cast<float*>(mytab + 128 * q);
+            d[0] = v.x; d[32] = v.y; d[64] = v.z; d[96] = v.w;        // (both halves write the same values)
+        } else {
+            lev[0] = v.x; lev[1] = v.y; lev[2] = v.z; lev[3] = v.w;
+        }
+    }
 
-    // Operands of one slice (16 of a step's 64 features).  WIDE keeps the looked-up values and packs them right before
-    // the MFMAs, a slice after the lookups were issued.
-    struct Slice { bf16x8_t f[TM]; uint32_t e[8]; bf16x8_t wf; };
-    uint32_t c[4 * NP], SL = 0, SH = 0;
-    float a0 = 0.0f, a1 = 0.0f;
-    auto new_group = [&](float a) __attribute__((always_inline)) {    // the tables of my row's next group
-        if (WIDE) {
+    struct Codes { uint32_t c[4 * NP]; float a0, a1; };               // of one superstep: 128 codes and two scales
+    auto fetch = [&](int ss, Codes& o) __attribute__((always_inline)) {
+        const int gh = ss * 4 + 2 * h;
+        uint32_t b0, b1;
+        if (!ODD || ss + 1 < nsuper) {                                // uniform
+            uint32_t d[4 * NP + 4];
 #pragma unroll
-            for (int q = 0; q < NLEV; ++q) {
-                const float v = lev[q] * a;
-                *reinterpret_cast<uint32_t*>(mytab + 256 * q) = pack_bf16x2(v, v);
+            for (int q = 0; q < NP + (ODD ? 1 : 0); ++q) {
+                const uint4 v = *reinterpret_cast<const uint4*>(my_code + 512 + q * 1024 + lane * 16);
+                d[4 * q] = v.x; d[4 * q + 1] = v.y; d[4 * q + 2] = v.z; d[4 * q + 3] = v.w;
             }
-        } else {
-            const uint32_t P01 = pack_bf16x2(lev[0] * a, lev[1] * a), P23 = pack_bf16x2(lev[2] * a, lev[3] * a);
-            SL = __builtin_amdgcn_perm(P23, P01, nk.sell);
-            SH = __builtin_amdgcn_perm(P23, P01, nk.selh);
-        }
-    };
-    auto decode = [&](int j, int kk, Slice& o) __attribute__((always_inline)) {
-        const uint32_t c2 = c[2 * j + (kk >> 1)] >> (16 * (kk & 1)), c1 = c[j] >> (8 * kk);
-        const uint32_t c21 = one ? c1 : c2;
-        if (WIDE) {
-            const uint32_t cw = four ? c[(4 * j + kk) % (4 * NP)] : c21;
+            b0 = *reinterpret_cast<const uint32_t*>(my_code + lane * 4);
+            b1 = *reinterpret_cast<const uint32_t*>(my_code + 256 + lane * 4);
+            const uint32_t e = srow + (uint32_t)gh;                   // (a zeroed scale's parity does not matter)
+            b0 >>= (e & scale_sh) * 16; b1 >>= (~e & scale_sh) * 16;
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                o.e[i] = *reinterpret_cast<const uint32_t*>(mytab + (__builtin_amdgcn_ubfe(cw, (uint32_t)(i * bits), (uint32_t)bits) << 8));
+            for (int i = 0; i < 4 * NP; ++i) o.c[i] = ODD && mis ? d[ODD ? i + 2 : i] : d[i];
         } else {
-            o.wf = narrow8(c21, SL, SH, nk);
+            b0 = load_scale(p, srow + min(gh, G - 1));
+            b1 = load_scale(p, srow + min(gh + 1, G - 1));
+            const uint8_t* q0 = p.packed + rec.offset + (size_t)gh * 8 * bits;
+            const int have = min(max(G - gh, 0), 2) * 8 * bits;
+#pragma unroll
+            for (int q = 0; q < 2 * NP; ++q) {
+                const uint2 v = 8 * q + 8 <= have ? load8_u(q0 + 8 * q) : make_uint2(0u, 0u);
+                o.c[2 * q] = v.x; o.c[2 * q + 1] = v.y;
+            }
         }
+        o.a0 = gh < G ? __builtin_bit_cast(float, scale_of(p, b0)) : 0.0f;
+        o.a1 = gh + 1 < G ? __builtin_bit_cast(float, scale_of(p, b1)) : 0.0f;
     };
-    auto read_act = [&](int stage, int kk, Slice& o) __attribute__((always_inline)) {
+    Codes cur, nxt;
+    uint32_t SL = 0, SH = 0;
+    // Slice q (0..15) of a superstep: 16 of a step's 64 features, step q / 4.  q = 16, 17: the next superstep's first.
+    auto word = [&](int q, bool want4) __attribute__((always_inline)) -> uint32_t {
+        const Codes& o = q < 16 ? cur : nxt;
+        const int j = (q >> 2) & 3, kk = q & 3;
+        const uint32_t c2 = o.c[2 * j + (kk >> 1)] >> (16 * (kk & 1)), c1 = o.c[j] >> (8 * kk);
+        const uint32_t c21 = one ? c1 : c2;
+        return want4 && four ? o.c[(q & 15) % (4 * NP)] : c21;
+    };
+    auto new_group = [&](float a) __attribute__((always_inline)) {    // narrow rows: the byte tables of the next group
+        const uint32_t P01 = pack_bf16x2(lev[0] * a, lev[1] * a), P23 = pack_bf16x2(lev[2] * a, lev[3] * a);
+        SL = __builtin_amdgcn_perm(P23, P01, nk.sell);
+        SH = __builtin_amdgcn_perm(P23, P01, nk.selh);
+    };
+    auto look = [&](int q, float (&e)[8]) __attribute__((always_inline)) {
+        const uint32_t cw = word(q, true);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            e[i] = *reinterpret_cast<const float*>(mytab + (__builtin_amdgcn_ubfe(cw, (uint32_t)(i * bits), (uint32_t)bits) << 7));
+    };
+    auto pack = [&](int q, const float (&e)[8]) __attribute__((always_inline)) -> bf16x8_t {
+        const float a = q < 8 ? cur.a0 : q < 16 ? cur.a1 : nxt.a0;
+        return frag_of(pack_bf16x2(e[0] * a, e[1] * a), pack_bf16x2(e[2] * a, e[3] * a), pack_bf16x2(e[4] * a, e[5] * a), pack_bf16x2(e[6] * a, e[7] * a));
+    };
+    struct Acts { bf16x8_t f[TM]; };
+    auto read_act = [&](int stage, int kk, Acts& o) __attribute__((always_inline)) {
         const uint8_t* sb = smem + stage * STAGE + kof[kk];
 #pragma unroll
         for (int tt = 0; tt < TM; ++tt) o.f[tt] = *reinterpret_cast<const bf16x8_t*>(sb + tt * 4096);
     };
-    auto multiply = [&](const Slice& o) __attribute__((always_inline)) {
-        const bf16x8_t wf = WIDE ? frag_of(__builtin_amdgcn_perm(o.e[1], o.e[0], 0x05040100u), __builtin_amdgcn_perm(o.e[3], o.e[2], 0x05040100u),
-                                           __builtin_amdgcn_perm(o.e[5], o.e[4], 0x05040100u), __builtin_amdgcn_perm(o.e[7], o.e[6], 0x05040100u))
-                                 : o.wf;
-#pragma unroll
-        for (int tt = 0; tt < TM; ++tt) acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, o.f[tt], acc[tt], 0, 0, 0);
-    };
-
-    // The instruction order of a slice at TM = 4: after each MFMA a share of the work that prepares the next slice
-    // (MFMAs issued back to back hold the wavefront at its next one for 32 cycles each; 94 -> 90 us on 4096 x 4096,
-    // 2048 tokens; at lower tiles no gain).
+    // The instruction order of a slice: after each MFMA a share of the work that prepares the next ones (MFMAs issued back
+    // to back hold the wavefront at its next one for 32 cycles each).
     auto spread = [&]() __attribute__((always_inline)) {
-        if (WIDE) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+        constexpr int NV = WIDE ? 34 : 22, ND = WIDE ? TM + 8 : TM;
 #pragma unroll
         for (int t = 0; t < TM; ++t) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, WIDE ? 3 : 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, (NV + TM - 1) / TM, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, (ND + TM - 1) / TM, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-
-    uint4 cn[NP];
-    uint32_t an[2];
-    auto next_super = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < NP; ++q) { c[4 * q] = cn[q].x; c[4 * q + 1] = cn[q].y; c[4 * q + 2] = cn[q].z; c[4 * q + 3] = cn[q].w; }
-        a0 = __builtin_bit_cast(float, scale_of(p, an[0])); a1 = __builtin_bit_cast(float, scale_of(p, an[1]));
-    };
-    load_super(s_lo, cn, an);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // all three activation tiles
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // all three activation tiles, the first codes
     __syncthreads();
-    next_super();
-    new_group(a0);
-    Slice sl[2];
-    decode(0, 0, sl[0]);
-    read_act(0, 0, sl[0]);
+    fetch(s_lo, cur);
+    Acts ac[2];
+    bf16x8_t wf[2];
+    float e[2][8];
+    if (WIDE) {
+        look(0, e[0]);
+        look(1, e[1]);
+        wf[0] = pack(0, e[0]);
+    } else {
+        new_group(cur.a0);
+        wf[0] = narrow8(word(0, false), SL, SH, nk);
+    }
+    read_act(0, 0, ac[0]);
 
     // Step t.  Its barrier sits before the last slice, when every wavefront holds that slice's operands: stage t % 3 is
-    // then free for tile t + 3, and the operands of (step t + 1, slice 0) are read under the last slice's MFMAs.
+    // then free for tile t + 3, whose transfers go out one per slice from there on (several at once hold up the
+    // wavefront), and the operands of (step t + 1, slice 0) are read under the last slice's MFMAs.  The codes of superstep
+    // ss + 1 are sent for in its predecessor's first step, into a place that has been read, and read in the last.
     int st = 0;                                                       // stage of step t
     for (int ss = s_lo; ss < s_hi; ++ss) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = ss * 4 + j;
-            if (t >= t_hi) break;                                     // uniform
-            const int stn = st == 2 ? 0 : st + 1;
+        for (int q = 0; q < 16; ++q) {
+            const int j = q >> 2, kk = q & 3;
+            const int stn = st == 2 ? 0 : st + 1, stp = st == 0 ? 2 : st - 1;
+            if (kk == 3) {
+                // tile t + 1 has landed when no more is outstanding than was issued for tile t + 2 and, in a superstep's
+                // second step, for the codes before it
+                if (j == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM + NCODE) : "memory");
+                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM) : "memory");
+                __syncthreads();
+                if (j == 0) issue_codes(ss + 1);
 #pragma unroll
-            for (int kk = 0; kk < 3; ++kk) {
-                read_act(st, kk + 1, sl[(kk + 1) & 1]);
-                decode(j, kk + 1, sl[(kk + 1) & 1]);
-                if (TM < 4) __builtin_amdgcn_sched_barrier(0);
-                multiply(sl[kk & 1]);
-                if (TM == 4) spread();
+                for (int i = 0; i < TM / 4; ++i) issue1(j == 0 ? ss : ss + 1, (j + 3) & 3, st, i);
+                read_act(stn, 0, ac[(q + 1) & 1]);
+            } else {
+#pragma unroll
+                for (int i = (kk + 1) * TM / 4; i < (kk + 2) * TM / 4; ++i) {
+                    if (j < 2) issue1(ss, j + 2, stp, i);
+                    else issue1(ss + 1, j - 2, stp, i);
+                }
+                if (q == 12) fetch(ss + 1, nxt);
+                read_act(st, kk + 1, ac[(q + 1) & 1]);
             }
-            // Tile t + 1 has landed when no more is outstanding than was issued for tile t + 2, TM transfers at least.  (Loads
-            // issued behind those are not counted on: the compiler may order, join or wait for them as it likes.)
-            if (t + 3 <= t_hi) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TM) : "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            if (j == 3) next_super();                                 // (the loaded codes are waited for here, not behind the transfers below)
-            __builtin_amdgcn_sched_barrier(0);
-            if (t + 3 < t_hi) issue(t + 3, st);
-            __builtin_amdgcn_sched_barrier(0);
-            if (j == 0 && ss + 1 < s_hi) load_super(ss + 1, cn, an);
-            if (j == 1) new_group(a1);
-            if (j == 3) new_group(a0);
-            read_act(stn, 0, sl[0]);
-            decode((j + 1) & 3, 0, sl[0]);
-            if (TM < 4) __builtin_amdgcn_sched_barrier(0);
-            multiply(sl[1]);
-            if (TM == 4) spread();
-            st = stn;
+            if (WIDE) {
+                look(q + 2, e[q & 1]);
+                wf[(q + 1) & 1] = pack(q + 1, e[(q + 1) & 1]);
+            } else {
+                if (q == 7) new_group(cur.a1);
+                if (q == 15) new_group(nxt.a0);
+                wf[(q + 1) & 1] = narrow8(word(q + 1, false), SL, SH, nk);
+            }
+#pragma unroll
+            for (int tt = 0; tt < TM; ++tt) acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[q & 1], ac[q & 1].f[tt], acc[tt], 0, 0, 0);
+            spread();
+            if (kk == 3) st = stn;
         }
+        cur = nxt;
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // transfers past the end: none may land in what comes next
 
     // the rank-r term: the last split contracts over t = s x A^T, 64 ranks at a time; rank 64 e + 16 kk + 8 h + i
     if (p.r > 0 && s_hi == nsuper) {
@@ -677,14 +714,26 @@ __global__ __launch_bounds__(256) void mid_sum_kernel(const float4* __restrict__
     if (m < M && col < cols) *reinterpret_cast<uint2*>(out + (size_t)m * cols + col) = make_uint2(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w));
 }
 
+template <int TM, bool WIDE, bool ODD>
+hipError_t launch_mid_fwd(const MidParams& p, unsigned grid, hipStream_t st) {
+    constexpr int sh = FwdLds<TM, WIDE, ODD>::BYTES;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mid_fwd_kernel<TM, WIDE, ODD>), hipFuncAttributeMaxDynamicSharedMemorySize, sh);
+    if (attr != hipSuccess) return attr;
+    mid_fwd_kernel<TM, WIDE, ODD><<<dim3(grid), dim3(MID_THREADS), sh, st>>>(p);
+    return hipGetLastError();
+}
+
+template <int TM, bool WIDE>
+hipError_t launch_mid_fwd_any(const MidParams& p, hipStream_t st) {
+    const unsigned grid = (unsigned)(p.ntiles * p.splits);
+    return (p.G & 1) ? launch_mid_fwd<TM, WIDE, true>(p, grid, st) : launch_mid_fwd<TM, WIDE, false>(p, grid, st);
+}
+
 template <int TM, bool WIDE>
 hipError_t launch_mid_variant(const MidParams& p, int op, hipStream_t st) {
     const unsigned grid = (unsigned)(p.ntiles * p.splits);
     if (op == 0) {
-        constexpr int sh = 3 * TM * 4096 + (WIDE ? 4 * 4096 : 0);
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mid_fwd_kernel<TM, WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize, sh);
-        if (attr != hipSuccess) return attr;
-        mid_fwd_kernel<TM, WIDE><<<dim3(grid), dim3(MID_THREADS), sh, st>>>(p);
+        return launch_mid_fwd_any<TM, WIDE>(p, st);
     } else {
         using L = BwdLds<TM, WIDE>;
         constexpr int most = L::TAB0 + 2 * 64 * (WIDE ? 64 : 16);
@@ -700,32 +749,35 @@ hipError_t launch_mid_variant(const MidParams& p, int op, hipStream_t st) {
 }  // namespace
 
 // ---- which calls take these kernels, with which tile height and how many splits: the shortest estimated time.  The
-// estimate of a plan is a launch cost, the steps of a workgroup times the time of a step, and with splits the partial
-// tiles' way out and back.  A step takes `solo` us while its compute unit has few workgroups and `share` us per resident
-// workgroup once their instructions fill it; the figures are least-squares fits to 2493 timings (7 shapes from
-// 4096 x 1024 to 5120 x 13824, 24 to 2048 tokens, all heights, 1 to 32 splits; rms error 7 - 14 %, and the plan picked is
-// on average within 1 % of the best one measured).  The 256-column kernels' time, fitted in the same way, is compared
-// with it: they win once their tiles fill the chip, from about 1300 tokens of a 4096 x 4096 layer (forward) or 700 (input
-// gradient) on: 2048 tokens at 50/50 % of 1-/2-bit rows, forward 70 us against 75, input gradient 80 against 94.
+// estimate of a plan is a launch cost, the steps of a workgroup times the time of a step, a cost per round of workgroups,
+// and with splits the partial tiles' way out and back.  A step takes `solo` us while its compute unit has few workgroups
+// and `share` us per resident workgroup once their instructions fill it.  The figures are fits to timings of every height
+// with 1 to 24 splits (8 shapes from 1024 x 1024 to 5120 x 13824, an odd group count among them, 24 to 2048 tokens; calls
+// repeated on two sets of buffers, without a rank-r term).  Forward: 5040 timings, rms error 8 %, the plan picked within
+// 0.4 to 0.9 % of the best one measured on average.  Input gradient: 2493, 7 - 14 %, 1 %.  The 256-column kernels' time,
+// fitted in the same way, is compared with it: they win once their tiles fill the chip.  Forward, 4096 x 4096, 2048 tokens:
+// 50/50 % of 1-/2-bit rows 72 us against 73 here, 50/25/25 % of 1-/2-/4-bit rows 96 against 88.  Input gradient from about
+// 700 tokens on: 2048 tokens of 50/50 % 80 us against 94.
+constexpr int kHeights = 5;
+static const int kMidHeight[kHeights] = {1, 2, 3, 4, 6};              // TM: 32 tokens each; 6 in the forward only
 struct MidCost {
-    double solo[4], share[4];        // us per step (64 of the contraction) at TM = 1..4
-    double launch, split, per_byte;  // us per call; us more when split; us per byte of partial tiles
+    double solo[kHeights], share[kHeights];  // us per step (64 of the contraction)
+    double launch, round, split, per_byte;   // us per call; per round of workgroups; more when split; per byte of partial tiles
     double big_launch, big_step;     // the 256-column kernel: us per call, us per step of a 256 x 256 tile
 };
 static const MidCost kMidCost[2][3] = {
     // forward: 1- and 2-bit rows only; with 4-bit rows, up to kMidLutBooks codebooks; with 4-bit rows, more codebooks
-    {{{0.47, 0.47, 0.53, 0.77}, {0.24, 0.39, 0.45, 0.60}, 3.9, 6.7, 1.6e-7, 5.4, 1.32},
-     {{0.47, 0.64, 0.65, 0.80}, {0.35, 0.41, 0.54, 0.60}, 6.0, 5.2, 2.6e-7, 7.9, 1.89},
-     {{0.48, 0.63, 0.66, 0.81}, {0.36, 0.42, 0.55, 0.62}, 7.3, 3.8, 2.5e-7, 8.6, 1.87}},
+    {{{0.35, 0.34, 0.43, 0.52, 0.70}, {0.23, 0.29, 0.36, 0.43, 0.57}, 3.6, 0.3, 3.2, 3.5e-7, 5.0, 1.29},
+     {{0.46, 0.51, 0.61, 0.69, 0.81}, {0.35, 0.41, 0.47, 0.54, 0.74}, 5.6, 0.1, 2.9, 3.1e-7, 10.7, 1.70},
+     {{0.46, 0.53, 0.61, 0.68, 0.80}, {0.33, 0.42, 0.47, 0.57, 0.81}, 5.4, 0.3, 3.2, 2.9e-7, 11.6, 1.73}},
     // input gradient
-    {{{0.62, 0.73, 0.81, 0.95}, {0.47, 0.55, 0.58, 0.66}, 6.0, 4.7, 2.8e-7, 14.8, 1.28},
-     {{0.80, 1.01, 0.95, 1.01}, {0.51, 0.65, 0.68, 0.76}, 7.1, 4.3, 2.7e-7, 9.6, 2.03},
-     {{0.78, 0.84, 1.00, 1.00}, {0.64, 0.68, 0.70, 0.80}, 8.7, 2.8, 2.8e-7, 14.8, 2.50}}};
-// Workgroups per compute unit that the fit was made with, at TM = 1..4: part of the fitted model, not what a build holds.  By
-// registers and LDS the kernels hold, forward: 4, 3, 3, 3 without 4-bit rows and 4, 3, 2, 2 with them; input gradient: 3, 2, 2,
-// 2, and with 4-bit rows of more than kMidLutBooks codebooks 2, 2, 2, 1.  The fitted step times took up the difference.  (The
-// timings were of calls repeated on one set of buffers, without a rank-r term.)
-static const int kMidResident[2][4] = {{4, 3, 2, 2}, {3, 3, 2, 2}};
+    {{{0.62, 0.73, 0.81, 0.95}, {0.47, 0.55, 0.58, 0.66}, 6.0, 0.0, 4.7, 2.8e-7, 14.8, 1.28},
+     {{0.80, 1.01, 0.95, 1.01}, {0.51, 0.65, 0.68, 0.76}, 7.1, 0.0, 4.3, 2.7e-7, 9.6, 2.03},
+     {{0.78, 0.84, 1.00, 1.00}, {0.64, 0.68, 0.70, 0.80}, 8.7, 0.0, 2.8, 2.8e-7, 14.8, 2.50}}};
+// Workgroups per compute unit that the fits were made with.  Forward: what the kernels hold by registers and LDS, without
+// and with 4-bit rows.  Input gradient: part of the fitted model, not what a build holds (3, 2, 2, 2, and with 4-bit rows of
+// more than kMidLutBooks codebooks 2, 2, 2, 1); the fitted step times took up the difference.
+static const int kMidResident[2][2][kHeights] = {{{5, 4, 3, 2, 1}, {4, 3, 2, 2, 1}}, {{3, 3, 2, 2}, {3, 3, 2, 2}}};
 
 static std::atomic<int> g_mid_forced{0};                              // rows << 8 | splits
 void force_mid_plan(int rows, int splits) { g_mid_forced.store(rows << 8 | splits); }
@@ -737,7 +789,7 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
     const int tiles_c = (cols + kMidCols - 1) / kMidCols, cus = device_compute_units();
     const size_t cap = std::min(part_bytes, kMidPartMax);
     if (const int forced = g_mid_forced.load()) {
-        const int TM = (forced >> 8) / 32, per = (units + (forced & 255) - 1) / (forced & 255);
+        const int TM = op == 1 ? std::min((forced >> 8) / 32, 4) : (forced >> 8) / 32, per = (units + (forced & 255) - 1) / (forced & 255);
         best = MidPlan{TM, tiles_c, (M + 32 * TM - 1) / (32 * TM), (units + per - 1) / per, per};
         if (best.splits > 1 && mid_part_bytes(best) > cap) { best.splits = 1; best.per_split = units; }
         return best;
@@ -747,17 +799,18 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
     const MidCost& mc = kMidCost[op][cls];
     double best_t = 1e300;
     // with a table per row the input gradient's LDS holds one workgroup of four tile rows per compute unit, not two
-    const int tm_max = op == 1 && cls == 2 ? 3 : 4;
-    for (int TM = 1; TM <= tm_max && (TM == 1 || 32 * (TM - 1) < M); ++TM) {
+    const int heights = op == 0 ? 5 : cls == 2 ? 3 : 4;
+    for (int i = 0; i < heights && (i == 0 || 32 * kMidHeight[i - 1] < M); ++i) {
+        const int TM = kMidHeight[i];
         MidPlan pl{TM, tiles_c, (M + 32 * TM - 1) / (32 * TM), 0, 0};
-        const int res = kMidResident[op][TM - 1];
+        const int res = kMidResident[op][wide][i];
         for (int S = 1; S <= kMidMaxSplits && S <= units; S += S < 6 ? 1 : S < 12 ? 2 : 4) {
             pl.per_split = (units + S - 1) / S;
             pl.splits = (units + pl.per_split - 1) / pl.per_split;
             if (pl.splits > 1 && mid_part_bytes(pl) > cap) break;
             const long long wgs = (long long)pl.tiles_c * pl.tiles_m * pl.splits, n = (wgs + cus - 1) / cus;
-            auto step = [&](long long k) { return k ? std::max(mc.solo[TM - 1], (double)k * mc.share[TM - 1]) : 0.0; };
-            double t = mc.launch + (double)pl.per_split * unit * ((double)(n / res) * step(res) + step(n % res));
+            auto step = [&](long long k) { return k ? std::max(mc.solo[i], (double)k * mc.share[i]) : 0.0; };
+            double t = mc.launch + (double)pl.per_split * unit * ((double)(n / res) * step(res) + step(n % res)) + (double)((n + res - 1) / res) * mc.round;
             if (pl.splits > 1) t += mc.split + (double)mid_part_bytes(pl) * mc.per_byte;
             if (t < best_t * (1.0 - 1e-9)) { best_t = t; best = pl; }
         }
@@ -768,9 +821,9 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
         const BwdSplitPlan sp = gemm_bwd_split_plan(N, K, M);
         if (sp.splits > 1) big_t += 5.0 + (double)sp.splits * sp.tail * BM * BN * sizeof(float) * mc.per_byte;
     }
-    // (the two estimates' errors are about this large: without the margin 2048 tokens of a 4096 x 4096 layer came here
-    // and a training step on it took 1 % longer)
-    if (big_t <= 1.08 * best_t) best = MidPlan{0, 0, 0, 0, 0};
+    // (the two estimates' errors are about this large; input gradient: without the margin 2048 tokens of a 4096 x 4096
+    // layer came here and a training step on it took 1 % longer)
+    if (big_t <= (op == 0 ? 1.02 : 1.08) * best_t) best = MidPlan{0, 0, 0, 0, 0};
     return best;
 }
 
@@ -787,6 +840,7 @@ hipError_t launch_gemm_mid(const MidParams& p_in, int op, int TM, bool wide, hip
         if (TM == 2) e = wide ? launch_mid_variant<2, true>(p, op, st) : launch_mid_variant<2, false>(p, op, st);
         if (TM == 3) e = wide ? launch_mid_variant<3, true>(p, op, st) : launch_mid_variant<3, false>(p, op, st);
         if (TM == 4) e = wide ? launch_mid_variant<4, true>(p, op, st) : launch_mid_variant<4, false>(p, op, st);
+        if (TM == 6 && op == 0) e = wide ? launch_mid_fwd_any<6, true>(p, st) : launch_mid_fwd_any<6, false>(p, st);
         if (e != hipSuccess) return e;
         if (p.splits <= 1) continue;
         mid_sum_kernel<<<dim3((unsigned)((size_t)p.ntiles * TM * 4)), dim3(256), 0, st>>>(reinterpret_cast<const float4*>(p.part), p.splits, p.ntiles, p.tile0,

@@ -174,7 +174,7 @@ struct KernelTimer {
 };
 // partial tiles of a mid-token GEMM's splits: at most this much of a call's workspace; one output tile's, at most
 constexpr size_t kMidPartMax = (size_t)64 << 20;
-constexpr size_t kMidTileMax = (size_t)2 << 20;      // 32 splits of 128 x 128 outputs
+constexpr size_t kMidTileMax = (size_t)3 << 20;      // 32 splits of 192 x 128 outputs
 size_t linear_workspace_min(const lowra_layout& L, int op, int M, int r);     // less than this is refused
 size_t linear_workspace_bytes(const lowra_layout& L, int op, int M, int r);   // what lowra_workspace_bytes reports: room to split as well
 void plan_fwd_tiling(int N, int M, int units, int* rows_a, int* rows_b, int* cols_a);

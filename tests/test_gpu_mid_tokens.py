@@ -114,6 +114,41 @@ def test_every_variant(rows, K, splits, tables):
         assert rel_err(g, ref) <= REL_TOL and rel_err(g, bf16_host_f64(gemm)) <= ORDER_TOL
 
 
+# The forward's instantiations of the other parity of the number of groups (with an odd one the codes are staged in pieces
+# that start 8 bytes early, and the last superstep is not staged at all: three groups are that superstep alone), and its
+# tiles of 192 tokens.
+@pytest.mark.parametrize("rows,K", [(32, 1152), (64, 1216), (96, 1280), (128, 1088), (192, 1088), (192, 1152), (192, 1216), (192, 1280), (192, 192), (32, 192)])
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("tables", ["narrow", "shared"])
+def test_forward_staged_codes(rows, K, splits, tables):
+    if splits > (K // 64 + 3) // 4:
+        splits = 1
+    N, M, r = 328, rows + 17, 40
+    bf16_scales = splits == 3 and K in (1088, 1152)
+    print(f"[mid forward rows {rows} K {K} splits {splits} {tables}]", flush=True)
+    L = synth.make_custom(N, K, M, r, fractions=NARROW if tables == "narrow" else MIXED, seed=610 + rows)
+    D = DeviceLayer(L)
+    if bf16_scales:
+        D.layout.set_scale_dtype(torch.bfloat16)
+    packed, absmax = lowra.lowra_quantize(D.layout, D.W, D.thr)
+    rp, ra = orc.quantize(L.W, L.bits, L.cb, L.thresholds, **({"scale_dtype": "bf16"} if bf16_scales else {}))
+    ref = orc.linear_fwd(rp, ra, L.bits, L.cb, L.mappings, L.x, L.A, L.B, L.s)
+    call = lambda: lowra.lowra_linear_fwd(D.layout, packed, absmax, D.mp, D.x, D.A, D.B, L.s)
+    lowra.lowra_set_mid_tiling(rows, splits)
+    try:
+        assert lowra.lowra_plan_mid_tiling(lowra.OP_LINEAR_FWD, N, K, M, tables != "narrow", 3) == (rows, splits)
+        got = call()
+        lowra.lowra_set_mid_tiling()
+        lowra.lowra_set_linear_path(lowra.PATH_GEMM)
+        gemm = call()
+    finally:
+        lowra.lowra_set_mid_tiling()
+        lowra.lowra_set_linear_path(lowra.PATH_AUTO)
+    torch.cuda.synchronize()
+    g = bf16_host_f64(got)
+    assert rel_err(g, ref) <= REL_TOL and rel_err(g, bf16_host_f64(gemm)) <= ORDER_TOL
+
+
 @pytest.mark.parametrize("K", [320, 384, 448, 512])           # the last superstep of 256 features holds 1, 2, 3 or all 4 groups
 @pytest.mark.parametrize("fr", [NARROW, MIXED])
 def test_infinite_activations_at_the_end_of_a_row(K, fr):
