@@ -1,4 +1,5 @@
-"""Build the HIP library (csrc/*.hip -> liblowra_hip.so) for gfx950 with hipcc."""
+"""Build the HIP library (csrc/*.hip -> liblowra_hip.so) for gfx950 with hipcc, and the binding's native calls
+(csrc/call.cpp -> _lowra_call.so) with g++."""
 from __future__ import annotations
 
 import glob
@@ -9,6 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblowra_hip.so")
+CALL = os.path.join(HERE, "_lowra_call.so")
 OBJ = os.path.join(HERE, "_build")
 
 HIPCC_FLAGS = [
@@ -29,13 +31,30 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
+def _compile_call(verbose: bool) -> None:
+    import sysconfig
+
+    import torch
+
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I/opt/rocm/include", f"-I{t}/include",
+           f"-I{t}/include/torch/csrc/api/include", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "call.cpp"),
+           "-o", CALL, f"-L{t}/lib", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", f"-Wl,-rpath,{t}/lib"]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True, stderr=None if verbose else subprocess.PIPE)
+
+
 def build(verbose: bool = False, jobs: int | None = None) -> str:
     """Compile every csrc/*.hip (one hipcc process per file, a few at a time) and link the library."""
     os.makedirs(OBJ, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     jobs = jobs or min(8, os.cpu_count() or 1, len(srcs))
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        call = pool.submit(_compile_call, verbose)
         objs = list(pool.map(lambda s: _compile(s, verbose), srcs))
+        call.result()
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     if verbose:
         print(" ".join(cmd))

@@ -7,6 +7,7 @@ There is no CPU fallback: a missing library or a failing call raises.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 
 import numpy as np
@@ -14,7 +15,9 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblowra_hip.so")
+CALL_PATH = os.path.join(_HERE, "_lowra_call.so")
 _lib = None
+_call = None        # csrc/call.cpp: the calls made once per layer, natively for plain tensors; None from it: go on here
 
 OK, INVALID_ARG, UNSUPPORTED, MISALIGNED, WORKSPACE_TOO_SMALL, HIP_ERROR, OUT_OF_MEMORY = range(7)
 STATIC_SCRATCH_BYTES, STATIC_ARRAY_BYTES = 4 << 20, 36 << 20
@@ -50,10 +53,11 @@ class LowraError(RuntimeError):
 
 def lib() -> C.CDLL:
     """Load liblowra_hip.so (built by paper_2502_08141_amd.build); raises if it is not there."""
-    global _lib
+    global _lib, _call
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise FileNotFoundError(f"{LIB_PATH} is missing: run `python -m paper_2502_08141_amd.build` first")
+        for path in (LIB_PATH, CALL_PATH):
+            if not os.path.exists(path):
+                raise FileNotFoundError(f"{path} is missing: run `python -m paper_2502_08141_amd.build` first")
         L = C.CDLL(LIB_PATH)
         vp, u8p, f32p, u16p = C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p
         L.lowra_status_string.restype = C.c_char_p
@@ -106,7 +110,12 @@ def lib() -> C.CDLL:
         L.lowra_set_mid_tiling.argtypes = [C.c_int, C.c_int]
         L.lowra_plan_mid_tiling.argtypes = [C.c_int] * 6 + [C.POINTER(C.c_int)] * 2
         L.lowra_set_kernel_timer.argtypes = [vp, vp]
-        _lib = L
+        spec = importlib.util.spec_from_file_location("_lowra_call", CALL_PATH)
+        call = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(call)
+        call.init(*(C.cast(f, C.c_void_p).value for f in (L.lowra_linear_fwd, L.lowra_linear_bwd_input, L.lowra_linear_side_product,
+                                                          L.lowra_adapter_grads, L.lowra_adapter_grads_from_side, L.lowra_dequantize)))
+        _lib, _call = L, call
     return _lib
 
 
@@ -159,12 +168,18 @@ class Layout:
         self.handle = h
         self.packed_bytes = int(lib().lowra_packed_bytes(h))
         self.scale_dtype = torch.float32
+        self._describe()
+
+    def _describe(self):
+        """What the native calls read of a layout (csrc/call.cpp); None once it is closed."""
+        self.native = (self.handle.value, self.N, self.K, self.C, self.packed_bytes, self.scale_dtype is torch.bfloat16) if self.handle else None
 
     def set_scale_dtype(self, dtype):
         """torch.float32 (default) or torch.bfloat16: the type of the stored group scales (lowra_layout_set_scale_dtype)."""
         code = {torch.float32: SCALE_FP32, torch.bfloat16: SCALE_BF16}[dtype]
         _check(lib().lowra_layout_set_scale_dtype(self.handle, code), "lowra_layout_set_scale_dtype")
         self.scale_dtype = dtype
+        self._describe()
         return self
 
     def workspace_bytes(self, op: int, M: int, r: int) -> int:
@@ -173,7 +188,7 @@ class Layout:
     def close(self):
         if getattr(self, "handle", None):
             lib().lowra_layout_destroy(self.handle)
-            self.handle, self.packed_bytes = None, 0
+            self.handle, self.packed_bytes, self.native = None, 0, None
 
     def __del__(self):
         try:
@@ -236,8 +251,19 @@ def _state(layout, packed, absmax, mappings):
         raise ValueError("quantized state does not match the layout")
 
 
+def _native(result, where: str):
+    """What a native call returned, unless it is a status."""
+    if result.__class__ is int:
+        raise LowraError(result, where)
+    return result
+
+
 def lowra_dequantize(layout: Layout, packed, absmax, mappings, out_dtype=torch.bfloat16, out=None):
     """-> What [N,K] in bf16 (default) or fp32."""
+    if out is None and out_dtype is torch.bfloat16 and layout.__class__ is Layout:
+        res = _call.dequantize(layout.native, packed, absmax, mappings)
+        if res is not None:
+            return _native(res, "lowra_dequantize")
     _state(layout, packed, absmax, mappings)
     code = {torch.bfloat16: OUT_BF16, torch.float32: OUT_FP32}[out_dtype]
     if out is None:
@@ -281,6 +307,10 @@ def _linear(fn, name, op, layout, packed, absmax, mappings, act, act_cols, out_c
 
 def lowra_linear_fwd(layout: Layout, packed, absmax, mappings, x, A, B, s, y=None, workspace=None):
     """y [M,N] bf16 = x What^T + s (x A^T) B^T."""
+    if y is None and workspace is not None and layout.__class__ is Layout:
+        res = _call.linear(0, layout.native, packed, absmax, mappings, x, A, B, s, workspace)
+        if res is not None:
+            return _native(res, "lowra_linear_fwd")
     return _linear(lib().lowra_linear_fwd, "lowra_linear_fwd", OP_LINEAR_FWD, layout, packed, absmax, mappings,
                    x, layout.K, layout.N, A, B, s, y, workspace)
 
@@ -308,6 +338,10 @@ def lowra_linear_fwd_static(layout: Layout, packed, absmax, mappings, x, A, B, s
 
 def lowra_linear_bwd_input(layout: Layout, packed, absmax, mappings, dY, A, B, s, dX=None, workspace=None):
     """dX [M,K] bf16 = dY What + s (dY B) A."""
+    if dX is None and workspace is not None and layout.__class__ is Layout:
+        res = _call.linear(1, layout.native, packed, absmax, mappings, dY, A, B, s, workspace)
+        if res is not None:
+            return _native(res, "lowra_linear_bwd_input")
     return _linear(lib().lowra_linear_bwd_input, "lowra_linear_bwd_input", OP_LINEAR_BWD_INPUT, layout, packed,
                    absmax, mappings, dY, layout.N, layout.K, A, B, s, dX, workspace)
 
@@ -337,6 +371,10 @@ def lowra_average_thresholds(layout: Layout, thresholds):
 
 def lowra_adapter_grads(layout: Layout, x, dY, A, B, s, workspace=None):
     """x [M,K], dY [M,N], A [r,K], B [N,r] bf16 -> (dA fp32 [r,K], dB fp32 [N,r])."""
+    if workspace is not None and layout.__class__ is Layout:
+        res = _call.grads(layout.native, x, dY, A, B, s, workspace)
+        if res is not None:
+            return _native(res, "lowra_adapter_grads")
     for t, nme in ((x, "x"), (dY, "dY"), (A, "A"), (B, "B")):
         _dev(t, torch.bfloat16, nme)
     M, r = int(x.shape[0]), int(A.shape[0])
@@ -354,6 +392,10 @@ def lowra_adapter_grads(layout: Layout, x, dY, A, B, s, workspace=None):
 
 def lowra_linear_side_product(layout: Layout, op: int, M: int, r: int, workspace):
     """The rank-r intermediate a finished linear call left in `workspace`: a bf16 [M,64] view of it, or None."""
+    if layout.__class__ is Layout:
+        res = _call.side_product(layout.native, op, M, r, workspace)
+        if res is not None:
+            return res[0]
     _dev(workspace, torch.uint8, "workspace")
     p = lib().lowra_linear_side_product(layout.handle, int(op), int(M), int(r), _ptr(workspace))
     if not p:
@@ -364,6 +406,10 @@ def lowra_linear_side_product(layout: Layout, op: int, M: int, r: int, workspace
 
 def lowra_adapter_grads_from_side(layout: Layout, x, dY, r, st, su, workspace=None):
     """x [M,K], dY [M,N], st = s x A^T, su = s dY B (bf16 [M,64], from lowra_linear_side_product) -> (dA fp32 [r,K], dB fp32 [N,r])."""
+    if workspace is not None and layout.__class__ is Layout:
+        res = _call.grads_from_side(layout.native, x, dY, r, st, su, workspace)
+        if res is not None:
+            return _native(res, "lowra_adapter_grads_from_side")
     for t, nme in ((x, "x"), (dY, "dY"), (st, "st"), (su, "su")):
         _dev(t, torch.bfloat16, nme)
     M, r = int(x.shape[0]), int(r)
