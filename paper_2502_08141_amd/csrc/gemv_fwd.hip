@@ -24,9 +24,16 @@
 // fit, else one round ahead -- so that no operand load of x ever is a per-lane request and no
 // round needs a barrier.
 //
-// The rank-r term needs t = s x A^T first: a small kernel writes partial sums of t per 256-column
-// block; every workgroup of the main kernel adds them up (a few KB from L2) and multiplies
-// [B rows] [t]^T with one more MFMA per 32 ranks.
+// The rank-r term needs t = x A^T first: a small kernel writes partial sums of t per 256-column block, the
+// main kernel's threads share them out (a few KB from L2), and the wavefront that adds up the results multiplies [B rows] [t]^T
+// with one MFMA per 32 ranks.  For short contractions and low ranks the workgroups form t themselves, beside the products with
+// the codes (FUSE), and the small kernel falls away.
+//
+// A call on one matrix is a chain of round trips and of instructions that every wavefront of a workgroup issues (four per
+// SIMD: 16 cycles an instruction).  So the chain's head, the row record, is asked for first; the levels come by one
+// load of one wavefront; nothing waits for t before the end; and there are no more wavefronts than blocks.  One call, before -> after:
+// 256 x 512, 16 tokens 9.0 -> 5.0 us; 4096 x 1024, 4 tokens 9.0 -> 6.1; 11008 x 4096, 1 token 17.7 -> 15.2;
+// 4096 x 4096, 1 token 9.4 -> 9.2; three 4096 x 4096 matrices in one launch 19.8 -> 17.2.
 #include <algorithm>
 
 #include "gemm_common.h"
@@ -72,149 +79,221 @@ __device__ __forceinline__ void transpose4(uint32_t (&z)[4]) {
     z[0] = r01.x; z[1] = r01.y; z[2] = r23.x; z[3] = r23.y;
 }
 
-template <int W, int PER>
+constexpr int GV_LEV = 20;                   // floats per channel of the staged levels
+constexpr int GV_FIXED = 16 * GV_TABROW + 16 * GV_LEV * 4 + 64;      // LDS in front of t
+// Sums that a workgroup keeps per entry of t: one of every wavefront's block (FUSE), or of the blocks that its threads share
+// between them; and their bytes
+constexpr int gemv_t_parts(int W, int RT, bool fuse) { return RT == 0 ? 0 : fuse ? W : 16 * RT < W * 64 ? W * 64 / (16 * RT) : 1; }
+constexpr int gemv_t_bytes(int W, int RT, bool fuse) { return gemv_t_parts(W, RT, fuse) * 16 * RT * 4; }
+
+// FUSE: t comes from the workgroup itself (one round, r <= 16); else from the partial sums in p.tp
+template <int W, int PER, bool FUSE>
 __device__ __forceinline__ void gemv_body(const GemvParams& p, const int strip) {
+    static_assert(!FUSE || PER == 1, "a wavefront forms t beside the products of its only block");
     extern __shared__ __align__(16) uint8_t gv_smem[];
-    // LDS: pair tables [16 channels][GV_TABROW bytes] | channel numbers [16] | t (bf16 [16][RT]) |
+    // LDS: pair tables [16 channels][GV_TABROW bytes] | levels [16][GV_LEV] | channel numbers [16] | sums of t [tparts][16 tokens][RT] |
     //      [xbufs buffers][W pieces][rows2 KB] activations (rows2 = pairs of token rows; xbufs = all
     //      rounds when they fit, else 2).  After its last round a wavefront reuses the head of its
     //      piece of buffer 0 for its partial results [16 channels][16 tokens].
-    constexpr int TAB0 = 0, NL0 = TAB0 + 16 * GV_TABROW, T0 = NL0 + 64;
+    constexpr int LEV0 = 16 * GV_TABROW, NL0 = LEV0 + 16 * GV_LEV * 4, T0 = GV_FIXED;
+    const int nt = 16 * p.RT, X0 = T0 + p.tparts * nt * 4;
+    float* t_lds = reinterpret_cast<float*>(gv_smem + T0);
     const int rows2 = (min(p.M, 16) + 1) >> 1;
     const int XPIECE = rows2 * 1024, XBUF = W * XPIECE;
-    const int X0 = T0 + 16 * p.RT * 2;
-    int* n_lds = reinterpret_cast<int*>(gv_smem + NL0);
-    uint16_t* t_lds = reinterpret_cast<uint16_t*>(gv_smem + T0);
     const uint32_t smem_lds = (uint32_t)(uintptr_t)(lptr_t)gv_smem;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i = lane & 15, kg = lane >> 4;
-    const int row0 = strip * 16;
     const int nblk = (p.G + 3) >> 2;                               // blocks of 4 groups
-    const int per = (nblk + W - 1) / W;                            // rounds: blocks per wavefront (<= PER)
+    const int per = PER == 1 ? 1 : (nblk + W - 1) / W;             // rounds: blocks per wavefront (<= PER)
+    const int blk0 = wave * per;
+    const bool live = blk0 < nblk;                                 // (with few blocks some wavefronts have none)
+    const bf16x8_t zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
-    {
-        // One DMA instruction moves 2 token rows x 512 B of my block of round q into that round's
-        // buffer; chunk c of token row m lands at chunk c ^ (m & 15).
-        const int tok = lane >> 5;
-        const bool x_all = p.xbufs >= per;                         // every round has a buffer of its own: all asked for at once
-        auto xbuf_of = [&](int q) { return x_all ? q : (q & 1); };
-        auto issue_x = [&](int q) {
-            const int blk = min(wave * per + q, nblk - 1);
-            for (int pr = 0; pr < rows2; ++pr) {                    // uniform
-                const int m = min(2 * pr + tok, p.M - 1);
-                const int lc = (lane & 31) ^ ((2 * pr + tok) & 15);
-                const uint32_t col = min((uint32_t)blk * 256u + (uint32_t)lc * 8u, (uint32_t)p.K - 8u);   // past K: unused
-                dma16_s(p.x, ((uint32_t)m * (uint32_t)p.K + col) * 2u,
-                        smem_lds + X0 + xbuf_of(q) * XBUF + wave * XPIECE + pr * 1024);
-            }
-        };
-        if (x_all) {
-            for (int q = 0; q < per; ++q) issue_x(q);                // uniform
-        } else {
-            issue_x(0);
-        }
-
-        const SortedRow rec = p.sorted_rows[row0 + i];
-        const int bits = (int)(rec.bits_cb & 0xffu);
-        const bool row_ok = rec.n >= 0;                            // padding rows are recorded as 1-bit rows
-        const int nc = row_ok ? rec.n : 0;
-        const uint8_t* rowp = p.packed + rec.offset;
-        const uint8_t* pend16 = p.packed + p.packed_bytes - 16;
-        const float* mrow = p.mappings + (size_t)(rec.bits_cb >> 8) * kTableStride;
-        const bool two = bits == 2, four = bits == 4;
-
-        // levels for my entries of my channel's pair table: entry e = two codes (low, high) -> two bf16
-        constexpr int NE = 256 / (4 * W);
-        const int nent = 1 << (2 * bits);
-        const uint32_t cmask = (1u << bits) - 1u;
-        float tlo[NE], thi[NE];
+    // What a strip waits for is a chain: row record -> codes, scales and levels -> pair tables -> products.  So the record is
+    // asked for first, and A, which takes longest, behind it.  Loads come back in order and the compiler does not count the
+    // transfers, so activations and sums of t follow the codes where one strip has the unit to itself (one round: 9.6 -> 9.2 us
+    // for 4096 x 4096); with several rounds they fill the wait for the record (11008 x 4096: 16.4 -> 15.2).
+    const SortedRow rec = p.sorted_rows[strip * 16 + i];
+    bf16x8_t af[8];                                                // FUSE: A[i][32 j + 8 kg ..] of my block
+    constexpr int TU = 4 * PER < 16 ? 4 * PER : 16;                // else: sums of the blocks tpart, tpart + tparts, .. of entry `to`
+    float tsum[TU];
+    int tpart = 0, to = threadIdx.x;
+    if (FUSE) {
+        if (live) {
+            const uint16_t* ar = p.A + (size_t)min(i, p.r - 1) * p.K + blk0 * 256 + 8 * kg;
 #pragma unroll
-        for (int j = 0; j < NE; ++j) {
-            const int e = (int)(threadIdx.x >> 4) + 4 * W * j;
-            const bool e_ok = row_ok && e < nent;
-            tlo[j] = e_ok ? mrow[e & cmask] : 0.0f;
-            thi[j] = e_ok ? mrow[e >> bits] : 0.0f;
+            for (int j = 0; j < 8; ++j) af[j] = blk0 * 256 + 32 * j < p.K ? *reinterpret_cast<const bf16x8_t*>(ar + 32 * j) : zero8;
         }
+    }
 
-        // every load of codes and scales of all my rounds, back to back
-        const bool wave_has4 = __builtin_amdgcn_ballot_w64(four) != 0;
-        const bool vec_sc = (p.G & 3) == 0;                          // a block's four scales are one aligned 16-byte load
-        uint4 ca[PER], cb[PER];
-        float4 sc[PER];
-        bool hi8[PER];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int blk = wave * per + q;
-            const int g = min(4 * blk + kg, p.G - 1);              // clamped: groups past the row get a zero scale below
-            const uint8_t* a0 = rowp + (size_t)g * 8 * bits;
-            const uint8_t* a0c = a0 < pend16 ? a0 : pend16;         // a 1-bit group is 8 B: its 16-byte load may be pulled back
-            hi8[q] = a0 != a0c;                                     // ... then the group sits in the upper 8 bytes
-            const uint8_t* a1 = four ? a0 + 16 : a0c;
-            if (q < per) {                                          // uniform
-                ca[q] = *reinterpret_cast<const uint4*>(a0c);
-                cb[q] = wave_has4 ? *reinterpret_cast<const uint4*>(a1) : zero4();
-                const float* ar = p.absmax + (size_t)nc * p.G;
-                if (vec_sc) {
-                    sc[q] = *reinterpret_cast<const float4*>(ar + min(4 * blk, p.G - 4));
-                } else {
-                    sc[q].x = ar[min(4 * blk, p.G - 1)]; sc[q].y = ar[min(4 * blk + 1, p.G - 1)];
-                    sc[q].z = ar[min(4 * blk + 2, p.G - 1)]; sc[q].w = ar[min(4 * blk + 3, p.G - 1)];
-                }
+    // One DMA instruction moves 2 token rows x 512 B of my block of round q into that round's
+    // buffer; chunk c of token row m lands at chunk c ^ (m & 15).
+    const int tok = lane >> 5;
+    const bool x_all = PER == 1 || p.xbufs >= per;                 // every round has a buffer of its own: all asked for at once
+    auto xbuf_of = [&](int q) { return x_all ? q : (q & 1); };
+    auto issue_x = [&](int q) {
+        const int blk = min(blk0 + q, nblk - 1);
+        for (int pr = 0; pr < rows2; ++pr) {                        // uniform
+            const int m = 2 * pr + tok;
+            const uint32_t col = min((uint32_t)blk * 256u + (uint32_t)(((lane & 31) ^ (m & 15)) * 8), (uint32_t)p.K - 8u);   // past K: unused
+            dma16_s(p.x, ((uint32_t)min(m, p.M - 1) * (uint32_t)p.K + col) * 2u, smem_lds + X0 + xbuf_of(q) * XBUF + wave * XPIECE + pr * 1024);
+        }
+    };
+    auto ask_inputs = [&]() __attribute__((always_inline)) {       // activations, sums of t
+        if (live) {
+            if (x_all) {
+                for (int q = 0; q < per; ++q) issue_x(q);            // uniform
             } else {
-                ca[q] = cb[q] = zero4(); sc[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                issue_x(0);
             }
         }
-
-        // my fragment of B for the first 32 ranks, asked for with everything else; my channel number for the final store
-        bf16x8_t bfr0 = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (wave == 0 && p.RT > 0 && (p.r & 7) == 0 && row_ok && kg * 8 < p.r)
-            bfr0 = *reinterpret_cast<const bf16x8_t*>(p.B + (size_t)nc * p.r + kg * 8);
-        if (wave == 0 && kg == 0) n_lds[i] = rec.n;
-
-        // my channel's pair table (unscaled levels; the group scale multiplies the group's dot product)
-        uint8_t* tabp = gv_smem + TAB0 + i * GV_TABROW;
+        if (!FUSE && p.RT > 0) {
+            for (int w = wave * 64; w >= nt; w -= nt) ++tpart;     // uniform: nt is a multiple of 256
+            to -= tpart * nt;
 #pragma unroll
-        for (int j = 0; j < NE; ++j) {
-            const int e = (int)(threadIdx.x >> 4) + 4 * W * j;
-            if (row_ok && e < nent) *reinterpret_cast<uint32_t*>(tabp + 4 * e) = pack_bf16x2(tlo[j], thi[j]);
-        }
-
-        // ---- t = s * sum of the partials (bf16, [16][RT]), by all wavefronts
-        if (p.RT > 0) {
-            for (int o = threadIdx.x; o < 16 * p.RT; o += W * 64) {
-                float v = 0.0f;
-                for (int b0 = 0; b0 < nblk; b0 += 16) {             // 16 loads in flight, not one after the other
-                    float tmp[16];
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) tmp[u] = p.tp[(size_t)min(b0 + u, nblk - 1) * 16 * p.RT + o];
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) v += b0 + u < nblk ? tmp[u] : 0.0f;
-                }
-                t_lds[o] = (uint16_t)(pack_bf16x2(v * p.s, 0.0f) & 0xffffu);
+            for (int u = 0; u < TU; ++u) {
+                const int b = tpart + u * p.tparts;
+                tsum[u] = tpart < p.tparts && b < nblk ? p.tp[(size_t)b * nt + to] : 0.0f;     // uniform condition
             }
         }
-        __syncthreads();                                           // t, pair tables
+    };
+    if (PER > 1) ask_inputs();
+    const int bits = (int)(rec.bits_cb & 0xffu);
+    const bool row_ok = rec.n >= 0;                                // padding rows are recorded as 1-bit rows
+    const int nc = row_ok ? rec.n : 0;
+    const bool two = bits == 2, four = bits == 4;
+    // The levels of the strip's channels, 64 bytes each, by one wavefront's single load (gathered entry by entry for the pair
+    // tables they were 128 wavefront instructions of the unit's one address pipe).
+    const float* mrow = p.mappings + (size_t)(rec.bits_cb >> 8) * kTableStride;
+    float4 lv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (wave == 0) lv = *reinterpret_cast<const float4*>(mrow + 4 * kg);
 
+    // every load of codes and scales of all my rounds, back to back
+    const bool wave_has4 = __builtin_amdgcn_ballot_w64(four) != 0;
+    const bool vec_sc = (p.G & 3) == 0;                            // a block's four scales are one aligned 16-byte load
+    uint4 ca[PER], cb[PER];
+    float4 sc[PER];
+    bool hi8[PER];
+    const uint8_t* rowp = p.packed + rec.offset;
+    const uint8_t* pend16 = p.packed + p.packed_bytes - 16;
+    const float* ar = p.absmax + (size_t)nc * p.G;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int blk = blk0 + q;
+        ca[q] = cb[q] = zero4(); sc[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f); hi8[q] = false;
+        if (q < per && blk < nblk) {                                // uniform
+            const int g = min(4 * blk + kg, p.G - 1);              // clamped: groups past the row get a zero scale below
+            const uint8_t* a0 = rowp + (size_t)(g * 8 * bits);
+            const uint8_t* a0c = a0 < pend16 ? a0 : pend16;         // a 1-bit group is 8 B: its 16-byte load may be pulled back
+            hi8[q] = a0 != a0c && bits == 1;                        // ... then the group sits in the upper 8 bytes
+            ca[q] = *reinterpret_cast<const uint4*>(a0c);
+            if (wave_has4) cb[q] = *reinterpret_cast<const uint4*>(four ? a0 + 16 : a0c);
+            if (vec_sc) {
+                sc[q] = *reinterpret_cast<const float4*>(ar + 4 * blk);
+            } else {
+                sc[q].x = ar[4 * blk]; sc[q].y = ar[min(4 * blk + 1, p.G - 1)];
+                sc[q].z = ar[min(4 * blk + 2, p.G - 1)]; sc[q].w = ar[min(4 * blk + 3, p.G - 1)];
+            }
+        }
+    }
+    if (PER == 1) ask_inputs();
+    // my fragments of B for the first 64 ranks, asked for with everything else
+    bf16x8_t bfr0 = zero8, bfr1 = zero8;
+    if (wave == 0 && p.RT > 0 && (p.r & 7) == 0) {
+        if (row_ok && kg * 8 < p.r) bfr0 = *reinterpret_cast<const bf16x8_t*>(p.B + (size_t)nc * p.r + kg * 8);
+        if (!FUSE && row_ok && 32 + kg * 8 < p.r) bfr1 = *reinterpret_cast<const bf16x8_t*>(p.B + (size_t)nc * p.r + 32 + kg * 8);
+    }
+
+    float* lev = reinterpret_cast<float*>(gv_smem + LEV0) + i * GV_LEV;
+    if (wave == 0) {
+        *reinterpret_cast<float4*>(lev + 4 * kg) = lv;
+        if (kg == 0) reinterpret_cast<int*>(gv_smem + NL0)[i] = rec.n;
+    }
+    __syncthreads();                                               // the levels
+    // my channel's pair table, entry e = two codes (low, high) -> two bf16 (unscaled levels; the group scale multiplies the
+    // group's dot product)
+    uint8_t* tabp = gv_smem + i * GV_TABROW;
+    const int nent = 1 << (2 * bits);
+    for (int e = (int)(threadIdx.x >> 4); e < nent; e += 4 * W)
+        *reinterpret_cast<uint32_t*>(tabp + 4 * e) = pack_bf16x2(lev[e & ((1 << bits) - 1)], lev[e >> bits]);
+    if (!FUSE && p.RT > 0 && tpart < p.tparts) {
+        for (int o = to; o < nt; o += W * 64) {                    // (more entries than threads: one part, the later entries from memory)
+            float v = 0.0f;
+            if (o == to) {
+#pragma unroll
+                for (int u = 0; u < TU; ++u) v += tsum[u];
+            }
+            for (int b = o == to ? tpart + TU * p.tparts : tpart; b < nblk; b += 4 * p.tparts) {         // four loads in flight
+                float w[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) w[u] = p.tp[(size_t)min(b + u * p.tparts, nblk - 1) * nt + o];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v += b + u * p.tparts < nblk ? w[u] : 0.0f;
+            }
+            t_lds[tpart * nt + o] = v;
+        }
+    }
+    __syncthreads();                                               // pair tables
+
+    // + [s t as bf16] x [B rows], t the sum of `parts` of them
+    auto fragment_b = [&](int j0) __attribute__((always_inline)) -> bf16x8_t {
+        bf16x8_t f = zero8;
+        if (row_ok && j0 < p.r) {
+            const uint16_t* br = p.B + (size_t)nc * p.r + j0;
+            if ((p.r & 7) == 0) {
+                f = *reinterpret_cast<const bf16x8_t*>(br);
+            } else {
+                uint32_t tmp[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) tmp[e] = j0 + e < p.r ? (uint32_t)br[e] : 0u;
+                f = __builtin_bit_cast(bf16x8_t, make_uint4(tmp[0] | (tmp[1] << 16), tmp[2] | (tmp[3] << 16), tmp[4] | (tmp[5] << 16), tmp[6] | (tmp[7] << 16)));
+            }
+        }
+        return f;
+    };
+    auto fragment_t = [&](int j0, int parts) __attribute__((always_inline)) -> bf16x8_t {
+        float t[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        if (j0 < p.RT) {
+            for (int q = 0; q < parts; ++q) {
+                const float* src = t_lds + q * nt + i * p.RT + j0;
+                const float4 a = *reinterpret_cast<const float4*>(src), b = *reinterpret_cast<const float4*>(src + 4);
+                t[0] += a.x; t[1] += a.y; t[2] += a.z; t[3] += a.w; t[4] += b.x; t[5] += b.y; t[6] += b.z; t[7] += b.w;
+            }
+            if (FUSE) {                                            // (a rank past r is the last one again)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) t[e] = j0 + e < p.r ? t[e] : 0.0f;
+            }
+        }
+        return __builtin_bit_cast(bf16x8_t, make_uint4(pack_bf16x2(t[0] * p.s, t[1] * p.s), pack_bf16x2(t[2] * p.s, t[3] * p.s),
+                                                       pack_bf16x2(t[4] * p.s, t[5] * p.s), pack_bf16x2(t[6] * p.s, t[7] * p.s)));
+    };
+    auto rank_r = [&](floatx4_t acc, int parts) __attribute__((always_inline)) -> floatx4_t {
+        if (p.RT == 0) return acc;                                 // uniform, as the rest
+        const bool at_hand = (p.r & 7) == 0;
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fragment_t(kg * 8, parts), at_hand ? bfr0 : fragment_b(kg * 8), acc, 0, 0, 0);
+        if (FUSE || p.RT <= 32) return acc;
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fragment_t(32 + kg * 8, parts), at_hand ? bfr1 : fragment_b(32 + kg * 8), acc, 0, 0, 0);
+        for (int e0 = 64; e0 < p.RT; e0 += 32) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fragment_t(e0 + kg * 8, parts), fragment_b(e0 + kg * 8), acc, 0, 0, 0);
+        return acc;
+    };
+    if (live) {
         const uint32_t fw2 = 2u * (uint32_t)bits;                  // bits of one table index (two codes)
-        floatx4_t tot = {0.0f, 0.0f, 0.0f, 0.0f};
-        const bf16x8_t zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+        floatx4_t tot = {0.0f, 0.0f, 0.0f, 0.0f}, tf = tot;
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
-            if (q < per) {                                          // uniform
+            const int blk = blk0 + q;
+            if (q < per && blk < nblk) {                            // uniform
                 // my block of this round has landed (so has everything else I asked for); ask for the next
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 if (!x_all && q + 1 < per) issue_x(q + 1);
-                const int blk = wave * per + q;
-                const bool b_ok = row_ok && blk < nblk;
-                const float a4[4] = {(b_ok && 4 * blk < p.G) ? sc[q].x : 0.0f, (b_ok && 4 * blk + 1 < p.G) ? sc[q].y : 0.0f,
-                                     (b_ok && 4 * blk + 2 < p.G) ? sc[q].z : 0.0f, (b_ok && 4 * blk + 3 < p.G) ? sc[q].w : 0.0f};
+                const float a4[4] = {row_ok ? sc[q].x : 0.0f, row_ok && 4 * blk + 1 < p.G ? sc[q].y : 0.0f,
+                                     row_ok && 4 * blk + 2 < p.G ? sc[q].z : 0.0f, row_ok && 4 * blk + 3 < p.G ? sc[q].w : 0.0f};
                 // I loaded group kg of my channel; MFMA step (g, h) wants from me the 8 codes
                 // k = 64 g + 32 h + 8 kg .. + 8 of group g: piece kg of each half of the group goes
                 // to lane kg of the lane that loaded it
-                const bool up = hi8[q] && !two && !four;
-                const uint32_t c0 = up ? ca[q].z : ca[q].x, c1 = up ? ca[q].w : ca[q].y;     // a 1-bit row uses 8 of its 16 bytes
+                const uint32_t c0 = hi8[q] ? ca[q].z : ca[q].x, c1 = hi8[q] ? ca[q].w : ca[q].y;     // a 1-bit row uses 8 of its 16 bytes
                 const uint32_t D[8] = {ca[q].x, ca[q].y, ca[q].z, ca[q].w, cb[q].x, cb[q].y, cb[q].z, cb[q].w};
                 uint32_t za[4], zb[4];
 #pragma unroll
@@ -241,73 +320,70 @@ __device__ __forceinline__ void gemv_body(const GemvParams& p, const int strip) 
                             d[pp] = *reinterpret_cast<const uint32_t*>(tabp + 4u * __builtin_amdgcn_ubfe(cs, pp * fw2, fw2));
                         const bf16x8_t xf = *reinterpret_cast<const bf16x8_t*>(xp + (((8 * g + 4 * h + kg) ^ i) << 4));
                         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, __builtin_bit_cast(bf16x8_t, make_uint4(d[0], d[1], d[2], d[3])), acc, 0, 0, 0);
+                        if (FUSE) tf = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[2 * g + h], xf, tf, 0, 0, 0);      // rank 4 kg + v of token i
                     }
 #pragma unroll
                     for (int v = 0; v < 4; ++v) tot[v] += a4[g] * acc[v];
                 }
             }
         }
-        // ---- rank-r term (wavefront 0): [t] x [B rows]
-        if (wave == 0 && p.RT > 0) {
-            for (int e0 = 0; e0 < p.RT; e0 += 32) {
-                const int j0 = e0 + kg * 8;
-                bf16x8_t tf = zero8, bfr = zero8;
-                if (j0 < p.RT) tf = *reinterpret_cast<const bf16x8_t*>(t_lds + i * p.RT + j0);
-                if (row_ok && j0 < p.r) {
-                    const uint16_t* br = p.B + (size_t)nc * p.r + j0;
-                    if ((p.r & 7) == 0) {
-                        bfr = e0 == 0 ? bfr0 : *reinterpret_cast<const bf16x8_t*>(br);
-                    } else {
-                        uint32_t tmp[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) tmp[e] = j0 + e < p.r ? (uint32_t)br[e] : 0u;
-                        bfr = __builtin_bit_cast(bf16x8_t, make_uint4(tmp[0] | (tmp[1] << 16), tmp[2] | (tmp[3] << 16),
-                                                                         tmp[4] | (tmp[5] << 16), tmp[6] | (tmp[7] << 16)));
-                    }
-                }
-                tot = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf, bfr, tot, 0, 0, 0);
-            }
-        }
+        if (!FUSE && wave == 0) tot = rank_r(tot, p.tparts);
         // my piece of buffer 0 is dead (all my rounds are done, all transfers have landed)
         float* part = reinterpret_cast<float*>(gv_smem + X0 + wave * XPIECE);
         *reinterpret_cast<float4*>(part + i * 16 + 4 * kg) = make_float4(tot[0], tot[1], tot[2], tot[3]);   // [channel][token]
+        if (FUSE) *reinterpret_cast<float4*>(t_lds + wave * 256 + i * 16 + 4 * kg) = make_float4(tf[0], tf[1], tf[2], tf[3]);     // [token][rank]
     }
     __syncthreads();
 
-    // reduce over wavefronts, store bf16
+    // the sum over the wavefronts, in their order, stored as bf16
+    const int waves = PER == 1 ? min(W, nblk) : (nblk + per - 1) / per;
+    if (FUSE) {                                                    // by one wavefront, which has the rank-r term to add
+        if (wave != 0) return;
+        floatx4_t tot = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int w = 0; w < waves; ++w) {
+            const float4 v = *reinterpret_cast<const float4*>(gv_smem + X0 + w * XPIECE + (i * 16 + 4 * kg) * 4);
+            tot[0] += v.x; tot[1] += v.y; tot[2] += v.z; tot[3] += v.w;
+        }
+        tot = rank_r(tot, waves);
+        if (row_ok) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (4 * kg + v < p.M) p.y[(size_t)(4 * kg + v) * p.N + nc] = (uint16_t)(pack_bf16x2(tot[v], 0.0f) & 0xffffu);
+        }
+        return;
+    }
     for (int o = threadIdx.x; o < 256; o += W * 64) {
-        const int rl = o >> 4, m = o & 15;
-        const int n = n_lds[rl];
+        const int m = o & 15, n = reinterpret_cast<const int*>(gv_smem + NL0)[o >> 4];
         if (m < p.M && n >= 0) {
             float v = 0.0f;
-#pragma unroll
-            for (int w = 0; w < W; ++w) v += reinterpret_cast<const float*>(gv_smem + X0 + w * XPIECE)[o];
+            for (int w = 0; w < waves; ++w) v += reinterpret_cast<const float*>(gv_smem + X0 + w * XPIECE)[o];
             p.y[(size_t)m * p.N + n] = (uint16_t)(pack_bf16x2(v, 0.0f) & 0xffffu);
         }
     }
 }
 
-template <int W, int PER>
+template <int W, int PER, bool FUSE>
 __global__ __launch_bounds__(W * 64) void gemv_fwd_kernel(GemvParams p) {
-    gemv_body<W, PER>(p, blockIdx.x);
+    gemv_body<W, PER, FUSE>(p, blockIdx.x);
 }
 // every matrix of a batch that takes this instantiation, in one launch: workgroup = one 16-channel strip of one matrix
-template <int W, int PER>
+template <int W, int PER, bool FUSE>
 __global__ __launch_bounds__(W * 64) void gemv_fwd_batch_kernel(const GemvParams* __restrict__ descs, const int* __restrict__ strip0,
                                                                 const int* __restrict__ owner) {
     const int m = owner[blockIdx.x];
     const GemvParams p = descs[m];
-    gemv_body<W, PER>(p, (int)blockIdx.x - strip0[m]);
+    gemv_body<W, PER, FUSE>(p, (int)blockIdx.x - strip0[m]);
 }
 
 // LDS bytes of an instantiation for this matrix (0: does not fit); sets the number of activation buffers
-template <int W, int PER>
+template <int W, int PER, bool FUSE>
 static size_t gemv_lds(GemvParams& p) {
-    constexpr int fixed = 16 * GV_TABROW + 64;
+    constexpr int fixed = GV_FIXED;
     constexpr int kMaxLds = 160 * 1024;
     const int rows2 = (std::min(p.M, 16) + 1) / 2;
     const int nblk = (p.G + 3) / 4, per = (nblk + W - 1) / W;
-    const size_t base = (size_t)fixed + (size_t)16 * p.RT * 2, xbuf = (size_t)W * rows2 * 1024;
+    p.tparts = gemv_t_parts(W, p.RT, FUSE);
+    const size_t base = (size_t)fixed + gemv_t_bytes(W, p.RT, FUSE), xbuf = (size_t)W * rows2 * 1024;
     p.xbufs = base + per * xbuf <= (size_t)kMaxLds ? per : 2;     // a buffer per round when they fit
     // ... but not at the price of the second workgroup on a compute unit (5120 features, 6 tokens, three matrices of 5120
     // channels: 34 -> 25 us)
@@ -315,22 +391,22 @@ static size_t gemv_lds(GemvParams& p) {
     const size_t sh = base + (size_t)p.xbufs * xbuf;
     return sh > (size_t)kMaxLds ? 0 : sh;
 }
-template <int W, int PER>
+template <int W, int PER, bool FUSE>
 static hipError_t gemv_attr() {
-    static hipError_t a0 = hipFuncSetAttribute(reinterpret_cast<const void*>(gemv_fwd_kernel<W, PER>),
+    static hipError_t a0 = hipFuncSetAttribute(reinterpret_cast<const void*>(gemv_fwd_kernel<W, PER, FUSE>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    static hipError_t a1 = hipFuncSetAttribute(reinterpret_cast<const void*>(gemv_fwd_batch_kernel<W, PER>),
+    static hipError_t a1 = hipFuncSetAttribute(reinterpret_cast<const void*>(gemv_fwd_batch_kernel<W, PER, FUSE>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     return a0 != hipSuccess ? a0 : a1;
 }
-template <int W, int PER>
+template <int W, int PER, bool FUSE>
 static hipError_t launch_one(GemvParams p, hipStream_t st) {
-    const hipError_t attr = gemv_attr<W, PER>();
+    const hipError_t attr = gemv_attr<W, PER, FUSE>();
     if (attr != hipSuccess) return attr;
-    const size_t sh = gemv_lds<W, PER>(p);
+    const size_t sh = gemv_lds<W, PER, FUSE>(p);
     if (sh == 0) return hipErrorInvalidValue;
     const dim3 grid((p.N + 15) / 16);
-    gemv_fwd_kernel<W, PER><<<grid, dim3(W * 64), sh, st>>>(p);
+    gemv_fwd_kernel<W, PER, FUSE><<<grid, dim3(W * 64), sh, st>>>(p);
     return hipGetLastError();
 }
 
@@ -352,58 +428,76 @@ bool gemv_fwd_fits(int K) { return (K + 255) / 256 <= 8 * GV_MAXR; }
 // whenever their activation buffers fit; with more strips than compute units two 8-wavefront
 // workgroups per unit (when their buffers fit twice) overlap one strip's loads with the other's
 // arithmetic.
-struct GemvChoice { int W, PER; };
-static GemvChoice gemv_choose(const GemvParams& p, bool many_strips = false) {
+// Short contractions take as many wavefronts as they have blocks: every wavefront issues the instructions in front of the
+// first product, so idle ones cost time.
+struct GemvChoice { int W, PER, fuse; };
+static GemvChoice gemv_choose_waves(const GemvParams& p, bool many_strips) {
     const int nblk = (p.G + 3) / 4;
     const int rows2 = (std::min(p.M, 16) + 1) / 2;
-    const bool fit16 = (size_t)16 * GV_TABROW + 64 + (size_t)16 * p.RT * 2 +
+    const bool fit16 = (size_t)GV_FIXED + gemv_t_bytes(16, p.RT, p.RT == 16) +
                        (size_t)std::min((nblk + 15) / 16, 2) * 16 * rows2 * 1024 <= (size_t)160 * 1024;
     const int nstrips = (p.N + 15) / 16;
-    const size_t lds8 = (size_t)16 * GV_TABROW + 64 + (size_t)16 * p.RT * 2 + (size_t)std::min((nblk + 7) / 8, 2) * 8 * rows2 * 1024;
+    const size_t lds8 = (size_t)GV_FIXED + gemv_t_bytes(8, p.RT, p.RT == 16) + (size_t)std::min((nblk + 7) / 8, 2) * 8 * rows2 * 1024;
     // (up to 24 blocks: 5120 features, three rounds; one token, three matrices of 5120 channels 34 -> 24 us, two of 13824
     // 59 -> 38 us against one 16-wavefront workgroup per unit)
     const bool pair8 = (many_strips || nstrips > compute_units_cached()) && 2 * lds8 <= (size_t)150 * 1024 && nblk <= 24;
     if (fit16 && !pair8) {
-        if (nblk <= 16) return {16, 1};     // K <= 4096
-        if (nblk <= 32) return {16, 2};
-        if (nblk <= 48) return {16, 3};     // K = 11008
-        if (nblk <= 64) return {16, 4};
+        if (nblk <= 4) return {4, 1, 0};
+        if (nblk <= 8) return {8, 1, 0};
+        if (nblk <= 16) return {16, 1, 0};  // K <= 4096
+        if (nblk <= 32) return {16, 2, 0};
+        if (nblk <= 48) return {16, 3, 0};  // K = 11008
+        if (nblk <= 64) return {16, 4, 0};
     }
-    if (nblk <= 4) return {4, 1};
-    if (nblk <= 8) return {4, 2};
-    if (nblk <= 16) return {8, 2};          // K <= 4096
-    if (nblk <= 32) return {8, 4};
-    if (nblk <= 48) return {8, 6};          // K = 11008
-    return {8, 8};
+    if (nblk <= 4) return {4, 1, 0};
+    if (nblk <= 8) return {4, 2, 0};
+    if (nblk <= 16) return {8, 2, 0};       // K <= 4096
+    if (nblk <= 32) return {8, 4, 0};
+    if (nblk <= 48) return {8, 6, 0};       // K = 11008
+    return {8, 8, 0};
 }
-// calls f.template operator()<W, PER>() for the chosen instantiation
+// Whether the workgroups form t = x A^T themselves.  It saves the partial sums' launch (2.7 us on the GPU, 2.6 us on the host) and
+// costs every workgroup A: a compute unit gathers about 30 GB/s, 64 KB in 2 us, and pays that for each round of strips.
+// `strips`: of the launch.
+static bool gemv_fuses(const GemvParams& p, const GemvChoice& c, int strips) {
+    const long long rounds = (strips + compute_units_cached() - 1) / compute_units_cached();
+    return c.PER == 1 && p.r > 0 && p.r <= 16 && rounds * p.r * p.K <= 32768;
+}
+static GemvChoice gemv_choose(const GemvParams& p, bool many_strips, int strips) {
+    GemvChoice c = gemv_choose_waves(p, many_strips);
+    c.fuse = gemv_fuses(p, c, strips);
+    return c;
+}
+// calls f.template operator()<W, PER, FUSE>() for the chosen instantiation
 template <typename F>
 static hipError_t gemv_dispatch(GemvChoice c, F&& f) {
-    if (c.W == 16 && c.PER == 1) return f.template operator()<16, 1>();
-    if (c.W == 16 && c.PER == 2) return f.template operator()<16, 2>();
-    if (c.W == 16 && c.PER == 3) return f.template operator()<16, 3>();
-    if (c.W == 16 && c.PER == 4) return f.template operator()<16, 4>();
-    if (c.W == 4 && c.PER == 1) return f.template operator()<4, 1>();
-    if (c.W == 4 && c.PER == 2) return f.template operator()<4, 2>();
-    if (c.W == 8 && c.PER == 2) return f.template operator()<8, 2>();
-    if (c.W == 8 && c.PER == 4) return f.template operator()<8, 4>();
-    if (c.W == 8 && c.PER == 6) return f.template operator()<8, 6>();
-    if (c.W == 8 && c.PER == 8) return f.template operator()<8, 8>();
+    if (c.W == 4 && c.PER == 1) return c.fuse ? f.template operator()<4, 1, true>() : f.template operator()<4, 1, false>();
+    if (c.W == 8 && c.PER == 1) return c.fuse ? f.template operator()<8, 1, true>() : f.template operator()<8, 1, false>();
+    if (c.W == 16 && c.PER == 1) return c.fuse ? f.template operator()<16, 1, true>() : f.template operator()<16, 1, false>();
+    if (c.fuse) return hipErrorInvalidValue;
+    if (c.W == 16 && c.PER == 2) return f.template operator()<16, 2, false>();
+    if (c.W == 16 && c.PER == 3) return f.template operator()<16, 3, false>();
+    if (c.W == 16 && c.PER == 4) return f.template operator()<16, 4, false>();
+    if (c.W == 4 && c.PER == 2) return f.template operator()<4, 2, false>();
+    if (c.W == 8 && c.PER == 2) return f.template operator()<8, 2, false>();
+    if (c.W == 8 && c.PER == 4) return f.template operator()<8, 4, false>();
+    if (c.W == 8 && c.PER == 6) return f.template operator()<8, 6, false>();
+    if (c.W == 8 && c.PER == 8) return f.template operator()<8, 8, false>();
     return hipErrorInvalidValue;
 }
 struct LaunchSingle {
     const GemvParams& p; hipStream_t st;
-    template <int W, int PER> hipError_t operator()() const { return launch_one<W, PER>(p, st); }
+    template <int W, int PER, bool FUSE> hipError_t operator()() const { return launch_one<W, PER, FUSE>(p, st); }
 };
 
 hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
-    const int nblk = (p.G + 3) / 4;
-    if (p.RT > 0) {
-        gemv_t_partial_kernel<<<dim3(nblk), dim3(64), 0, st>>>(p.x, p.M, p.K, p.A, p.r, p.RT, p.tp);
+    const GemvChoice c = gemv_choose(p, false, (p.N + 15) / 16);
+    if (p.RT > 0 && !c.fuse) {
+        gemv_t_partial_kernel<<<dim3((p.G + 3) / 4), dim3(64), 0, st>>>(p.x, p.M, p.K, p.A, p.r, p.RT, p.tp);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return gemv_dispatch(gemv_choose(p), LaunchSingle{p, st});
+    return gemv_dispatch(c, LaunchSingle{p, st});
 }
 
 // Which kernel a batch takes: estimated times, fitted to runs of one to seven matrices of 1024 to 13824 features with 1
@@ -414,13 +508,13 @@ hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
 // seven matrices in one batch 59 / 56.
 // LDS of an 8-wavefront workgroup with two activation buffers per wavefront, or fewer where it has fewer rounds
 static size_t lds8_of(const GemvParams& p, int per) {
-    return (size_t)16 * GV_TABROW + 64 + (size_t)16 * p.RT * 2 + (size_t)std::min(per, 2) * 8 * ((std::min(p.M, 16) + 1) / 2) * 1024;
+    return (size_t)GV_FIXED + gemv_t_bytes(8, p.RT, p.RT == 16) + (size_t)std::min(per, 2) * 8 * ((std::min(p.M, 16) + 1) / 2) * 1024;
 }
 double gemv_batch_us(const std::vector<GemvParams>& items) {
     double t = items.empty() || items[0].RT == 0 ? 3.0 : 5.0;
     double rounds16[5] = {0, 0, 0, 0, 0};
     for (GemvParams p : items) {
-        const GemvChoice c = gemv_choose(p, LOWRA_BATCH_SMALL_WG != 0);
+        const GemvChoice c = gemv_choose_waves(p, LOWRA_BATCH_SMALL_WG != 0);
         const int nblk = (p.G + 3) / 4, per = (nblk + c.W - 1) / c.W, strips = (p.N + 15) / 16;
         if (c.W == 16) rounds16[std::min(per, 4)] += (double)strips / compute_units_cached();
         else if (c.W == 8) t += (2 * lds8_of(p, per) > (size_t)160 * 1024 ? 0.0111 : per > 2 ? 0.0066 : 0.0083) * strips * per;   // one workgroup per unit, or more
@@ -445,17 +539,17 @@ double gemv_stream_batch_us(const std::vector<GemvParams>& items) {
 // matrices that take the same instantiation with the same LDS size.
 struct PrepareDesc {
     GemvParams& p; size_t& sh;
-    template <int W, int PER> hipError_t operator()() const {
-        const hipError_t attr = gemv_attr<W, PER>();
+    template <int W, int PER, bool FUSE> hipError_t operator()() const {
+        const hipError_t attr = gemv_attr<W, PER, FUSE>();
         if (attr != hipSuccess) return attr;
-        sh = gemv_lds<W, PER>(p);
+        sh = gemv_lds<W, PER, FUSE>(p);
         return sh ? hipSuccess : hipErrorInvalidValue;
     }
 };
 struct LaunchGroup {
     const GemvBatchGroup& g; hipStream_t st;
-    template <int W, int PER> hipError_t operator()() const {
-        gemv_fwd_batch_kernel<W, PER><<<dim3(g.nstrips), dim3(W * 64), g.sh, st>>>(g.d_descs, g.d_strip0, g.d_owner);
+    template <int W, int PER, bool FUSE> hipError_t operator()() const {
+        gemv_fwd_batch_kernel<W, PER, FUSE><<<dim3(g.nstrips), dim3(W * 64), g.sh, st>>>(g.d_descs, g.d_strip0, g.d_owner);
         return hipGetLastError();
     }
 };
@@ -476,21 +570,26 @@ static hipError_t to_device(const std::vector<T>& v, T** out) {
 
 hipError_t gemv_batch_build(std::vector<GemvParams>& items, lowra_fwd_batch& b) {
     hipError_t e;
-    struct Key { int W, PER; size_t sh; };
+    struct Key { int W, PER, fuse; size_t sh; };
     std::vector<Key> keys;
     std::vector<std::vector<GemvParams>> members;
+    int strips = 0;
+    for (const auto& p : items) strips += (p.N + 15) / 16;
+    std::vector<GemvParams> tdescs;
+    std::vector<int> blk0(1, 0);
     for (auto& p : items) {
-        const GemvChoice c = gemv_choose(p, LOWRA_BATCH_SMALL_WG != 0);
+        const GemvChoice c = gemv_choose(p, LOWRA_BATCH_SMALL_WG != 0, strips);
+        if (p.RT > 0 && !c.fuse) { tdescs.push_back(p); blk0.push_back(blk0.back() + (p.G + 3) / 4); }
         size_t sh = 0;
         if ((e = gemv_dispatch(c, PrepareDesc{p, sh})) != hipSuccess) return e;
         size_t k = 0;
-        while (k < keys.size() && !(keys[k].W == c.W && keys[k].PER == c.PER && keys[k].sh == sh)) ++k;
-        if (k == keys.size()) { keys.push_back(Key{c.W, c.PER, sh}); members.emplace_back(); }
+        while (k < keys.size() && !(keys[k].W == c.W && keys[k].PER == c.PER && keys[k].fuse == c.fuse && keys[k].sh == sh)) ++k;
+        if (k == keys.size()) { keys.push_back(Key{c.W, c.PER, c.fuse, sh}); members.emplace_back(); }
         members[k].push_back(p);
     }
     for (size_t k = 0; k < keys.size(); ++k) {
         GemvBatchGroup g{};
-        g.W = keys[k].W; g.PER = keys[k].PER; g.sh = keys[k].sh; g.nmat = (int)members[k].size();
+        g.W = keys[k].W; g.PER = keys[k].PER; g.fuse = keys[k].fuse; g.sh = keys[k].sh; g.nmat = (int)members[k].size();
         std::vector<int> strip0(members[k].size() + 1, 0);
         for (size_t m = 0; m < members[k].size(); ++m) strip0[m + 1] = strip0[m] + (members[k][m].N + 15) / 16;
         g.nstrips = strip0.back();
@@ -502,10 +601,6 @@ hipError_t gemv_batch_build(std::vector<GemvParams>& items, lowra_fwd_batch& b) 
         if ((e = to_device(strip0, &b.groups.back().d_strip0)) != hipSuccess) return e;
         if ((e = to_device(owner, &b.groups.back().d_owner)) != hipSuccess) return e;
     }
-    std::vector<GemvParams> tdescs;
-    std::vector<int> blk0(1, 0);
-    for (auto& p : items)
-        if (p.RT > 0) { tdescs.push_back(p); blk0.push_back(blk0.back() + (p.G + 3) / 4); }
     b.nt = (int)tdescs.size(); b.nblk_total = blk0.back();
     if (b.nt > 0) {
         std::vector<int> owner((size_t)b.nblk_total);
@@ -527,7 +622,7 @@ hipError_t gemv_batch_run(const lowra_fwd_batch& b, hipStream_t st) {
     if (b.groups.empty()) return hipSuccess;
     KernelTimer timer(st);
     for (const auto& g : b.groups) {
-        const hipError_t e = gemv_dispatch(GemvChoice{g.W, g.PER}, LaunchGroup{g, st});
+        const hipError_t e = gemv_dispatch(GemvChoice{g.W, g.PER, g.fuse}, LaunchGroup{g, st});
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -35,7 +35,7 @@ namespace lowra {
 struct GemvParams;
 // one launch of the small-token kernel: the matrices of a batch that take the same instantiation
 struct GemvBatchGroup {
-    int W, PER;
+    int W, PER, fuse;
     size_t sh;                  // dynamic LDS bytes
     int nmat, nstrips;
     GemvParams* d_descs;        // [nmat] device

@@ -1,0 +1,45 @@
+"""The small-token forward where its instantiation changes: 4, 8 or 16 wavefronts of one block of 256 features each, t = x A^T
+formed by the workgroups themselves (up to 16 ranks and 32768 entries of A) or summed from partial sums."""
+import pytest
+import torch
+
+from oracle import lowra_oracle as orc
+from paper_2502_08141_amd import lowra, synth
+from tests.gpu_util import REL_TOL, DeviceLayer, bf16_host_f64, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K,r", [(64, 8), (192, 16), (1024, 16), (1024, 17), (1088, 16), (2048, 16), (2048, 24), (2112, 15), (2112, 16), (4096, 8),
+                                 (4096, 9), (4032, 3), (4160, 8), (1088, 64), (2048, 100)])
+@pytest.mark.parametrize("M,N", [(1, 264), (3, 8), (16, 40)])
+def test_wavefronts_and_ranks(K, r, M, N):
+    print(f"[small K {K} r {r} M {M} N {N}]", flush=True)
+    L = synth.make_custom(N, K, M, r, fractions=(0.4, 0.3, 0.3), seed=K % 89 + r)
+    D = DeviceLayer(L)
+    D.quantize()
+    rp, ra = orc.quantize(L.W, L.bits, L.cb, L.thresholds)
+    ref = orc.linear_fwd(rp, ra, L.bits, L.cb, L.mappings, L.x, L.A, L.B, L.s)
+    got = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, D.x, D.A, D.B, L.s)
+    batch = lowra.FwdBatch([(D.layout, D.packed, D.absmax, D.x, D.A, D.B)] * 2, D.mp, L.s) if K >= 256 else None
+    torch.cuda.synchronize()
+    assert rel_err(bf16_host_f64(got), ref) <= REL_TOL
+    if batch is not None:
+        for y in batch.run():
+            torch.cuda.synchronize()
+            assert rel_err(bf16_host_f64(y), ref) <= REL_TOL
+        batch.close()
+
+
+def test_an_infinite_adapter_entry_stays_in_its_rank():
+    """Lanes past the last rank repeat its row of A; what they form must not reach the result."""
+    L = synth.make_custom(40, 512, 2, 5, fractions=(0.4, 0.3, 0.3), seed=3)
+    D = DeviceLayer(L)
+    D.quantize()
+    A, B = D.A.clone(), D.B.clone()
+    A[4, 7] = float("inf")
+    B[:, 4] = 1.0
+    x = D.x.clone()
+    x[:, 7] = 1.0
+    got = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, x, A, B, 1.0).float()
+    assert torch.isposinf(got).all()
