@@ -185,22 +185,41 @@ __global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict_
         out[e] = s;
     }
 }
-// The same sum written transposed, out[j][c]: a workgroup takes 16 columns c, reads their partial rows as they lie
-// (64 ranks = 256 contiguous bytes per column), and turns the tile through LDS so that the stores run along c too.
+// The chunk sums of a launch's products in one launch (a second one cost 3.2 to 4.8 us behind the first).  A workgroup takes
+// 16 columns c and reads their partial rows as they lie (64 ranks = 256 contiguous bytes per column): out[c][j], or written
+// transposed, out[j][c], the tile turned through LDS so that the stores run along c too.
 constexpr int AG_RT_COLS = 16;
-__global__ __launch_bounds__(256) void tn_reduce_t_kernel(const float* __restrict__ partial, int nchunks, int C, int r,
-                                                          float* __restrict__ out) {
+struct TnSum { const float* partial; float* out; int nchunks, C, transposed, nwg; };
+__global__ __launch_bounds__(256) void tn_sum_kernel(const TnSum a, const TnSum b, int r) {
     __shared__ float tile[AG_RT_COLS][65];
-    const int c0 = blockIdx.x * AG_RT_COLS, tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    float s[AG_RT_COLS / 4];
+    const bool second = (int)blockIdx.x >= a.nwg;             // uniform
+    const float* __restrict__ partial = second ? b.partial : a.partial;
+    float* __restrict__ out = second ? b.out : a.out;
+    const int nchunks = second ? b.nchunks : a.nchunks, C = second ? b.C : a.C;
+    const int wg = (int)blockIdx.x - (second ? a.nwg : 0);
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6, c0 = wg * AG_RT_COLS;
+    float s[AG_RT_COLS / 4];                                  // thread (tx, ty): rank tx of columns c0 + ty + 4 q, chunks in order
 #pragma unroll
     for (int q = 0; q < AG_RT_COLS / 4; ++q) s[q] = 0.0f;
-    for (int k = 0; k < nchunks; ++k) {                       // fixed order; thread (tx, ty): rank tx of columns c0 + ty + 4 q
+    for (int k0 = 0; k0 < nchunks; k0 += 4) {                 // four chunks in flight, not one round trip after the other
+        float v[4][AG_RT_COLS / 4];
 #pragma unroll
-        for (int q = 0; q < AG_RT_COLS / 4; ++q) {
-            const int c = min(c0 + ty + 4 * q, C - 1);        // past the last column: a valid address, never stored
-            s[q] += partial[((size_t)k * C + c) * 64 + tx];
-        }
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int q = 0; q < AG_RT_COLS / 4; ++q) {
+                const int c = min(c0 + ty + 4 * q, C - 1);    // past the last column: a valid address, never stored
+                v[k][q] = partial[((size_t)min(k0 + k, nchunks - 1) * C + c) * 64 + tx];
+            }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int q = 0; q < AG_RT_COLS / 4; ++q) s[q] += k0 + k < nchunks ? v[k][q] : 0.0f;
+    }
+    if (second ? !b.transposed : !a.transposed) {
+#pragma unroll
+        for (int q = 0; q < AG_RT_COLS / 4; ++q)
+            if (c0 + ty + 4 * q < C && tx < r) out[(size_t)(c0 + ty + 4 * q) * r + tx] = s[q];
+        return;
     }
 #pragma unroll
     for (int q = 0; q < AG_RT_COLS / 4; ++q) tile[ty + 4 * q][tx] = s[q];
@@ -234,13 +253,9 @@ static TnProb tn_prob(const TnCall& c, int M) {
     const int tiles = (c.C + AG_COLS - 1) / AG_COLS;
     return TnProb{c.P, c.Q, c.partial, pl.chunks == 1 ? c.out : nullptr, c.C, pl.chunk_rows, c.transposed, tiles, tiles * pl.chunks};
 }
-static hipError_t tn_finish(const TnCall& c, int M, int r, hipStream_t st) {      // the chunk sum, where there are chunks
+static TnSum tn_sum(const TnCall& c, int M) {           // the chunk sum, where there are chunks (else no workgroups)
     const TnPlan pl = tn_plan(c.C, M, c.other_tiles);
-    if (pl.chunks == 1) return hipSuccess;
-    const size_t tot = (size_t)c.C * r;
-    if (c.transposed) tn_reduce_t_kernel<<<dim3((unsigned)((c.C + AG_RT_COLS - 1) / AG_RT_COLS)), dim3(256), 0, st>>>(c.partial, pl.chunks, c.C, r, c.out);
-    else tn_reduce_kernel<<<dim3((unsigned)std::min<size_t>((tot + 255) / 256, 4096)), dim3(256), 0, st>>>(c.partial, pl.chunks, c.C, 64, r, c.out);
-    return hipGetLastError();
+    return TnSum{c.partial, c.out, pl.chunks, c.C, c.transposed, pl.chunks == 1 ? 0 : (c.C + AG_RT_COLS - 1) / AG_RT_COLS};
 }
 static hipError_t launch_tn(const TnCall* c0, const TnCall* c1, int M, int r, hipStream_t st) {
     const size_t sh = std::max((size_t)4 * 2 * 2 * AG_TILEB, (size_t)4 * AG_COLS * (64 + 1) * sizeof(float));
@@ -254,8 +269,13 @@ static hipError_t launch_tn(const TnCall* c0, const TnCall* c1, int M, int r, hi
     tn_skinny_kernel<1><<<dim3(pa.nwg + pb.nwg), dim3(256), sh, st>>>(pa, pb, M, r);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if ((e = tn_finish(*c0, M, r, st)) != hipSuccess) return e;
-    return c1 ? tn_finish(*c1, M, r, st) : hipSuccess;
+    const TnSum sa = tn_sum(*c0, M);
+    TnSum sb = sa;
+    sb.nwg = 0;
+    if (c1) sb = tn_sum(*c1, M);
+    if (sa.nwg + sb.nwg == 0) return hipSuccess;
+    tn_sum_kernel<<<dim3((unsigned)(sa.nwg + sb.nwg)), dim3(256), 0, st>>>(sa, sb, r);
+    return hipGetLastError();
 }
 hipError_t launch_tn_skinny(const uint16_t* P, int C, int M, const uint16_t* Q, int RP, int r, int transposed,
                             float* partial, float* out, hipStream_t st) {
@@ -279,6 +299,9 @@ hipError_t launch_skinny_ws(const uint16_t* P, int ldp, int M, const uint16_t* Q
 size_t skinny_scratch_bytes(int M, int Kc, int RP);
 hipError_t launch_skinny_qt(const uint16_t* P, int ldp, int M, const uint16_t* Qt, int r, int Kc, float s, uint16_t* out,
                             float* scratch, bool split, float* few, hipStream_t st);
+bool skinny_pairs(int M, int K, int N, int r);
+hipError_t launch_skinny_pair(const uint16_t* x, int K, const uint16_t* A, uint16_t* t, const uint16_t* dY, int N, const uint16_t* B, uint16_t* u,
+                              int M, int r, float s, float* few, hipStream_t st);
 hipError_t launch_transpose(const uint16_t* src, int R, int c, uint16_t* dst, hipStream_t st);
 
 static inline size_t ag_align(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -305,7 +328,11 @@ hipError_t launch_adapter_grads(const lowra_layout& L, const uint16_t* x, const 
     uint16_t* bt = reinterpret_cast<uint16_t*>(ws + 2 * tu);
     float* partial = reinterpret_cast<float*>(ws + 2 * tu + ag_align((size_t)r * L.N * 2));   // scratch of the side products, then the partial tiles
     hipError_t e;
-    // (few tokens' partial sums, at most L.K or L.N rows of 256 bytes, fit the region: it holds at least L.N + L.K such rows)
+    // (few tokens' partial sums, at most L.K and L.N rows of 256 bytes, fit the region: it holds at least L.N + L.K such rows)
+    if (skinny_pairs(M, L.K, L.N, r)) {
+        if ((e = launch_skinny_pair(x, L.K, A, ts, dY, L.N, B, us, M, r, s, partial, st)) != hipSuccess) return e;
+        return launch_adapter_grads_from_side(L, x, dY, M, r, ts, us, dA, dB, workspace, st);
+    }
     if ((e = launch_skinny_ws(x, L.K, M, A, L.K, r, L.K, s, ts, kGradRP, partial, true, partial, st)) != hipSuccess) return e;       // s t = s x A^T
     if (r % 8 == 0) {                                                                                   // s u = s dY B, B read in place
         if ((e = launch_skinny_qt(dY, L.N, M, B, r, L.N, s, us, partial, true, partial, st)) != hipSuccess) return e;

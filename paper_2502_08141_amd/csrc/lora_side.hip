@@ -52,10 +52,10 @@ typedef __attribute__((address_space(3))) sk_v4i16_t* sk_lds_v4i16_ptr;
 // workgroup per slice and skinny_sum_kernel, without room for partial sums.  At the end of a slice the multiplying wavefronts
 // leave their sums in LDS behind the stages (two buffers in turn), and after the stage's barrier add them up as the others do.
 template <int CT, int KW, int NC, int RING, int PT = 1, bool QT = false, bool WALK = false>
-__global__ __launch_bounds__(128 * NC) void skinny_nt_kernel(const uint16_t* __restrict__ P, int ldp, int M,
-                                                            const uint16_t* __restrict__ Q, int ldq, int r,
-                                                            int Kc, float s, uint16_t* __restrict__ out,
-                                                            float* __restrict__ partial, int kslice) {
+__device__ __forceinline__ void skinny_nt_body(const uint16_t* __restrict__ P, int ldp, int M,
+                                               const uint16_t* __restrict__ Q, int ldq, int r,
+                                               int Kc, float s, uint16_t* __restrict__ out,
+                                               float* __restrict__ partial, int kslice, const int block, const int slice_of) {
     extern __shared__ __align__(16) uint8_t smem[];
     constexpr int RP = CT * 16, PR = PT * 16, ROWS = PR + RP, ROWBYTES = KW * 2, CPR = KW / 8;   // chunks per row
     constexpr int STAGE = ROWS * ROWBYTES, RPI = 1024 / ROWBYTES;                   // rows per DMA instruction
@@ -70,9 +70,9 @@ __global__ __launch_bounds__(128 * NC) void skinny_nt_kernel(const uint16_t* __r
     const bool mover = wave >= NC;
     const int sw = mover ? wave - NC : wave;
     const int i = lane & 15, kg = lane >> 4;
-    const int m0 = blockIdx.x * PR;
+    const int m0 = block * PR;
     // my slice of the contraction (kslice: a multiple of KW); WALK: all of it
-    const int kbeg = WALK ? 0 : blockIdx.y * kslice, kend = WALK ? Kc : min(kbeg + kslice, Kc);
+    const int kbeg = WALK ? 0 : slice_of * kslice, kend = WALK ? Kc : min(kbeg + kslice, Kc);
     const int nst = (kend - kbeg + KW - 1) / KW;
 
     floatx4_t acc[PT][CT];
@@ -215,10 +215,29 @@ __global__ __launch_bounds__(128 * NC) void skinny_nt_kernel(const uint16_t* __r
         for (int w = 0; w < NC; ++w) v += red[(w * PR + row) * RP + col];
         const int mo = m0 + row;
         if (mo < M) {
-            if (partial) partial[((size_t)blockIdx.y * M + mo) * RP + col] = v;          // one slice: unscaled, summed later
+            if (partial) partial[((size_t)slice_of * M + mo) * RP + col] = v;            // one slice: unscaled, summed later
             else out[(size_t)mo * RP + col] = (uint16_t)(pack_bf16x2(v * s, 0.0f) & 0xffffu);
         }
     }
+}
+template <int CT, int KW, int NC, int RING, int PT = 1, bool QT = false, bool WALK = false>
+__global__ __launch_bounds__(128 * NC) void skinny_nt_kernel(const uint16_t* __restrict__ P, int ldp, int M,
+                                                            const uint16_t* __restrict__ Q, int ldq, int r,
+                                                            int Kc, float s, uint16_t* __restrict__ out,
+                                                            float* __restrict__ partial, int kslice) {
+    skinny_nt_body<CT, KW, NC, RING, PT, QT, WALK>(P, ldp, M, Q, ldq, r, Kc, s, out, partial, kslice, blockIdx.x, blockIdx.y);
+}
+
+// The two products of a step's adapter gradients, t = s x A^T and u = s dY B, in one launch where both take 16-row workgroups:
+// a second launch costs 1.6 us on the GPU and 2.6 on the host, as much as either does at few tokens.
+struct SkinnyHalf {
+    const uint16_t* P; const uint16_t* Q; uint16_t* out; float* partial;     // partial: null without slices
+    int ldp, ldq, Kc, kslice, slices;
+};
+__global__ __launch_bounds__(512) void skinny_pair_kernel(const SkinnyHalf a, const SkinnyHalf b, int M, int r, float s, int blocks) {
+    const int wg = blockIdx.x, na = blocks * a.slices;
+    if (wg < na) skinny_nt_body<4, 128, 4, 7, 1, false>(a.P, a.ldp, M, a.Q, a.ldq, r, a.Kc, s, a.out, a.partial, a.kslice, wg % blocks, wg / blocks);
+    else skinny_nt_body<4, 128, 4, 7, 1, true>(b.P, b.ldp, M, b.Q, b.ldq, r, b.Kc, s, b.out, b.partial, b.kslice, (wg - na) % blocks, (wg - na) / blocks);
 }
 
 // out = bf16(s * sum over the slices of partial [slices][M x RP])
@@ -232,6 +251,22 @@ __global__ __launch_bounds__(256) void skinny_sum_kernel(const float4* __restric
         v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
     }
     out[e] = make_uint2(pack_bf16x2(v.x * s, v.y * s), pack_bf16x2(v.z * s, v.w * s));
+}
+
+// the same for both halves of a pair, n4 float4 per slice of either (a half without slices is not summed)
+__global__ __launch_bounds__(256) void skinny_sum_pair_kernel(const SkinnyHalf a, const SkinnyHalf b, int n4, float s) {
+    const int e2 = blockIdx.x * 256 + threadIdx.x;
+    const bool second = a.slices == 1 || e2 >= n4;
+    const int e = e2 - (second && a.slices > 1 ? n4 : 0);
+    if (e >= n4 || (second && b.slices == 1)) return;         // past the last sum (the grid is whole workgroups)
+    const float4* partial = reinterpret_cast<const float4*>(second ? b.partial : a.partial);
+    const int slices = second ? b.slices : a.slices;
+    float4 v = partial[e];
+    for (int q = 1; q < slices; ++q) {
+        const float4 w = partial[(size_t)q * n4 + e];
+        v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+    }
+    reinterpret_cast<uint2*>(second ? b.out : a.out)[e] = make_uint2(pack_bf16x2(v.x * s, v.y * s), pack_bf16x2(v.z * s, v.w * s));
 }
 
 // dst [R, CP] = src [R, c] padded with zero columns.
@@ -388,6 +423,31 @@ hipError_t launch_skinny_ws(const uint16_t* P, int ldp, int M, const uint16_t* Q
 hipError_t launch_skinny_qt(const uint16_t* P, int ldp, int M, const uint16_t* Qt, int r, int Kc, float s, uint16_t* out,
                             float* scratch, bool split, float* few, hipStream_t st) {
     return launch_skinny_any<true>(P, ldp, M, Qt, r, r, Kc, s, out, 64, scratch, split, few, st);
+}
+// Whether t = s x A^T and u = s dY B of an N x K matrix share a launch: ranks that B can be read in place with, and token
+// counts whose workgroups all have 16 rows and, together, a unit each or nearly so (beyond, they fill the chip one after
+// the other).  `few`: room for N + K rows of 64 floats.  The same sums in the same order as the single launches.
+static bool skinny_half_plain(int M, int Kc, int r) {
+    return r * (long long)Kc * 2 < (1LL << 31) && (long long)M * Kc * 2 < (1LL << 31) && skinny_plan(M, Kc, 64).slices == 1;
+}
+bool skinny_pairs(int M, int K, int N, int r) {
+    return r % 8 == 0 && r <= 64 && M >= 1 && 4 * ((M + 15) / 16) <= device_compute_units() && skinny_half_plain(M, K, r) && skinny_half_plain(M, N, r);
+}
+hipError_t launch_skinny_pair(const uint16_t* x, int K, const uint16_t* A, uint16_t* t, const uint16_t* dY, int N, const uint16_t* B, uint16_t* u,
+                              int M, int r, float s, float* few, hipStream_t st) {
+    constexpr int sh = 7 * (16 + 64) * 128 * 2;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_pair_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, sh);
+    if (attr != hipSuccess) return attr;
+    const SkinnyPlan pa = skinny_few_plan(M, K, 64), pb = skinny_few_plan(M, N, 64);
+    const SkinnyHalf a{x, A, t, pa.slices > 1 ? few : nullptr, K, K, K, pa.slices > 1 ? pa.kslice : K, pa.slices};
+    const SkinnyHalf b{dY, B, u, pb.slices > 1 ? few + (size_t)K * 64 : nullptr, N, r, N, pb.slices > 1 ? pb.kslice : N, pb.slices};
+    const int blocks = (M + 15) / 16;
+    skinny_pair_kernel<<<dim3(blocks * (a.slices + b.slices)), dim3(512), sh, st>>>(a, b, M, r, s, blocks);
+    hipError_t e = hipGetLastError();
+    const int halves = (a.slices > 1) + (b.slices > 1), n4 = M * 16;
+    if (e != hipSuccess || halves == 0) return e;
+    skinny_sum_pair_kernel<<<dim3((halves * n4 + 255) / 256), dim3(256), 0, st>>>(a, b, n4, s);
+    return hipGetLastError();
 }
 hipError_t launch_skinny(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
                          float s, uint16_t* out, int RP, hipStream_t st) {
