@@ -257,31 +257,35 @@ static TnSum tn_sum(const TnCall& c, int M) {           // the chunk sum, where 
     const TnPlan pl = tn_plan(c.C, M, c.other_tiles);
     return TnSum{c.partial, c.out, pl.chunks, c.C, c.transposed, pl.chunks == 1 ? 0 : (c.C + AG_RT_COLS - 1) / AG_RT_COLS};
 }
+static size_t tn_lds_bytes() { return std::max((size_t)4 * 2 * 2 * AG_TILEB, (size_t)4 * AG_COLS * (64 + 1) * sizeof(float)); }
 static hipError_t launch_tn(const TnCall* c0, const TnCall* c1, int M, int r, hipStream_t st) {
-    const size_t sh = std::max((size_t)4 * 2 * 2 * AG_TILEB, (size_t)4 * AG_COLS * (64 + 1) * sizeof(float));
+    const size_t sh = tn_lds_bytes();
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(tn_skinny_kernel<1>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
     const TnProb pa = tn_prob(*c0, M);
-    TnProb pb = pa;
-    pb.nwg = 0;
-    if (c1) pb = tn_prob(*c1, M);
+    const TnProb pb = tn_prob(*c1, M);
     tn_skinny_kernel<1><<<dim3(pa.nwg + pb.nwg), dim3(256), sh, st>>>(pa, pb, M, r);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const TnSum sa = tn_sum(*c0, M);
-    TnSum sb = sa;
-    sb.nwg = 0;
-    if (c1) sb = tn_sum(*c1, M);
+    const TnSum sa = tn_sum(*c0, M), sb = tn_sum(*c1, M);
     if (sa.nwg + sb.nwg == 0) return hipSuccess;
     tn_sum_kernel<<<dim3((unsigned)(sa.nwg + sb.nwg)), dim3(256), 0, st>>>(sa, sb, r);
     return hipGetLastError();
 }
-hipError_t launch_tn_skinny(const uint16_t* P, int C, int M, const uint16_t* Q, int RP, int r, int transposed,
-                            float* partial, float* out, hipStream_t st) {
-    if (RP != 64) return hipErrorInvalidValue;                 // two Q tiles per stage would not fit the staging area
-    const TnCall c{P, C, Q, transposed, partial, out, 0};
-    return launch_tn(&c, nullptr, M, r, st);
+// The partial sums alone, [chunks][C][64], for a caller that adds the chunks itself
+hipError_t launch_tn_partial(const uint16_t* P, int C, int M, const uint16_t* Q, float* partial, int* chunks, hipStream_t st) {
+    const size_t sh = tn_lds_bytes();
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(tn_skinny_kernel<1>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (attr != hipSuccess) return attr;
+    TnProb pa = tn_prob(TnCall{P, C, Q, 0, partial, nullptr, 0}, M), pb;
+    pa.direct = nullptr;
+    pb = pa;
+    pb.nwg = 0;
+    *chunks = pa.nwg / pa.tiles;
+    tn_skinny_kernel<1><<<dim3(pa.nwg), dim3(256), sh, st>>>(pa, pb, M, 64);
+    return hipGetLastError();
 }
 
 // No tokens: both gradients are zero (the reduction over zero chunks writes exactly that; a kernel

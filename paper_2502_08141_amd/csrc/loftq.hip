@@ -20,11 +20,11 @@ namespace lowra {
 hipError_t launch_skinny(const uint16_t* P, int ldp, int M, const uint16_t* Q, int ldq, int r, int Kc,
                          float s, uint16_t* out, int RP, hipStream_t st);
 size_t tn_partial_bytes(int C, int M, int RP);
-hipError_t launch_tn_skinny(const uint16_t* P, int C, int M, const uint16_t* Q, int RP, int r, int transposed,
-                            float* partial, float* out, hipStream_t st);
+hipError_t launch_tn_partial(const uint16_t* P, int C, int M, const uint16_t* Q, float* partial, int* chunks, hipStream_t st);
 
 constexpr int LQ_RP = 64;      // rank padded to the side products' row length
-constexpr int LQ_GCH = 128;    // columns of Z per partial Gram matrix
+constexpr int LQ_GT = 32;      // columns of Z per tile of its Gram matrix
+constexpr int LQ_GBLOCKS = 136, LQ_GENTRIES = 16 * LQ_GBLOCKS;       // 4 x 4 blocks on and below the diagonal of a 64 x 64 matrix
 
 // ---- F = W - Y At^T: Y [N][64] bf16 (B, padded with zero columns), At [K][64] bf16 (A^T, padded)
 // A wavefront owns 32 channels x 128 input features: its 32 x 64 piece of Y stays in registers,
@@ -109,91 +109,93 @@ __global__ __launch_bounds__(256) void residual_of_decode_kernel(const RowInfo* 
     }
 }
 
-// ---- partial Gram matrices of Z [r][K]: the sum over a chunk's columns of Z[i][k] Z[j][k] (fp64), kept block by block:
-// Gp[chunk][16 bj + bi][4 u + v] is entry (4 bi + u, 4 bj + v), so that a thread writes its block as one 128-byte line.
-// Only the blocks on and below the diagonal are written or read.
-// One workgroup per (chunk, band of 16 rows): the contraction is bound by a compute unit's fp64 rate, so the 64 x 64
-// outputs of a chunk are dealt over four workgroups.  Wavefront w takes the chunk's columns [32 w, 32 w + 32), lane
-// (bi, bj) the 4 x 4 block of rows 16 band + 4 bi.., columns 4 bj.. ; the four wavefronts' sums meet in LDS and are
-// added in wavefront order.
-__global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ Z, int K, int r, double* __restrict__ Gp) {
+// ---- Z = the sum of its chunks' partial sums [nchunks][K][64], in chunk order, left as Zt [K][64]; and partial Gram matrices
+// of it (fp64): the sum over a workgroup's columns k of Z[i][k] Z[j][k], block by block, Gp[workgroup][block][4 u + v] being entry
+// (4 bi + u, 4 bj + v) of block bi (bi + 1) / 2 + bj, bj <= bi.
+// A workgroup takes `per` tiles of 32 columns one after the other.  The contraction is bound by a compute unit's fp64 rate, so
+// the tiles are small (128 workgroups at 4096 columns); wavefront w takes the rows [16 w, 16 w + 16) of the result, lane
+// (bi, bj) the 4 x 4 block of rows 16 w + 4 bi .., columns 4 bj ..: no sum over wavefronts.  At 64 x 4096 with four chunks
+// 6.2 us; a launch for the sum, transposed, and one for the Gram matrices took 3.9 + 7.1.
+__global__ __launch_bounds__(256) void zsum_gram_kernel(const float* __restrict__ partial, int nchunks, int K, float* __restrict__ Zt,
+                                                        double* __restrict__ Gp, int per) {
     constexpr int ZS = 68;                                           // row stride of zt: 16-byte aligned rows
-    __shared__ __align__(16) float zt[LQ_GCH * ZS];                  // zt[k][i], the chunk transposed
-    __shared__ double comb[3][16][64];                               // [wavefront - 1][element][lane]
-    const int chunk = blockIdx.x >> 2, band = blockIdx.x & 3;
-    const int c0 = chunk * LQ_GCH, tid = threadIdx.x;
-    const int lc = (tid & 31) * 4;                                   // my four columns of a row
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        const int i = (tid >> 5) + 8 * p;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i < r) {
-            const float* src = Z + (size_t)i * K + c0 + lc;
-            if (c0 + lc < K) v = *reinterpret_cast<const float4*>(src);      // K is a multiple of 64
-        }
-        zt[(lc + 0) * ZS + i] = v.x; zt[(lc + 1) * ZS + i] = v.y; zt[(lc + 2) * ZS + i] = v.z; zt[(lc + 3) * ZS + i] = v.w;
-    }
-    __syncthreads();
-    const int wave = tid >> 6, lane = tid & 63, bi = lane >> 4, bj = lane & 15;
-    const int row0 = 16 * band + 4 * bi;
+    __shared__ __align__(16) float zt[LQ_GT * ZS];                   // zt[k][i]
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, bi = lane >> 4, bj = lane & 15;
+    const int row0 = 16 * wave + 4 * bi, lc = tid >> 3, lr = (tid & 7) * 8;      // I bring ranks lr .. + 7 of column lc
     double g[4][4];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int v = 0; v < 4; ++v) g[u][v] = 0.0;
-    if (4 * bj <= row0) {                                            // blocks above the diagonal: nothing to do
-        const float* za = zt + (32 * wave) * ZS + row0;
-        const float* zb = zt + (32 * wave) * ZS + 4 * bj;
+    const int t_hi = min(((int)blockIdx.x + 1) * per, K / LQ_GT);    // K is a multiple of 64
+    for (int t = blockIdx.x * per; t < t_hi; ++t) {
+        const size_t at = (size_t)(t * LQ_GT + lc) * 64 + lr;
+        float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b = a;
+        for (int k0 = 0; k0 < nchunks; k0 += 4) {                    // four chunks in flight
+            float4 p[4], q[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float* src = partial + (size_t)min(k0 + k, nchunks - 1) * K * 64 + at;
+                p[k] = *reinterpret_cast<const float4*>(src); q[k] = *reinterpret_cast<const float4*>(src + 4);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k0 + k < nchunks) {
+                    a.x += p[k].x; a.y += p[k].y; a.z += p[k].z; a.w += p[k].w;
+                    b.x += q[k].x; b.y += q[k].y; b.z += q[k].z; b.w += q[k].w;
+                }
+        }
+        *reinterpret_cast<float4*>(Zt + at) = a; *reinterpret_cast<float4*>(Zt + at + 4) = b;
+        __syncthreads();                                             // the tile before has been read
+        *reinterpret_cast<float4*>(zt + lc * ZS + lr) = a; *reinterpret_cast<float4*>(zt + lc * ZS + lr + 4) = b;
+        __syncthreads();
+        if (4 * bj <= row0) {                                        // blocks above the diagonal: nothing to do
 #pragma unroll 4
-        for (int k = 0; k < 32; ++k) {
-            const float4 a4 = *reinterpret_cast<const float4*>(za + k * ZS);
-            const float4 b4 = *reinterpret_cast<const float4*>(zb + k * ZS);
-            const double a[4] = {a4.x, a4.y, a4.z, a4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
+            for (int k = 0; k < LQ_GT; ++k) {
+                const float4 a4 = *reinterpret_cast<const float4*>(zt + k * ZS + row0);
+                const float4 b4 = *reinterpret_cast<const float4*>(zt + k * ZS + 4 * bj);
+                const double x[4] = {a4.x, a4.y, a4.z, a4.w}, y[4] = {b4.x, b4.y, b4.z, b4.w};
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+                for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) g[u][v] = fma(a[u], b[v], g[u][v]);
+                    for (int v = 0; v < 4; ++v) g[u][v] = fma(x[u], y[v], g[u][v]);
+            }
         }
     }
-    if (wave > 0) {
+    if (4 * bj <= row0) {
+        const int r4 = row0 >> 2;
+        double* out = Gp + (size_t)blockIdx.x * LQ_GENTRIES + (r4 * (r4 + 1) / 2 + bj) * 16;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) comb[wave - 1][4 * u + v][lane] = g[u][v];
-    }
-    __syncthreads();
-    if (wave == 0 && 4 * bj <= row0) {
-        double* out = Gp + (size_t)chunk * 4096 + (16 * bj + 4 * band + bi) * 16;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            double4 o;
-            o.x = ((g[u][0] + comb[0][4 * u + 0][lane]) + comb[1][4 * u + 0][lane]) + comb[2][4 * u + 0][lane];
-            o.y = ((g[u][1] + comb[0][4 * u + 1][lane]) + comb[1][4 * u + 1][lane]) + comb[2][4 * u + 1][lane];
-            o.z = ((g[u][2] + comb[0][4 * u + 2][lane]) + comb[1][4 * u + 2][lane]) + comb[2][4 * u + 2][lane];
-            o.w = ((g[u][3] + comb[0][4 * u + 3][lane]) + comb[1][4 * u + 3][lane]) + comb[2][4 * u + 3][lane];
-            *reinterpret_cast<double4*>(out + 4 * u) = o;
-        }
+        for (int u = 0; u < 4; ++u) *reinterpret_cast<double4*>(out + 4 * u) = make_double4(g[u][0], g[u][1], g[u][2], g[u][3]);
     }
 }
 
-// ---- G [64][64] (the blocks on and below the diagonal) = the sum of the partial matrices, entry by entry in chunk order.  A kernel
-// of its own because one compute unit fetches about 30 GB/s: the 0.5 MB of partial matrices took a single workgroup of
-// the factorisation 18 us; spread over the chip the sum is a microsecond.
-__global__ __launch_bounds__(64) void gram_sum_kernel(const double* __restrict__ Gp, int chunks, double* __restrict__ G) {
-    const int e = blockIdx.x * 64 + threadIdx.x;                     // entry 4 u + v of block 16 bj + bi
-    const int bj = e >> 8, bi = (e >> 4) & 15;
-    if (bj > bi) return;
+// ---- G [64][64] (the blocks on and below the diagonal) = the sum of the partial matrices.  A kernel of its own because one
+// compute unit fetches about 30 GB/s: the partial matrices took a single workgroup of the factorisation 18 us; spread over
+// the chip it takes 4 us, launch included.  Four threads share an entry, a run of partial matrices each, added in their order.
+__global__ __launch_bounds__(256) void gram_sum_kernel(const double* __restrict__ Gp, int parts, double* __restrict__ G) {
+    __shared__ double run[4][64];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + lane;                            // entry 4 u + v of a block
+    const int each = (parts + 3) / 4, hi = min((q + 1) * each, parts);
     double sum = 0.0;
-    for (int c0 = 0; c0 < chunks; c0 += 16) {
+    for (int c0 = q * each; c0 < hi; c0 += 16) {
         double part[16];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) part[q] = Gp[(size_t)(c0 + q < chunks ? c0 + q : chunks - 1) * 4096 + e];
+        for (int i = 0; i < 16; ++i) part[i] = Gp[(size_t)min(c0 + i, hi - 1) * LQ_GENTRIES + e];
 #pragma unroll
-        for (int q = 0; q < 16; ++q)
-            if (c0 + q < chunks) sum += part[q];
+        for (int i = 0; i < 16; ++i)
+            if (c0 + i < hi) sum += part[i];
     }
-    G[(4 * bi + ((e >> 2) & 3)) * 64 + 4 * bj + (e & 3)] = sum;
+    run[q][lane] = sum;
+    __syncthreads();
+    if (q > 0) return;
+    int bi = 0;
+    while ((bi + 1) * (bi + 2) / 2 <= e >> 4) ++bi;
+    const int bj = (e >> 4) - bi * (bi + 1) / 2;
+    G[(4 * bi + ((e >> 2) & 3)) * 64 + 4 * bj + (e & 3)] = ((run[0][lane] + run[1][lane]) + run[2][lane]) + run[3][lane];
 }
+static_assert(LQ_GENTRIES % 64 == 0, "whole workgroups of entries");
 
 // ---- G = L L^T (fp64) and A = L^-1 Z by forward substitution: orthonormal rows, written as bf16 [64][K] (rows >= r zero)
 // and transposed, At [K][64].  One workgroup of eight wavefronts per 64 columns of Z; every workgroup factors G for
@@ -254,7 +256,7 @@ __device__ __forceinline__ void lq_invert_from(double (&x)[4], const double (&l)
 
 constexpr int LQ_APPLY_THREADS = 512;
 constexpr int LQ_LS = 68;                                            // row stride of Ls: 16-byte reads of 16 rows meet all banks
-__global__ __launch_bounds__(LQ_APPLY_THREADS) void factor_apply_kernel(const float* __restrict__ Z, const double* __restrict__ G, int K, int r,
+__global__ __launch_bounds__(LQ_APPLY_THREADS) void factor_apply_kernel(const float* __restrict__ Zt, const double* __restrict__ G, int K, int r,
                                                                         uint16_t* __restrict__ A, uint16_t* __restrict__ At) {
     __shared__ double2 pan[2][4][64];                                // [buffer][pair of columns of the panel][row]
     __shared__ double2 diag[4][16][8];                               // the 16 x 16 blocks on L's diagonal (below their diagonals)
@@ -273,9 +275,13 @@ __global__ __launch_bounds__(LQ_APPLY_THREADS) void factor_apply_kernel(const fl
     double maxdiag = G[lane * 65];
     floatx4_t s[4];                                                  // s[b][v]: row 16 b + 4 h + v of column k
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) s[b][v] = (w < 4 && 16 * b + 4 * h + v < r) ? Z[(size_t)(16 * b + 4 * h + v) * K + k] : 0.0f;
+    for (int b = 0; b < 4; ++b) {
+        s[b] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        if (w < 4) {                                                 // (columns of Zt from r on are zeros: the matching ones of Y are)
+            const float4 z = *reinterpret_cast<const float4*>(Zt + (size_t)k * 64 + 16 * b + 4 * h);
+            s[b] = floatx4_t{z.x, z.y, z.z, z.w};
+        }
+    }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) maxdiag = fmax(maxdiag, __shfl_xor(maxdiag, o, 64));
     const double tiny = 1e-12 * fmax(maxdiag, 0.0);
@@ -382,7 +388,7 @@ __global__ __launch_bounds__(256) void copy_cols_kernel(const uint16_t* __restri
 static inline size_t lq_align(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct LoftqWs {
-    size_t F, E, Y, Z, partial, Gp, G, A, At, total;
+    size_t F, E, Y, Z, partial, Gp, Gp_bytes, G, A, At, total;
 };
 static LoftqWs loftq_ws(int N, int K) {
     LoftqWs w;
@@ -392,7 +398,7 @@ static LoftqWs loftq_ws(int N, int K) {
     w.Y = o; o += lq_align((size_t)N * LQ_RP * 2);
     w.Z = o; o += lq_align((size_t)LQ_RP * K * 4);
     w.partial = o; o += lq_align(tn_partial_bytes(K, N, LQ_RP));
-    w.Gp = o; o += lq_align((size_t)((K + LQ_GCH - 1) / LQ_GCH) * 4096 * sizeof(double));
+    w.Gp = o; w.Gp_bytes = lq_align((size_t)((K + 127) / 128) * 4096 * sizeof(double)); o += w.Gp_bytes;
     w.G = o; o += lq_align(4096 * sizeof(double));
     w.A = o; o += lq_align((size_t)LQ_RP * K * 2);
     w.At = o; o += lq_align((size_t)K * LQ_RP * 2);
@@ -414,13 +420,17 @@ hipError_t launch_loftq(const lowra_layout& L, const float* W, const float* thre
     float* F = reinterpret_cast<float*>(ws + o.F);
     uint16_t* E = reinterpret_cast<uint16_t*>(ws + o.E);
     uint16_t* Y = reinterpret_cast<uint16_t*>(ws + o.Y);
-    float* Z = reinterpret_cast<float*>(ws + o.Z);
+    float* Zt = reinterpret_cast<float*>(ws + o.Z);
     float* partial = reinterpret_cast<float*>(ws + o.partial);
-    double* Gp = reinterpret_cast<double*>(ws + o.Gp);
+    // The partial Gram matrices, one per tile of Z where there is room: in the place of F, which is used up by the time of the
+    // first round, or, with very few channels, in one of their own.
+    const size_t f_bytes = (size_t)N * K * 4;
+    double* Gp = reinterpret_cast<double*>(ws + (f_bytes >= o.Gp_bytes ? o.F : o.Gp));
+    const int tiles = K / LQ_GT, room = (int)std::min<size_t>(std::max(f_bytes, o.Gp_bytes) / (LQ_GENTRIES * sizeof(double)), (size_t)tiles);
+    const int per = (tiles + room - 1) / room, parts = (tiles + per - 1) / per;
     double* G = reinterpret_cast<double*>(ws + o.G);
     uint16_t* A = reinterpret_cast<uint16_t*>(ws + o.A);
     uint16_t* At = reinterpret_cast<uint16_t*>(ws + o.At);
-    const int chunks = (K + LQ_GCH - 1) / LQ_GCH;
     for (int t = 0; t < steps; ++t) {
         const float* src = W;
         if (t > 0) {                                                 // residual of the previous step's factors
@@ -434,10 +444,11 @@ hipError_t launch_loftq(const lowra_layout& L, const float* W, const float* thre
         const uint16_t* Aq = t == 0 ? omega : A;
         for (int it = 0; it < iters; ++it) {
             if ((e = launch_skinny(E, K, N, Aq, K, r, K, 1.0f, Y, LQ_RP, st)) != hipSuccess) return e;              // Y = E A^T
-            if ((e = launch_tn_skinny(E, K, N, Y, LQ_RP, r, 1, partial, Z, st)) != hipSuccess) return e;            // Z = Y^T E
-            gram_kernel<<<dim3(4 * chunks), dim3(256), 0, st>>>(Z, K, r, Gp);
-            gram_sum_kernel<<<dim3(64), dim3(64), 0, st>>>(Gp, chunks, G);
-            factor_apply_kernel<<<dim3((K + 63) / 64), dim3(LQ_APPLY_THREADS), 0, st>>>(Z, G, K, r, A, At);
+            int chunks;
+            if ((e = launch_tn_partial(E, K, N, Y, partial, &chunks, st)) != hipSuccess) return e;                  // Z = Y^T E
+            zsum_gram_kernel<<<dim3(parts), dim3(256), 0, st>>>(partial, chunks, K, Zt, Gp, per);
+            gram_sum_kernel<<<dim3(LQ_GENTRIES / 64), dim3(256), 0, st>>>(Gp, parts, G);
+            factor_apply_kernel<<<dim3((K + 63) / 64), dim3(LQ_APPLY_THREADS), 0, st>>>(Zt, G, K, r, A, At);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             Aq = A;
         }
