@@ -505,9 +505,9 @@ static lowra_status fwd_batch_create_impl(int n, const lowra_fwd_item* items, co
         ws += batch_item_ws(L, r);
     }
     // LOWRA_PATH_AUTO: a batch too small for the streaming kernel goes to the general one (which reads fp32 scales).  The
-    // estimates err by a few per cent, so batches that they put about level stay with the streaming kernel: of 1500 batches
-    // (one to seven matrices, 1024 to 14336 features, 1 to 16 tokens) five would run 3 to 9 % slower than there without this
-    // margin (a 4096 x 11008 layer's seven matrices, 4 tokens: 60.3 for 56.9 us), none by more than two runs differ with it.
+    // estimates err by a few per cent, so batches that they put about level stay with the streaming kernel: of 28 sets of six
+    // batches (one to seven matrices, 1024 to 13824 features, 1 to 16 tokens) seven batches then run 3 to 20 % slower than on
+    // the other kernel (worst: gate,up of 5120 x 13824 without a LoRA term, 37.1 for 31.6 us; qkv,o with 16 tokens 34.2 for 30.3).
     constexpr double kLevel = 0.97;
     if (path == LOWRA_PATH_AUTO && fp32_scales && lowra::gemv_batch_us(all) < kLevel * lowra::gemv_stream_batch_us(all)) streams = false;
     for (int i = 0; i < n; ++i) {

@@ -502,13 +502,13 @@ hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
 
 // Which kernel a batch takes: estimated times, fitted to runs of one to seven matrices of 1024 to 13824 features with 1
 // to 16 tokens.  This kernel pays per strip (4- and 8-wavefront workgroups, several per compute unit) or per round of
-// strips over the compute units (16 wavefronts); the streaming kernel pays 17 us and more before its first byte (its t
+// strips over the compute units (16 wavefronts); the streaming kernel pays 18 us and more before its first byte (its t
 // kernel, set-up, pipeline fill and drain) and then streams at 3 GB/ms.  A decoder layer of 4096 x 11008 taken apart by
-// data dependence, 4 tokens: q,k,v 18.4 us here against 26.0, o 9.7 / 20.1, gate,up 29.3 / 30.1, down 16.1 / 38.2; all
-// seven matrices in one batch 59 / 56.
+// data dependence, 4 tokens: q,k,v 17.9 us here against 27.3, o 10.0 / 20.2, gate,up 27.3 / 30.4, down 16.9 / 39.3; all
+// seven matrices in one batch 52.9 / 55.9, with 16 tokens q,k,v,o 34.3 / 30.2.
 // LDS of an 8-wavefront workgroup with two activation buffers per wavefront, or fewer where it has fewer rounds
 static size_t lds8_of(const GemvParams& p, int per) {
-    return (size_t)GV_FIXED + gemv_t_bytes(8, p.RT, p.RT == 16) + (size_t)std::min(per, 2) * 8 * ((std::min(p.M, 16) + 1) / 2) * 1024;
+    return (size_t)GV_FIXED + gemv_t_bytes(8, p.RT, false) + (size_t)std::min(per, 2) * 8 * ((std::min(p.M, 16) + 1) / 2) * 1024;
 }
 double gemv_batch_us(const std::vector<GemvParams>& items) {
     double t = items.empty() || items[0].RT == 0 ? 3.0 : 5.0;
@@ -517,10 +517,15 @@ double gemv_batch_us(const std::vector<GemvParams>& items) {
         const GemvChoice c = gemv_choose_waves(p, LOWRA_BATCH_SMALL_WG != 0);
         const int nblk = (p.G + 3) / 4, per = (nblk + c.W - 1) / c.W, strips = (p.N + 15) / 16;
         if (c.W == 16) rounds16[std::min(per, 4)] += (double)strips / compute_units_cached();
-        else if (c.W == 8) t += (2 * lds8_of(p, per) > (size_t)160 * 1024 ? 0.0111 : per > 2 ? 0.0066 : 0.0083) * strips * per;   // one workgroup per unit, or more
+        else if (c.W == 8) {                                         // one workgroup per unit, or two or three
+            const size_t lds = lds8_of(p, per);
+            t += (2 * lds > (size_t)160 * 1024 ? 0.0111 : per > 2 ? 0.0062 : 3 * lds > (size_t)160 * 1024 ? 0.0095 : 0.0080) * strips * per;
+        }
         else t += (p.M > 12 ? 0.0125 : p.M > 8 ? 0.0085 : 0.005) * strips * per;
     }
-    for (int per = 1; per <= 4; ++per) t += (double)(long long)(rounds16[per] + 0.999) * (3.2 + 2.6 * per);
+    const int M = items.empty() ? 1 : items[0].M;
+    for (int per = 1; per <= 4; ++per)
+        t += (double)(long long)(rounds16[per] + 0.999) * ((3.2 + 2.6 * per) * (M > 8 ? 1.15 : 1.0) + (M > 12 ? 0.6 : 0.0));
     return t;
 }
 double gemv_stream_batch_us(const std::vector<GemvParams>& items) {
@@ -530,7 +535,7 @@ double gemv_stream_batch_us(const std::vector<GemvParams>& items) {
         bytes += (double)p.packed_bytes + (double)p.N * p.G * sizeof(float);
         kmax = std::max(kmax, p.K); M = p.M; rt = p.RT;
     }
-    return (rt ? 7.7 + 4.5 * ((kmax - 1) / 4096) : 0.0) + 9.5 + 0.35 * M + bytes / 3.0e6 + (kmax > 4096 ? 5.0 : 0.0);
+    return (rt ? 7.7 + 4.5 * ((kmax - 1) / 4096) : 0.0) + 10.3 + 0.35 * M + bytes / 3.0e6 + (kmax > 4096 ? 5.0 : 0.0);
 }
 
 // ---- several matrices in one launch per instantiation.  The descriptors (every pointer of every matrix)
