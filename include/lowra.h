@@ -308,8 +308,7 @@ lowra_status lowra_set_fwd_tiling(int rows_a, int rows_b, int cols_a);
 lowra_status lowra_plan_fwd_tiling(int N, int M, int compute_units, int* rows_a, int* rows_b, int* cols_a);
 
 /* Test and measurement hook: the plan of the mid-token GEMMs, which take linear calls under LOWRA_PATH_AUTO whose output
- * has too few tiles for the 256-column kernels.  While rows (32, 64, 96, 128 or 192 tokens a tile; the
- * input gradient takes 128 for 192) and splits (1..32 workgroups
+ * has too few tiles for the 256-column kernels.  While rows (32, 64, 96, 128 or 192 tokens a tile) and splits (1..32 workgroups
  * that share a tile's contraction; as many as it has steps, and one where the partial tiles would exceed 64 MiB) are set,
  * every call that no small-token kernel takes and whose K is at least 128 runs them with that plan;
  * lowra_set_mid_tiling(0, 0) returns to the planner.  The order of the fp32 sums depends on the splits.  Process-wide (one

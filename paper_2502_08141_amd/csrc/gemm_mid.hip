@@ -5,7 +5,7 @@
 // The 256-column kernels of gemm_fwd.hip and gemm_bwd.hip hold a compute unit with one workgroup of 256 x (128..256)
 // outputs that walks the whole contraction.  With few output tiles that leaves most of the chip idle: 128 tokens of a
 // 4096 x 4096 matrix are 16 workgroups and 64 steps in a row.  Here a workgroup owns 128 output columns x 32 TM tokens
-// (TM = 1..4, forward also 6), two or three of them share a compute unit and cover each other's latencies, and the contraction is split
+// (TM = 1..4 or 6), up to five of them share a compute unit and cover each other's latencies, and the contraction is split
 // between workgroups until they fill the chip; the splits leave fp32 partial tiles in accumulator order that
 // mid_sum_kernel adds in split order (deterministic, no atomics).  Any K from 128 on (an odd number of groups
 // included), any mix of widths, any number of codebooks.
@@ -28,8 +28,6 @@ typedef unsigned int u32x4v_t __attribute__((ext_vector_type(4)));
 typedef short mid_v4i16_t __attribute__((ext_vector_type(4)));
 typedef short mid_v8i16_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) mid_v4i16_t* mid_lds_v4i16_ptr;
-
-__device__ const uint4 mid_zeros[1] = {};        // what a transfer reads for features or channels past the end of a token's row
 
 // packed rows start at multiples of 8 bytes only (K = 64 x an odd number): no 16-byte alignment to rely on
 __device__ __forceinline__ uint4 load16_u(const uint8_t* q) {
@@ -427,7 +425,12 @@ struct BwdLds {
     // TAB0: WIDE with shared tables: all of them, once; else two buffers of a step's 64 rows (64 or 16 bytes each)
 };
 
-template <int TM, bool WIDE>
+// SHARED (with WIDE): at most kMidLutBooks codebooks, kept in LDS as a whole.
+// What bounds it: plain-ALU and LDS issue of the decode, 160 and 50 instructions per step beside 4 TM MFMAs (11008 x 4096, 333
+// tokens: VALU 30 % of a wavefront's life, LDS busy 40 % of the unit's, a quarter of that in conflicts).  So a step is one run
+// of instructions without branches (68.0 -> 64.2 us; 4096 x 1024, 777 tokens 30.3 -> 28.6), and tiles of 192 tokens halve the
+// decode of those of 96 (68.7 -> 63.2).
+template <int TM, bool WIDE, bool SHARED>
 __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     extern __shared__ __align__(16) uint8_t smem[];
     using L = BwdLds<TM, WIDE>;
@@ -445,13 +448,12 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     const int G = p.G, K = p.K, N = p.N;
     const int nsteps = (N + 63) >> 6;
     const int s_lo = split * p.per_split, s_hi = min(s_lo + p.per_split, nsteps);
-    const bool shared_tab = WIDE && p.C <= kMidLutBooks;
-    if (shared_tab)
+    if (SHARED)
         for (int e = tid; e < p.C * kTableStride; e += MID_THREADS) reinterpret_cast<float*>(smem + L::TAB0)[e] = p.mappings[e];
 
     // ---- activations: dY[m0.., 64 s ..], 128 bytes per token row, chunk c at c ^ ((row >> 1) & 7)
     const int m_last = p.M - 1 - m0;
-    const uint16_t* act0 = p.act + (size_t)m0 * N;
+    const bufdesc_t act = buffer_desc(p.act + (size_t)m0 * N);
     uint32_t voff[TM];
     int coff[TM];
 #pragma unroll
@@ -462,57 +464,51 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
     }
     auto issue = [&](int s, int buf) __attribute__((always_inline)) {
         const uint32_t dst = smem_lds + buf * L::A + wave * (TM * 1024);
-        if (s * 64 + 64 <= N) {
+        const int left = N - s * 64;                                  // channels past N are zeros, against the last row's weights again
 #pragma unroll
-            for (int i = 0; i < TM; ++i) dma16_s(act0 + s * 64, voff[i], dst + i * 1024);
-        } else {                                                      // channels past N are zeros, against the last row's weights again
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                if (coff[i] < N - s * 64) dma16_s(act0 + s * 64, voff[i], dst + i * 1024);
-                else dma16_s(mid_zeros, 0u, dst + i * 1024);
-            }
-        }
+        for (int i = 0; i < TM; ++i) dma16_b(act, coff[i] < left ? voff[i] : 0x80000000u, (uint32_t)s * 128u, dst + i * 1024);
     };
 
     // ---- mover role
     const int mrow = 16 * wave + (lane >> 2), piece = lane & 3;
     const int g0 = k0 >> 6;
     const bool two_groups = g0 + 1 < G;
-    // The step's wait counts four loads (codes, two scales, record) behind the activation transfers.  So the second scale is
-    // a load of its own in the last column tile as well, where it repeats the first (for columns that are never stored): its
-    // distance is opaque to the compiler, which can neither drop nor join the two, and none is replaced by zero: channels past
-    // N meet zero activations.
-    int second = __builtin_amdgcn_readfirstlane(two_groups ? 1 : 0);
-    asm volatile("" : "+s"(second));
-    struct Raw { uint4 codes; float4 lev; uint32_t a0, a1; RowInfo rec; };
+    // the scale I bring: piece 1 the tile's second group's (in the last column tile, where there is none, the first again, for
+    // columns that are never stored), the others the first's
+    const int my_group = g0 + (piece == 1 && two_groups ? 1 : 0);
+    struct Raw { uint4 codes; float4 lev; uint32_t a, e; RowInfo rec; };
+    const int sh = p.scale_bf16 ? 1 : 0;                              // bf16: the dword that holds the scale, no branch
+    const uint32_t* const scales = static_cast<const uint32_t*>(p.absmax);
     auto load_rec = [&](int s) -> RowInfo { return p.rows[min(s * 64 + mrow, N - 1)]; };
     auto load_raw = [&](int s, const RowInfo& rec, Raw& d) __attribute__((always_inline)) {
         const int ncl = min(s * 64 + mrow, N - 1), bits = rec.bits();
         const int row_bytes = K / 8 * bits;
         // a piece past the row's codes of this tile fetches the last one again; 16 bytes before the row's end at the latest
         const int off = min(k0 / 8 * bits + 16 * min(piece, bits - 1), row_bytes - 16);
-        d.codes = load16_u(p.packed + rec.offset + off);
-        if (!shared_tab) d.lev = *reinterpret_cast<const float4*>(p.mappings + (size_t)rec.cb() * kTableStride + (WIDE ? 4 * piece : 0));
-        d.a0 = load_scale(p, (size_t)ncl * G + g0);
-        d.a1 = load_scale(p, (size_t)ncl * G + g0 + second);
+        d.codes = load16_u(p.packed + (uint32_t)(rec.offset + (uint32_t)off));
+        if (!SHARED) d.lev = *reinterpret_cast<const float4*>(p.mappings + (size_t)rec.cb() * kTableStride + (WIDE ? 4 * piece : 0));
+        d.e = (uint32_t)ncl * (uint32_t)G + (uint32_t)my_group;
+        d.a = scales[d.e >> sh];
         d.rec = rec;
     };
+    // (without branches: the four movers of a row write its record's four words, and what pieces past a narrow row's second
+    // repeat goes to the same place)
+    const int slot = WIDE ? piece : min(piece, 1);
     auto stage_in = [&](int buf, const Raw& d) __attribute__((always_inline)) {
-        if (WIDE || piece < 2)
-            *reinterpret_cast<uint4*>(smem + L::C0 + buf * L::C + mrow * (WIDE ? 64 : 32) + ((piece ^ (WIDE ? (mrow >> 2) & 3 : (mrow >> 3) & 1)) << 4)) = d.codes;
-        if (piece == 0)
-            *reinterpret_cast<uint4*>(smem + L::META0 + buf * 1024 + mrow * 16) = make_uint4(scale_of(p, d.a0), scale_of(p, d.a1), d.rec.bits_cb, 0u);
-        if (WIDE && !shared_tab) {                                    // level q of row r at 256 q + 4 r: a lookup touches bank r whatever the code
+        *reinterpret_cast<uint4*>(smem + L::C0 + buf * L::C + mrow * (WIDE ? 64 : 32) + ((slot ^ (WIDE ? (mrow >> 2) & 3 : (mrow >> 3) & 1)) << 4)) = d.codes;
+        const uint32_t scale = (d.a >> ((d.e & sh) * 16)) << (sh * 16);
+        *reinterpret_cast<uint32_t*>(smem + L::META0 + buf * 1024 + mrow * 16 + piece * 4) = piece == 2 ? d.rec.bits_cb : scale;
+        if (WIDE && !SHARED) {                                        // level q of row r at 256 q + 4 r: a lookup touches bank r whatever the code
             float* tab = reinterpret_cast<float*>(smem + L::TAB0 + buf * (64 * ROWTAB) + piece * 1024 + mrow * 4);
             tab[0] = d.lev.x; tab[64] = d.lev.y; tab[128] = d.lev.z; tab[192] = d.lev.w;
-        } else if (!WIDE && piece == 0) {
+        } else if (!WIDE) {
             *reinterpret_cast<float4*>(smem + L::TAB0 + buf * (64 * ROWTAB) + mrow * ROWTAB) = d.lev;
         }
     };
 
     // ---- decoder role: 32 weights of row `lane`, features 32 wave .. + 31 of the tile (group wave / 2)
     const bool tail_shift = !two_groups && K >= 128;                  // a 1-bit row's 16 bytes then start one group early
-    const int tab_shift = shared_tab ? 2 : 8;                         // uniform
+    constexpr int tab_shift = SHARED ? 2 : 8;
     struct Dec { uint32_t lo, hi, c4[4]; float a, v[2][8]; int bits; const uint8_t* tb; uint32_t SL, SH; };
     Dec d;
     auto decode_begin = [&](int buf) __attribute__((always_inline)) {
@@ -530,7 +526,7 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
         d.hi = (wave & 1) ? q.w : q.y;
         if (WIDE) {
             d.c4[0] = q.x; d.c4[1] = q.y; d.c4[2] = q.z; d.c4[3] = q.w;
-            d.tb = smem + L::TAB0 + (shared_tab ? (int)(meta.z >> 8) * (kTableStride * 4) : buf * (64 * ROWTAB) + lane * 4);
+            d.tb = smem + L::TAB0 + (SHARED ? (int)(meta.z >> 8) * (kTableStride * 4) : buf * (64 * ROWTAB) + lane * 4);
         } else {
             const NarrowConsts nk = narrow_consts(!one);
             const float4 lv = *reinterpret_cast<const float4*>(smem + L::TAB0 + buf * (64 * ROWTAB) + lane * ROWTAB);
@@ -642,9 +638,9 @@ __global__ __launch_bounds__(MID_THREADS, 2) void mid_bwd_kernel(MidParams p) {
         decode_look(3);
         decode_put(2, wn);
         decode_put(3, wn);
-        // the activation transfers of step s + 1 are older than the loads for the steps ahead: at least four of those
-        // (codes, two scales, record) may stay in flight
-        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        // the activation transfers of step s + 1 are older than the loads for the steps ahead: at least three of those
+        // (codes, scale, record) may stay in flight
+        asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
         __syncthreads();
         stage_in(b ^ 1, raw);                                         // step s + 3
         asm volatile("" : "+v"(rec.offset), "+v"(rec.bits_cb));       // wait for the record here, not behind the transfers below
@@ -729,19 +725,27 @@ hipError_t launch_mid_fwd_any(const MidParams& p, hipStream_t st) {
     return (p.G & 1) ? launch_mid_fwd<TM, WIDE, true>(p, grid, st) : launch_mid_fwd<TM, WIDE, false>(p, grid, st);
 }
 
+template <int TM, bool WIDE, bool SHARED>
+hipError_t launch_mid_bwd(const MidParams& p, unsigned grid, hipStream_t st) {
+    using L = BwdLds<TM, WIDE>;
+    constexpr int most = L::TAB0 + 2 * 64 * (WIDE ? 64 : 16);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mid_bwd_kernel<TM, WIDE, SHARED>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (attr != hipSuccess) return attr;
+    const int sh = SHARED ? L::TAB0 + p.C * kTableStride * 4 : most;
+    static_assert(kMidLutBooks * kTableStride * 4 <= 2 * 64 * 64, "either table scheme fits the region");
+    mid_bwd_kernel<TM, WIDE, SHARED><<<dim3(grid), dim3(MID_THREADS), sh, st>>>(p);
+    return hipGetLastError();
+}
+
 template <int TM, bool WIDE>
 hipError_t launch_mid_variant(const MidParams& p, int op, hipStream_t st) {
     const unsigned grid = (unsigned)(p.ntiles * p.splits);
     if (op == 0) {
         return launch_mid_fwd_any<TM, WIDE>(p, st);
     } else {
-        using L = BwdLds<TM, WIDE>;
-        constexpr int most = L::TAB0 + 2 * 64 * (WIDE ? 64 : 16);
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(mid_bwd_kernel<TM, WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
-        if (attr != hipSuccess) return attr;
-        const int sh = WIDE && p.C <= kMidLutBooks ? L::TAB0 + p.C * kTableStride * 4 : most;
-        static_assert(kMidLutBooks * kTableStride * 4 <= 2 * 64 * 64, "either table scheme fits the region");
-        mid_bwd_kernel<TM, WIDE><<<dim3(grid), dim3(MID_THREADS), sh, st>>>(p);
+        const bool shared = WIDE && p.C <= kMidLutBooks;
+        const hipError_t e = shared ? launch_mid_bwd<TM, WIDE, WIDE>(p, grid, st) : launch_mid_bwd<TM, WIDE, false>(p, grid, st);
+        if (e != hipSuccess) return e;
     }
     return hipGetLastError();
 }
@@ -754,12 +758,12 @@ hipError_t launch_mid_variant(const MidParams& p, int op, hipStream_t st) {
 // and `share` us per resident workgroup once their instructions fill it.  The figures are fits to timings of every height
 // with 1 to 24 splits (8 shapes from 1024 x 1024 to 5120 x 13824, an odd group count among them, 24 to 2048 tokens; calls
 // repeated on two sets of buffers, without a rank-r term).  Forward: 5040 timings, rms error 8 %, the plan picked within
-// 0.4 to 0.9 % of the best one measured on average.  Input gradient: 2493, 7 - 14 %, 1 %.  The 256-column kernels' time,
-// fitted in the same way, is compared with it: they win once their tiles fill the chip.  Forward, 4096 x 4096, 2048 tokens:
-// 50/50 % of 1-/2-bit rows 72 us against 73 here, 50/25/25 % of 1-/2-/4-bit rows 96 against 88.  Input gradient from about
-// 700 tokens on: 2048 tokens of 50/50 % 80 us against 94.
+// 0.4 to 0.9 % of the best one measured on average.  Input gradient: 5721, 7 - 8 %, 0.4 to 0.7 %.  The 256-column kernels'
+// time, fitted in the same way, is compared with it: they win once their tiles fill the chip.  Forward, 4096 x 4096, 2048
+// tokens: 50/50 % of 1-/2-bit rows 72 us against 73 here, 50/25/25 % of 1-/2-/4-bit rows 96 against 88; input gradient 80
+// against 94, and with 4-bit rows level (98.6), from about 1000 tokens on.
 constexpr int kHeights = 5;
-static const int kMidHeight[kHeights] = {1, 2, 3, 4, 6};              // TM: 32 tokens each; 6 in the forward only
+static const int kMidHeight[kHeights] = {1, 2, 3, 4, 6};              // TM: 32 tokens each
 struct MidCost {
     double solo[kHeights], share[kHeights];  // us per step (64 of the contraction)
     double launch, round, split, per_byte;   // us per call; per round of workgroups; more when split; per byte of partial tiles
@@ -771,13 +775,11 @@ static const MidCost kMidCost[2][3] = {
      {{0.46, 0.51, 0.61, 0.69, 0.81}, {0.35, 0.41, 0.47, 0.54, 0.74}, 5.6, 0.1, 2.9, 3.1e-7, 10.7, 1.70},
      {{0.46, 0.53, 0.61, 0.68, 0.80}, {0.33, 0.42, 0.47, 0.57, 0.81}, 5.4, 0.3, 3.2, 2.9e-7, 11.6, 1.73}},
     // input gradient
-    {{{0.62, 0.73, 0.81, 0.95}, {0.47, 0.55, 0.58, 0.66}, 6.0, 0.0, 4.7, 2.8e-7, 14.8, 1.28},
-     {{0.80, 1.01, 0.95, 1.01}, {0.51, 0.65, 0.68, 0.76}, 7.1, 0.0, 4.3, 2.7e-7, 9.6, 2.03},
-     {{0.78, 0.84, 1.00, 1.00}, {0.64, 0.68, 0.70, 0.80}, 8.7, 0.0, 2.8, 2.8e-7, 14.8, 2.50}}};
-// Workgroups per compute unit that the fits were made with.  Forward: what the kernels hold by registers and LDS, without
-// and with 4-bit rows.  Input gradient: part of the fitted model, not what a build holds (3, 2, 2, 2, and with 4-bit rows of
-// more than kMidLutBooks codebooks 2, 2, 2, 1); the fitted step times took up the difference.
-static const int kMidResident[2][2][kHeights] = {{{5, 4, 3, 2, 1}, {4, 3, 2, 2, 1}}, {{3, 3, 2, 2}, {3, 3, 2, 2}}};
+    {{{0.56, 0.61, 0.71, 0.89, 0.98}, {0.38, 0.46, 0.51, 0.63, 0.87}, 4.5, 0.1, 2.9, 4.2e-7, 7.3, 1.22},
+     {{0.56, 0.73, 0.82, 0.90, 1.13}, {0.46, 0.56, 0.62, 0.71, 1.13}, 5.4, 1.0, 2.9, 3.3e-7, 9.4, 1.72},
+     {{0.69, 0.69, 0.80, 0.92, 1.37}, {0.53, 0.54, 0.66, 0.50, 1.29}, 5.5, 1.0, 2.2, 3.9e-7, 6.9, 2.72}}};
+// Workgroups per compute unit that the fits were made with: what the kernels hold by registers and LDS, by class as above.
+static const int kMidResident[2][3][kHeights] = {{{5, 4, 3, 2, 1}, {4, 3, 2, 2, 1}, {4, 3, 2, 2, 1}}, {{3, 2, 2, 2, 1}, {3, 2, 2, 2, 1}, {2, 2, 2, 1, 1}}};
 
 static std::atomic<int> g_mid_forced{0};                              // rows << 8 | splits
 void force_mid_plan(int rows, int splits) { g_mid_forced.store(rows << 8 | splits); }
@@ -789,7 +791,7 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
     const int tiles_c = (cols + kMidCols - 1) / kMidCols, cus = device_compute_units();
     const size_t cap = std::min(part_bytes, kMidPartMax);
     if (const int forced = g_mid_forced.load()) {
-        const int TM = op == 1 ? std::min((forced >> 8) / 32, 4) : (forced >> 8) / 32, per = (units + (forced & 255) - 1) / (forced & 255);
+        const int TM = (forced >> 8) / 32, per = (units + (forced & 255) - 1) / (forced & 255);
         best = MidPlan{TM, tiles_c, (M + 32 * TM - 1) / (32 * TM), (units + per - 1) / per, per};
         if (best.splits > 1 && mid_part_bytes(best) > cap) { best.splits = 1; best.per_split = units; }
         return best;
@@ -798,12 +800,10 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
     const int cls = !wide ? 0 : C <= kMidLutBooks ? 1 : 2;
     const MidCost& mc = kMidCost[op][cls];
     double best_t = 1e300;
-    // with a table per row the input gradient's LDS holds one workgroup of four tile rows per compute unit, not two
-    const int heights = op == 0 ? 5 : cls == 2 ? 3 : 4;
-    for (int i = 0; i < heights && (i == 0 || 32 * kMidHeight[i - 1] < M); ++i) {
+    for (int i = 0; i < kHeights && (i == 0 || 32 * kMidHeight[i - 1] < M); ++i) {
         const int TM = kMidHeight[i];
         MidPlan pl{TM, tiles_c, (M + 32 * TM - 1) / (32 * TM), 0, 0};
-        const int res = kMidResident[op][wide][i];
+        const int res = kMidResident[op][cls][i];
         for (int S = 1; S <= kMidMaxSplits && S <= units; S += S < 6 ? 1 : S < 12 ? 2 : 4) {
             pl.per_split = (units + S - 1) / S;
             pl.splits = (units + pl.per_split - 1) / pl.per_split;
@@ -821,9 +821,7 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
         const BwdSplitPlan sp = gemm_bwd_split_plan(N, K, M);
         if (sp.splits > 1) big_t += 5.0 + (double)sp.splits * sp.tail * BM * BN * sizeof(float) * mc.per_byte;
     }
-    // (the two estimates' errors are about this large; input gradient: without the margin 2048 tokens of a 4096 x 4096
-    // layer came here and a training step on it took 1 % longer)
-    if (big_t <= (op == 0 ? 1.02 : 1.08) * best_t) best = MidPlan{0, 0, 0, 0, 0};
+    if (big_t <= 1.02 * best_t) best = MidPlan{0, 0, 0, 0, 0};        // (about level: the 256-column kernels need no partial tiles)
     return best;
 }
 
@@ -840,7 +838,7 @@ hipError_t launch_gemm_mid(const MidParams& p_in, int op, int TM, bool wide, hip
         if (TM == 2) e = wide ? launch_mid_variant<2, true>(p, op, st) : launch_mid_variant<2, false>(p, op, st);
         if (TM == 3) e = wide ? launch_mid_variant<3, true>(p, op, st) : launch_mid_variant<3, false>(p, op, st);
         if (TM == 4) e = wide ? launch_mid_variant<4, true>(p, op, st) : launch_mid_variant<4, false>(p, op, st);
-        if (TM == 6 && op == 0) e = wide ? launch_mid_fwd_any<6, true>(p, st) : launch_mid_fwd_any<6, false>(p, st);
+        if (TM == 6) e = wide ? launch_mid_variant<6, true>(p, op, st) : launch_mid_variant<6, false>(p, op, st);
         if (e != hipSuccess) return e;
         if (p.splits <= 1) continue;
         mid_sum_kernel<<<dim3((unsigned)((size_t)p.ntiles * TM * 4)), dim3(256), 0, st>>>(reinterpret_cast<const float4*>(p.part), p.splits, p.ntiles, p.tile0,

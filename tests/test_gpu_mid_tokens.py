@@ -114,6 +114,28 @@ def test_every_variant(rows, K, splits, tables):
         assert rel_err(g, ref) <= REL_TOL and rel_err(g, bf16_host_f64(gemm)) <= ORDER_TOL
 
 
+# Tiles of 192 tokens of the input gradient, in every class of tables (with 4-bit rows: up to 64 codebooks, or more).
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("tables", ["narrow", "shared", "channel"])
+def test_input_gradient_of_192_token_tiles(splits, tables):
+    N, K, M, r = 328, 1088, 209, 40
+    L = synth.make_custom(N, K, M, r, fractions=NARROW if tables == "narrow" else MIXED, seed=600 + splits, per_channel_tables=tables == "channel")
+    D = DeviceLayer(L)
+    if splits == 3:
+        D.layout.set_scale_dtype(torch.bfloat16)
+    packed, absmax = lowra.lowra_quantize(D.layout, D.W, D.thr)
+    rp, ra = orc.quantize(L.W, L.bits, L.cb, L.thresholds, **({"scale_dtype": "bf16"} if splits == 3 else {}))
+    ref = orc.linear_bwd_input(rp, ra, L.bits, L.cb, L.mappings, L.dY, L.A, L.B, L.s, L.K)
+    lowra.lowra_set_mid_tiling(192, splits)
+    try:
+        assert lowra.lowra_plan_mid_tiling(lowra.OP_LINEAR_BWD_INPUT, N, K, M, tables != "narrow", L.mappings.shape[0]) == (192, splits)
+        got = lowra.lowra_linear_bwd_input(D.layout, packed, absmax, D.mp, D.dY, D.A, D.B, L.s)
+    finally:
+        lowra.lowra_set_mid_tiling()
+    torch.cuda.synchronize()
+    assert rel_err(bf16_host_f64(got), ref) <= REL_TOL
+
+
 # The forward's instantiations of the other parity of the number of groups (with an odd one the codes are staged in pieces
 # that start 8 bytes early, and the last superstep is not staged at all: three groups are that superstep alone), and its
 # tiles of 192 tokens.
