@@ -278,8 +278,9 @@ hipError_t launch_learn_tables(const lowra_layout& L, const float* W, const floa
 // Threshold averaging (Sec. 5): entry j of every b-bit channel becomes the mean of entry j over
 // the matrix's b-bit channels.  One workgroup per (width, entry): fixed-order fp64 sum, then the
 // write-back.  In place on thr [N][16].  A column's entries lie in one cache line each, so a workgroup's time is
-// that of its round trips: 1024 threads with twelve channels each in flight per trip.  11008 channels, half of
-// them 1- and half 2-bit: 14.5 us; 256 threads with one dependent pair of loads at a time took 34.
+// that of its round trips: 1024 threads with twelve channels each in flight per trip, and no record is read a second
+// time for the write-back while one trip covers the matrix.  11008 channels, half of them 1- and half 2-bit: 13.2 us; with a
+// record per store in turn 14.6; 256 threads with one dependent pair of loads at a time took 34.
 __global__ __launch_bounds__(1024) void average_thresholds_kernel(const RowInfo* __restrict__ rows, int N, float* __restrict__ thr) {
     __shared__ double part[16];
     __shared__ int cnt_part[16];
@@ -290,15 +291,22 @@ __global__ __launch_bounds__(1024) void average_thresholds_kernel(const RowInfo*
     constexpr int U = 12;
     double s = 0.0;
     int c = 0;
+    // which of the channels n0, n0 + 1024, .. of a trip have my width: bit i
+    auto mine_of = [&](int n0) __attribute__((always_inline)) -> unsigned {
+        unsigned m = 0;
+#pragma unroll
+        for (int i = 0; i < U; ++i) m |= n0 + 1024 * i < N && (int)(rows[min(n0 + 1024 * i, N - 1)].bits_cb & 0xffu) == b ? 1u << i : 0u;
+        return m;
+    };
+    unsigned mine = 0;
     for (int n0 = tid; n0 < N; n0 += 1024 * U) {
-        bool mine[U];
+        mine = mine_of(n0);
         float v[U];
 #pragma unroll
-        for (int i = 0; i < U; ++i) mine[i] = n0 + 1024 * i < N && (int)(rows[min(n0 + 1024 * i, N - 1)].bits_cb & 0xffu) == b;
+        for (int i = 0; i < U; ++i) v[i] = mine >> i & 1 ? thr[(size_t)(n0 + 1024 * i) * kTableStride + j] : 0.0f;
 #pragma unroll
-        for (int i = 0; i < U; ++i) v[i] = mine[i] ? thr[(size_t)(n0 + 1024 * i) * kTableStride + j] : 0.0f;
-#pragma unroll
-        for (int i = 0; i < U; ++i) { s += (double)v[i]; c += mine[i] ? 1 : 0; }
+        for (int i = 0; i < U; ++i) s += (double)v[i];
+        c += __popc(mine);
     }
     s = wave_sum(s);
     for (int o = 32; o; o >>= 1) c += __shfl_xor(c, o);
@@ -310,8 +318,12 @@ __global__ __launch_bounds__(1024) void average_thresholds_kernel(const RowInfo*
     for (int w = 0; w < 16; ++w) { tot += part[w]; cnt += cnt_part[w]; }
     if (cnt == 0) return;
     const float m = (float)(tot / (double)cnt);
-    for (int n = tid; n < N; n += 1024)
-        if ((int)(rows[n].bits_cb & 0xffu) == b) thr[(size_t)n * kTableStride + j] = m;
+    for (int n0 = tid; n0 < N; n0 += 1024 * U) {
+        if (N > 1024 * U) mine = mine_of(n0);                           // uniform; one trip: still at hand
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (mine >> i & 1) thr[(size_t)(n0 + 1024 * i) * kTableStride + j] = m;
+    }
 }
 
 hipError_t launch_average_thresholds(const lowra_layout& L, float* thr, hipStream_t st) {
