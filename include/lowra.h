@@ -327,10 +327,10 @@ lowra_status lowra_plan_mid_tiling(int op, int N, int K, int M, int has_4bit, in
  * same activations, or a pass over a whole weight set).  A single matrix at 1-2 bits is only a few MB,
  * less than the chip must have in flight to cover one memory round trip, so one launch per matrix cannot
  * stream at the memory's rate; here every pointer of every matrix is fixed when the batch is created
- * (descriptors in device memory), and a run is one launch for the rank-r partial sums plus one launch
- * per group of matrices that take the same kernel instantiation.  Per matrix the arithmetic is that of
- * lowra_linear_fwd on the small-token path (the contraction may be split over another number of
- * wavefronts: same sums, fp32 order may differ).
+ * (descriptors in device memory), and a run is at most one launch for the rank-r partial sums (none
+ * where the workgroups form them) plus one launch per group of matrices that take the same kernel
+ * instantiation.  Per matrix the arithmetic is that of lowra_linear_fwd on the small-token path (the
+ * contraction may be split over another number of wavefronts: same sums, fp32 order may differ).
  *   items: host array of n entries (read during create only); every pointer in an item is a device
  *   pointer with the layout / dtype of the same argument of lowra_linear_fwd; the tensors must stay
  *   valid and in place for the life of the batch; items may share x, A, B but not y.
