@@ -28,11 +28,11 @@ __device__ __forceinline__ void t_partial_body(const uint16_t* __restrict__ x, i
         floatx4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[j], xf[j], acc, 0, 0, 0);
-        // lane (i, kg) holds D[rank 16 c + 4 kg + v][token i]
+        // lane (i, kg) holds D[rank 16 c + 4 kg + v][token i]; ranks past r are zeros whatever x holds (zeros of A times an
+        // infinity would be none)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) tp[((size_t)b * 16 + i) * RT + c * 16 + 4 * kg + v] = acc[v];
+        for (int v = 0; v < 4; ++v) tp[((size_t)b * 16 + i) * RT + c * 16 + 4 * kg + v] = c * 16 + 4 * kg + v < r ? acc[v] : 0.0f;
     }
 }
-
 
 }  // namespace lowra

@@ -43,3 +43,24 @@ def test_an_infinite_adapter_entry_stays_in_its_rank():
     x[:, 7] = 1.0
     got = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, x, A, B, 1.0).float()
     assert torch.isposinf(got).all()
+
+
+@pytest.mark.parametrize("K", [64, 192, 320, 1088, 2112, 4160])
+@pytest.mark.parametrize("r", [0, 8, 24])
+@pytest.mark.parametrize("M", [1, 16])
+def test_an_infinite_last_feature_stays_infinite(K, r, M):
+    """What fills up the last block of 256 features, and the ranks up to 16 or 32, must not make a NaN of an infinity."""
+    N = 40
+    L = synth.make_custom(N, K, M, max(r, 1), fractions=(0.4, 0.3, 0.3), seed=K + r)
+    D = DeviceLayer(L)
+    D.quantize()
+    sign = torch.sign(lowra.lowra_dequantize(D.layout, D.packed, D.absmax, D.mp)[:, -1])
+    assert (sign != 0).all()
+    x, A, B = D.x.clone(), None, None
+    x[:, -1] = float("inf")
+    if r:                                                    # a term of the same sign
+        A, B = D.A.clone(), sign[:, None].expand(N, r).contiguous()
+        A[:, -1] = 1.0
+    got = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, x, A, B, 1.0).float()
+    want = (sign.float() * float("inf")).expand(M, N)
+    assert torch.equal(got, want)
