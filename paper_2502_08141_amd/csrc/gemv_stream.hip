@@ -469,7 +469,8 @@ __device__ __forceinline__ void gs_t_body(const GsTItem it) {
     for (int o = threadIdx.x; o < 16 * GS_TROW; o += GS_THREADS) {
         float v = 0.0f;
         for (int w = 0; w < GS_W; ++w) v += tsum[w][o / GS_TROW][o % GS_TROW];
-        as_global(it.t)[o] = (uint16_t)(pack_bf16x2(v * it.s, 0.0f) & 0xffffu);
+        // (a rank past r was formed as zeros of A times x: no zero where x is infinite)
+        as_global(it.t)[o] = o % GS_TROW < it.r ? (uint16_t)(pack_bf16x2(v * it.s, 0.0f) & 0xffffu) : 0;
     }
 }
 __global__ __launch_bounds__(GS_THREADS) void gemv_stream_t_kernel(const GsTItem* __restrict__ items) { gs_t_body(items[blockIdx.x]); }

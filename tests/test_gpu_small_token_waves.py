@@ -64,3 +64,28 @@ def test_an_infinite_last_feature_stays_infinite(K, r, M):
     got = lowra.lowra_linear_fwd(D.layout, D.packed, D.absmax, D.mp, x, A, B, 1.0).float()
     want = (sign.float() * float("inf")).expand(M, N)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("path", [lowra.PATH_GEMV, lowra.PATH_GEMV_GENERAL])
+@pytest.mark.parametrize("r", [0, 8, 24])
+def test_an_infinite_feature_in_a_batch(path, r):
+    """Either kernel of a batch: ranks past r, which it fills up, must not make a NaN of an infinity."""
+    N, K, M = 40, 1024, 3
+    L = synth.make_custom(N, K, M, max(r, 1), fractions=(0.4, 0.3, 0.3), seed=r)
+    D = DeviceLayer(L)
+    D.quantize()
+    sign = torch.sign(lowra.lowra_dequantize(D.layout, D.packed, D.absmax, D.mp)[:, 5])
+    x, A, B = D.x.clone(), None, None
+    x[:, 5] = float("inf")
+    if r:
+        A, B = D.A.clone(), sign[:, None].expand(N, r).contiguous()
+        A[:, 5] = 1.0
+    lowra.lowra_set_linear_path(path)
+    try:
+        batch = lowra.FwdBatch([(D.layout, D.packed, D.absmax, x, A, B)] * 2, D.mp, 1.0)
+    finally:
+        lowra.lowra_set_linear_path(lowra.PATH_AUTO)
+    want = (sign.float() * float("inf")).expand(M, N)
+    for y in batch.run():
+        assert torch.equal(y.float(), want)
+    batch.close()
