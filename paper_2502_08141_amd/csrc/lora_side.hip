@@ -192,7 +192,7 @@ __device__ __forceinline__ void skinny_nt_body(const uint16_t* __restrict__ P, i
 #pragma unroll
             for (int e = 0; e < PER; ++e) {
                 const int idx = threadIdx.x + 64 * NC * e, mo = m0 + idx / RP;
-                if (mo < M) out[(size_t)mo * RP + idx % RP] = (uint16_t)(pack_bf16x2(total[e] * s, 0.0f) & 0xffffu);
+                if (mo < M) out[(size_t)mo * RP + idx % RP] = idx % RP < r ? (uint16_t)(pack_bf16x2(total[e] * s, 0.0f) & 0xffffu) : 0;
             }
         }
     }
@@ -214,6 +214,7 @@ __device__ __forceinline__ void skinny_nt_body(const uint16_t* __restrict__ P, i
 #pragma unroll
         for (int w = 0; w < NC; ++w) v += red[(w * PR + row) * RP + col];
         const int mo = m0 + row;
+        if (col >= r) v = 0.0f;                                      // (formed as P times zeros, which is NaN where P is infinite)
         if (mo < M) {
             if (partial) partial[((size_t)slice_of * M + mo) * RP + col] = v;            // one slice: unscaled, summed later
             else out[(size_t)mo * RP + col] = (uint16_t)(pack_bf16x2(v * s, 0.0f) & 0xffffu);

@@ -79,3 +79,29 @@ def test_adapter_gradients_form_the_same_products(N, K, M, r, path):
             assert torch.equal(dA, rA) and torch.equal(dB, rB), f"least workspace: {least}"
     finally:
         lowra.lowra_set_linear_path(lowra.PATH_AUTO)
+
+
+@pytest.mark.parametrize("N,K,M,r", [(264, 1600, 40, 8), (264, 4160, 333, 40), (1600, 2048, 700, 24), (264, 1024, 1200, 5)])
+def test_infinite_activations_stay_in_their_ranks(N, K, M, r):
+    """What fills the intermediate up to 64 ranks is zero whatever the activations hold: zeros of A or B times an infinity are none."""
+    D = DeviceLayer(synth.make_custom(N, K, M, r, fractions=(0.5, 0.5, 0.0), seed=850 + r))
+    D.quantize()
+    What = lowra.lowra_dequantize(D.layout, D.packed, D.absmax, D.mp)
+    for op, call, act, W in ((lowra.OP_LINEAR_FWD, lowra.lowra_linear_fwd, D.x, What), (lowra.OP_LINEAR_BWD_INPUT, lowra.lowra_linear_bwd_input, D.dY, What.T)):
+        a, A, B = act.clone(), D.A.clone(), D.B.clone()
+        a[1, 3] = float("inf")
+        sign = torch.sign(W[:, 3]).bfloat16()                # a rank-r term of the weights' signs
+        assert (sign != 0).all()
+        if op == lowra.OP_LINEAR_FWD:
+            A[:, 3], B[:] = 1.0, sign[:, None]
+        else:
+            B[3], A[:] = 1.0, sign
+        full = D.layout.workspace_bytes(op, M, r)
+        run = lambda ws: call(D.layout, D.packed, D.absmax, D.mp, a, A, B, 1.0, workspace=ws)
+        for size in (full, least_workspace(run, full)):
+            ws = torch.full((size,), 0xff, dtype=torch.uint8, device="cuda")
+            out = run(ws).float()
+            side = lowra.lowra_linear_side_product(D.layout, op, M, r, ws)
+            assert torch.isposinf(side[1, :r]).all() and not side[:, r:].any()
+            assert torch.equal(out[1], sign.float() * float("inf"))
+            assert torch.isfinite(out[0]).all() and torch.isfinite(out[2:]).all()
