@@ -81,22 +81,22 @@ __device__ __forceinline__ void transpose4(uint32_t (&z)[4]) {
 
 constexpr int GV_LEV = 20;                   // floats per channel of the staged levels
 constexpr int GV_FIXED = 16 * GV_TABROW + 16 * GV_LEV * 4 + 64;      // LDS in front of t
-// Sums that a workgroup keeps per entry of t: one of every wavefront's block (FUSE), or of the blocks that its threads share
-// between them; and their bytes
-constexpr int gemv_t_parts(int W, int RT, bool fuse) { return RT == 0 ? 0 : fuse ? W : 16 * RT < W * 64 ? W * 64 / (16 * RT) : 1; }
-constexpr int gemv_t_bytes(int W, int RT, bool fuse) { return gemv_t_parts(W, RT, fuse) * 16 * RT * 4; }
+// Sums that a workgroup keeps per entry of t: one of every wavefront's block (FUSE), with several rounds one of the blocks that
+// each of an entry's threads adds up, else the whole sum, scaled and rounded to bf16; and their bytes
+constexpr int gemv_t_parts(int W, int PER, int RT, bool fuse) { return RT == 0 ? 0 : fuse ? W : PER > 1 && 16 * RT < W * 64 ? W * 64 / (16 * RT) : 1; }
+constexpr int gemv_t_bytes(int W, int PER, int RT, bool fuse) { return gemv_t_parts(W, PER, RT, fuse) * 16 * RT * (PER > 1 || fuse ? 4 : 2); }
 
 // FUSE: t comes from the workgroup itself (one round, r <= 16); else from the partial sums in p.tp
 template <int W, int PER, bool FUSE>
 __device__ __forceinline__ void gemv_body(const GemvParams& p, const int strip) {
     static_assert(!FUSE || PER == 1, "a wavefront forms t beside the products of its only block");
     extern __shared__ __align__(16) uint8_t gv_smem[];
-    // LDS: pair tables [16 channels][GV_TABROW bytes] | levels [16][GV_LEV] | channel numbers [16] | sums of t [tparts][16 tokens][RT] |
+    // LDS: pair tables [16 channels][GV_TABROW bytes] | levels [16][GV_LEV] | channel numbers [16] | t: sums [tparts][16 tokens][RT] or bf16 [16][RT] |
     //      [xbufs buffers][W pieces][rows2 KB] activations (rows2 = pairs of token rows; xbufs = all
     //      rounds when they fit, else 2).  After its last round a wavefront reuses the head of its
     //      piece of buffer 0 for its partial results [16 channels][16 tokens].
     constexpr int LEV0 = 16 * GV_TABROW, NL0 = LEV0 + 16 * GV_LEV * 4, T0 = GV_FIXED;
-    const int nt = 16 * p.RT, X0 = T0 + p.tparts * nt * 4;
+    const int nt = 16 * p.RT, X0 = T0 + p.tparts * nt * (PER > 1 || FUSE ? 4 : 2);
     float* t_lds = reinterpret_cast<float*>(gv_smem + T0);
     const int rows2 = (min(p.M, 16) + 1) >> 1;
     const int XPIECE = rows2 * 1024, XBUF = W * XPIECE;
@@ -113,11 +113,12 @@ __device__ __forceinline__ void gemv_body(const GemvParams& p, const int strip) 
 
     // What a strip waits for is a chain: row record -> codes, scales and levels -> pair tables -> products.  So the record is
     // asked for first, and A, which takes longest, behind it.  Loads come back in order and the compiler does not count the
-    // transfers, so activations and sums of t follow the codes where one strip has the unit to itself (one round: 9.6 -> 9.2 us
-    // for 4096 x 4096); with several rounds they fill the wait for the record (11008 x 4096: 16.4 -> 15.2).
+    // transfers: what it waits for, it waits for with transfers behind it.  So with one round activations and sums of t are
+    // asked for behind the levels, which the pair tables wait for (4096 x 4096, rank 64, 1 to 16 tokens: 1.2 % less than in
+    // front of the levels' write); with several rounds they fill the wait for the record (11008 x 4096: 16.4 -> 15.2 us).
     const SortedRow rec = p.sorted_rows[strip * 16 + i];
     bf16x8_t af[8];                                                // FUSE: A[i][32 j + 8 kg ..] of my block
-    constexpr int TU = 4 * PER < 16 ? 4 * PER : 16;                // else: sums of the blocks tpart, tpart + tparts, .. of entry `to`
+    constexpr int TU = PER == 1 ? 16 : 4 * PER < 16 ? 4 * PER : 16;    // else: sums of the blocks tpart, tpart + tparts, .. of entry `to`
     float tsum[TU];
     int tpart = 0, to = threadIdx.x;
     if (FUSE) {
@@ -211,7 +212,6 @@ __device__ __forceinline__ void gemv_body(const GemvParams& p, const int strip) 
             }
         }
     }
-    if (PER == 1) ask_inputs();
     // my fragments of B for the first 64 ranks, asked for with everything else
     bf16x8_t bfr0 = zero8, bfr1 = zero8;
     if (wave == 0 && p.RT > 0 && (p.r & 7) == 0) {
@@ -224,6 +224,7 @@ __device__ __forceinline__ void gemv_body(const GemvParams& p, const int strip) 
         *reinterpret_cast<float4*>(lev + 4 * kg) = lv;
         if (kg == 0) reinterpret_cast<int*>(gv_smem + NL0)[i] = rec.n;
     }
+    if (PER == 1) ask_inputs();
     __syncthreads();                                               // the levels
     // my channel's pair table, entry e = two codes (low, high) -> two bf16 (unscaled levels; the group scale multiplies the
     // group's dot product)
@@ -238,14 +239,25 @@ __device__ __forceinline__ void gemv_body(const GemvParams& p, const int strip) 
 #pragma unroll
                 for (int u = 0; u < TU; ++u) v += tsum[u];
             }
-            for (int b = o == to ? tpart + TU * p.tparts : tpart; b < nblk; b += 4 * p.tparts) {         // four loads in flight
+            int b = o == to ? tpart + TU * p.tparts : tpart;
+            if (W == 8 && PER >= 6 && p.tparts == 1) {             // long contractions of higher ranks: more of them in flight (4096 x 11008,
+                for (; b < nblk; b += 16) {                        // 16 tokens, rank 64: 24.4 -> 23.0 us; shorter ones have no registers to spare)
+                    float w[16];
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) w[u] = p.tp[(size_t)min(b + u, nblk - 1) * nt + o];
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) v += b + u < nblk ? w[u] : 0.0f;
+                }
+            }
+            for (; b < nblk; b += 4 * p.tparts) {         // four loads in flight
                 float w[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) w[u] = p.tp[(size_t)min(b + u * p.tparts, nblk - 1) * nt + o];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) v += b + u * p.tparts < nblk ? w[u] : 0.0f;
             }
-            t_lds[tpart * nt + o] = v;
+            if (PER == 1) reinterpret_cast<uint16_t*>(t_lds)[o] = (uint16_t)(pack_bf16x2(v * p.s, 0.0f) & 0xffffu);
+            else t_lds[tpart * nt + o] = v;
         }
     }
     __syncthreads();                                               // pair tables
@@ -267,6 +279,7 @@ __device__ __forceinline__ void gemv_body(const GemvParams& p, const int strip) 
         return f;
     };
     auto fragment_t = [&](int j0, int parts) __attribute__((always_inline)) -> bf16x8_t {
+        if (PER == 1 && !FUSE) return j0 < p.RT ? *reinterpret_cast<const bf16x8_t*>(reinterpret_cast<const uint16_t*>(t_lds) + i * p.RT + j0) : zero8;
         float t[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         if (j0 < p.RT) {
             for (int q = 0; q < parts; ++q) {
@@ -395,8 +408,8 @@ static size_t gemv_lds(GemvParams& p) {
     constexpr int kMaxLds = 160 * 1024;
     const int rows2 = (std::min(p.M, 16) + 1) / 2;
     const int nblk = (p.G + 3) / 4, per = (nblk + W - 1) / W;
-    p.tparts = gemv_t_parts(W, p.RT, FUSE);
-    const size_t base = (size_t)fixed + gemv_t_bytes(W, p.RT, FUSE), xbuf = (size_t)W * rows2 * 1024;
+    p.tparts = gemv_t_parts(W, PER, p.RT, FUSE);
+    const size_t base = (size_t)fixed + gemv_t_bytes(W, PER, p.RT, FUSE), xbuf = (size_t)W * rows2 * 1024;
     p.xbufs = base + per * xbuf <= (size_t)kMaxLds ? per : 2;     // a buffer per round when they fit
     // ... but not at the price of the second workgroup on a compute unit (5120 features, 6 tokens, three matrices of 5120
     // channels: 34 -> 25 us)
@@ -447,10 +460,10 @@ struct GemvChoice { int W, PER, fuse; };
 static GemvChoice gemv_choose_waves(const GemvParams& p, bool many_strips) {
     const int nblk = (p.G + 3) / 4;
     const int rows2 = (std::min(p.M, 16) + 1) / 2;
-    const bool fit16 = (size_t)GV_FIXED + gemv_t_bytes(16, p.RT, p.RT == 16) +
+    const bool fit16 = (size_t)GV_FIXED + gemv_t_bytes(16, 1, p.RT, p.RT == 16) +
                        (size_t)std::min((nblk + 15) / 16, 2) * 16 * rows2 * 1024 <= (size_t)160 * 1024;
     const int nstrips = (p.N + 15) / 16;
-    const size_t lds8 = (size_t)GV_FIXED + gemv_t_bytes(8, p.RT, p.RT == 16) + (size_t)std::min((nblk + 7) / 8, 2) * 8 * rows2 * 1024;
+    const size_t lds8 = (size_t)GV_FIXED + gemv_t_bytes(8, 1, p.RT, p.RT == 16) + (size_t)std::min((nblk + 7) / 8, 2) * 8 * rows2 * 1024;
     // (up to 24 blocks: 5120 features, three rounds; one token, three matrices of 5120 channels 34 -> 24 us, two of 13824
     // 59 -> 38 us against one 16-wavefront workgroup per unit)
     const bool pair8 = (many_strips || nstrips > compute_units_cached()) && 2 * lds8 <= (size_t)150 * 1024 && nblk <= 24;
@@ -521,7 +534,7 @@ hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
 // seven matrices in one batch 52.9 / 55.9, with 16 tokens q,k,v,o 34.3 / 30.2.
 // LDS of an 8-wavefront workgroup with two activation buffers per wavefront, or fewer where it has fewer rounds
 static size_t lds8_of(const GemvParams& p, int per) {
-    return (size_t)GV_FIXED + gemv_t_bytes(8, p.RT, false) + (size_t)std::min(per, 2) * 8 * ((std::min(p.M, 16) + 1) / 2) * 1024;
+    return (size_t)GV_FIXED + gemv_t_bytes(8, 2, p.RT, false) + (size_t)std::min(per, 2) * 8 * ((std::min(p.M, 16) + 1) / 2) * 1024;
 }
 double gemv_batch_us(const std::vector<GemvParams>& items) {
     double t = items.empty() || items[0].RT == 0 ? 3.0 : 5.0;
