@@ -322,6 +322,13 @@ lowra_status lowra_set_mid_tiling(int rows, int splits);
  * pointer. */
 lowra_status lowra_plan_mid_tiling(int op, int N, int K, int M, int has_4bit, int codebooks, int* rows, int* splits);
 
+/* Host only: what the general small-token forward launches for an N x K matrix with M <= 16 tokens and rank r, on the current
+ * device's compute units (256 without one): workgroups of *wavefronts wavefronts with *rounds blocks of 256 features each, and
+ * whether they form x A^T themselves (*fused).  batch_strips: 0 for a call on the matrix alone, else the 16-channel strips of
+ * the batch it is in.  INVALID_ARG: a size or a strip count out of range, K % 64 != 0, a null pointer; UNSUPPORTED: K beyond the
+ * kernel's 16384 or r beyond 128. */
+lowra_status lowra_plan_small_fwd(int N, int K, int M, int r, int batch_strips, int* wavefronts, int* rounds, int* fused);
+
 /* Several small-token forwards as one run (the operation of lowra_linear_fwd, Sec. 2.1 / Sec. 3, for
  * M <= 16 tokens on n independent matrices: e.g. the projections of one decoder layer that read the
  * same activations, or a pass over a whole weight set).  A single matrix at 1-2 bits is only a few MB,

@@ -687,4 +687,11 @@ lowra_status lowra_plan_mid_tiling(int op, int N, int K, int M, int has_4bit, in
     return LOWRA_OK;
 }
 
+lowra_status lowra_plan_small_fwd(int N, int K, int M, int r, int batch_strips, int* wavefronts, int* rounds, int* fused) {
+    if (N <= 0 || K <= 0 || K % lowra::kGroup != 0 || M <= 0 || M > 16 || r < 0 || batch_strips < 0 || !wavefronts || !rounds || !fused) return LOWRA_INVALID_ARG;
+    if (!lowra::gemv_fwd_fits(K) || r > kMaxRank) return LOWRA_UNSUPPORTED;
+    lowra::gemv_plan(N, K, M, r, batch_strips, wavefronts, rounds, fused);
+    return LOWRA_OK;
+}
+
 }  // extern "C"

@@ -31,7 +31,7 @@
 //
 // A call on one matrix is a chain of round trips and of instructions that every wavefront of a workgroup issues (four per
 // SIMD: 16 cycles an instruction).  So the chain's head, the row record, is asked for first; the levels come by one
-// load of one wavefront; nothing waits for t before the end; and there are no more wavefronts than blocks.  One call, before -> after:
+// load of one wavefront; nothing waits for t before the end; and few blocks take fewer wavefronts.  One call, before -> after:
 // 256 x 512, 16 tokens 9.0 -> 5.0 us; 4096 x 1024, 4 tokens 9.0 -> 6.1; 11008 x 4096, 1 token 17.7 -> 15.2;
 // 4096 x 4096, 1 token 9.4 -> 9.2; three 4096 x 4096 matrices in one launch 19.8 -> 17.2.
 #include <algorithm>
@@ -450,49 +450,55 @@ static int compute_units_cached() {
 bool gemv_fwd_fits(int K) { return (K + 255) / 256 <= 8 * GV_MAXR; }
 
 // The instantiation a matrix takes.  Rounds per wavefront fix the register footprint, so the kernel is
-// compiled for a few depths; 16 wavefronts (4 per SIMD hide the LDS and decode latencies better)
-// whenever their activation buffers fit; with more strips than compute units two 8-wavefront
-// workgroups per unit (when their buffers fit twice) overlap one strip's loads with the other's
+// compiled for a few depths; the smallest of 4, 8 and 16 wavefronts that covers the blocks (16 beyond: 4 per SIMD hide the
+// LDS and decode latencies better), some of them idle, whenever its activation buffers fit; with more strips than compute
+// units two 8-wavefront workgroups per unit (when their buffers fit twice) overlap one strip's loads with the other's
 // arithmetic.
-// Short contractions take as many wavefronts as they have blocks: every wavefront issues the instructions in front of the
-// first product, so idle ones cost time.
 struct GemvChoice { int W, PER, fuse; };
-static GemvChoice gemv_choose_waves(const GemvParams& p, bool many_strips) {
+// Whether the workgroups form t = x A^T themselves.  It saves the partial sums' launch (2.7 us on the GPU, 2.6 us on the host) and
+// costs every workgroup A: a compute unit gathers about 30 GB/s, 64 KB in 2 us, and pays that for each round of strips.
+// `strips`: of the launch.  (GPU time, formed here against the launch: 2048 features, rank 16 0.95; 4096, rank 8 1.01, rank 16 1.12.)
+static bool gemv_fuses(const GemvParams& p, int strips) {
+    const long long rounds = (strips + compute_units_cached() - 1) / compute_units_cached();
+    return p.r > 0 && p.r <= 16 && rounds * p.r * p.K <= 32768;
+}
+// LDS of an instantiation with two activation buffers per wavefront, or one where it has one round
+static size_t gemv_lds_least(const GemvParams& p, const GemvChoice& c) {
+    const int nblk = (p.G + 3) / 4, rows2 = (std::min(p.M, 16) + 1) / 2;
+    return (size_t)GV_FIXED + gemv_t_bytes(c.W, c.PER, p.RT, c.fuse) + (size_t)std::min((nblk + c.W - 1) / c.W, 2) * c.W * rows2 * 1024;
+}
+// many_strips: the matrix shares its launch; strips: of the launch
+static GemvChoice gemv_choose(const GemvParams& p, bool many_strips, int strips) {
+    constexpr size_t kMaxLds = 160 * 1024;
     const int nblk = (p.G + 3) / 4;
-    const int rows2 = (std::min(p.M, 16) + 1) / 2;
-    const bool fit16 = (size_t)GV_FIXED + gemv_t_bytes(16, 1, p.RT, p.RT == 16) +
-                       (size_t)std::min((nblk + 15) / 16, 2) * 16 * rows2 * 1024 <= (size_t)160 * 1024;
-    const int nstrips = (p.N + 15) / 16;
-    const size_t lds8 = (size_t)GV_FIXED + gemv_t_bytes(8, 1, p.RT, p.RT == 16) + (size_t)std::min((nblk + 7) / 8, 2) * 8 * rows2 * 1024;
+    const bool fuses = gemv_fuses(p, strips);
     // (up to 24 blocks: 5120 features, three rounds; one token, three matrices of 5120 channels 34 -> 24 us, two of 13824
     // 59 -> 38 us against one 16-wavefront workgroup per unit)
-    const bool pair8 = (many_strips || nstrips > compute_units_cached()) && 2 * lds8 <= (size_t)150 * 1024 && nblk <= 24;
-    if (fit16 && !pair8) {
-        if (nblk <= 4) return {4, 1, 0};
-        if (nblk <= 8) return {8, 1, 0};
-        if (nblk <= 16) return {16, 1, 0};  // K <= 4096
-        if (nblk <= 32) return {16, 2, 0};
-        if (nblk <= 48) return {16, 3, 0};  // K = 11008
-        if (nblk <= 64) return {16, 4, 0};
+    const size_t lds8 = gemv_lds_least(p, {8, 2, 0});
+    const bool pair8 = (many_strips || (p.N + 15) / 16 > compute_units_cached()) && 2 * lds8 <= (size_t)150 * 1024 && nblk <= 24;
+    if (!pair8) {
+        // What counts is the LDS of the form that the call will have: with 15 and 16 tokens the sums of 16 wavefronts that form t
+        // are 1.5 KB too many, and then t comes from its own launch rather than through half as many wavefronts (4096 x 4096,
+        // 16 tokens, rank 8: 10.4 -> 10.15 us; 2048 x 2048, rank 16, where 8 wavefronts fit either way, 9.75 -> 7.6).
+        GemvChoice c = nblk <= 4 ? GemvChoice{4, 1, 0} : nblk <= 8 ? GemvChoice{8, 1, 0} : nblk <= 16 ? GemvChoice{16, 1, 0}      // K <= 4096
+                     : nblk <= 32 ? GemvChoice{16, 2, 0} : nblk <= 48 ? GemvChoice{16, 3, 0} : GemvChoice{16, 4, 0};               // K <= 12288: three
+        c.fuse = c.PER == 1 && fuses;
+        if (c.fuse && gemv_lds_least(p, c) > kMaxLds) c.fuse = 0;
+        if (gemv_lds_least(p, c) <= kMaxLds) return c;
     }
-    if (nblk <= 4) return {4, 1, 0};
+    if (nblk <= 4) return {4, 1, fuses};
     if (nblk <= 8) return {4, 2, 0};
     if (nblk <= 16) return {8, 2, 0};       // K <= 4096
     if (nblk <= 32) return {8, 4, 0};
     if (nblk <= 48) return {8, 6, 0};       // K = 11008
     return {8, 8, 0};
 }
-// Whether the workgroups form t = x A^T themselves.  It saves the partial sums' launch (2.7 us on the GPU, 2.6 us on the host) and
-// costs every workgroup A: a compute unit gathers about 30 GB/s, 64 KB in 2 us, and pays that for each round of strips.
-// `strips`: of the launch.
-static bool gemv_fuses(const GemvParams& p, const GemvChoice& c, int strips) {
-    const long long rounds = (strips + compute_units_cached() - 1) / compute_units_cached();
-    return c.PER == 1 && p.r > 0 && p.r <= 16 && rounds * p.r * p.K <= 32768;
-}
-static GemvChoice gemv_choose(const GemvParams& p, bool many_strips, int strips) {
-    GemvChoice c = gemv_choose_waves(p, many_strips);
-    c.fuse = gemv_fuses(p, c, strips);
-    return c;
+void gemv_plan(int N, int K, int M, int r, int batch_strips, int* wavefronts, int* rounds, int* fused) {
+    GemvParams p{};
+    p.N = N; p.K = K; p.G = K / kGroup; p.M = M; p.r = r; p.RT = r > 0 ? (r + 15) / 16 * 16 : 0;
+    const bool batch = batch_strips > 0;
+    const GemvChoice c = gemv_choose(p, batch && LOWRA_BATCH_SMALL_WG != 0, batch ? batch_strips : (N + 15) / 16);
+    *wavefronts = c.W; *rounds = ((p.G + 3) / 4 + c.W - 1) / c.W; *fused = c.fuse;
 }
 // calls f.template operator()<W, PER, FUSE>() for the chosen instantiation
 template <typename F>
@@ -532,19 +538,17 @@ hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
 // kernel, set-up, pipeline fill and drain) and then streams at 3 GB/ms.  A decoder layer of 4096 x 11008 taken apart by
 // data dependence, 4 tokens: q,k,v 17.9 us here against 27.3, o 10.0 / 20.2, gate,up 27.3 / 30.4, down 16.9 / 39.3; all
 // seven matrices in one batch 52.9 / 55.9, with 16 tokens q,k,v,o 34.3 / 30.2.
-// LDS of an 8-wavefront workgroup with two activation buffers per wavefront, or fewer where it has fewer rounds
-static size_t lds8_of(const GemvParams& p, int per) {
-    return (size_t)GV_FIXED + gemv_t_bytes(8, 2, p.RT, false) + (size_t)std::min(per, 2) * 8 * ((std::min(p.M, 16) + 1) / 2) * 1024;
-}
 double gemv_batch_us(const std::vector<GemvParams>& items) {
     double t = items.empty() || items[0].RT == 0 ? 3.0 : 5.0;
     double rounds16[5] = {0, 0, 0, 0, 0};
-    for (GemvParams p : items) {
-        const GemvChoice c = gemv_choose_waves(p, LOWRA_BATCH_SMALL_WG != 0);
+    int strips_all = 0;
+    for (const GemvParams& p : items) strips_all += (p.N + 15) / 16;
+    for (const GemvParams& p : items) {
+        const GemvChoice c = gemv_choose(p, LOWRA_BATCH_SMALL_WG != 0, strips_all);
         const int nblk = (p.G + 3) / 4, per = (nblk + c.W - 1) / c.W, strips = (p.N + 15) / 16;
         if (c.W == 16) rounds16[std::min(per, 4)] += (double)strips / compute_units_cached();
         else if (c.W == 8) {                                         // one workgroup per unit, or two or three
-            const size_t lds = lds8_of(p, per);
+            const size_t lds = gemv_lds_least(p, c);
             t += (2 * lds > (size_t)160 * 1024 ? 0.0111 : per > 2 ? 0.0062 : 3 * lds > (size_t)160 * 1024 ? 0.0095 : 0.0080) * strips * per;
         }
         else t += (p.M > 12 ? 0.0125 : p.M > 8 ? 0.0085 : 0.005) * strips * per;

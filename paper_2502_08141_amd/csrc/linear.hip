@@ -169,7 +169,6 @@ static size_t bwd_split_bytes(const lowra_layout& L, int M) {
 }
 
 // The small-token path pads the tokens to one 16-row MFMA tile.
-bool gemv_fwd_fits(int K);
 bool gemv_fwd_supported(const lowra_layout& L, int M) { return M <= 16 && gemv_fwd_fits(L.K); }
 static size_t gemv_workspace_bytes(const lowra_layout& L, int r) {
     return r > 0 ? (size_t)((L.K + 255) / 256) * 16 * round_up(r, 16) * sizeof(float) : 0;

@@ -123,6 +123,7 @@ hipError_t launch_loftq(const lowra_layout& L, const float* W, const float* thre
                         int iters, const uint16_t* omega, uint8_t* packed, float* absmax, uint16_t* A_out, uint16_t* B_out,
                         void* workspace, hipStream_t st);
 
+bool gemv_fwd_fits(int K);
 bool gemv_fwd_supported(const lowra_layout& L, int M);
 bool gemv_stream_supported(const lowra_layout& L, int M, int r);
 size_t gemv_stream_workspace_bytes(const lowra_layout& L, int M, int r);
@@ -141,6 +142,8 @@ hipError_t gemv_stream_bwd_batch_run(const GbBatch& b, hipStream_t st);
 void gemv_stream_bwd_batch_free(GbBatch& b);
 double gemv_batch_us(const std::vector<GemvParams>& items);          // estimated time of a run by the general kernel ...
 double gemv_stream_batch_us(const std::vector<GemvParams>& items);   // ... and by the streaming kernel
+// the general small-token forward's instantiation for a matrix by itself (batch_strips 0) or in a batch of that many strips
+void gemv_plan(int N, int K, int M, int r, int batch_strips, int* wavefronts, int* rounds, int* fused);
 hipError_t gemv_batch_build(std::vector<GemvParams>& items, lowra_fwd_batch& b);
 hipError_t gemv_batch_run(const lowra_fwd_batch& b, hipStream_t st);
 void gemv_batch_free(lowra_fwd_batch& b);

@@ -30,7 +30,7 @@ SYMBOLS = [
     "lowra_status_string", "lowra_plan_rows", "lowra_layout_create", "lowra_layout_destroy", "lowra_layout_set_scale_dtype",
     "lowra_packed_bytes", "lowra_workspace_bytes", "lowra_quantize", "lowra_quantize_batch", "lowra_dequantize",
     "lowra_linear_fwd", "lowra_linear_fwd_static", "lowra_linear_bwd_input", "lowra_set_linear_path", "lowra_set_fwd_tiling", "lowra_plan_fwd_tiling", "lowra_set_mid_tiling",
-    "lowra_plan_mid_tiling", "lowra_set_kernel_timer",
+    "lowra_plan_mid_tiling", "lowra_plan_small_fwd", "lowra_set_kernel_timer",
     "lowra_learn_tables", "lowra_average_thresholds", "lowra_channel_mse", "lowra_assign_precisions",
     "lowra_adapter_grads", "lowra_linear_side_product", "lowra_adapter_grads_from_side", "lowra_loftq_init",
     "lowra_fwd_batch_workspace_bytes", "lowra_fwd_batch_create", "lowra_fwd_batch_run", "lowra_fwd_batch_destroy",
@@ -109,6 +109,7 @@ def lib() -> C.CDLL:
         L.lowra_plan_fwd_tiling.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
         L.lowra_set_mid_tiling.argtypes = [C.c_int, C.c_int]
         L.lowra_plan_mid_tiling.argtypes = [C.c_int] * 6 + [C.POINTER(C.c_int)] * 2
+        L.lowra_plan_small_fwd.argtypes = [C.c_int] * 5 + [C.POINTER(C.c_int)] * 3
         L.lowra_set_kernel_timer.argtypes = [vp, vp]
         spec = importlib.util.spec_from_file_location("_lowra_call", CALL_PATH)
         call = importlib.util.module_from_spec(spec)
@@ -598,6 +599,13 @@ def lowra_plan_mid_tiling(op: int, N: int, K: int, M: int, has_4bit: bool, codeb
     _check(lib().lowra_plan_mid_tiling(int(op), int(N), int(K), int(M), int(has_4bit), int(codebooks), C.byref(rows), C.byref(splits)),
            "lowra_plan_mid_tiling")
     return rows.value, splits.value
+
+
+def lowra_plan_small_fwd(N: int, K: int, M: int, r: int, batch_strips: int = 0):
+    """(wavefronts, rounds, fused) of the general small-token forward (host only)."""
+    w, n, f = C.c_int(), C.c_int(), C.c_int()
+    _check(lib().lowra_plan_small_fwd(int(N), int(K), int(M), int(r), int(batch_strips), C.byref(w), C.byref(n), C.byref(f)), "lowra_plan_small_fwd")
+    return w.value, n.value, bool(f.value)
 
 
 def lowra_set_kernel_timer(start_event=None, stop_event=None):

@@ -164,3 +164,29 @@ def test_mid_token_planner():
     finally:
         lowra.lowra_set_mid_tiling()
     assert lowra.lowra_plan_mid_tiling(FWD, 11008, 4096, 4096, True, 3) == (0, 0)
+
+
+def test_small_forward_planner():
+    """Host only: the general small-token forward's wavefronts.  A low rank needs no more of a workgroup's memory than a high one
+    where its t comes from a launch of its own, so it must not run through fewer wavefronts; and where the form that makes t
+    itself is the only one that does not fit, the other is taken before fewer wavefronts are."""
+    plan = lowra.lowra_plan_small_fwd
+    assert plan(4096, 4096, 16, 8) == plan(4096, 4096, 15, 8) == (16, 1, False)     # the sums of 16 wavefronts do not fit beside 16 tokens
+    assert plan(4096, 4096, 14, 8) == (16, 1, True)
+    assert plan(4096, 4096, 16, 16) == plan(4096, 4096, 16, 32) == (16, 1, False)
+    assert plan(4096, 2048, 16, 16) == (8, 1, True)
+    assert plan(4096, 11008, 8, 16) == (16, 3, False) and plan(4096, 11008, 9, 16) == (8, 6, False)
+    assert plan(11008, 4096, 4, 16) == (8, 2, False) and plan(11008, 4096, 16, 16) == (16, 1, False)
+    for K in list(range(64, 4096, 192)) + list(range(4096, 16385, 1024)):
+        for M in range(1, 17):
+            for N, strips in ((8, 0), (4096, 0), (4104, 0), (4096, 768)):
+                # (with many strips a rank's few KB also decide whether two smaller workgroups share a unit)
+                waves = [plan(N, K, M, r, strips)[0] for r in ((0, 8, 16, 17, 64, 128) if N <= 4096 and not strips else (8, 16, 17))]
+                assert all(a >= b for a, b in zip(waves, waves[1:])), (N, K, M, strips, waves)
+                for r in (0, 8, 16, 64):
+                    w, rounds, fused = plan(N, K, M, r, strips)
+                    assert w * rounds * 256 >= K and (not fused or (rounds == 1 and 0 < r <= 16)), (N, K, M, r, strips)
+    for bad in [(0, 256, 1, 0, 0), (8, 100, 1, 0, 0), (8, 256, 17, 0, 0), (8, 256, 1, -1, 0), (8, 256, 1, 0, -1)]:
+        with pytest.raises(lowra.LowraError):
+            plan(*bad)
+    assert pytest.raises(lowra.LowraError, plan, 8, 16448, 1, 0).value.status == lowra.UNSUPPORTED
