@@ -401,21 +401,25 @@ __global__ __launch_bounds__(W * 64) void gemv_fwd_batch_kernel(const GemvParams
     gemv_body<W, PER, FUSE>(p, (int)blockIdx.x - strip0[m]);
 }
 
-// LDS bytes of an instantiation for this matrix (0: does not fit); sets the number of activation buffers
-template <int W, int PER, bool FUSE>
-static size_t gemv_lds(GemvParams& p) {
-    constexpr int fixed = GV_FIXED;
+struct GemvChoice { int W, PER, fuse; };
+// LDS bytes of an instantiation for this matrix (0: does not fit), and its number of activation buffers
+static size_t gemv_lds(const GemvParams& p, const GemvChoice& c, int* xbufs) {
     constexpr int kMaxLds = 160 * 1024;
     const int rows2 = (std::min(p.M, 16) + 1) / 2;
-    const int nblk = (p.G + 3) / 4, per = (nblk + W - 1) / W;
-    p.tparts = gemv_t_parts(W, PER, p.RT, FUSE);
-    const size_t base = (size_t)fixed + gemv_t_bytes(W, PER, p.RT, FUSE), xbuf = (size_t)W * rows2 * 1024;
-    p.xbufs = base + per * xbuf <= (size_t)kMaxLds ? per : 2;     // a buffer per round when they fit
+    const int nblk = (p.G + 3) / 4, per = (nblk + c.W - 1) / c.W;
+    const size_t base = (size_t)GV_FIXED + gemv_t_bytes(c.W, c.PER, p.RT, c.fuse), xbuf = (size_t)c.W * rows2 * 1024;
+    int bufs = base + per * xbuf <= (size_t)kMaxLds ? per : 2;     // a buffer per round when they fit
     // ... but not at the price of the second workgroup on a compute unit (5120 features, 6 tokens, three matrices of 5120
     // channels: 34 -> 25 us)
-    if (W == 8 && per > 2 && 2 * (base + per * xbuf) > (size_t)kMaxLds && 2 * (base + 2 * xbuf) <= (size_t)kMaxLds) p.xbufs = 2;
-    const size_t sh = base + (size_t)p.xbufs * xbuf;
+    if (c.W == 8 && per > 2 && 2 * (base + per * xbuf) > (size_t)kMaxLds && 2 * (base + 2 * xbuf) <= (size_t)kMaxLds) bufs = 2;
+    *xbufs = bufs;
+    const size_t sh = base + (size_t)bufs * xbuf;
     return sh > (size_t)kMaxLds ? 0 : sh;
+}
+template <int W, int PER, bool FUSE>
+static size_t gemv_lds(GemvParams& p) {
+    p.tparts = gemv_t_parts(W, PER, p.RT, FUSE);
+    return gemv_lds(p, GemvChoice{W, PER, FUSE}, &p.xbufs);
 }
 template <int W, int PER, bool FUSE>
 static hipError_t gemv_attr() {
@@ -454,7 +458,6 @@ bool gemv_fwd_fits(int K) { return (K + 255) / 256 <= 8 * GV_MAXR; }
 // LDS and decode latencies better), some of them idle, whenever its activation buffers fit; with more strips than compute
 // units two 8-wavefront workgroups per unit (when their buffers fit twice) overlap one strip's loads with the other's
 // arithmetic.
-struct GemvChoice { int W, PER, fuse; };
 // Whether the workgroups form t = x A^T themselves.  It saves the partial sums' launch (2.7 us on the GPU, 2.6 us on the host) and
 // costs every workgroup A: a compute unit gathers about 30 GB/s, 64 KB in 2 us, and pays that for each round of strips.
 // `strips`: of the launch.  (GPU time, formed here against the launch: 2048 features, rank 16 0.95; 4096, rank 8 1.01, rank 16 1.12.)
@@ -484,6 +487,9 @@ static GemvChoice gemv_choose(const GemvParams& p, bool many_strips, int strips)
                      : nblk <= 32 ? GemvChoice{16, 2, 0} : nblk <= 48 ? GemvChoice{16, 3, 0} : GemvChoice{16, 4, 0};               // K <= 12288: three
         c.fuse = c.PER == 1 && fuses;
         if (c.fuse && gemv_lds_least(p, c) > kMaxLds) c.fuse = 0;
+        // nor is it formed in the workgroup where several rounds of strips would then have a unit each to themselves (three
+        // 2048 x 2048 matrices in a launch, 13 tokens, rank 8: 12.6 -> 10.7 us)
+        if (c.fuse && strips > compute_units_cached() && 2 * gemv_lds_least(p, c) > kMaxLds && 2 * gemv_lds_least(p, {c.W, c.PER, 0}) <= kMaxLds) c.fuse = 0;
         if (gemv_lds_least(p, c) <= kMaxLds) return c;
     }
     if (nblk <= 4) return {4, 1, fuses};
@@ -492,6 +498,29 @@ static GemvChoice gemv_choose(const GemvParams& p, bool many_strips, int strips)
     if (nblk <= 32) return {8, 4, 0};
     if (nblk <= 48) return {8, 6, 0};       // K = 11008
     return {8, 8, 0};
+}
+// The instantiations of a batch's matrices.  Those of one round whose strips together fill the chip once at most take the widest
+// of theirs: every further instantiation is a launch of its own, 4 us and more behind the one before, and idle wavefronts cost
+// less (1024 x 1024 and 1024 x 2816, 16 tokens, rank 16: 14.9 -> 8.8 us, 16 tokens without a rank-r term 10.5 -> 5.7).
+static std::vector<GemvChoice> gemv_choose_batch(const std::vector<GemvParams>& items) {
+    int strips = 0, strips1 = 0, W = 0;
+    for (const GemvParams& p : items) strips += (p.N + 15) / 16;
+    std::vector<GemvChoice> out;
+    for (const GemvParams& p : items) {
+        out.push_back(gemv_choose(p, LOWRA_BATCH_SMALL_WG != 0, strips));
+        if (out.back().PER == 1) { strips1 += (p.N + 15) / 16; W = std::max(W, out.back().W); }
+    }
+    if (strips1 > compute_units_cached()) return out;
+    bool fuse = true;                                              // all of them or none: one launch
+    for (size_t i = 0; i < items.size(); ++i)
+        if (out[i].PER == 1 && out[i].W < W) {
+            out[i].W = W;
+            if (gemv_lds_least(items[i], out[i]) > (size_t)160 * 1024) out[i].fuse = 0;
+        }
+    for (const GemvChoice& c : out) fuse = fuse && (c.PER != 1 || c.fuse);
+    for (GemvChoice& c : out)
+        if (c.PER == 1) c.fuse = fuse;
+    return out;
 }
 void gemv_plan(int N, int K, int M, int r, int batch_strips, int* wavefronts, int* rounds, int* fused) {
     GemvParams p{};
@@ -541,10 +570,10 @@ hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
 double gemv_batch_us(const std::vector<GemvParams>& items) {
     double t = items.empty() || items[0].RT == 0 ? 3.0 : 5.0;
     double rounds16[5] = {0, 0, 0, 0, 0};
-    int strips_all = 0;
-    for (const GemvParams& p : items) strips_all += (p.N + 15) / 16;
-    for (const GemvParams& p : items) {
-        const GemvChoice c = gemv_choose(p, LOWRA_BATCH_SMALL_WG != 0, strips_all);
+    const std::vector<GemvChoice> choices = gemv_choose_batch(items);
+    for (size_t i = 0; i < items.size(); ++i) {
+        const GemvParams& p = items[i];
+        const GemvChoice c = choices[i];
         const int nblk = (p.G + 3) / 4, per = (nblk + c.W - 1) / c.W, strips = (p.N + 15) / 16;
         if (c.W == 16) rounds16[std::min(per, 4)] += (double)strips / compute_units_cached();
         else if (c.W == 8) {                                         // one workgroup per unit, or two or three
@@ -608,12 +637,12 @@ hipError_t gemv_batch_build(std::vector<GemvParams>& items, lowra_fwd_batch& b) 
     struct Key { int W, PER, fuse; size_t sh; };
     std::vector<Key> keys;
     std::vector<std::vector<GemvParams>> members;
-    int strips = 0;
-    for (const auto& p : items) strips += (p.N + 15) / 16;
+    const std::vector<GemvChoice> choices = gemv_choose_batch(items);
     std::vector<GemvParams> tdescs;
     std::vector<int> blk0(1, 0);
-    for (auto& p : items) {
-        const GemvChoice c = gemv_choose(p, LOWRA_BATCH_SMALL_WG != 0, strips);
+    for (size_t i = 0; i < items.size(); ++i) {
+        GemvParams& p = items[i];
+        const GemvChoice c = choices[i];
         if (p.RT > 0 && !c.fuse) { tdescs.push_back(p); blk0.push_back(blk0.back() + (p.G + 3) / 4); }
         size_t sh = 0;
         if ((e = gemv_dispatch(c, PrepareDesc{p, sh})) != hipSuccess) return e;

@@ -16,6 +16,9 @@ BATCHES = {
     "5120 features": [(1032, 5120), (264, 5120)],
     "mixed lengths": [(264, 2048), (136, 6144), (520, 4096)],
     "long rows": [(136, 11008)],
+    "few strips, one launch": [(136, 512), (264, 1024), (136, 2816)],     # 4, 8 and 16 wavefronts by themselves
+    "many strips": [(4200, 1024), (136, 2816)],
+    "with one that only the general kernel takes": [(264, 2048), (136, 2112)],
 }
 
 
