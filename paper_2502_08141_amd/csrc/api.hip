@@ -504,12 +504,20 @@ static lowra_status fwd_batch_create_impl(int n, const lowra_fwd_item* items, co
         fp32_scales = fp32_scales && !L.scale_bf16;
         ws += batch_item_ws(L, r);
     }
-    // LOWRA_PATH_AUTO: a batch too small for the streaming kernel goes to the general one (which reads fp32 scales).  The
-    // estimates err by a few per cent, so batches that they put about level stay with the streaming kernel: of 28 sets of six
-    // batches (one to seven matrices, 1024 to 13824 features, 1 to 16 tokens) seven batches then run 3 to 20 % slower than on
-    // the other kernel (worst: gate,up of 5120 x 13824 without a LoRA term, 37.1 for 31.6 us; qkv,o with 16 tokens 34.2 for 30.3).
-    constexpr double kLevel = 0.97;
-    if (path == LOWRA_PATH_AUTO && fp32_scales && lowra::gemv_batch_us(all) < kLevel * lowra::gemv_stream_batch_us(all)) streams = false;
+    // LOWRA_PATH_AUTO: the general kernel (which reads fp32 scales) takes the batch where it is estimated to be the faster one;
+    // matrices that the streaming kernel does not take are the general kernel's either way.  Of 5120 batches (one to seven matrices
+    // of 1024 to 13824 features, 1 to 16 tokens, ranks 0 to 32) 155 run more than 3 % and 23 more than 10 % slower than with the
+    // other choice (worst: three 3072 x 3072 matrices of 1.15 bits, 7 tokens, no rank-r term, 15.8 for 12.3 us), 0.3 % on average.
+    if (path == LOWRA_PATH_AUTO && fp32_scales) {
+        std::vector<lowra::GemvParams> rest, taken;
+        std::vector<int> n4, n4_rest, n4_taken;
+        for (int i = 0; i < n; ++i) {
+            const bool takes = lowra::gemv_stream_supported(*items[i].layout, M, r);
+            n4.push_back(items[i].layout->n_by_bits[4]);
+            (takes ? taken : rest).push_back(all[i]); (takes ? n4_taken : n4_rest).push_back(n4.back());
+        }
+        streams = lowra::gemv_batch_us(all, n4) >= lowra::gemv_stream_batch_us(taken, n4_taken) + lowra::gemv_batch_us(rest, n4_rest);
+    }
     for (int i = 0; i < n; ++i) {
         const lowra_layout& L = *items[i].layout;
         // the streaming kernel builds one set of tables per launch: its matrices must agree on the codebooks' widths

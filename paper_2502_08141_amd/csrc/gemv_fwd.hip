@@ -35,6 +35,7 @@
 // 256 x 512, 16 tokens 9.0 -> 5.0 us; 4096 x 1024, 4 tokens 9.0 -> 6.1; 11008 x 4096, 1 token 17.7 -> 15.2;
 // 4096 x 4096, 1 token 9.4 -> 9.2; three 4096 x 4096 matrices in one launch 19.8 -> 17.2.
 #include <algorithm>
+#include <cmath>
 
 #include "gemm_common.h"
 #include "gemv_t.h"
@@ -561,40 +562,59 @@ hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
     return gemv_dispatch(c, LaunchSingle{p, st});
 }
 
-// Which kernel a batch takes: estimated times, fitted to runs of one to seven matrices of 1024 to 13824 features with 1
-// to 16 tokens.  This kernel pays per strip (4- and 8-wavefront workgroups, several per compute unit) or per round of
-// strips over the compute units (16 wavefronts); the streaming kernel pays 18 us and more before its first byte (its t
-// kernel, set-up, pipeline fill and drain) and then streams at 3 GB/ms.  A decoder layer of 4096 x 11008 taken apart by
-// data dependence, 4 tokens: q,k,v 17.9 us here against 27.3, o 10.0 / 20.2, gate,up 27.3 / 30.4, down 16.9 / 39.3; all
-// seven matrices in one batch 52.9 / 55.9, with 16 tokens q,k,v,o 34.3 / 30.2.
-double gemv_batch_us(const std::vector<GemvParams>& items) {
-    double t = items.empty() || items[0].RT == 0 ? 3.0 : 5.0;
-    double rounds16[5] = {0, 0, 0, 0, 0};
+// Which kernel a batch takes: estimated times, fits to 4736 batches (one to seven matrices of 1024 to 13824 features, every
+// token count from 1 to 16, ranks 0, 8, 16 and 32, 1.15 and 2 bits; least squares of the relative error: 8 % here, 4 % for the
+// streaming kernel).  This kernel takes its instantiations' launches one after the other; each takes as many rounds as its strips
+// fill the compute units with as many workgroups as they hold, and a round costs a fixed part and a part per block of 256
+// features.  The streaming kernel pays 11 us before and behind its stream, and with a rank-r term its t kernel, which is a
+// chain over the features.  A decoder layer of 4096 x 11008 taken apart by data dependence, 4 tokens, rank 16: q,k,v 17.7 us here
+// against 26.8, o 10.3 / 20.3, gate,up 27.6 / 30.4, down 17.4 / 39.1; all seven matrices in one batch 53.8 / 55.5, and without
+// a rank-r term 48.3 / 38.6.
+double gemv_batch_us(const std::vector<GemvParams>& items, const std::vector<int>& n4) {
+    if (items.empty()) return 0.0;
     const std::vector<GemvChoice> choices = gemv_choose_batch(items);
+    struct Launch { GemvChoice c; size_t lds; double strips, blocks; };
+    std::vector<Launch> launches;
+    double channels = 0.0, wide = 0.0, kmax = 0.0;
+    bool t_launch = false;
     for (size_t i = 0; i < items.size(); ++i) {
         const GemvParams& p = items[i];
         const GemvChoice c = choices[i];
-        const int nblk = (p.G + 3) / 4, per = (nblk + c.W - 1) / c.W, strips = (p.N + 15) / 16;
-        if (c.W == 16) rounds16[std::min(per, 4)] += (double)strips / compute_units_cached();
-        else if (c.W == 8) {                                         // one workgroup per unit, or two or three
-            const size_t lds = gemv_lds_least(p, c);
-            t += (2 * lds > (size_t)160 * 1024 ? 0.0111 : per > 2 ? 0.0062 : 3 * lds > (size_t)160 * 1024 ? 0.0095 : 0.0080) * strips * per;
-        }
-        else t += (p.M > 12 ? 0.0125 : p.M > 8 ? 0.0085 : 0.005) * strips * per;
+        int xbufs;
+        const size_t lds = gemv_lds(p, c, &xbufs);
+        size_t l = 0;
+        while (l < launches.size() && !(launches[l].c.W == c.W && launches[l].c.PER == c.PER && launches[l].c.fuse == c.fuse && launches[l].lds == lds)) ++l;
+        if (l == launches.size()) launches.push_back(Launch{c, lds, 0.0, 0.0});
+        const int strips = (p.N + 15) / 16, nblk = (p.G + 3) / 4;
+        launches[l].strips += strips; launches[l].blocks += (double)strips * ((nblk + c.W - 1) / c.W);
+        channels += p.N; wide += n4[i]; kmax = std::max(kmax, (double)p.K);
+        t_launch = t_launch || (p.RT > 0 && !c.fuse);
     }
-    const int M = items.empty() ? 1 : items[0].M;
-    for (int per = 1; per <= 4; ++per)
-        t += (double)(long long)(rounds16[per] + 0.999) * ((3.2 + 2.6 * per) * (M > 8 ? 1.15 : 1.0) + (M > 12 ? 0.6 : 0.0));
+    const double M = items[0].M, ranks = items[0].RT / 16;
+    double t = 0.91 + 0.93 * (double)launches.size() + (t_launch ? 2.62 + 0.47 * (1.0 + ranks) * kmax / 4096.0 : 0.0);
+    for (const Launch& l : launches) {
+        // workgroups of a unit by LDS and by registers
+        const int most = l.c.W == 16 ? (l.c.PER == 1 ? 2 : 1) : l.c.W == 8 ? (l.c.PER <= 2 ? 3 : l.c.PER <= 4 ? 2 : 1) : (l.c.PER == 1 ? 7 : 6);
+        const int n = std::max(1, std::min(most, (int)((size_t)160 * 1024 / std::max<size_t>(l.lds, 1))));
+        double rounds = l.strips / (double)(compute_units_cached() * n);
+        rounds = n == 1 ? std::ceil(rounds - 1e-9) : rounds < 1.0 ? 0.5 + 0.5 * rounds : rounds;
+        const double fixed = l.c.W == 16 ? 2.44 : l.c.W == 4 ? 1.97 : n == 1 ? 2.24 : n == 2 ? 3.88 : 0.0;
+        const double block = l.c.W == 16 ? 2.03 : l.c.W == 4 ? 2.54 : n == 1 ? 1.32 : n == 2 ? 1.56 : 4.27;
+        t += rounds * (fixed + l.blocks / l.strips * (block + 0.013 * M + 2.0 * wide / channels) + 0.46 * ranks);
+    }
     return t;
 }
-double gemv_stream_batch_us(const std::vector<GemvParams>& items) {
-    double bytes = 0.0;
-    int kmax = 0, M = 1, rt = 0;
-    for (const GemvParams& p : items) {
-        bytes += (double)p.packed_bytes + (double)p.N * p.G * sizeof(float);
-        kmax = std::max(kmax, p.K); M = p.M; rt = p.RT;
+double gemv_stream_batch_us(const std::vector<GemvParams>& items, const std::vector<int>& n4) {
+    if (items.empty()) return 0.0;
+    double units = 0.0, kmax = 0.0;                                // strips x chunks of 4096 features, 4-bit ones twice, per compute unit
+    for (size_t i = 0; i < items.size(); ++i) {
+        const GemvParams& p = items[i];
+        units += (double)((p.N + 15) / 16) * ((p.K + 4095) / 4096) * (1.0 + (double)n4[i] / p.N) / compute_units_cached();
+        kmax = std::max(kmax, (double)p.K);
     }
-    return (rt ? 7.7 + 4.5 * ((kmax - 1) / 4096) : 0.0) + 10.3 + 0.35 * M + bytes / 3.0e6 + (kmax > 4096 ? 5.0 : 0.0);
+    const double M = items[0].M, r = items[0].r;
+    return 10.6 + 0.13 * M + units * (1.46 + 0.028 * M) + (kmax > 4096.0 ? 3.6 : 0.0) +
+           (r > 0 ? 1.9 + kmax / 4096.0 * (2.46 + 0.16 * r + 0.204 * M) : 0.0);
 }
 
 // ---- several matrices in one launch per instantiation.  The descriptors (every pointer of every matrix)

@@ -140,8 +140,9 @@ hipError_t gemv_stream_bwd_batch_build(const std::vector<GbBatchItem>& items, co
                                        float* part, GbBatch& b);
 hipError_t gemv_stream_bwd_batch_run(const GbBatch& b, hipStream_t st);
 void gemv_stream_bwd_batch_free(GbBatch& b);
-double gemv_batch_us(const std::vector<GemvParams>& items);          // estimated time of a run by the general kernel ...
-double gemv_stream_batch_us(const std::vector<GemvParams>& items);   // ... and by the streaming kernel
+// estimated time of a run by the general kernel, and by the streaming kernel (n4: the matrices' 4-bit channels)
+double gemv_batch_us(const std::vector<GemvParams>& items, const std::vector<int>& n4);
+double gemv_stream_batch_us(const std::vector<GemvParams>& items, const std::vector<int>& n4);
 // the general small-token forward's instantiation for a matrix by itself (batch_strips 0) or in a batch of that many strips
 void gemv_plan(int N, int K, int M, int r, int batch_strips, int* wavefronts, int* rounds, int* fused);
 hipError_t gemv_batch_build(std::vector<GemvParams>& items, lowra_fwd_batch& b);
