@@ -37,16 +37,21 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
-def _compile_call(verbose: bool) -> None:
+def call_command(src: str, out: str) -> list[str]:
+    """How csrc/call.cpp becomes an extension module."""
     import sysconfig
 
     import torch
 
     t = os.path.dirname(torch.__file__)
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I/opt/rocm/include", f"-I{t}/include",
-           f"-I{t}/include/torch/csrc/api/include", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "call.cpp"),
-           "-o", CALL, f"-L{t}/lib", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", f"-Wl,-rpath,{t}/lib"]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I/opt/rocm/include", f"-I{t}/include",
+            f"-I{t}/include/torch/csrc/api/include", "-I" + sysconfig.get_paths()["include"], src,
+            "-o", out, f"-L{t}/lib", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", f"-Wl,-rpath,{t}/lib"]
+
+
+def _compile_call(verbose: bool) -> None:
+    cmd = call_command(os.path.join(CSRC, "call.cpp"), CALL)
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True, stderr=None if verbose else subprocess.PIPE)

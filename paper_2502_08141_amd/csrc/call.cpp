@@ -5,7 +5,9 @@
 // these calls take on the GPU; here it spends about 2.  Only the plain case is handled -- exact torch.Tensor arguments that
 // pass every check, and no torch mode that wants to see the allocations.  For anything else (a subclass, a wrong type, shape or
 // device, an exception from torch) the functions return None with nothing launched, and lowra.py goes through its own checks,
-// which raise what they always raised.  Nothing is kept between calls but the library's entry points.
+// which raise what they always raised.  So every object that a call returns exists before the library is called.  The interpreter's
+// lock is given up for the allocations too, as torch.empty does (one may wait for the GPU).  Nothing is kept between calls but
+// the library's entry points.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -63,14 +65,20 @@ PyObject* none() {
     PyErr_Clear();
     Py_RETURN_NONE;
 }
-// (status, result): the status is the library's, the result what the caller returns when it is zero
+// the interpreter's lock, given up for a scope
+struct Unlocked {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+at::Tensor empty(at::IntArrayRef sizes, const at::TensorOptions& options) {
+    Unlocked u;
+    return at::empty(sizes, options);
+}
+// what the caller returns: the result, or the library's status when that is not zero
 PyObject* done(int status, PyObject* result) {
-    if (!result) return nullptr;
-    if (status != 0) {
-        Py_DECREF(result);
-        return PyLong_FromLong(status);
-    }
-    return result;
+    if (status == 0) return result;
+    Py_DECREF(result);
+    return PyLong_FromLong(status);
 }
 
 // linear(which, layout, packed, absmax, mappings, act, A, B, s, workspace): which = 0 forward, 1 input gradient
@@ -102,15 +110,18 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
         void* const wp = ws.data_ptr();
         const size_t ws_bytes = (size_t)ws.numel() * ws.element_size();
         const float s = (float)PyFloat_AS_DOUBLE(a[8]);
-        at::Tensor out = at::empty({M, cols}, act->options());
-        int status;
+        at::Tensor out = empty({M, cols}, act->options());
+        void *po = out.data_ptr(), *st = current_stream();
         const void *pp = packed->data_ptr(), *pa = absmax->data_ptr(), *pm = mappings->data_ptr(), *px = act->data_ptr();
         const void *pA = A ? A->data_ptr() : nullptr, *pB = B ? B->data_ptr() : nullptr;
-        void *po = out.data_ptr(), *st = current_stream();
-        Py_BEGIN_ALLOW_THREADS
-        status = lib_linear[which](l.handle, pp, pa, pm, px, (int)M, pA, pB, (int)r, s, po, wp, ws_bytes, st);
-        Py_END_ALLOW_THREADS
-        return done(status, THPVariable_Wrap(std::move(out)));
+        PyObject* res = THPVariable_Wrap(std::move(out));
+        if (!res) return none();
+        int status;
+        {
+            Unlocked u;
+            status = lib_linear[which](l.handle, pp, pa, pm, px, (int)M, pA, pB, (int)r, s, po, wp, ws_bytes, st);
+        }
+        return done(status, res);
     } catch (...) {
         return none();
     }
@@ -141,8 +152,7 @@ PyObject* side_product(PyObject*, PyObject* const* a, Py_ssize_t n) {
     }
 }
 
-PyObject* pair(int status, at::Tensor dA, at::Tensor dB) {
-    if (status != 0) return PyLong_FromLong(status);
+PyObject* pair(at::Tensor dA, at::Tensor dB) {
     PyObject* x = THPVariable_Wrap(std::move(dA));
     PyObject* y = x ? THPVariable_Wrap(std::move(dB)) : nullptr;
     PyObject* t = y ? PyTuple_Pack(2, x, y) : nullptr;
@@ -164,16 +174,19 @@ PyObject* grads(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int64_t M = x->size(0), r = A->size(0);
         if (M > INT32_MAX || r > INT32_MAX || !shape2(*x, M, l.K) || !shape2(*dY, M, l.N) || !shape2(*A, r, l.K) || !shape2(*B, l.N, r)) return none();
         const auto opt = x->options().dtype(at::kFloat);
-        at::Tensor dA = at::empty({r, l.K}, opt), dB = at::empty({l.N, r}, opt);
+        at::Tensor dA = empty({r, l.K}, opt), dB = empty({l.N, r}, opt);
         const void *px = x->data_ptr(), *py = dY->data_ptr(), *pA = A->data_ptr(), *pB = B->data_ptr();
         void *qa = dA.data_ptr(), *qb = dB.data_ptr(), *wp = ws->data_ptr(), *st = current_stream();
         const size_t ws_bytes = (size_t)ws->numel();
         const float s = (float)PyFloat_AS_DOUBLE(a[5]);
+        PyObject* res = pair(std::move(dA), std::move(dB));
+        if (!res) return none();
         int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = lib_grads(l.handle, px, py, (int)M, pA, pB, (int)r, s, qa, qb, wp, ws_bytes, st);
-        Py_END_ALLOW_THREADS
-        return pair(status, std::move(dA), std::move(dB));
+        {
+            Unlocked u;
+            status = lib_grads(l.handle, px, py, (int)M, pA, pB, (int)r, s, qa, qb, wp, ws_bytes, st);
+        }
+        return done(status, res);
     } catch (...) {
         return none();
     }
@@ -193,15 +206,18 @@ PyObject* grads_from_side(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int64_t M = x->size(0);
         if (M > INT32_MAX || !shape2(*x, M, l.K) || !shape2(*dY, M, l.N) || !shape2(*ts, M, 64) || !shape2(*us, M, 64)) return none();
         const auto opt = x->options().dtype(at::kFloat);
-        at::Tensor dA = at::empty({r, l.K}, opt), dB = at::empty({l.N, r}, opt);
+        at::Tensor dA = empty({r, l.K}, opt), dB = empty({l.N, r}, opt);
         const void *px = x->data_ptr(), *py = dY->data_ptr(), *pt = ts->data_ptr(), *pu = us->data_ptr();
         void *qa = dA.data_ptr(), *qb = dB.data_ptr(), *wp = ws->data_ptr(), *st = current_stream();
         const size_t ws_bytes = (size_t)ws->numel();
+        PyObject* res = pair(std::move(dA), std::move(dB));
+        if (!res) return none();
         int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = lib_grads_side(l.handle, px, py, (int)M, (int)r, pt, pu, qa, qb, wp, ws_bytes, st);
-        Py_END_ALLOW_THREADS
-        return pair(status, std::move(dA), std::move(dB));
+        {
+            Unlocked u;
+            status = lib_grads_side(l.handle, px, py, (int)M, (int)r, pt, pu, qa, qb, wp, ws_bytes, st);
+        }
+        return done(status, res);
     } catch (...) {
         return none();
     }
@@ -218,14 +234,17 @@ PyObject* dequantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor* absmax = plain(a[2], l.bf16_scales ? at::kBFloat16 : at::kFloat);
         const at::Tensor* mappings = plain(a[3], at::kFloat);
         if (!state_ok(l, packed, absmax, mappings)) return none();
-        at::Tensor out = at::empty({l.N, l.K}, packed->options().dtype(at::kBFloat16));
+        at::Tensor out = empty({l.N, l.K}, packed->options().dtype(at::kBFloat16));
         const void *pp = packed->data_ptr(), *pa = absmax->data_ptr(), *pm = mappings->data_ptr();
         void *po = out.data_ptr(), *st = current_stream();
+        PyObject* res = THPVariable_Wrap(std::move(out));
+        if (!res) return none();
         int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = lib_dequant(l.handle, pp, pa, pm, 0, po, st);
-        Py_END_ALLOW_THREADS
-        return done(status, THPVariable_Wrap(std::move(out)));
+        {
+            Unlocked u;
+            status = lib_dequant(l.handle, pp, pa, pm, 0, po, st);
+        }
+        return done(status, res);
     } catch (...) {
         return none();
     }
