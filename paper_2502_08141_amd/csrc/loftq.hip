@@ -387,6 +387,8 @@ __global__ __launch_bounds__(256) void copy_cols_kernel(const uint16_t* __restri
 
 static inline size_t lq_align(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// Gp: the partial Gram matrices.  They lie in the place of F, which is used up by the time of the first round, or, with so few
+// channels that F is smaller than 32 KB per 128 features, in a place of their own.
 struct LoftqWs {
     size_t F, E, Y, Z, partial, Gp, Gp_bytes, G, A, At, total;
 };
@@ -398,7 +400,9 @@ static LoftqWs loftq_ws(int N, int K) {
     w.Y = o; o += lq_align((size_t)N * LQ_RP * 2);
     w.Z = o; o += lq_align((size_t)LQ_RP * K * 4);
     w.partial = o; o += lq_align(tn_partial_bytes(K, N, LQ_RP));
-    w.Gp = o; w.Gp_bytes = lq_align((size_t)((K + 127) / 128) * 4096 * sizeof(double)); o += w.Gp_bytes;
+    w.Gp = w.F; w.Gp_bytes = (size_t)N * K * 4;
+    const size_t own = (size_t)((K + 127) / 128) * 4096 * sizeof(double);
+    if (w.Gp_bytes < own) { w.Gp = o; w.Gp_bytes = own; o += lq_align(own); }
     w.G = o; o += lq_align(4096 * sizeof(double));
     w.A = o; o += lq_align((size_t)LQ_RP * K * 2);
     w.At = o; o += lq_align((size_t)K * LQ_RP * 2);
@@ -422,11 +426,8 @@ hipError_t launch_loftq(const lowra_layout& L, const float* W, const float* thre
     uint16_t* Y = reinterpret_cast<uint16_t*>(ws + o.Y);
     float* Zt = reinterpret_cast<float*>(ws + o.Z);
     float* partial = reinterpret_cast<float*>(ws + o.partial);
-    // The partial Gram matrices, one per tile of Z where there is room: in the place of F, which is used up by the time of the
-    // first round, or, with very few channels, in one of their own.
-    const size_t f_bytes = (size_t)N * K * 4;
-    double* Gp = reinterpret_cast<double*>(ws + (f_bytes >= o.Gp_bytes ? o.F : o.Gp));
-    const int tiles = K / LQ_GT, room = (int)std::min<size_t>(std::max(f_bytes, o.Gp_bytes) / (LQ_GENTRIES * sizeof(double)), (size_t)tiles);
+    double* Gp = reinterpret_cast<double*>(ws + o.Gp);
+    const int tiles = K / LQ_GT, room = (int)std::min<size_t>(o.Gp_bytes / (LQ_GENTRIES * sizeof(double)), (size_t)tiles);     // a partial matrix per tile, or fewer
     const int per = (tiles + room - 1) / room, parts = (tiles + per - 1) / per;
     double* G = reinterpret_cast<double*>(ws + o.G);
     uint16_t* A = reinterpret_cast<uint16_t*>(ws + o.A);

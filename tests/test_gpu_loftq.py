@@ -264,3 +264,27 @@ def test_loftq_nearly_dependent_start(r):
     assert np.isfinite(A).all() and np.abs(A @ A.T - np.eye(r)).max() <= ORTHONORMAL_TOL
     E = W.astype(np.float64) - orc.dequantize(p, a, bits, cb, mp, K, "fp32")
     assert rel_err(B, E @ A.T) <= REL_TOL
+
+
+@pytest.mark.parametrize("N,K", [(8, 64), (8, 1088), (56, 1088), (64, 1088), (72, 1088), (136, 4096)])
+def test_loftq_reported_workspace(N, K):
+    """Few channels: where the partial Gram matrices have a place of their own (32 KB per 128 features are more than the fp32
+    residual) and where they lie in the residual's.  The reported bytes are enough, whatever they hold, and are not exceeded;
+    in the second case they are the residual, its bf16 copy, the factors, one chunk's sums and one Gram matrix."""
+    print(f"[loftq workspace {N}x{K}]", flush=True)
+    W, bits, cb, cbb, thr, mp = make(9, N, K, (0.4, 0.3, 0.3))
+    lay = lowra.Layout(K, bits, cb, cbb)
+    om = bf16_dev(synth.to_bf16_bits(np.random.default_rng([4, N]).normal(0, 1, (8, K))))
+    need = lay.workspace_bytes(lowra.OP_LOFTQ_INIT, 0, 8)
+    if 4 * N * K >= (32 << 10) * -(-K // 128):
+        assert need <= 6 * N * K + 128 * N + 4 * 64 * K * 2 + 2 * 64 * K * 2 + 8 * 4096 + 9 * 256
+    outs = []
+    for fill in (0x00, 0xff):
+        ws = torch.full((need + 4096,), fill, dtype=torch.uint8, device="cuda")
+        outs.append(lowra.lowra_loftq_init(lay, torch.from_numpy(W).cuda(), torch.from_numpy(thr).cuda(), torch.from_numpy(mp).cuda(), 8, om,
+                                           steps=2, power_iterations=2, workspace=ws[:need]))
+        assert bool((ws[need:] == fill).all())
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)) and torch.isfinite(a.float()).all()
+    with pytest.raises(lowra.LowraError, match="workspace too small"):
+        lowra.lowra_loftq_init(lay, torch.from_numpy(W).cuda(), torch.from_numpy(thr).cuda(), torch.from_numpy(mp).cuda(), 8, om, workspace=ws[:need - 256])
