@@ -174,17 +174,6 @@ __global__ __launch_bounds__(256) void tn_skinny_kernel(const TnProb pa, const T
     }
 }
 
-// out[c][j] = sum over chunks of partial[chunk][c][j], j < r
-__global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict__ partial, int nchunks, int C, int RP, int r,
-                                                        float* __restrict__ out) {
-    const size_t tot = (size_t)C * r;
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < tot; e += (size_t)gridDim.x * 256) {
-        const int c = (int)(e / r), j = (int)(e % r);
-        float s = 0.0f;
-        for (int k = 0; k < nchunks; ++k) s += partial[((size_t)k * C + c) * RP + j];
-        out[e] = s;
-    }
-}
 // The chunk sums of a launch's products in one launch (a second one cost 3.2 to 4.8 us behind the first).  A workgroup takes
 // 16 columns c and reads their partial rows as they lie (64 ranks = 256 contiguous bytes per column): out[c][j], or written
 // transposed, out[j][c], the tile turned through LDS so that the stores run along c too.
@@ -288,12 +277,14 @@ hipError_t launch_tn_partial(const uint16_t* P, int C, int M, const uint16_t* Q,
     return hipGetLastError();
 }
 
-// No tokens: both gradients are zero (the reduction over zero chunks writes exactly that; a kernel
-// rather than a memset, so the call can be captured into a graph).
+// No tokens: both gradients are zero (a kernel rather than a memset, so the call can be captured into a graph).
+__global__ __launch_bounds__(256) void zero_kernel(float* __restrict__ out, size_t n) {
+    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) out[e] = 0.0f;
+}
 hipError_t launch_zero_grads(int N, int K, int r, float* dA, float* dB, hipStream_t st) {
     const size_t ta = (size_t)r * K, tb = (size_t)N * r;
-    if (ta) tn_reduce_kernel<<<dim3((unsigned)std::min<size_t>((ta + 255) / 256, 4096)), dim3(256), 0, st>>>(nullptr, 0, K, 64, r, dA);
-    if (tb) tn_reduce_kernel<<<dim3((unsigned)std::min<size_t>((tb + 255) / 256, 4096)), dim3(256), 0, st>>>(nullptr, 0, N, 64, r, dB);
+    if (ta) zero_kernel<<<dim3((unsigned)std::min<size_t>((ta + 255) / 256, 4096)), dim3(256), 0, st>>>(dA, ta);
+    if (tb) zero_kernel<<<dim3((unsigned)std::min<size_t>((tb + 255) / 256, 4096)), dim3(256), 0, st>>>(dB, tb);
     return hipGetLastError();
 }
 
