@@ -105,3 +105,16 @@ def test_infinite_activations_stay_in_their_ranks(N, K, M, r):
             assert torch.isposinf(side[1, :r]).all() and not side[:, r:].any()
             assert torch.equal(out[1], sign.float() * float("inf"))
             assert torch.isfinite(out[0]).all() and torch.isfinite(out[2:]).all()
+
+
+@pytest.mark.parametrize("N,K,M,r", [(264, 1088, 33, 64), (264, 4096, 20, 8), (4096, 1088, 20, 64), (2048, 4096, 17, 16), (1536, 4096, 1, 8),
+                                     (264, 1600, 1024, 8), (264, 1600, 1025, 8)])
+def test_both_products_in_one_launch(N, K, M, r):
+    """Neither, one and both of the two contractions split between workgroups, with the fewest tokens, the most that share a
+    launch and one more: the same bits as the products of the linear calls, from a workspace of NaN."""
+    test_adapter_gradients_form_the_same_products(N, K, M, r, lowra.PATH_GEMM)
+    D = DeviceLayer(synth.make_custom(N, K, M, r, fractions=(0.5, 0.5, 0.0), seed=830 + r))
+    ws = torch.full((D.layout.workspace_bytes(lowra.OP_ADAPTER_GRADS, M, r),), 0xff, dtype=torch.uint8, device="cuda")
+    got = lowra.lowra_adapter_grads(D.layout, D.x, D.dY, D.A, D.B, D.L.s, workspace=ws)
+    want = lowra.lowra_adapter_grads(D.layout, D.x, D.dY, D.A, D.B, D.L.s)
+    assert all(torch.equal(a, b) and torch.isfinite(a).all() for a, b in zip(got, want))
