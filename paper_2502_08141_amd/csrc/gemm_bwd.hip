@@ -139,15 +139,12 @@ __global__ __launch_bounds__(NTHREADS) void linear_bwd_kernel(GemmParams p_in) {
             for (int i = 0; i < 8; ++i)
                 dma16(base + a_voff_main[i], lds_of(sdst) + wave * 8192 + i * 1024);
         } else if (nt < nt_main) {
-            // ragged last step: chunks past N are clamped onto the last valid chunk (their weights are zero)
-            const uint8_t* base = reinterpret_cast<const uint8_t*>(p.act + (size_t)m0 * p.ld_act);
-            const int last_chunk = p.N / 8 - 1;
+            // ragged last step: chunks past N are zeros, as their weights are (an infinity times zero would be none)
+            const bufdesc_t act = buffer_desc(p.act + (size_t)m0 * p.ld_act);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                int ch = nt * 8 + (int)a_chunk(i);
-                ch = ch < last_chunk ? ch : last_chunk;
-                dma16(base + a_row_c(i) * (uint32_t)p.ld_act * 2u + (uint32_t)ch * 16u, lds_of(sdst) + wave * 8192 + i * 1024);
-            }
+            for (int i = 0; i < 8; ++i)
+                dma16_b(act, nt * 8 + (int)a_chunk(i) < p.N / 8 ? a_voff_main[i] : 0x80000000u, (uint32_t)nt * (BK * 2u),
+                        lds_of(sdst) + wave * 8192 + i * 1024);
         } else {
             const uint8_t* base = reinterpret_cast<const uint8_t*>(p.ext_act + (size_t)m0 * p.RP + (size_t)(nt - nt_main) * BK);
 #pragma unroll
