@@ -1,4 +1,4 @@
-"""The 256-column GEMMs where the contraction ends inside a step of 64 channels or features."""
+"""Contractions that end inside a step: of 64 channels or features in the 256-column GEMMs, of 64 tokens in the adapter gradients."""
 import pytest
 import torch
 
@@ -37,3 +37,29 @@ def test_infinite_activations_in_the_last_step(N, K, M, fr, r):
                 assert torch.isfinite(out[0]).all() and torch.isfinite(out[2:]).all(), (fwd, at)
     finally:
         lowra.lowra_set_linear_path(lowra.PATH_AUTO)
+
+
+@pytest.mark.parametrize("N,K,M,r", [(40, 1088, 1, 5), (264, 1600, 17, 64), (8, 64, 65, 8), (136, 4096, 300, 24), (1544, 1088, 2100, 64)])
+def test_infinite_activations_of_the_last_token(N, K, M, r):
+    """Adapter gradients: an infinity in the last token's features or channels makes the gradients of that feature or channel
+    infinite, of the rank-r intermediate's sign, and no other; likewise one in the intermediate, for its rank."""
+    print(f"[inf token {N}x{K} M{M} r{r}]", flush=True)
+    D = DeviceLayer(synth.make_custom(N, K, M, r, fractions=(0.5, 0.5, 0.0), seed=920 + r))
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    side = [torch.randn(M, 64, generator=gen, device="cuda").bfloat16() for _ in range(2)]
+    for s in side:
+        s[:, r:] = 0
+        assert (s[-1, :r] != 0).all()
+    inf = float("inf")
+    grads = lambda x=D.x, dY=D.dY, st=side[0], su=side[1]: lowra.lowra_adapter_grads_from_side(D.layout, x, dY, r, st, su)
+    for hit in ("x", "dY", "st", "su"):
+        t = {"x": D.x, "dY": D.dY, "st": side[0], "su": side[1]}[hit].clone()
+        at = r - 1 if hit in ("st", "su") else t.shape[1] - 1
+        t[-1, at] = inf
+        dA, dB = grads(**{hit: t})
+        other = {"x": side[1][-1, :r], "dY": side[0][-1, :r], "st": D.dY[-1], "su": D.x[-1]}[hit].float()
+        g, rest = (dA, dB) if hit in ("x", "su") else (dB.T, dA)         # [r, features or channels]
+        line, keep = (g[:, at], g[:, :at]) if hit in ("x", "dY") else (g[at], g[:at])
+        nz = other != 0
+        assert torch.equal(line[nz], (other.sign() * inf)[nz]), hit
+        assert torch.isfinite(keep).all() and torch.isfinite(rest).all(), hit
