@@ -815,13 +815,14 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
             if (t < best_t * (1.0 - 1e-9)) { best_t = t; best = pl; }
         }
     }
-    const double big = op == 0 ? gemm_fwd_steps(N, K, M, (best_t - mc.big_launch) / mc.big_step) : gemm_bwd_steps(N, K, M);
+    constexpr double kLevel = 1.02;      // about level: the 256-column kernels need no partial tiles
+    const double big = op == 0 ? gemm_fwd_steps(N, K, M, (kLevel * best_t - mc.big_launch) / mc.big_step) : gemm_bwd_steps(N, K, M);
     double big_t = mc.big_launch + big * mc.big_step;
     if (op == 1) {
         const BwdSplitPlan sp = gemm_bwd_split_plan(N, K, M);
         if (sp.splits > 1) big_t += 5.0 + (double)sp.splits * sp.tail * BM * BN * sizeof(float) * mc.per_byte;
     }
-    if (big_t <= 1.02 * best_t) best = MidPlan{0, 0, 0, 0, 0};        // (about level: the 256-column kernels need no partial tiles)
+    if (big_t <= kLevel * best_t) best = MidPlan{0, 0, 0, 0, 0};
     return best;
 }
 

@@ -166,6 +166,17 @@ def test_mid_token_planner():
     assert lowra.lowra_plan_mid_tiling(FWD, 11008, 4096, 4096, True, 3) == (0, 0)
 
 
+def test_mid_token_planner_odd_groups():
+    """Host only: with an odd number of groups the 256-column forward takes three to six times the mid-token kernel's time per
+    step, so no call goes there that the planner compares (up to 16 workgroups of 128 x 128 outputs per unit)."""
+    for N in (3000, 4096, 8184, 13824):
+        for K in range(192, 6000, 128):
+            for M in (*range(64, 4200, 224), 3072, 6000, 8192):
+                if -(-N // 128) * -(-M // 128) <= 16 * 256:
+                    for wide, books in ((False, 3), (False, N), (True, 3), (True, N)):
+                        assert lowra.lowra_plan_mid_tiling(lowra.OP_LINEAR_FWD, N, K, M, wide, books) != (0, 0), (N, K, M, wide, books)
+
+
 def test_small_forward_planner():
     """Host only: the general small-token forward's wavefronts.  A low rank needs no more of a workgroup's memory than a high one
     where its t comes from a launch of its own, so it must not run through fewer wavefronts; and where the form that makes t
