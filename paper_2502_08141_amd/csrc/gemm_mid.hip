@@ -126,7 +126,8 @@ __device__ __forceinline__ void mid_epilogue(const MidParams& p, const floatx16_
 // scales are staged in LDS by counted transfers, an odd number of groups is its own instantiation; with a branch at every
 // transfer the compiler emptied the matrix pipe at each.  4096 x 4096, 512 tokens, 50/50 % of 1-/2-bit rows 39 -> 30 us;
 // 4096 x 1024, 777 tokens with 4-bit rows 19.8 -> 17.1.  (b) Tiles of 192 tokens, which halve the decode of tiles of 96:
-// 11008 x 4096, 333 tokens, 50/25/25 %: 77 us -> 70 (a) -> 55.  They leave LDS for one workgroup per unit.
+// 11008 x 4096, 333 tokens, 50/25/25 %: 77 us -> 70 (a) -> 55 in calls that follow each other (waited for, or in a kernel
+// trace, a launch takes 58 to 62).  They leave LDS for one workgroup per unit.
 template <int TM, bool WIDE, bool ODD>
 struct FwdLds {
     static constexpr int STAGE = TM * 4096;                           // 32 TM token rows x 128 bytes

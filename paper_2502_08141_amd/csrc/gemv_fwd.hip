@@ -31,9 +31,10 @@
 //
 // A call on one matrix is a chain of round trips and of instructions that every wavefront of a workgroup issues (four per
 // SIMD: 16 cycles an instruction).  So the chain's head, the row record, is asked for first; the levels come by one
-// load of one wavefront; nothing waits for t before the end; and few blocks take fewer wavefronts.  One call, before -> after:
-// 256 x 512, 16 tokens 9.0 -> 5.0 us; 4096 x 1024, 4 tokens 9.0 -> 6.1; 11008 x 4096, 1 token 17.7 -> 15.2;
-// 4096 x 4096, 1 token 9.4 -> 9.2; three 4096 x 4096 matrices in one launch 19.8 -> 17.2.
+// load of one wavefront; nothing waits for t before the end; and few blocks take fewer wavefronts.  A call in a captured graph,
+// before -> after: 256 x 512, rank 8, 16 tokens 9.0 -> 5.0 us; 4096 x 1024, 4 tokens, rank 16 8.7 -> 6.0, rank 64 11.1 -> 9.3;
+// 11008 x 4096, rank 16, 1 token 15.9 -> 14.5; three 4096 x 4096 matrices in one launch 17.7 -> 16.1; and level: one 4096 x 4096
+// matrix, 1 token, rank 16 8.65, rank 64 10.9 -> 11.0.
 #include <algorithm>
 #include <cmath>
 
