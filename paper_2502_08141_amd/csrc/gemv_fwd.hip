@@ -41,10 +41,6 @@
 #include "gemm_common.h"
 #include "gemv_t.h"
 
-#ifndef LOWRA_BATCH_SMALL_WG
-#define LOWRA_BATCH_SMALL_WG 1
-#endif
-
 namespace lowra {
 
 constexpr int GV_XROW = 512;                 // bytes per token row of a staged activation block (256 bf16)
@@ -472,15 +468,16 @@ static size_t gemv_lds_least(const GemvParams& p, const GemvChoice& c) {
     const int nblk = (p.G + 3) / 4, rows2 = (std::min(p.M, 16) + 1) / 2;
     return (size_t)GV_FIXED + gemv_t_bytes(c.W, c.PER, p.RT, c.fuse) + (size_t)std::min((nblk + c.W - 1) / c.W, 2) * c.W * rows2 * 1024;
 }
-// many_strips: the matrix shares its launch; strips: of the launch
-static GemvChoice gemv_choose(const GemvParams& p, bool many_strips, int strips) {
+// strips: of the launch
+static GemvChoice gemv_choose(const GemvParams& p, int strips) {
     constexpr size_t kMaxLds = 160 * 1024;
     const int nblk = (p.G + 3) / 4;
     const bool fuses = gemv_fuses(p, strips);
     // (up to 24 blocks: 5120 features, three rounds; one token, three matrices of 5120 channels 34 -> 24 us, two of 13824
-    // 59 -> 38 us against one 16-wavefront workgroup per unit)
+    // 59 -> 38 us against one 16-wavefront workgroup per unit; a batch whose strips have a unit each takes the 16, as a call does:
+    // one 2048 x 2048 matrix, 4 tokens, rank 16 9.2 -> 7.2 us, one of 4096 9.95 -> 9.3)
     const size_t lds8 = gemv_lds_least(p, {8, 2, 0});
-    const bool pair8 = (many_strips || (p.N + 15) / 16 > compute_units_cached()) && 2 * lds8 <= (size_t)150 * 1024 && nblk <= 24;
+    const bool pair8 = strips > compute_units_cached() && 2 * lds8 <= (size_t)150 * 1024 && nblk <= 24;
     if (!pair8) {
         // What counts is the LDS of the form that the call will have: with 15 and 16 tokens the sums of 16 wavefronts that form t
         // are 1.5 KB too many, and then t comes from its own launch rather than through half as many wavefronts (4096 x 4096,
@@ -509,7 +506,7 @@ static std::vector<GemvChoice> gemv_choose_batch(const std::vector<GemvParams>& 
     for (const GemvParams& p : items) strips += (p.N + 15) / 16;
     std::vector<GemvChoice> out;
     for (const GemvParams& p : items) {
-        out.push_back(gemv_choose(p, LOWRA_BATCH_SMALL_WG != 0, strips));
+        out.push_back(gemv_choose(p, strips));
         if (out.back().PER == 1) { strips1 += (p.N + 15) / 16; W = std::max(W, out.back().W); }
     }
     if (strips1 > compute_units_cached()) return out;
@@ -527,8 +524,7 @@ static std::vector<GemvChoice> gemv_choose_batch(const std::vector<GemvParams>& 
 void gemv_plan(int N, int K, int M, int r, int batch_strips, int* wavefronts, int* rounds, int* fused) {
     GemvParams p{};
     p.N = N; p.K = K; p.G = K / kGroup; p.M = M; p.r = r; p.RT = r > 0 ? (r + 15) / 16 * 16 : 0;
-    const bool batch = batch_strips > 0;
-    const GemvChoice c = gemv_choose(p, batch && LOWRA_BATCH_SMALL_WG != 0, batch ? batch_strips : (N + 15) / 16);
+    const GemvChoice c = gemv_choose(p, batch_strips > 0 ? batch_strips : (N + 15) / 16);
     *wavefronts = c.W; *rounds = ((p.G + 3) / 4 + c.W - 1) / c.W; *fused = c.fuse;
 }
 // calls f.template operator()<W, PER, FUSE>() for the chosen instantiation
@@ -554,7 +550,7 @@ struct LaunchSingle {
 };
 
 hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
-    const GemvChoice c = gemv_choose(p, false, (p.N + 15) / 16);
+    const GemvChoice c = gemv_choose(p, (p.N + 15) / 16);
     if (p.RT > 0 && !c.fuse) {
         gemv_t_partial_kernel<<<dim3((p.G + 3) / 4), dim3(64), 0, st>>>(p.x, p.M, p.K, p.A, p.r, p.RT, p.tp);
         const hipError_t e = hipGetLastError();

@@ -195,6 +195,8 @@ def test_small_forward_planner():
                 waves = [plan(N, K, M, r, strips)[0] for r in ((0, 8, 16, 17, 64, 128) if N <= 4096 and not strips else (8, 16, 17))]
                 assert all(a >= b for a, b in zip(waves, waves[1:])), (N, K, M, strips, waves)
                 for r in (0, 8, 16, 64):
+                    if N <= 4096:                            # a batch whose strips have a unit each takes what a call does
+                        assert plan(N, K, M, r, -(-N // 16)) == plan(N, K, M, r), (N, K, M, r)
                     w, rounds, fused = plan(N, K, M, r, strips)
                     assert w * rounds * 256 >= K and (not fused or (rounds == 1 and 0 < r <= 16)), (N, K, M, r, strips)
     for bad in [(0, 256, 1, 0, 0), (8, 100, 1, 0, 0), (8, 256, 17, 0, 0), (8, 256, 1, -1, 0), (8, 256, 1, 0, -1)]:
