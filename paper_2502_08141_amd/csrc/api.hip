@@ -505,9 +505,10 @@ static lowra_status fwd_batch_create_impl(int n, const lowra_fwd_item* items, co
         ws += batch_item_ws(L, r);
     }
     // LOWRA_PATH_AUTO: the general kernel (which reads fp32 scales) takes the batch where it is estimated to be the faster one;
-    // matrices that the streaming kernel does not take are the general kernel's either way.  Of 5120 batches (one to seven matrices
-    // of 1024 to 13824 features, 1 to 16 tokens, ranks 0 to 32) 155 run more than 3 % and 23 more than 10 % slower than with the
-    // other choice (worst: three 3072 x 3072 matrices of 1.15 bits, 7 tokens, no rank-r term, 15.8 for 12.3 us), 0.3 % on average.
+    // matrices that the streaming kernel does not take are the general kernel's either way.  Of 13824 batches (one to seven matrices
+    // of 1024 to 16384 features, 1 to 16 tokens, ranks 0 to 32) 204 run more than 3 % and 30 more than 10 % slower than with the
+    // other choice (worst: seven matrices of a 1536 x 4096 layer at 2 bits, 10 tokens, no rank-r term, 20.3 for 16.4 us), 0.1 % on
+    // average.
     if (path == LOWRA_PATH_AUTO && fp32_scales) {
         std::vector<lowra::GemvParams> rest, taken;
         std::vector<int> n4, n4_rest, n4_taken;

@@ -559,20 +559,23 @@ hipError_t launch_gemv_fwd(const GemvParams& p, hipStream_t st) {
     return gemv_dispatch(c, LaunchSingle{p, st});
 }
 
-// Which kernel a batch takes: estimated times, fits to 4736 batches (one to seven matrices of 1024 to 13824 features, every
-// token count from 1 to 16, ranks 0, 8, 16 and 32, 1.15 and 2 bits; least squares of the relative error: 8 % here, 4 % for the
-// streaming kernel).  This kernel takes its instantiations' launches one after the other; each takes as many rounds as its strips
-// fill the compute units with as many workgroups as they hold, and a round costs a fixed part and a part per block of 256
-// features.  The streaming kernel pays 11 us before and behind its stream, and with a rank-r term its t kernel, which is a
-// chain over the features.  A decoder layer of 4096 x 11008 taken apart by data dependence, 4 tokens, rank 16: q,k,v 17.7 us here
-// against 26.8, o 10.3 / 20.3, gate,up 27.6 / 30.4, down 17.4 / 39.1; all seven matrices in one batch 53.8 / 55.5, and without
-// a rank-r term 48.3 / 38.6.
+// Which kernel a batch takes: estimated times, fits to 13824 batches (the projections of layers of nine sizes, 1024 x 2816 to
+// 6144 x 16384, one to seven matrices, every token count from 1 to 16, ranks 0, 8, 16 and 32, 1.15 to 2.5 bits with and without
+// 4-bit rows; least squares of the relative error, batches that both kernels run in about the same time counted up to eleven times:
+// 8 % here, 6 % for the streaming kernel).
+// This kernel takes its instantiations' launches one after the other; each takes as many rounds as its strips fill the compute
+// units with as many workgroups as they hold.  A round costs a fixed part, a part per block of 256 features that a wavefront walks
+// and a part by the wavefronts that have a block (12 of 16 at 3072 features: without it q,k,v,o there were put at 21.0 us for 18.5,
+// and at 26.5 for 27.1 at 4096).  The streaming kernel pays 11 us before and behind its stream, and with a rank-r term its t
+// kernel, which is a chain over the features.  A decoder layer of 4096 x 11008 taken apart by data dependence, 4 tokens, rank 16:
+// q,k,v 17.7 us here against 26.8, o 10.3 / 20.3, gate,up 27.6 / 30.4, down 17.4 / 39.1; all seven matrices in one batch 53.8 /
+// 55.5, and without a rank-r term 48.3 / 38.6.
 double gemv_batch_us(const std::vector<GemvParams>& items, const std::vector<int>& n4) {
     if (items.empty()) return 0.0;
     const std::vector<GemvChoice> choices = gemv_choose_batch(items);
-    struct Launch { GemvChoice c; size_t lds; double strips, blocks; };
+    struct Launch { GemvChoice c; size_t lds; double strips, blocks, busy, wide; };
     std::vector<Launch> launches;
-    double channels = 0.0, wide = 0.0, kmax = 0.0;
+    double kmax = 0.0;
     bool t_launch = false;
     for (size_t i = 0; i < items.size(); ++i) {
         const GemvParams& p = items[i];
@@ -581,23 +584,25 @@ double gemv_batch_us(const std::vector<GemvParams>& items, const std::vector<int
         const size_t lds = gemv_lds(p, c, &xbufs);
         size_t l = 0;
         while (l < launches.size() && !(launches[l].c.W == c.W && launches[l].c.PER == c.PER && launches[l].c.fuse == c.fuse && launches[l].lds == lds)) ++l;
-        if (l == launches.size()) launches.push_back(Launch{c, lds, 0.0, 0.0});
+        if (l == launches.size()) launches.push_back(Launch{c, lds, 0.0, 0.0, 0.0, 0.0});
         const int strips = (p.N + 15) / 16, nblk = (p.G + 3) / 4;
+        const double busy = (double)strips * nblk / c.W;
         launches[l].strips += strips; launches[l].blocks += (double)strips * ((nblk + c.W - 1) / c.W);
-        channels += p.N; wide += n4[i]; kmax = std::max(kmax, (double)p.K);
+        launches[l].busy += busy; launches[l].wide += busy * n4[i] / p.N;
+        kmax = std::max(kmax, (double)p.K);
         t_launch = t_launch || (p.RT > 0 && !c.fuse);
     }
     const double M = items[0].M, ranks = items[0].RT / 16;
-    double t = 0.91 + 0.93 * (double)launches.size() + (t_launch ? 2.62 + 0.47 * (1.0 + ranks) * kmax / 4096.0 : 0.0);
+    double t = 1.42 + (t_launch ? 2.47 + 0.56 * (1.0 + ranks) * kmax / 4096.0 : 0.0);
     for (const Launch& l : launches) {
         // workgroups of a unit by LDS and by registers
         const int most = l.c.W == 16 ? (l.c.PER == 1 ? 2 : 1) : l.c.W == 8 ? (l.c.PER <= 2 ? 3 : l.c.PER <= 4 ? 2 : 1) : (l.c.PER == 1 ? 7 : 6);
         const int n = std::max(1, std::min(most, (int)((size_t)160 * 1024 / std::max<size_t>(l.lds, 1))));
         double rounds = l.strips / (double)(compute_units_cached() * n);
         rounds = n == 1 ? std::ceil(rounds - 1e-9) : rounds < 1.0 ? 0.5 + 0.5 * rounds : rounds;
-        const double fixed = l.c.W == 16 ? 2.44 : l.c.W == 4 ? 1.97 : n == 1 ? 2.24 : n == 2 ? 3.88 : 0.0;
-        const double block = l.c.W == 16 ? 2.03 : l.c.W == 4 ? 2.54 : n == 1 ? 1.32 : n == 2 ? 1.56 : 4.27;
-        t += rounds * (fixed + l.blocks / l.strips * (block + 0.013 * M + 2.0 * wide / channels) + 0.46 * ranks);
+        const double fixed = l.c.W == 16 ? (n == 1 ? 1.69 : 4.1) : l.c.W == 4 ? 5.02 : n == 1 ? 2.62 : n == 2 ? 3.91 : 3.66;
+        const double busy = l.c.W == 16 ? (n == 1 ? 2.08 : 2.16) : l.c.W == 4 ? 0.17 : n == 1 ? 0.44 : n == 2 ? 0.89 : 2.34;
+        t += rounds * (fixed + (l.busy * (busy + 0.035 * M) + l.wide * 2.36 + l.blocks * 0.68) / l.strips + 0.45 * ranks + (l.c.fuse ? 1.9 : 0.0));
     }
     return t;
 }
@@ -610,8 +615,8 @@ double gemv_stream_batch_us(const std::vector<GemvParams>& items, const std::vec
         kmax = std::max(kmax, (double)p.K);
     }
     const double M = items[0].M, r = items[0].r;
-    return 10.6 + 0.13 * M + units * (1.46 + 0.028 * M) + (kmax > 4096.0 ? 3.6 : 0.0) +
-           (r > 0 ? 1.9 + kmax / 4096.0 * (2.46 + 0.16 * r + 0.204 * M) : 0.0);
+    return 11.48 + 0.049 * M + units * (1.191 + 0.053 * M) + (kmax > 4096.0 ? 4.77 : 0.0) +
+           (r > 0 ? 1.62 + kmax / 4096.0 * (2.9 + 0.165 * r + 0.118 * M) : 0.0);
 }
 
 // ---- several matrices in one launch per instantiation.  The descriptors (every pointer of every matrix)
