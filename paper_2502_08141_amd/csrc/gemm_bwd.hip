@@ -816,10 +816,17 @@ BwdSplitPlan gemm_bwd_split_plan(int N, int K, int M) {
     return pl;
 }
 
-double gemm_bwd_steps(int N, int K, int M) {
+BwdWork gemm_bwd_work(int N, int K, int M, bool any4) {
     const BwdSplitPlan pl = gemm_bwd_split_plan(N, K, M);
-    const int cus = device_compute_units(), steps = (N + BK - 1) / BK, whole = pl.splits > 1 ? pl.first : pl.first + pl.tail;
-    return (double)((whole + cus - 1) / cus) * steps + (pl.splits > 1 ? pl.rows_per_split / BK : 0);
+    const int cus = device_compute_units(), whole = pl.splits > 1 ? pl.first : pl.first + pl.tail;
+    BwdWork w{0.0, 0.0, 0.0, pl.splits > 1 ? (double)pl.splits * pl.tail * BM * BN * sizeof(float) : 0.0};
+    auto add = [&](int rounds, int rows) {                            // the kernel's own rule for its pipeline
+        const int steps = (rows + BK - 1) / BK, full = rows / BK, piped = !any4 && (K & 255) == 0 && full >= 8 ? full - 1 : 0;
+        w.rounds += rounds; w.pipelined += (double)rounds * piped; w.general += (double)rounds * (steps - piped);
+    };
+    add((whole + cus - 1) / cus, N);
+    if (pl.splits > 1) add(1, pl.rows_per_split);
+    return w;
 }
 
 }  // namespace lowra

@@ -46,6 +46,9 @@ struct GemmParams {
 // plan of a split input gradient (gemm_bwd_split_plan): workgroups per split tile, rows of the matrix per split,
 // first split tile, number of split tiles
 struct BwdSplitPlan { int splits, rows_per_split, first, tail; };
+// What such a plan comes to: rounds of workgroups, their steps in the pipeline and in general form, and
+// the bytes of partial tiles
+struct BwdWork { double rounds, pipelined, general, part_bytes; };
 
 struct GemvParams {
     const SortedRow* sorted_rows;

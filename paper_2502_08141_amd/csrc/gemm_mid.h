@@ -27,10 +27,10 @@ struct MidParams {
 };
 
 struct MidPlan { int TM, tiles_c, tiles_m, splits, per_split; };         // TM == 0: the call belongs to another kernel
-// contraction steps of a whole 256 x 256 tile that the 256-column kernels' plans come to (forward: any value above
-// `enough` may stand for a larger one)
+// contraction steps of a whole 256 x 256 tile that the 256-column forward's plan comes to (any value above `enough` may stand
+// for a larger one)
 double gemm_fwd_steps(int N, int K, int M, double enough);
-double gemm_bwd_steps(int N, int K, int M);
+BwdWork gemm_bwd_work(int N, int K, int M, bool any4);
 BwdSplitPlan gemm_bwd_split_plan(int N, int K, int M);
 MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_bytes);
 void force_mid_plan(int rows, int splits);         // lowra_set_mid_tiling; 0, 0: the planner

@@ -760,25 +760,35 @@ hipError_t launch_mid_variant(const MidParams& p, int op, hipStream_t st) {
 // with 1 to 24 splits (8 shapes from 1024 x 1024 to 5120 x 13824, an odd group count among them, 24 to 2048 tokens; calls
 // repeated on two sets of buffers, without a rank-r term).  Forward: 5040 timings, rms error 8 %, the plan picked within
 // 0.4 to 0.9 % of the best one measured on average.  Input gradient: 5721, 7 - 8 %, 0.4 to 0.7 %.  The 256-column kernels'
-// time, fitted in the same way, is compared with it: they win once their tiles fill the chip.  Forward, 4096 x 4096, 2048
+// time is compared with it: they win once their tiles fill the chip.  Forward, 4096 x 4096, 2048
 // tokens: 50/50 % of 1-/2-bit rows 72 us against 73 here, 50/25/25 % of 1-/2-/4-bit rows 96 against 88; input gradient 80
 // against 94, and with 4-bit rows level (98.6), from about 1000 tokens on.
+// The 256-column input gradient is taken as rounds of workgroups, each with a fixed part (prologue, pipeline fill, output), its
+// steps, those outside the pipeline 2.4 times as long, and the partial tiles: 896 timings of PATH_GEMM at each mix (72 to 5120
+// channels, 256 to 13824 features, 257 to 4096 tokens), rms error 6 % and 5 %.  As a launch and steps of one length (rms error 45 %)
+// it was put at less than half its time for few channels and for K % 256 != 0: 264 x 5504, 3072 tokens took 62 us where 128-column
+// tiles take 32, 4096 x 4160, 2048 tokens 228 for 127.
 constexpr int kHeights = 5;
 static const int kMidHeight[kHeights] = {1, 2, 3, 4, 6};              // TM: 32 tokens each
 struct MidCost {
     double solo[kHeights], share[kHeights];  // us per step (64 of the contraction)
     double launch, round, split, per_byte;   // us per call; per round of workgroups; more when split; per byte of partial tiles
-    double big_launch, big_step;     // the 256-column kernel: us per call, us per step of a 256 x 256 tile
 };
 static const MidCost kMidCost[2][3] = {
     // forward: 1- and 2-bit rows only; with 4-bit rows, up to kMidLutBooks codebooks; with 4-bit rows, more codebooks
-    {{{0.35, 0.34, 0.43, 0.52, 0.70}, {0.23, 0.29, 0.36, 0.43, 0.57}, 3.6, 0.3, 3.2, 3.5e-7, 5.0, 1.29},
-     {{0.46, 0.51, 0.61, 0.69, 0.81}, {0.35, 0.41, 0.47, 0.54, 0.74}, 5.6, 0.1, 2.9, 3.1e-7, 10.7, 1.70},
-     {{0.46, 0.53, 0.61, 0.68, 0.80}, {0.33, 0.42, 0.47, 0.57, 0.81}, 5.4, 0.3, 3.2, 2.9e-7, 11.6, 1.73}},
+    {{{0.35, 0.34, 0.43, 0.52, 0.70}, {0.23, 0.29, 0.36, 0.43, 0.57}, 3.6, 0.3, 3.2, 3.5e-7},
+     {{0.46, 0.51, 0.61, 0.69, 0.81}, {0.35, 0.41, 0.47, 0.54, 0.74}, 5.6, 0.1, 2.9, 3.1e-7},
+     {{0.46, 0.53, 0.61, 0.68, 0.80}, {0.33, 0.42, 0.47, 0.57, 0.81}, 5.4, 0.3, 3.2, 2.9e-7}},
     // input gradient
-    {{{0.56, 0.61, 0.71, 0.89, 0.98}, {0.38, 0.46, 0.51, 0.63, 0.87}, 4.5, 0.1, 2.9, 4.2e-7, 7.3, 1.22},
-     {{0.56, 0.73, 0.82, 0.90, 1.13}, {0.46, 0.56, 0.62, 0.71, 1.13}, 5.4, 1.0, 2.9, 3.3e-7, 9.4, 1.72},
-     {{0.69, 0.69, 0.80, 0.92, 1.37}, {0.53, 0.54, 0.66, 0.50, 1.29}, 5.5, 1.0, 2.2, 3.9e-7, 6.9, 2.72}}};
+    {{{0.56, 0.61, 0.71, 0.89, 0.98}, {0.38, 0.46, 0.51, 0.63, 0.87}, 4.5, 0.1, 2.9, 4.2e-7},
+     {{0.56, 0.73, 0.82, 0.90, 1.13}, {0.46, 0.56, 0.62, 0.71, 1.13}, 5.4, 1.0, 2.9, 3.3e-7},
+     {{0.69, 0.69, 0.80, 0.92, 1.37}, {0.53, 0.54, 0.66, 0.50, 1.29}, 5.5, 1.0, 2.2, 3.9e-7}}};
+// The 256-column kernels, by class as above.  Forward: us per call, us per step of a 256 x 256 tile.  Input gradient: us per call,
+// per round of workgroups, per step in the pipeline and in general form, more when split, per byte of partial tiles (with more
+// codebooks: the earlier fit, a launch and steps).
+static const double kBigFwd[3][2] = {{5.0, 1.29}, {10.7, 1.70}, {11.6, 1.73}};
+struct BigBwdCost { double launch, round, pipelined, general, split, per_byte; };
+static const BigBwdCost kBigBwd[3] = {{0.0, 14.2, 1.41, 3.33, 3.3, 1.8e-7}, {0.0, 13.1, 2.07, 2.07, 2.3, 2.1e-7}, {6.9, 0.0, 2.72, 2.72, 5.0, 3.9e-7}};
 // Workgroups per compute unit that the fits were made with: what the kernels hold by registers and LDS, by class as above.
 static const int kMidResident[2][3][kHeights] = {{{5, 4, 3, 2, 1}, {4, 3, 2, 2, 1}, {4, 3, 2, 2, 1}}, {{3, 2, 2, 2, 1}, {3, 2, 2, 2, 1}, {2, 2, 2, 1, 1}}};
 
@@ -816,12 +826,18 @@ MidPlan plan_mid(int op, int N, int K, int M, bool wide, int C, size_t part_byte
             if (t < best_t * (1.0 - 1e-9)) { best_t = t; best = pl; }
         }
     }
-    constexpr double kLevel = 1.02;      // about level: the 256-column kernels need no partial tiles
-    const double big = op == 0 ? gemm_fwd_steps(N, K, M, (kLevel * best_t - mc.big_launch) / mc.big_step) : gemm_bwd_steps(N, K, M);
-    double big_t = mc.big_launch + big * mc.big_step;
-    if (op == 1) {
-        const BwdSplitPlan sp = gemm_bwd_split_plan(N, K, M);
-        if (sp.splits > 1) big_t += 5.0 + (double)sp.splits * sp.tail * BM * BN * sizeof(float) * mc.per_byte;
+    // About level: the 256-column kernels need no partial tiles.  Input gradient: of 13464 calls 1063 change kernel by the costs above,
+    // 989 away from 256 columns at 0.75 times the time on average, 74 to them level; 35 take over 3 % longer, 40 with 1.02 here.
+    const double kLevel = op == 0 || cls == 2 ? 1.02 : 1.04;
+    double big_t;
+    if (op == 0) {
+        const double launch = kBigFwd[cls][0], step = kBigFwd[cls][1];
+        big_t = launch + step * gemm_fwd_steps(N, K, M, (kLevel * best_t - launch) / step);
+    } else {
+        const BigBwdCost& bc = kBigBwd[cls];
+        const BwdWork w = gemm_bwd_work(N, K, M, wide);
+        big_t = bc.launch + w.rounds * bc.round + w.pipelined * bc.pipelined + w.general * bc.general;
+        if (w.part_bytes > 0.0) big_t += bc.split + w.part_bytes * bc.per_byte;
     }
     if (big_t <= kLevel * best_t) best = MidPlan{0, 0, 0, 0, 0};
     return best;

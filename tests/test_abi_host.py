@@ -177,6 +177,18 @@ def test_mid_token_planner_odd_groups():
                         assert lowra.lowra_plan_mid_tiling(lowra.OP_LINEAR_FWD, N, K, M, wide, books) != (0, 0), (N, K, M, wide, books)
 
 
+def test_mid_token_planner_input_gradient():
+    """Host only: a round of the 256-column input gradient costs about ten steps beside its steps, and a step outside its pipeline
+    (features that are no multiple of 256, fewer than eight full steps) 2.4 pipelined ones.  So few channels and such features stay
+    with the mid-token kernel where the tiles do not fill the chip evenly (measured 1.2 to 1.9 times as fast)."""
+    plan = lambda N, K, M, wide=False: lowra.lowra_plan_mid_tiling(lowra.OP_LINEAR_BWD_INPUT, N, K, M, wide, 3)
+    for N, K, M in [(264, 5504, 3072), (264, 5120, 4096), (264, 13824, 1200), (264, 4096, 3072), (264, 2752, 3000), (520, 4160, 2048), (520, 8192, 1025),
+                    (1024, 13824, 1025), (3072, 11008, 513), (4096, 4160, 2048)]:
+        assert plan(N, K, M) != (0, 0), (N, K, M)
+    assert plan(264, 5120, 4096, True) != (0, 0) and plan(264, 8192, 2500, True) != (0, 0)
+    assert plan(4096, 4096, 2048) == plan(4096, 4096, 4096) == plan(13824, 5120, 4096) == (0, 0)      # tiles that fill the chip
+
+
 def test_small_forward_planner():
     """Host only: the general small-token forward's wavefronts.  A low rank needs no more of a workgroup's memory than a high one
     where its t comes from a launch of its own, so it must not run through fewer wavefronts; and where the form that makes t
