@@ -767,7 +767,7 @@ hipError_t launch_mid_variant(const MidParams& p, int op, hipStream_t st) {
 // steps, those outside the pipeline 2.4 times as long, and the partial tiles: 896 timings of PATH_GEMM at each mix (72 to 5120
 // channels, 256 to 13824 features, 257 to 4096 tokens), rms error 6 % and 5 %.  As a launch and steps of one length (rms error 45 %)
 // it was put at less than half its time for few channels and for K % 256 != 0: 264 x 5504, 3072 tokens took 62 us where 128-column
-// tiles take 32, 4096 x 4160, 2048 tokens 228 for 127.
+// tiles take 30, 4096 x 4160, 2048 tokens 228 for 117.
 constexpr int kHeights = 5;
 static const int kMidHeight[kHeights] = {1, 2, 3, 4, 6};              // TM: 32 tokens each
 struct MidCost {
